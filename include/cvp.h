@@ -181,6 +181,23 @@ cvp_status cvp_project_ws(const cvp_geometry *g, const cvp_options *opts,
                           void *hip_stream);
 
 /*
+ * Scratch with which the operators run fastest: with project_bytes of it
+ * cvp_project_ws and cvp_project_views also copy the volume to [n2][n1][n3]
+ * order and read the copy column by column, and both directions make the
+ * cut-piece records of their views in one pass before the operator kernel
+ * instead of in every workgroup (unless the geometry caches them for opts, see
+ * cvp_geometry_cache_records; at most 8 GiB of records at a time, views
+ * beyond that in further launches).  Every work size an entry point accepts
+ * gives bitwise the same results; a call uses what fits.  The functions named
+ * ..._ws take optional scratch of any size, any alignment (NULL, 0: none) that
+ * overlaps no vector of the call, from a caller that keeps calls overlapping
+ * in time on distinct scratch; project_bytes also covers the view subsets,
+ * and a solver uses the larger of the two.
+ */
+cvp_status cvp_operator_workspace_size(const cvp_geometry *g, const cvp_options *opts, int64_t *project_bytes,
+                                       int64_t *backproject_bytes);
+
+/*
  * cvp_project_ws for callers that cannot allocate (code under HIP graph
  * capture, serving loops, harnesses that forbid hipMalloc): the per-group
  * maxima live in a fixed device array of the library, CVP_NOALLOC_MAX_GROUPS
@@ -221,6 +238,9 @@ cvp_status cvp_project_siddon(const cvp_geometry *g, int32_t K, const float *d_v
  */
 cvp_status cvp_backproject(const cvp_geometry *g, const cvp_options *opts,
                            const float *d_proj, float *d_vol, void *hip_stream);
+/* The same with operator scratch (cvp_operator_workspace_size). */
+cvp_status cvp_backproject_ws(const cvp_geometry *g, const cvp_options *opts, const float *d_proj, float *d_vol,
+                              void *d_work, int64_t work_bytes, void *hip_stream);
 
 /*
  * The operators restricted to a subset of the geometry's views: views
@@ -240,6 +260,9 @@ cvp_status cvp_project_views(const cvp_geometry *g, const cvp_options *opts, con
 cvp_status cvp_backproject_views(const cvp_geometry *g, const cvp_options *opts, const float *d_proj,
                                  float *d_vol, int32_t view0, int32_t view_stride, int32_t n_views,
                                  void *hip_stream);
+cvp_status cvp_backproject_views_ws(const cvp_geometry *g, const cvp_options *opts, const float *d_proj,
+                                    float *d_vol, int32_t view0, int32_t view_stride, int32_t n_views,
+                                    void *d_work, int64_t work_bytes, void *hip_stream);
 
 /*
  * Batches: several independent problems (each with its own geometry) in one
@@ -251,10 +274,13 @@ cvp_status cvp_backproject_views(const cvp_geometry *g, const cvp_options *opts,
  * backprojection).  The per-call pointer setup and the counter reset are one
  * tiny kernel on the same stream, so a batched call can be graph-captured.
  * n: 1..32 geometries on the same device; the batch keeps pointers to them
- * (they must outlive it) and owns small device tables.  When every member
- * has cached records (cvp_geometry_cache_records) at cvp_batch_create, the
- * batched kernels read them; a call after a member's table was freed or
- * rebuilt returns CVP_E_INVALID.
+ * (they must outlive it) and owns its device tables: room for a transposed
+ * copy of every volume and the members' cut-piece records, each up to 8 GiB
+ * (above that, or when the memory is not there, the launches do without).
+ * When every member has cached records (cvp_geometry_cache_records) at
+ * cvp_batch_create, the batched kernels read those instead of tables of the
+ * batch; a call after a member's table was freed or rebuilt then returns
+ * CVP_E_INVALID.
  */
 typedef struct cvp_batch cvp_batch;   /* opaque */
 cvp_status cvp_batch_create(const cvp_geometry *const *geoms, int32_t n, cvp_batch **out);
@@ -309,6 +335,13 @@ cvp_status cvp_cgls_start(const cvp_geometry *g, const cvp_options *opts, const 
 cvp_status cvp_cgls_iterate(const cvp_geometry *g, const cvp_options *opts, int32_t n_iter,
                             float *d_x, float *d_r, float *d_s, float *d_p, float *d_q,
                             void *d_work, void *hip_stream);
+/* The same with operator scratch (cvp_operator_workspace_size). */
+cvp_status cvp_cgls_start_ws(const cvp_geometry *g, const cvp_options *opts, const float *d_b,
+                             float *d_x, float *d_r, float *d_s, float *d_p, float *d_q,
+                             void *d_work, void *op_work, int64_t op_bytes, void *hip_stream);
+cvp_status cvp_cgls_iterate_ws(const cvp_geometry *g, const cvp_options *opts, int32_t n_iter,
+                               float *d_x, float *d_r, float *d_s, float *d_p, float *d_q,
+                               void *d_work, void *op_work, int64_t op_bytes, void *hip_stream);
 
 /*
  * Batched CGLS: every problem q of the batch runs the recurrences of
@@ -356,6 +389,13 @@ cvp_status cvp_sart_iterate(const cvp_geometry *g, const cvp_options *opts, int3
                             int32_t n_sweeps, float lambda, int32_t nonneg, const float *d_b, float *d_x,
                             const float *d_rowsum, const float *d_colsum, float *d_q, float *d_z,
                             void *hip_stream);
+cvp_status cvp_sart_setup_ws(const cvp_geometry *g, const cvp_options *opts, int32_t n_subsets,
+                             float *d_rowsum, float *d_colsum, float *d_q, void *op_work, int64_t op_bytes,
+                             void *hip_stream);
+cvp_status cvp_sart_iterate_ws(const cvp_geometry *g, const cvp_options *opts, int32_t n_subsets,
+                               int32_t n_sweeps, float lambda, int32_t nonneg, const float *d_b, float *d_x,
+                               const float *d_rowsum, const float *d_colsum, float *d_q, float *d_z,
+                               void *op_work, int64_t op_bytes, void *hip_stream);
 
 /*
  * LSQR (Paige & Saunders, ACM TOMS 8, 1982; Sec. V-E names it next to CGLS):
@@ -383,6 +423,12 @@ cvp_status cvp_lsqr_start(const cvp_geometry *g, const cvp_options *opts, const 
 cvp_status cvp_lsqr_iterate(const cvp_geometry *g, const cvp_options *opts, int32_t n_iter, float *d_x,
                             float *d_u, float *d_v, float *d_w, float *d_q, float *d_s, void *d_work,
                             void *hip_stream);
+cvp_status cvp_lsqr_start_ws(const cvp_geometry *g, const cvp_options *opts, const float *d_b, float *d_x,
+                             float *d_u, float *d_v, float *d_w, float *d_q, float *d_s, void *d_work,
+                             void *op_work, int64_t op_bytes, void *hip_stream);
+cvp_status cvp_lsqr_iterate_ws(const cvp_geometry *g, const cvp_options *opts, int32_t n_iter, float *d_x,
+                               float *d_u, float *d_v, float *d_w, float *d_q, float *d_s, void *d_work,
+                               void *op_work, int64_t op_bytes, void *hip_stream);
 
 /* *d_result = sum_i a[i] b[i] accumulated in FP64 (device scalar), using the
  * partials area of a CGLS workspace d_work.  n >= 0. */

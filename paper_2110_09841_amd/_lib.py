@@ -103,6 +103,18 @@ def _register_extra(L):
         "cvp_cgls_batched_iterate": ([vp, ctypes.POINTER(OptionsC), ctypes.c_int32] + [ctypes.POINTER(vp)] * 6
                                      + [vp], st),
         "cvp_project_workspace_size": ([vp, ctypes.POINTER(ctypes.c_int64)], st),
+        "cvp_operator_workspace_size": ([vp, ctypes.POINTER(OptionsC), ctypes.POINTER(ctypes.c_int64),
+                                         ctypes.POINTER(ctypes.c_int64)], st),
+        "cvp_backproject_ws": ([vp, ctypes.POINTER(OptionsC), vp, vp, vp, ctypes.c_int64, vp], st),
+        "cvp_backproject_views_ws": ([vp, ctypes.POINTER(OptionsC), vp, vp, ctypes.c_int32, ctypes.c_int32,
+                                      ctypes.c_int32, vp, ctypes.c_int64, vp], st),
+        "cvp_cgls_start_ws": ([vp, ctypes.POINTER(OptionsC)] + [vp] * 8 + [ctypes.c_int64, vp], st),
+        "cvp_cgls_iterate_ws": ([vp, ctypes.POINTER(OptionsC), ctypes.c_int32] + [vp] * 7 + [ctypes.c_int64, vp], st),
+        "cvp_sart_setup_ws": ([vp, ctypes.POINTER(OptionsC), ctypes.c_int32] + [vp] * 4 + [ctypes.c_int64, vp], st),
+        "cvp_sart_iterate_ws": ([vp, ctypes.POINTER(OptionsC), ctypes.c_int32, ctypes.c_int32, ctypes.c_float,
+                                 ctypes.c_int32] + [vp] * 7 + [ctypes.c_int64, vp], st),
+        "cvp_lsqr_start_ws": ([vp, ctypes.POINTER(OptionsC)] + [vp] * 9 + [ctypes.c_int64, vp], st),
+        "cvp_lsqr_iterate_ws": ([vp, ctypes.POINTER(OptionsC), ctypes.c_int32] + [vp] * 8 + [ctypes.c_int64, vp], st),
         "cvp_project_ws": ([vp, ctypes.POINTER(OptionsC), vp, vp, vp, ctypes.c_int64, vp], st),
         "cvp_project_noalloc": ([vp, ctypes.POINTER(OptionsC), vp, vp, vp], st),
         "cvp_project_siddon": ([vp, ctypes.c_int32, vp, vp, vp], st),

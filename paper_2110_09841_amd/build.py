@@ -3,6 +3,7 @@
 hipcc compiles the kernels and the C-ABI host code; packed FP32 instructions
 are disabled for every device compile.
 """
+import concurrent.futures
 import os
 import subprocess
 import sys
@@ -14,7 +15,10 @@ INCLUDE = os.path.join(ROOT, "include")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libcvp.so")
 
-SOURCES = ["cvp_kernels.hip", "cvp_siddon.hip", "cvp_blas.hip", "cvp_nn.hip", "cvp_synth.hip", "cvp_capi.cpp"]
+# (source, part): the operator kernels are compiled in three parts
+SOURCES = [("cvp_kernels.hip", 0), ("cvp_kernels.hip", 1), ("cvp_kernels.hip", 2), ("cvp_siddon.hip", None),
+           ("cvp_blas.hip", None), ("cvp_nn.hip", None), ("cvp_synth.hip", None), ("cvp_capi.cpp", None)]
+JOBS = 4      # compilations at a time
 ARCH = os.environ.get("CVP_OFFLOAD_ARCH", "gfx950")
 
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
@@ -30,15 +34,16 @@ def _run(cmd, verbose):
 
 def build(verbose: bool = False) -> str:
     os.makedirs(BUILD, exist_ok=True)
-    objs = []
-    for src in SOURCES:
+    objs, cmds = [], []
+    for src, part in SOURCES:
         path = os.path.join(CSRC, src)
-        obj = os.path.join(BUILD, src + ".o")
-        cmd = ["hipcc", "-c", path, "-o", obj] + COMMON + DEVICE
-        if src.endswith(".hip"):
-            cmd = ["hipcc", "-x", "hip", "-c", path, "-o", obj] + COMMON + DEVICE
-        _run(cmd, verbose)
+        obj = os.path.join(BUILD, src + ("" if part is None else ".%d" % part) + ".o")
+        lang = ["-x", "hip"] if src.endswith(".hip") else []
+        define = [] if part is None else ["-DCVP_PART=%d" % part]
+        cmds.append(["hipcc"] + lang + define + ["-c", path, "-o", obj] + COMMON + DEVICE)
         objs.append(obj)
+    with concurrent.futures.ThreadPoolExecutor(JOBS) as pool:
+        list(pool.map(lambda cmd: _run(cmd, verbose), cmds))
     tmp = LIB + ".tmp%d" % os.getpid()
     _run(["hipcc", "-shared", "-fPIC", "--offload-arch=" + ARCH, "-o", tmp] + objs, verbose)
     os.replace(tmp, LIB)

@@ -12,7 +12,7 @@ import numpy as np
 import torch
 
 from . import _lib
-from .cvp import Batch, Geometry, Options, _check_tensor, _ptr_array, _stream
+from .cvp import Batch, Geometry, Options, _check_tensor, _ptr_array, _stream, operator_scratch
 
 N_SCALARS = 16
 HISTORY = 4096
@@ -36,22 +36,27 @@ class CGLS:
         _lib.check(_lib.lib().cvp_cgls_workspace_size(geom.n_voxels, self.r.numel(), ctypes.byref(nbytes)))
         self.work = torch.zeros(nbytes.value // 8, dtype=torch.float64, device=dev)
         self._o = opts.c()
+        self.scratch = operator_scratch(geom, self._o, dev)
         self.graph = None
         self.graph_iters = 0
 
     def _ptrs(self):
         return [ctypes.c_void_p(t.data_ptr()) for t in (self.x, self.r, self.s, self.p, self.q, self.work)]
 
+    def _scratch(self):
+        return ctypes.c_void_p(self.scratch.data_ptr()), self.scratch.numel()
+
     def start(self):
         """r = b - A x0, s = A^T r, p = s, gamma0 = |s|^2."""
         x, r, s, p, q, w = self._ptrs()
-        _lib.check(_lib.lib().cvp_cgls_start(self.geom.handle, ctypes.byref(self._o),
-                                             ctypes.c_void_p(self.b.data_ptr()), x, r, s, p, q, w, _stream()))
+        _lib.check(_lib.lib().cvp_cgls_start_ws(self.geom.handle, ctypes.byref(self._o),
+                                                ctypes.c_void_p(self.b.data_ptr()), x, r, s, p, q, w,
+                                                *self._scratch(), _stream()))
 
     def iterate(self, n: int):
         x, r, s, p, q, w = self._ptrs()
-        _lib.check(_lib.lib().cvp_cgls_iterate(self.geom.handle, ctypes.byref(self._o), int(n),
-                                               x, r, s, p, q, w, _stream()))
+        _lib.check(_lib.lib().cvp_cgls_iterate_ws(self.geom.handle, ctypes.byref(self._o), int(n),
+                                                  x, r, s, p, q, w, *self._scratch(), _stream()))
 
     def capture(self, n: int):
         """Capture n iterations in one HIP graph (replayed by replay())."""

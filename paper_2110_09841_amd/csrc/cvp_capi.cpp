@@ -16,7 +16,9 @@
 #include "cvp_internal.h"
 
 namespace cvp {
-hipError_t configure_kernel_lds(size_t max_lds, size_t max_lds_batched);
+hipError_t configure_project_lds(size_t n);
+hipError_t configure_backproject_lds(size_t n);
+hipError_t configure_batched_lds(size_t n);
 constexpr size_t kLdsBudget = 30 * 1024;   // default projection plans: five workgroups per CU (160 KB LDS; 5 x 32 KB did not fit)
 constexpr size_t kBackLdsBudget = 52 * 1024;   // backprojection windows: three workgroups per CU
 constexpr size_t kBackLdsBudgetWide = 80 * 1024;   // records of up to kPmaxWide pieces per column: two per CU
@@ -30,7 +32,7 @@ constexpr size_t kLdsMax = 156 * 1024;      // any plan: one workgroup per CU at
 // budget, or four 40 KB workgroups would not fit a CU's 160 KB
 constexpr size_t kBatchStaticLds = 512;
 constexpr size_t kLdsBatchMax = kLdsMax;
-bool plan_projection(int N, int n2, int M, int nviews, int pmax, int force_u, ProjLaunch &L);
+bool plan_projection(const DevGeom &G, int nviews, int pmax, int force_u, ProjLaunch &L);
 bool plan_backprojection(const DevGeom &G, int pmax, double zabs, double Dmin, int force_gw,
                          int force_kp, BackLaunch &L, bool cached = false, size_t reserve = 0, int wpc = 0,
                          bool shared_req = false);
@@ -49,7 +51,8 @@ struct cvp_geometry {
     double zabs = 0.0, Dmin = 0.0;   // for launch planning
     int pmax = 4;                    // pieces per column the kernels keep (4, 8 or kPmaxWide)
     double wone_tt = 0.0, wsum_tt = 0.0;   // fixed-point bounds of the TT projector's weights
-    cvp::BackLaunch blc{};           // backprojection plan of the cached-record kernels
+    cvp::BackLaunch blc{};           // backprojection plan of the kernels that read a table of records
+    cvp::BackLaunch blt{};           // the same without a shared window (TT footprints)
     int bp_wpc = 0;                  // requested workgroups per CU of that plan (0: default)
     int bp_shared = 0;               // requested one window per workgroup in that plan
     float *d_rtab = nullptr;         // cached piece records (cvp_geometry_cache_records)
@@ -118,8 +121,9 @@ size_t backproject_lds_bytes(int gw, int pmax, int winCap)
 // the row tables in LDS).  force_u = 0: U as large as the default LDS budget
 // (five workgroups per compute unit) allows; otherwise U = force_u if its LDS
 // fits one workgroup.
-bool plan_projection(int N, int n2, int M, int nviews, int pmax, int force_u, ProjLaunch &L)
+static bool plan_projection_pad(int N, int n2, int M, int nviews, int pmax, int force_u, int pad, ProjLaunch &L)
 {
+    N += 2 * pad;
     // A work item keeps at most pmax pieces per column, and a column's pieces
     // inside a band of U detector columns are at most U; pmax = 8 with U <= 8
     // therefore serves footprints of any width.
@@ -141,8 +145,17 @@ bool plan_projection(int N, int n2, int M, int nviews, int pmax, int force_u, Pr
     L.items = L.nbands * nviews;
     L.chunk = nviews * ((L.nbands + 7) / 8);   // work items per XCD (bands interleaved over XCDs)
     L.pmax = pmax;
+    L.pad = pad;
     L.lds = project_lds_bytes(U, N, n2, pmax);
     return true;
+}
+
+// With the geometry's spare rows at both ends of a band column; without them
+// (pieces then take the general row loop) where only that fits the LDS.
+bool plan_projection(const DevGeom &G, int nviews, int pmax, int force_u, ProjLaunch &L)
+{
+    return plan_projection_pad(G.N, G.n2, G.M, nviews, pmax, force_u, G.rpad, L) ||
+           plan_projection_pad(G.N, G.n2, G.M, nviews, pmax, force_u, 0, L);
 }
 
 // Backprojection: stacks of GW columns x 64 kp voxels; the largest stack whose
@@ -315,6 +328,24 @@ struct Circular {
     double D, f, b1, b2, c1, c2, rmax;
 };
 
+// The backprojection plan of the cached-record kernels: the in-kernel plan's
+// stack shape when it fits their smaller LDS budget, else their default.
+static void replan_backprojection(cvp_geometry *g)
+{
+    cvp::BackLaunch bl{};
+    if (cvp::plan_backprojection(g->base, g->pmax, g->zabs, g->Dmin, g->bl.gw, g->bl.kp, bl, true, 0, g->bp_wpc,
+                                 g->bp_shared != 0) ||
+        cvp::plan_backprojection(g->base, g->pmax, g->zabs, g->Dmin, 0, 0, bl, true, 0, g->bp_wpc, g->bp_shared != 0))
+        g->blc = bl;
+    else
+        g->blc = g->bl;
+    g->blt = g->blc;
+    if (g->blc.shared && !cvp::plan_backprojection(g->base, g->pmax, g->zabs, g->Dmin, g->blc.gw, g->blc.kp, g->blt, true, 0,
+                                                   g->bp_wpc, false) &&
+        !cvp::plan_backprojection(g->base, g->pmax, g->zabs, g->Dmin, 0, 0, g->blt, true, 0, g->bp_wpc, false))
+        g->blt.gw = 0;     // none: the footprints are made in the kernel
+}
+
 // Builds the device tables and launch plans from per-view frames.  circ:
 // the orbit's constants (then the pixel factor tables keep the orbit's own
 // formulas in mm), or nullptr for general views.
@@ -406,7 +437,11 @@ cvp_status finish_geometry(const VolDet &vd, std::vector<cvp::ViewGeom> &views, 
     if (e != hipSuccess) { cvp_geometry_destroy(g); return device_fail(e, "device tables"); }
     static std::once_flag lds_once;
     static hipError_t lds_err = hipSuccess;
-    std::call_once(lds_once, [] { lds_err = cvp::configure_kernel_lds(cvp::kLdsMax, cvp::kLdsBatchMax); });
+    std::call_once(lds_once, [] {
+        lds_err = cvp::configure_project_lds(cvp::kLdsMax);
+        if (lds_err == hipSuccess) lds_err = cvp::configure_backproject_lds(cvp::kLdsMax);
+        if (lds_err == hipSuccess) lds_err = cvp::configure_batched_lds(cvp::kLdsBatchMax);
+    });
     if (lds_err != hipSuccess) { cvp_geometry_destroy(g); return device_fail(lds_err, "kernel LDS attribute"); }
 
     cvp::DevGeom &G = g->base;
@@ -425,6 +460,16 @@ cvp_status finish_geometry(const VolDet &vd, std::vector<cvp::ViewGeom> &views, 
     G.sigma = nullptr;
     G.sigma_views = shared ? 0 : 1;
     G.raw_volume = 0;
+    {
+        // the most rows a piece can touch: beta = a3 (f/b2) / D of the nearest
+        // depth, the box half-width rho |t - c2| with rho <= (hd / 2) / D (the
+        // depth variance of a convex piece is at most that of a uniform
+        // depth over its range), one more row for the alignment
+        double c2max = 0.0;
+        for (const cvp::ViewGeom &W : views) c2max = std::max(c2max, std::max(W.c2 + 0.5, N - 0.5 - W.c2));
+        const double rows = a3 * fb2max / Dmin + hd / Dmin * c2max + 1.1;
+        G.rpad = rows < cvp::kFixedRowsMax ? std::max(2, (int)std::ceil(rows)) : cvp::kFixedRowsMax;
+    }
     {
         // Any pixel's summed weight per unit |mu| is at most its solid angle
         // (<= b1 b2 / f^2) times the integral of r^-2 r^2 dr (or of r^2 dr for
@@ -453,7 +498,7 @@ cvp_status finish_geometry(const VolDet &vd, std::vector<cvp::ViewGeom> &views, 
     g->zabs = zabs;
     g->Dmin = Dmin;
     g->pmax = pmax;
-    if (!cvp::plan_projection(N, n2, M, V, pmax, 0, g->pl)) {
+    if (!cvp::plan_projection(G, V, pmax, 0, g->pl)) {
         cvp_geometry_destroy(g);
         return fail(CVP_E_UNSUPPORTED, "detector rows (%d) or volume rows (%d) too large for the projection LDS layout", N, n2);
     }
@@ -461,6 +506,7 @@ cvp_status finish_geometry(const VolDet &vd, std::vector<cvp::ViewGeom> &views, 
         cvp_geometry_destroy(g);
         return fail(CVP_E_UNSUPPORTED, "backprojection LDS window too small");
     }
+    replan_backprojection(g);
     *out = g;
     return ok();
 }
@@ -621,7 +667,7 @@ cvp_status cvp_geometry_set_launch(cvp_geometry *g, const cvp_launch *in)
     const cvp::DevGeom &G = g->base;
     cvp::ProjLaunch pl{};
     cvp::BackLaunch bl{};
-    if (!cvp::plan_projection(G.N, G.n2, G.M, G.nviews, g->pmax, u, pl)) {
+    if (!cvp::plan_projection(G, G.nviews, g->pmax, u, pl)) {
         if (g->pmax > 8 && u > 8)
             return fail(CVP_E_UNSUPPORTED, "launch.proj_band_cols = %d: voxels span more than 8 detector columns, "
                                            "bands are limited to 8", u);
@@ -638,14 +684,23 @@ cvp_status cvp_geometry_set_launch(cvp_geometry *g, const cvp_launch *in)
         if (!cvp::plan_backprojection(G, g->pmax, g->zabs, g->Dmin, gw, kp, bl) &&
             !cvp::plan_backprojection(G, g->pmax, g->zabs, g->Dmin, 0, 0, bl))
             return fail(CVP_E_UNSUPPORTED, "backprojection plan");
-    } else if (!cvp::plan_backprojection(G, g->pmax, g->zabs, g->Dmin, gw, kp, bl)) {
-        return fail(CVP_E_UNSUPPORTED, "launch.bp_stack_cols = %d, bp_passes = %d: does not fit LDS", gw, kp);
+    } else {
+        if (!cvp::plan_backprojection(G, g->pmax, g->zabs, g->Dmin, gw, kp, bl))
+            return fail(CVP_E_UNSUPPORTED, "launch.bp_stack_cols = %d, bp_passes = %d: does not fit LDS", gw, kp);
+        // launches with records in their scratch take the same shape where it fits
+        if (!cvp::plan_backprojection(G, g->pmax, g->zabs, g->Dmin, gw, kp, blc, true, 0, wpc, shw != 0) &&
+            !cvp::plan_backprojection(G, g->pmax, g->zabs, g->Dmin, 0, 0, blc, true, 0, wpc, shw != 0))
+            blc = bl;
     }
     g->pl = pl;
     g->bl = bl;
     g->blc = blc;
     g->bp_wpc = wpc;
     g->bp_shared = shw;
+    g->blt = blc;
+    if (blc.shared && !cvp::plan_backprojection(G, g->pmax, g->zabs, g->Dmin, blc.gw, blc.kp, g->blt, true, 0, wpc, false) &&
+        !cvp::plan_backprojection(G, g->pmax, g->zabs, g->Dmin, 0, 0, g->blt, true, 0, wpc, false))
+        g->blt.gw = 0;
     return ok();
 }
 
@@ -661,19 +716,6 @@ cvp_status cvp_geometry_sizes(const cvp_geometry *g, int64_t *n_voxels, int64_t 
 static int model_of(const cvp_options *o)
 {
     return o->variant == CVP_TT ? cvp::kModelTT : o->variant == CVP_EXACT ? cvp::kModelExact : cvp::kModelRelaxed;
-}
-
-// The backprojection plan of the cached-record kernels: the in-kernel plan's
-// stack shape when it fits their smaller LDS budget, else their default.
-static void replan_backprojection(cvp_geometry *g)
-{
-    cvp::BackLaunch bl{};
-    if (cvp::plan_backprojection(g->base, g->pmax, g->zabs, g->Dmin, g->bl.gw, g->bl.kp, bl, true, 0, g->bp_wpc,
-                                 g->bp_shared != 0) ||
-        cvp::plan_backprojection(g->base, g->pmax, g->zabs, g->Dmin, 0, 0, bl, true, 0, g->bp_wpc, g->bp_shared != 0))
-        g->blc = bl;
-    else
-        g->blc = g->bl;
 }
 
 // The backprojection plan of a prepared launch: cached records or not.
@@ -709,7 +751,7 @@ cvp_status cvp_geometry_cache_records(cvp_geometry *g, int32_t enable, int64_t *
         const size_t nb = (size_t)cols * sizeof(int);
         e = hipMalloc((void **)&g->d_rtab, rb);
         if (e == hipSuccess) e = hipMalloc((void **)&g->d_rtab_n, nb);
-        if (e == hipSuccess) e = cvp::launch_record_table(g->base, g->pmax, g->d_rtab, g->d_rtab_n, (hipStream_t)stream);
+        if (e == hipSuccess) e = cvp::launch_record_table(g->base, g->pmax, false, g->d_rtab, g->d_rtab_n, (hipStream_t)stream);
         if (e != hipSuccess) {
             if (g->d_rtab) (void)hipFree(g->d_rtab);
             if (g->d_rtab_n) (void)hipFree(g->d_rtab_n);
@@ -760,8 +802,193 @@ static cvp_status prepare(const cvp_geometry *g, const cvp_options *o, const voi
         G.rtab = g->d_rtab;
         G.rtab_n = g->d_rtab_n;
         G.rtab_pmax = g->pmax;
+        G.rtab_vs = 1;
     }
     return CVP_OK;
+}
+
+// ------------------------------------------------------- operator scratch
+//
+// With scratch a call lays out in it what its kernels read faster than what
+// they would make themselves: the transposed volume with its group maxima
+// (projection), and the cut-piece records of a run of views, made by one pass
+// before the operator kernel of those views (unless the geometry keeps all
+// records).  In the operator kernels that FP64 stage is repeated by every
+// band or stack that meets a column and takes the registers of one to two
+// waves per SIMD.  Every size gives the same bits.
+
+static int64_t align256(int64_t n) { return (n + 255) / 256 * 256; }
+static int64_t gmax_bytes(const cvp_geometry *g) { return cvp::group_max_cells(g->base) * (int64_t)sizeof(unsigned); }
+
+// Most bytes of records asked for at a time: longer runs of views are
+// launched in several pieces, each still thousands of workgroups (12.7 GB of
+// records at 512^3 x 248 views: two pieces).
+constexpr int64_t kTableBytes = int64_t(8) << 30;
+
+// Records of one view: rows padded to 256 bytes (records, counts).
+struct TableSize { int64_t rec, cnt; };
+static TableSize table_size(const cvp_geometry *g, int64_t views)
+{
+    const int64_t cols = views * g->base.n2 * g->base.n1;
+    return {align256(cols * g->pmax * cvp::kRecFloats * (int64_t)sizeof(float)), align256(cols * (int64_t)sizeof(int))};
+}
+static int64_t table_bytes(const cvp_geometry *g, int64_t views)
+{
+    const TableSize t = table_size(g, views);
+    return t.rec + t.cnt;
+}
+// The most views (a multiple of `unit`, or all of them) whose records fit.
+static int table_views(const cvp_geometry *g, int64_t bytes, int views, int unit)
+{
+    if (bytes >= table_bytes(g, views)) return views;
+    int64_t n = bytes > 0 ? bytes / (table_bytes(g, 1)) : 0;   // per-view sizes are padded: at most an underestimate
+    n = n / unit * unit;
+    return (int)n;
+}
+// The same number of pieces with views spread evenly over them.
+static int even_views(int views, int most, int unit)
+{
+    const int pieces = (views + most - 1) / most;
+    return std::min(most, ((views + pieces - 1) / pieces + unit - 1) / unit * unit);
+}
+
+struct Scratch {
+    char *p = nullptr;
+    int64_t n = 0;
+    Scratch(void *work, int64_t bytes)
+    {
+        // used from the first 256-byte boundary on
+        const int64_t skip = work ? (int64_t)((256 - (reinterpret_cast<uintptr_t>(work) & 255)) & 255) : 0;
+        if (work && bytes > skip) {
+            p = static_cast<char *>(work) + skip;
+            n = bytes - skip;
+        }
+    }
+    void *take(int64_t bytes)
+    {
+        bytes = align256(bytes);
+        if (bytes > n) return nullptr;
+        void *r = p;
+        p += bytes;
+        n -= bytes;
+        return r;
+    }
+};
+
+// Whether an operator call makes records in its scratch.
+static bool makes_records(const cvp_geometry *g, const cvp::DevGeom &G) { return !G.rtab && g->pmax <= 8; }
+
+// Views [q, q + c) of the launch G, reading the records at rec / cnt.
+static void launch_views(const cvp_geometry *g, cvp::DevGeom &G, int q, int c, float *rec, int *cnt)
+{
+    G.views += (int64_t)q * G.vstride;
+    G.nviews = c;
+    if (G.sigma && G.sigma_views) G.sigma += (int64_t)q * G.vstride * G.N * G.M;
+    G.rtab = rec;
+    G.rtab_n = cnt;
+    G.rtab_pmax = g->pmax;
+    G.rtab_vs = 1;
+}
+
+// b = A x over the views of G.  gmax: room for the group maxima where the
+// scratch has none (nullptr: the kernel scans its wedges).
+static hipError_t run_project(const cvp_geometry *g, const cvp::DevGeom &G, const cvp::ProjLaunch &pl, int model, bool ec,
+                              const float *vol, float *proj, unsigned *gmax, void *work, int64_t work_bytes,
+                              hipStream_t s, const double *stop = nullptr)
+{
+    Scratch w(work, work_bytes);
+    float *vt = nullptr;
+    if (void *m = w.take(gmax_bytes(g))) {
+        gmax = static_cast<unsigned *>(m);
+        vt = static_cast<float *>(w.take(g->nvox * (int64_t)sizeof(float)));
+    }
+    hipError_t e = hipSuccess;
+    if (vt) e = cvp::launch_transpose_max(G, vol, vt, gmax, s, stop);
+    else if (gmax) e = cvp::launch_group_max(G, vol, gmax, s, stop);
+    if (e != hipSuccess) return e;
+    const int most = vt && makes_records(g, G) ? table_views(g, w.n, G.nviews, 1) : 0;
+    if (most < std::min(G.nviews, 8)) return cvp::launch_project(G, pl, model, ec, vol, proj, gmax, vt, s, stop);
+    const int step = even_views(G.nviews, most, 1);
+    const TableSize ts = table_size(g, step);
+    float *rec = reinterpret_cast<float *>(w.p);
+    int *cnt = reinterpret_cast<int *>(w.p + ts.rec);
+    for (int q = 0; q < G.nviews && e == hipSuccess; q += step) {
+        cvp::DevGeom Gq = G;
+        launch_views(g, Gq, q, std::min(step, G.nviews - q), rec, cnt);
+        cvp::ProjLaunch L = pl;
+        L.items = L.nbands * Gq.nviews;
+        L.chunk = Gq.nviews * ((L.nbands + 7) / 8);
+        e = cvp::launch_record_table(Gq, g->pmax, model == cvp::kModelTT, rec, cnt, s, stop);
+        if (e == hipSuccess)
+            e = cvp::launch_project(Gq, L, model, ec, vol, proj + (int64_t)q * G.vstride * G.N * G.M, gmax, vt, s, stop);
+    }
+    return e;
+}
+
+// records: whether the calls make records in their scratch.
+static int64_t project_full_bytes(const cvp_geometry *g, bool records)
+{
+    int64_t n = align256(gmax_bytes(g)) + align256(g->nvox * (int64_t)sizeof(float)) + 256;
+    if (records) n += std::min(table_bytes(g, g->base.nviews), std::max(kTableBytes, table_bytes(g, 8)));
+    return n;
+}
+
+// x = A^T b over the views of G.
+static hipError_t run_backproject(const cvp_geometry *g, const cvp::DevGeom &G, int model, bool ec, const float *proj,
+                                  float *vol, void *work, int64_t work_bytes, hipStream_t s,
+                                  const double *stop = nullptr)
+{
+    const cvp::BackLaunch &bl = model == cvp::kModelTT ? g->blt : g->blc;
+    if (makes_records(g, G) && bl.gw > 0) {
+        Scratch w(work, work_bytes);
+        int step = table_views(g, w.n, G.nviews, cvp::kWaves);
+        cvp::BackPart part;
+        if (step < G.nviews) {
+            // several launches: the running sums wait in the scratch too
+            part.sums = static_cast<float *>(w.take(cvp::back_part_floats(bl) * (int64_t)sizeof(float)));
+            step = part.sums ? table_views(g, w.n, G.nviews, cvp::kWaves) : 0;
+            if (step >= 8) step = even_views(G.nviews, step, cvp::kWaves);
+        }
+        if (step >= std::min(G.nviews, 8)) {
+            const TableSize ts = table_size(g, step);
+            float *rec = reinterpret_cast<float *>(w.p);
+            int *cnt = reinterpret_cast<int *>(w.p + ts.rec);
+            hipError_t e = hipSuccess;
+            for (int q = 0; q < G.nviews && e == hipSuccess; q += step) {
+                cvp::DevGeom Gq = G;
+                launch_views(g, Gq, q, std::min(step, G.nviews - q), rec, cnt);
+                part.first = q == 0;
+                part.last = q + step >= G.nviews;
+                e = cvp::launch_record_table(Gq, g->pmax, model == cvp::kModelTT, rec, cnt, s, stop);
+                if (e == hipSuccess)
+                    e = cvp::launch_backproject(Gq, bl, model, ec, proj + (int64_t)q * G.vstride * G.N * G.M, vol, s,
+                                                stop, part);
+            }
+            return e;
+        }
+    }
+    return cvp::launch_backproject(G, back_plan(g, G), model, ec, proj, vol, s, stop);
+}
+
+static int64_t backproject_full_bytes(const cvp_geometry *g, bool records)
+{
+    if (!records) return 0;
+    const int64_t all = table_bytes(g, g->base.nviews), most = std::max(kTableBytes, table_bytes(g, 8));
+    if (all <= most) return all + 256;
+    const int64_t part = std::max(cvp::back_part_floats(g->blc), cvp::back_part_floats(g->blt));
+    return most + align256(part * (int64_t)sizeof(float)) + 256;
+}
+
+cvp_status cvp_operator_workspace_size(const cvp_geometry *g, const cvp_options *o, int64_t *project_bytes,
+                                       int64_t *backproject_bytes)
+{
+    if (!g) return fail(CVP_E_INVALID, "geometry is NULL");
+    if (!o) return fail(CVP_E_INVALID, "options is NULL");
+    if (!project_bytes || !backproject_bytes) return fail(CVP_E_INVALID, "bytes is NULL");
+    const bool records = g->pmax <= 8 && (o->variant == CVP_TT || !g->d_rtab);
+    *project_bytes = project_full_bytes(g, records);
+    *backproject_bytes = backproject_full_bytes(g, records);
+    return ok();
 }
 
 cvp_status cvp_project(const cvp_geometry *g, const cvp_options *o, const float *d_vol,
@@ -770,8 +997,8 @@ cvp_status cvp_project(const cvp_geometry *g, const cvp_options *o, const float 
     cvp::DevGeom G;
     cvp_status st = prepare(g, o, d_vol, d_proj, G);
     if (st != CVP_OK) return st;
-    hipError_t e = cvp::launch_project(G, g->pl, model_of(o), o->elevation_correction != 0,
-                                       d_vol, d_proj, nullptr, (hipStream_t)stream);
+    hipError_t e = run_project(g, G, g->pl, model_of(o), o->elevation_correction != 0, d_vol, d_proj, nullptr, nullptr, 0,
+                               (hipStream_t)stream);
     if (e != hipSuccess) return device_fail(e, "projection launch");
     return ok();
 }
@@ -798,8 +1025,8 @@ cvp_status cvp_project_ws(const cvp_geometry *g, const cvp_options *o, const flo
     if (reinterpret_cast<uintptr_t>(d_work) & 3) return fail(CVP_E_INVALID, "work must be 4-byte aligned");
     if (d_work == (const void *)d_vol || d_work == (void *)d_proj)
         return fail(CVP_E_INVALID, "work aliases the volume or the projections");
-    hipError_t e = cvp::launch_project(G, g->pl, model_of(o), o->elevation_correction != 0,
-                                       d_vol, d_proj, (unsigned *)d_work, (hipStream_t)stream);
+    hipError_t e = run_project(g, G, g->pl, model_of(o), o->elevation_correction != 0, d_vol, d_proj, (unsigned *)d_work,
+                               d_work, work_bytes, (hipStream_t)stream);
     if (e != hipSuccess) return device_fail(e, "projection launch");
     return ok();
 }
@@ -818,8 +1045,8 @@ cvp_status cvp_project_noalloc(const cvp_geometry *g, const cvp_options *o, cons
     unsigned *work = nullptr;
     hipError_t e = cvp::static_scratch(&work);
     if (e != hipSuccess) return device_fail(e, "scratch symbol address");
-    e = cvp::launch_project(G, g->pl, model_of(o), o->elevation_correction != 0, d_vol, d_proj, work,
-                            (hipStream_t)stream);
+    e = run_project(g, G, g->pl, model_of(o), o->elevation_correction != 0, d_vol, d_proj, work, nullptr, 0,
+                    (hipStream_t)stream);
     if (e != hipSuccess) return device_fail(e, "projection launch");
     return ok();
 }
@@ -836,16 +1063,32 @@ cvp_status cvp_project_siddon(const cvp_geometry *g, int32_t K, const float *d_v
     return ok();
 }
 
-cvp_status cvp_backproject(const cvp_geometry *g, const cvp_options *o, const float *d_proj,
-                           float *d_vol, void *stream)
+// Optional scratch of a call: NULL or work_bytes bytes that overlap none of
+// its vectors.
+static cvp_status check_work(const void *work, int64_t work_bytes, const void *in, const void *outp)
+{
+    if (work_bytes < 0) return fail(CVP_E_INVALID, "work_bytes = %lld", (long long)work_bytes);
+    if (work && (work == in || work == outp)) return fail(CVP_E_INVALID, "work aliases the volume or the projections");
+    return CVP_OK;
+}
+
+cvp_status cvp_backproject_ws(const cvp_geometry *g, const cvp_options *o, const float *d_proj, float *d_vol,
+                              void *d_work, int64_t work_bytes, void *stream)
 {
     cvp::DevGeom G;
     cvp_status st = prepare(g, o, d_proj, d_vol, G);
+    if (st == CVP_OK) st = check_work(d_work, work_bytes, d_proj, d_vol);
     if (st != CVP_OK) return st;
-    hipError_t e = cvp::launch_backproject(G, back_plan(g, G), model_of(o), o->elevation_correction != 0,
-                                           d_proj, d_vol, (hipStream_t)stream);
+    hipError_t e = run_backproject(g, G, model_of(o), o->elevation_correction != 0, d_proj, d_vol, d_work, work_bytes,
+                                   (hipStream_t)stream);
     if (e != hipSuccess) return device_fail(e, "backprojection launch");
     return ok();
+}
+
+cvp_status cvp_backproject(const cvp_geometry *g, const cvp_options *o, const float *d_proj,
+                           float *d_vol, void *stream)
+{
+    return cvp_backproject_ws(g, o, d_proj, d_vol, nullptr, 0, stream);
 }
 
 // Views v0, v0 + stride, ..., v0 + (count - 1) stride of a geometry: the
@@ -866,6 +1109,7 @@ static cvp_status view_subset(const cvp_geometry *g, int32_t view0, int32_t stri
     if (G.sigma && G.sigma_views) G.sigma += proj_offset;
     if (G.rtab) {
         const int64_t cols = (int64_t)view0 * G.n2 * G.n1;
+        G.rtab_vs = stride;
         G.rtab += cols * G.rtab_pmax * cvp::kRecFloats;
         G.rtab_n += cols;
     }
@@ -890,27 +1134,35 @@ cvp_status cvp_project_views(const cvp_geometry *g, const cvp_options *o, const 
         if (reinterpret_cast<uintptr_t>(d_work) & 3) return fail(CVP_E_INVALID, "work must be 4-byte aligned");
     }
     cvp::ProjLaunch pl{};
-    if (!cvp::plan_projection(G.N, G.n2, G.M, n_views, g->pmax, g->pl.U, pl))
+    if (!cvp::plan_projection(G, n_views, g->pmax, g->pl.U, pl))
         return fail(CVP_E_UNSUPPORTED, "projection plan");
-    hipError_t e = cvp::launch_project(G, pl, model_of(o), o->elevation_correction != 0, d_vol,
-                                       d_proj + off, (unsigned *)d_work, (hipStream_t)stream);
+    hipError_t e = run_project(g, G, pl, model_of(o), o->elevation_correction != 0, d_vol, d_proj + off,
+                               (unsigned *)d_work, d_work, work_bytes, (hipStream_t)stream);
     if (e != hipSuccess) return device_fail(e, "projection launch");
+    return ok();
+}
+
+cvp_status cvp_backproject_views_ws(const cvp_geometry *g, const cvp_options *o, const float *d_proj, float *d_vol,
+                                    int32_t view0, int32_t view_stride, int32_t n_views, void *d_work,
+                                    int64_t work_bytes, void *stream)
+{
+    cvp::DevGeom G;
+    cvp_status st = prepare(g, o, d_proj, d_vol, G);
+    if (st == CVP_OK) st = check_work(d_work, work_bytes, d_proj, d_vol);
+    if (st != CVP_OK) return st;
+    int64_t off = 0;
+    st = view_subset(g, view0, view_stride, n_views, G, off);
+    if (st != CVP_OK) return st;
+    hipError_t e = run_backproject(g, G, model_of(o), o->elevation_correction != 0, d_proj + off, d_vol, d_work,
+                                   work_bytes, (hipStream_t)stream);
+    if (e != hipSuccess) return device_fail(e, "backprojection launch");
     return ok();
 }
 
 cvp_status cvp_backproject_views(const cvp_geometry *g, const cvp_options *o, const float *d_proj, float *d_vol,
                                  int32_t view0, int32_t view_stride, int32_t n_views, void *stream)
 {
-    cvp::DevGeom G;
-    cvp_status st = prepare(g, o, d_proj, d_vol, G);
-    if (st != CVP_OK) return st;
-    int64_t off = 0;
-    st = view_subset(g, view0, view_stride, n_views, G, off);
-    if (st != CVP_OK) return st;
-    hipError_t e = cvp::launch_backproject(G, back_plan(g, G), model_of(o), o->elevation_correction != 0,
-                                           d_proj + off, d_vol, (hipStream_t)stream);
-    if (e != hipSuccess) return device_fail(e, "backprojection launch");
-    return ok();
+    return cvp_backproject_views_ws(g, o, d_proj, d_vol, view0, view_stride, n_views, nullptr, 0, stream);
 }
 
 }  // extern "C"
@@ -926,10 +1178,13 @@ struct cvp_batch {
     cvp::BatchTable *d_btab[6] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
     int *d_counter = nullptr;         // [0] projection, [1 + g] backprojection group g
     std::vector<unsigned *> d_gmax;   // per problem: per-group maxima of the volume
+    std::vector<float *> vts;         // per problem: its transposed volume (nullptr: none)
     size_t plds = 0, blds[6] = {0, 0, 0, 0, 0, 0};
     int pgrid = 0, bgrid[6] = {0, 0, 0, 0, 0, 0};
-    bool cached = false;                  // every member reads its geometry's cached records
-    std::vector<const float *> rtabs;     // the tables captured at creation
+    bool cached = false;                  // every member reads a table of records
+    std::vector<const float *> rtabs;     // the geometries' tables captured at creation (empty: the batch's own)
+    std::vector<void *> d_own;            // the batch's own tables and transposed volumes
+    bool vt = false;                      // the projection reads transposed volumes
 };
 
 extern "C" {
@@ -944,6 +1199,7 @@ void cvp_batch_destroy(cvp_batch *b)
     if (b->d_counter) (void)hipFree(b->d_counter);
     for (unsigned *t : b->d_gmax)
         if (t) (void)hipFree(t);
+    for (void *t : b->d_own) (void)hipFree(t);
     delete b;
 }
 
@@ -966,9 +1222,36 @@ cvp_status cvp_batch_create(const cvp_geometry *const *geoms, int32_t n, cvp_bat
     b->n = n;
     b->device = geoms[0]->device;
     b->geoms.assign(geoms, geoms + n);
-    // with every member's records cached the batched kernels read them too
+    // With every member's records cached the batched kernels read those; else
+    // the batch makes tables of its own for all of them, up to kTableBytes
+    // (launches on a larger batch make their records in the kernels).
+    bool own = false;
     b->cached = true;
     for (int q = 0; q < n; ++q) b->cached = b->cached && geoms[q]->d_rtab != nullptr;
+    std::vector<float *> recs(n, nullptr);
+    std::vector<int *> cnts(n, nullptr);
+    if (!b->cached) {
+        int64_t total = 0;
+        for (int q = 0; q < n; ++q) total += table_bytes(geoms[q], geoms[q]->base.nviews);
+        own = total <= kTableBytes;
+        for (int q = 0; q < n && own; ++q) {
+            const cvp_geometry *g = geoms[q];
+            void *t = nullptr;
+            own = hipMalloc(&t, table_bytes(g, g->base.nviews)) == hipSuccess;
+            if (!own) break;
+            b->d_own.push_back(t);
+            recs[q] = static_cast<float *>(t);
+            cnts[q] = reinterpret_cast<int *>(static_cast<char *>(t) + table_size(g, g->base.nviews).rec);
+            own = cvp::launch_record_table(g->base, g->pmax, false, recs[q], cnts[q], nullptr) == hipSuccess;
+        }
+        if (own) own = hipStreamSynchronize(nullptr) == hipSuccess;   // calls may come on any stream
+        if (!own) {
+            (void)hipGetLastError();
+            for (void *t : b->d_own) (void)hipFree(t);
+            b->d_own.clear();
+        }
+        b->cached = own;
+    }
     // Projection: every problem keeps its own plan (the batched kernel
     // dispatches on the piece stride per item), so its results are those of
     // its own launches.  Backprojection: every problem keeps its own piece
@@ -991,7 +1274,7 @@ cvp_status cvp_batch_create(const cvp_geometry *const *geoms, int32_t n, cvp_bat
             grp[q] = (pm == 4 ? 0 : 3) + gi;
         }
         if (!planned) {
-            delete b;
+            cvp_batch_destroy(b);
             return fail(CVP_E_UNSUPPORTED, "geoms[%d]: batched backprojection plan does not fit LDS", q);
         }
     }
@@ -1004,6 +1287,7 @@ cvp_status cvp_batch_create(const cvp_geometry *const *geoms, int32_t n, cvp_bat
         cvp::BatchProblem &P = probs[q];
         P.G = g->base;
         P.U = pl.U;
+        P.pad = pl.pad;
         P.pmax = pl.pmax;
         P.gw = bl.gw;
         P.kp = bl.kp;
@@ -1015,12 +1299,14 @@ cvp_status cvp_batch_create(const cvp_geometry *const *geoms, int32_t n, cvp_bat
         P.in = nullptr;
         P.out = nullptr;
         P.gmax = nullptr;   // set below
+        P.vt = nullptr;
         P.stop = nullptr;   // set per call
         if (b->cached) {
-            P.G.rtab = g->d_rtab;
-            P.G.rtab_n = g->d_rtab_n;
+            P.G.rtab = own ? recs[q] : g->d_rtab;
+            P.G.rtab_n = own ? cnts[q] : g->d_rtab_n;
             P.G.rtab_pmax = g->pmax;
-            b->rtabs.push_back(g->d_rtab);
+            P.G.rtab_vs = 1;
+            if (!own) b->rtabs.push_back(g->d_rtab);
         }
         b->plds = std::max(b->plds, pl.lds);
         b->blds[grp[q]] = std::max(b->blds[grp[q]], bl.lds);
@@ -1053,17 +1339,30 @@ cvp_status cvp_batch_create(const cvp_geometry *const *geoms, int32_t n, cvp_bat
         const cvp::BatchTable bt = table(bcost, true, gi);
         e = hipMalloc((void **)&b->d_btab[gi], sizeof(cvp::BatchTable));
         if (e == hipSuccess) e = hipMemcpy(b->d_btab[gi], &bt, sizeof(bt), hipMemcpyHostToDevice);
-        b->bgrid[gi] = cus * cvp::batched_blocks_per_cu(true, b->blds[gi], kGw[gi % 3], gi < 3 ? 4 : 8, b->cached);
+        b->bgrid[gi] = cus * cvp::batched_blocks_per_cu(true, b->blds[gi], kGw[gi % 3], gi < 3 ? 4 : 8, b->cached,
+                                                        b->vt);
     }
     b->d_gmax.assign(n, nullptr);
     for (int q = 0; q < n && e == hipSuccess; ++q) {
         e = hipMalloc((void **)&b->d_gmax[q], cvp::group_max_cells(probs[q].G) * sizeof(unsigned));
         probs[q].gmax = b->d_gmax[q];
     }
+    // room for the members' transposed volumes (up to kTableBytes)
+    int64_t volumes = 0;
+    for (int q = 0; q < n; ++q) volumes += geoms[q]->nvox * (int64_t)sizeof(float);
+    b->vt = e == hipSuccess && volumes <= kTableBytes;
+    for (int q = 0; q < n && b->vt; ++q) {
+        void *t = nullptr;
+        b->vt = hipMalloc(&t, geoms[q]->nvox * sizeof(float)) == hipSuccess;
+        if (b->vt) b->d_own.push_back(t);
+        probs[q].vt = static_cast<float *>(t);
+    }
+    if (!b->vt) (void)hipGetLastError();
+    for (int q = 0; q < n; ++q) b->vts.push_back(b->vt ? probs[q].vt : nullptr);
     if (e == hipSuccess) e = hipMemcpy(b->d_probs, probs.data(), n * sizeof(cvp::BatchProblem), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(b->d_ptab, &pt, sizeof(pt), hipMemcpyHostToDevice);
     if (e != hipSuccess) { cvp_batch_destroy(b); return device_fail(e, "batch tables"); }
-    b->pgrid = cus * cvp::batched_blocks_per_cu(false, b->plds, 16, 8, b->cached);
+    b->pgrid = cus * cvp::batched_blocks_per_cu(false, b->plds, 16, 8, b->cached, b->vt);
     *out = b;
     return ok();
 }
@@ -1075,7 +1374,7 @@ static cvp_status batched(const cvp_batch *b, const cvp_options *o, const float 
     if (!o) return fail(CVP_E_INVALID, "options is NULL");
     if (!ins || !outs) return fail(CVP_E_INVALID, "pointer array is NULL");
     if (o->variant == CVP_TT) return fail(CVP_E_UNSUPPORTED, "the batched launches run the cutting voxel projector only");
-    if (b->cached)
+    if (!b->rtabs.empty())
         for (int q = 0; q < b->n; ++q)
             if (b->geoms[q]->d_rtab != b->rtabs[q])
                 return fail(CVP_E_INVALID, "problem %d: its record table changed since cvp_batch_create "
@@ -1095,8 +1394,10 @@ static cvp_status batched(const cvp_batch *b, const cvp_options *o, const float 
     if (!backward) {
         // per-group maxima of every volume, for the projection items' scales
         for (int q = 0; q < b->n; ++q) {
-            hipError_t e = cvp::launch_group_max(b->geoms[q]->base, ins[q], b->d_gmax[q], (hipStream_t)stream,
-                                                 io.stop[q]);
+            hipError_t e = b->vt ? cvp::launch_transpose_max(b->geoms[q]->base, ins[q], b->vts[q], b->d_gmax[q],
+                                                             (hipStream_t)stream, io.stop[q])
+                                 : cvp::launch_group_max(b->geoms[q]->base, ins[q], b->d_gmax[q], (hipStream_t)stream,
+                                                         io.stop[q]);
             if (e != hipSuccess) return device_fail(e, "batched group maxima");
         }
     }
@@ -1104,14 +1405,14 @@ static cvp_status batched(const cvp_batch *b, const cvp_options *o, const float 
     hipError_t e = hipSuccess;
     if (!backward) {
         e = cvp::launch_batched(false, b->d_probs, b->d_ptab, b->d_counter, io, ex, ec, b->pgrid, b->plds, 16, 8,
-                                b->cached, (hipStream_t)stream);
+                                b->cached, b->vt, (hipStream_t)stream);
     } else {
         static const int kGw[3] = {16, 8, 4};
         for (int gi = 0; gi < 6 && e == hipSuccess; ++gi)
             if (b->d_btab[gi])
                 e = cvp::launch_batched(true, b->d_probs, b->d_btab[gi], b->d_counter + 1 + gi, io, ex, ec,
                                         b->bgrid[gi], b->blds[gi], kGw[gi % 3], gi < 3 ? 4 : 8, b->cached,
-                                        (hipStream_t)stream);
+                                        b->vt, (hipStream_t)stream);
     }
     if (e != hipSuccess) return device_fail(e, "batched launch");
     return ok();
@@ -1152,8 +1453,10 @@ static cvp_status cgls_args(const cvp_geometry *g, const cvp_options *o, const v
     return prepare(g, o, x, const_cast<void *>(r), G);
 }
 
-cvp_status cvp_cgls_start(const cvp_geometry *g, const cvp_options *o, const float *d_b, float *d_x,
-                          float *d_r, float *d_s, float *d_p, float *d_q, void *d_work, void *stream)
+
+cvp_status cvp_cgls_start_ws(const cvp_geometry *g, const cvp_options *o, const float *d_b, float *d_x,
+                             float *d_r, float *d_s, float *d_p, float *d_q, void *d_work, void *op_work,
+                             int64_t op_bytes, void *stream)
 {
     cvp::DevGeom G;
     if (!d_b) return fail(CVP_E_INVALID, "b is NULL");
@@ -1166,17 +1469,24 @@ cvp_status cvp_cgls_start(const cvp_geometry *g, const cvp_options *o, const flo
     const bool ec = o->elevation_correction != 0;
     // s (volume sized) is free until A^T r: it holds the projection's
     // per-group maxima
-    hipError_t e = cvp::launch_project(G, g->pl, ex, ec, d_x, d_q, (unsigned *)d_s, sm);
+    hipError_t e = run_project(g, G, g->pl, ex, ec, d_x, d_q, (unsigned *)d_s, op_work, op_bytes, sm);
     if (e == hipSuccess) e = cvp::blas_residual(d_r, d_b, d_q, g->npix, sm);
-    if (e == hipSuccess) e = cvp::launch_backproject(G, back_plan(g, G), ex, ec, d_r, d_s, sm);
+    if (e == hipSuccess) e = run_backproject(g, G, ex, ec, d_r, d_s, op_work, op_bytes, sm);
     if (e == hipSuccess) e = cvp::blas_update_p(d_p, d_s, g->nvox, sc, 1, sm);
     if (e == hipSuccess) e = cvp::blas_dot(d_s, d_s, g->nvox, part, sc, 0, nullptr, sm);
     if (e != hipSuccess) return device_fail(e, "cgls start");
     return ok();
 }
 
-cvp_status cvp_cgls_iterate(const cvp_geometry *g, const cvp_options *o, int32_t n_iter, float *d_x,
-                            float *d_r, float *d_s, float *d_p, float *d_q, void *d_work, void *stream)
+cvp_status cvp_cgls_start(const cvp_geometry *g, const cvp_options *o, const float *d_b, float *d_x,
+                          float *d_r, float *d_s, float *d_p, float *d_q, void *d_work, void *stream)
+{
+    return cvp_cgls_start_ws(g, o, d_b, d_x, d_r, d_s, d_p, d_q, d_work, nullptr, 0, stream);
+}
+
+cvp_status cvp_cgls_iterate_ws(const cvp_geometry *g, const cvp_options *o, int32_t n_iter, float *d_x,
+                               float *d_r, float *d_s, float *d_p, float *d_q, void *d_work, void *op_work,
+                               int64_t op_bytes, void *stream)
 {
     cvp::DevGeom G;
     if (n_iter < 0) return fail(CVP_E_INVALID, "n_iter = %d", n_iter);
@@ -1191,15 +1501,21 @@ cvp_status cvp_cgls_iterate(const cvp_geometry *g, const cvp_options *o, int32_t
     const double *stop = sc + cvp::kCglsStop;
     hipError_t e = hipSuccess;
     for (int it = 0; it < n_iter && e == hipSuccess; ++it) {
-        e = cvp::launch_project(G, g->pl, ex, ec, d_p, d_q, (unsigned *)d_s, sm, stop);       // q = A p (s free)
+        e = run_project(g, G, g->pl, ex, ec, d_p, d_q, (unsigned *)d_s, op_work, op_bytes, sm, stop);   // q = A p (s free)
         if (e == hipSuccess) e = cvp::blas_dot(d_q, d_q, g->npix, part, sc, 1, nullptr, sm, stop);   // alpha
         if (e == hipSuccess) e = cvp::blas_update_xr(d_x, d_p, g->nvox, d_r, d_q, g->npix, sc, part, sm, stop);
-        if (e == hipSuccess) e = cvp::launch_backproject(G, back_plan(g, G), ex, ec, d_r, d_s, sm, stop);   // s = A^T r
+        if (e == hipSuccess) e = run_backproject(g, G, ex, ec, d_r, d_s, op_work, op_bytes, sm, stop);   // s = A^T r
         if (e == hipSuccess) e = cvp::blas_dot(d_s, d_s, g->nvox, part, sc, 2, nullptr, sm, stop);   // beta
         if (e == hipSuccess) e = cvp::blas_update_p(d_p, d_s, g->nvox, sc, 0, sm, stop);           // p
     }
     if (e != hipSuccess) return device_fail(e, "cgls iterate");
     return ok();
+}
+
+cvp_status cvp_cgls_iterate(const cvp_geometry *g, const cvp_options *o, int32_t n_iter, float *d_x,
+                            float *d_r, float *d_s, float *d_p, float *d_q, void *d_work, void *stream)
+{
+    return cvp_cgls_iterate_ws(g, o, n_iter, d_x, d_r, d_s, d_p, d_q, d_work, nullptr, 0, stream);
 }
 
 // Batched CGLS: the single-problem recurrences per problem, each operator
@@ -1307,8 +1623,8 @@ cvp_status cvp_cgls_batched_iterate(const cvp_batch *bt, const cvp_options *o, i
 
 static int subset_count(int V, int T, int t) { return (V - t + T - 1) / T; }
 
-cvp_status cvp_sart_setup(const cvp_geometry *g, const cvp_options *o, int32_t n_subsets, float *d_rowsum,
-                          float *d_colsum, float *d_q, void *stream)
+cvp_status cvp_sart_setup_ws(const cvp_geometry *g, const cvp_options *o, int32_t n_subsets, float *d_rowsum,
+                             float *d_colsum, float *d_q, void *op_work, int64_t op_bytes, void *stream)
 {
     cvp::DevGeom G;
     if (!d_colsum || !d_q) return fail(CVP_E_INVALID, "colsum or q is NULL");
@@ -1322,21 +1638,28 @@ cvp_status cvp_sart_setup(const cvp_geometry *g, const cvp_options *o, int32_t n
     const bool ec = o->elevation_correction != 0;
     // R = A 1 (all views), C_t = A_t^T 1 (views t, t + T, ...)
     hipError_t e = cvp::blas_fill(d_colsum, g->nvox, 1.0f, sm);
-    if (e == hipSuccess) e = cvp::launch_project(G, g->pl, ex, ec, d_colsum, d_rowsum, nullptr, sm);
+    if (e == hipSuccess) e = run_project(g, G, g->pl, ex, ec, d_colsum, d_rowsum, nullptr, op_work, op_bytes, sm);
     if (e == hipSuccess) e = cvp::blas_fill(d_q, g->npix, 1.0f, sm);
     for (int t = 0; t < n_subsets && e == hipSuccess; ++t) {
         cvp::DevGeom Gt = G;
         int64_t off = 0;
         view_subset(g, t, n_subsets, subset_count(V, n_subsets, t), Gt, off);
-        e = cvp::launch_backproject(Gt, back_plan(g, Gt), ex, ec, d_q + off, d_colsum + (size_t)t * g->nvox, sm);
+        e = run_backproject(g, Gt, ex, ec, d_q + off, d_colsum + (size_t)t * g->nvox, op_work, op_bytes, sm);
     }
     if (e != hipSuccess) return device_fail(e, "sart setup");
     return ok();
 }
 
-cvp_status cvp_sart_iterate(const cvp_geometry *g, const cvp_options *o, int32_t n_subsets, int32_t n_sweeps,
-                            float lambda, int32_t nonneg, const float *d_b, float *d_x, const float *d_rowsum,
-                            const float *d_colsum, float *d_q, float *d_z, void *stream)
+cvp_status cvp_sart_setup(const cvp_geometry *g, const cvp_options *o, int32_t n_subsets, float *d_rowsum,
+                          float *d_colsum, float *d_q, void *stream)
+{
+    return cvp_sart_setup_ws(g, o, n_subsets, d_rowsum, d_colsum, d_q, nullptr, 0, stream);
+}
+
+cvp_status cvp_sart_iterate_ws(const cvp_geometry *g, const cvp_options *o, int32_t n_subsets, int32_t n_sweeps,
+                               float lambda, int32_t nonneg, const float *d_b, float *d_x, const float *d_rowsum,
+                               const float *d_colsum, float *d_q, float *d_z, void *op_work, int64_t op_bytes,
+                               void *stream)
 {
     cvp::DevGeom G;
     if (!d_b || !d_rowsum || !d_colsum || !d_q || !d_z) return fail(CVP_E_INVALID, "NULL pointer");
@@ -1360,18 +1683,26 @@ cvp_status cvp_sart_iterate(const cvp_geometry *g, const cvp_options *o, int32_t
             const int cnt = subset_count(V, n_subsets, t);
             view_subset(g, t, n_subsets, cnt, Gt, off);
             cvp::ProjLaunch pl{};
-            cvp::plan_projection(G.N, G.n2, G.M, cnt, g->pmax, g->pl.U, pl);
+            cvp::plan_projection(G, cnt, g->pmax, g->pl.U, pl);
             // q_t = A_t x (z is free: it holds the per-group maxima)
-            e = cvp::launch_project(Gt, pl, ex, ec, d_x, d_q + off, (unsigned *)d_z, sm);
+            e = run_project(g, Gt, pl, ex, ec, d_x, d_q + off, (unsigned *)d_z, op_work, op_bytes, sm);
             if (e == hipSuccess)
                 e = cvp::sart_residual_views(d_q + off, d_b + off, d_rowsum + off, nm, cnt, nm * n_subsets, sm);
-            if (e == hipSuccess) e = cvp::launch_backproject(Gt, back_plan(g, Gt), ex, ec, d_q + off, d_z, sm);
+            if (e == hipSuccess) e = run_backproject(g, Gt, ex, ec, d_q + off, d_z, op_work, op_bytes, sm);
             if (e == hipSuccess)
                 e = cvp::sart_update_x(d_x, d_z, d_colsum + (size_t)t * g->nvox, g->nvox, lambda, nonneg != 0, sm);
         }
     }
     if (e != hipSuccess) return device_fail(e, "sart iterate");
     return ok();
+}
+
+cvp_status cvp_sart_iterate(const cvp_geometry *g, const cvp_options *o, int32_t n_subsets, int32_t n_sweeps,
+                            float lambda, int32_t nonneg, const float *d_b, float *d_x, const float *d_rowsum,
+                            const float *d_colsum, float *d_q, float *d_z, void *stream)
+{
+    return cvp_sart_iterate_ws(g, o, n_subsets, n_sweeps, lambda, nonneg, d_b, d_x, d_rowsum, d_colsum, d_q, d_z, nullptr,
+                               0, stream);
 }
 
 // ------------------------------------------------------------------ LSQR
@@ -1399,8 +1730,9 @@ static cvp_status lsqr_args(const cvp_geometry *g, const cvp_options *o, const v
     return prepare(g, o, x, const_cast<void *>(u), G);
 }
 
-cvp_status cvp_lsqr_start(const cvp_geometry *g, const cvp_options *o, const float *d_b, float *d_x, float *d_u,
-                          float *d_v, float *d_w, float *d_q, float *d_s, void *d_work, void *stream)
+cvp_status cvp_lsqr_start_ws(const cvp_geometry *g, const cvp_options *o, const float *d_b, float *d_x, float *d_u,
+                             float *d_v, float *d_w, float *d_q, float *d_s, void *d_work, void *op_work,
+                             int64_t op_bytes, void *stream)
 {
     cvp::DevGeom G;
     if (!d_b) return fail(CVP_E_INVALID, "b is NULL");
@@ -1411,19 +1743,26 @@ cvp_status cvp_lsqr_start(const cvp_geometry *g, const cvp_options *o, const flo
     const int ex = model_of(o);
     const bool ec = o->elevation_correction != 0;
     // beta u = b - A x;  alpha v = A^T u;  w = v
-    hipError_t e = cvp::launch_project(G, g->pl, ex, ec, d_x, d_q, (unsigned *)d_s, sm);
+    hipError_t e = run_project(g, G, g->pl, ex, ec, d_x, d_q, (unsigned *)d_s, op_work, op_bytes, sm);
     if (e == hipSuccess) e = cvp::blas_residual(d_u, d_b, d_q, g->npix, sm);
     if (e == hipSuccess) e = cvp::lsqr_norm(d_u, g->npix, sc, cvp::kLsqrFinBeta0, sm);
     if (e == hipSuccess) e = cvp::lsqr_scale(d_u, g->npix, sc, cvp::kLsqrBeta, sm);
-    if (e == hipSuccess) e = cvp::launch_backproject(G, back_plan(g, G), ex, ec, d_u, d_v, sm);
+    if (e == hipSuccess) e = run_backproject(g, G, ex, ec, d_u, d_v, op_work, op_bytes, sm);
     if (e == hipSuccess) e = cvp::lsqr_norm(d_v, g->nvox, sc, cvp::kLsqrFinAlpha0, sm);
     if (e == hipSuccess) e = cvp::lsqr_update_vxw(d_v, d_x, d_w, g->nvox, sc, 1, sm);
     if (e != hipSuccess) return device_fail(e, "lsqr start");
     return ok();
 }
 
-cvp_status cvp_lsqr_iterate(const cvp_geometry *g, const cvp_options *o, int32_t n_iter, float *d_x, float *d_u,
-                            float *d_v, float *d_w, float *d_q, float *d_s, void *d_work, void *stream)
+cvp_status cvp_lsqr_start(const cvp_geometry *g, const cvp_options *o, const float *d_b, float *d_x, float *d_u,
+                          float *d_v, float *d_w, float *d_q, float *d_s, void *d_work, void *stream)
+{
+    return cvp_lsqr_start_ws(g, o, d_b, d_x, d_u, d_v, d_w, d_q, d_s, d_work, nullptr, 0, stream);
+}
+
+cvp_status cvp_lsqr_iterate_ws(const cvp_geometry *g, const cvp_options *o, int32_t n_iter, float *d_x, float *d_u,
+                               float *d_v, float *d_w, float *d_q, float *d_s, void *d_work, void *op_work,
+                               int64_t op_bytes, void *stream)
 {
     cvp::DevGeom G;
     if (n_iter < 0) return fail(CVP_E_INVALID, "n_iter = %d", n_iter);
@@ -1435,15 +1774,21 @@ cvp_status cvp_lsqr_iterate(const cvp_geometry *g, const cvp_options *o, int32_t
     const bool ec = o->elevation_correction != 0;
     hipError_t e = hipSuccess;
     for (int it = 0; it < n_iter && e == hipSuccess; ++it) {
-        e = cvp::launch_project(G, g->pl, ex, ec, d_v, d_q, (unsigned *)d_s, sm);                 // q = A v
+        e = run_project(g, G, g->pl, ex, ec, d_v, d_q, (unsigned *)d_s, op_work, op_bytes, sm);          // q = A v
         if (e == hipSuccess) e = cvp::lsqr_axpby_norm(d_u, d_q, g->npix, sc, cvp::kLsqrAlpha, cvp::kLsqrFinBeta, sm);
         if (e == hipSuccess) e = cvp::lsqr_scale(d_u, g->npix, sc, cvp::kLsqrBeta, sm);           // u /= beta
-        if (e == hipSuccess) e = cvp::launch_backproject(G, back_plan(g, G), ex, ec, d_u, d_s, sm);          // s = A^T u
+        if (e == hipSuccess) e = run_backproject(g, G, ex, ec, d_u, d_s, op_work, op_bytes, sm);             // s = A^T u
         if (e == hipSuccess) e = cvp::lsqr_axpby_norm(d_v, d_s, g->nvox, sc, cvp::kLsqrBeta, cvp::kLsqrFinAlpha, sm);
         if (e == hipSuccess) e = cvp::lsqr_update_vxw(d_v, d_x, d_w, g->nvox, sc, 0, sm);       // v, x, w
     }
     if (e != hipSuccess) return device_fail(e, "lsqr iterate");
     return ok();
+}
+
+cvp_status cvp_lsqr_iterate(const cvp_geometry *g, const cvp_options *o, int32_t n_iter, float *d_x, float *d_u,
+                            float *d_v, float *d_w, float *d_q, float *d_s, void *d_work, void *stream)
+{
+    return cvp_lsqr_iterate_ws(g, o, n_iter, d_x, d_u, d_v, d_w, d_q, d_s, d_work, nullptr, 0, stream);
 }
 
 cvp_status cvp_cgls_set_tolerance(void *d_work, double rho_tol, double gamma_ref, void *stream)

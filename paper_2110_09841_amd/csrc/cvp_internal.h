@@ -63,14 +63,26 @@ struct DevGeom {
     double wsum_bound, wsum_bound_raw;   // a pixel's summed weight per unit |mu|
     double wone_bound, wone_bound_raw;   // one (voxel, pixel) weight per unit |mu|
     // The geometry's cached piece records (nullptr: the kernels compute
-    // their own): rtab[((q n2 + j) n1 + i) pmax + s][kRecFloats] and the
-    // piece counts rtab_n[(q n2 + j) n1 + i] of column (i, j) in view q of
-    // the launch (q * vstride, from the launch's first view), pieces clipped
-    // to the detector columns; rtab_pmax slots per column.
+    // their own): rtab[((t n2 + j) n1 + i) pmax + s][kRecFloats] and the
+    // piece counts rtab_n[(t n2 + j) n1 + i] of column (i, j) in view q of
+    // the launch, t = q * rtab_vs (from the launch's first view; rtab_vs is
+    // the view stride for a geometry's whole table, 1 for a table made for
+    // the launch), pieces clipped to the detector columns; rtab_pmax slots
+    // per column.
     const float *rtab;
     const int *rtab_n;
     int rtab_pmax;
+    int rtab_vs;
+    int rpad;            // most rows of a straight-line (fixed row count) piece, and the spare rows its
+                         // kernels keep beyond each detector edge (<= kFixedRowsMax)
 };
+
+// Fixed row counts: a piece whose chi2 extent with its elevation-correction
+// margin is at most R - 1 rows touches at most R rows, and the kernels then
+// evaluate R rows for every lane without a loop.  piece_record stores the
+// count (0: none) above the detector column in the record's word 0, bits
+// 16..19 with the elevation correction, 20..22 without.
+constexpr int kFixedRowsMax = 6;
 
 struct ProjLaunch {
     int U;           // detector columns per band
@@ -78,6 +90,7 @@ struct ProjLaunch {
     int items;       // nbands * nviews
     int chunk;       // work-item slots per XCD (grid = 8 * chunk)
     int pmax;        // 4 or 8 (8 with U <= 8 for wider footprints)
+    int pad;         // spare rows at each end of a band column (the geometry's rpad, or 0 if they do not fit)
     size_t lds;      // dynamic LDS bytes
 };
 
@@ -102,6 +115,7 @@ struct BatchProblem {        // device table entry (one per problem)
     DevGeom G;
     int U;                   // projection band width
     int pitems;              // projection work items
+    int pad;                 // spare rows of a band column
     int pmax;                // the problem's projection piece stride (its own plan),
     int gw;                  // the batch's backprojection stack width,
     int kp;                  // passes per stack
@@ -112,6 +126,7 @@ struct BatchProblem {        // device table entry (one per problem)
     const float *in;         // set per call by batch_setup
     float *out;
     unsigned *gmax;          // the problem's per-group maxima (owned by the batch)
+    float *vt;               // its transposed volume (owned by the batch), or nullptr
     const double *stop;      // set per call: the problem's work items are skipped while *stop != 0
 };
 
@@ -131,11 +146,12 @@ struct BatchIO {             // per call, by value
 };
 
 // gw, pmax: the backprojection launch's stack width (16, 8 or 4) and piece
-// stride (4 or 8); cached: every member reads its geometry's cached records
+// stride (4 or 8); cached: every member reads a table of records; vt: the
+// projection reads the members' transposed volumes
 hipError_t launch_batched(bool backward, BatchProblem *probs, const BatchTable *tab, int *counter,
                           const BatchIO &io, bool exact, bool ec, int grid, size_t lds, int gw, int pmax, bool cached,
-                          hipStream_t s);
-int batched_blocks_per_cu(bool backward, size_t lds, int gw, int pmax, bool cached);
+                          bool vt, hipStream_t s);
+int batched_blocks_per_cu(bool backward, size_t lds, int gw, int pmax, bool cached, bool vt);
 size_t project_lds_bytes(int U, int N, int n2, int pmax);
 size_t backproject_lds_bytes(int gw, int pmax, int winCap);
 
@@ -178,11 +194,15 @@ hipError_t blas_update_p(float *p, const float *sv, int64_t n, const double *sc,
 hipError_t blas_set_tolerance(double *sc, double tol2, double ref, hipStream_t s);
 hipError_t blas_residual(float *r, const float *b, const float *q, int64_t n, hipStream_t s);
 
-// gmax: device scratch of group_max_cells(g) words for the per-group maxima
-// of |vol| (computed by the call), or nullptr (the kernel scans the wedges).
+// gmax: the per-group maxima of |vol| (launch_group_max or
+// launch_transpose_max), or nullptr (the kernel scans the wedges).  vt: with
+// gmax, the transposed volume (launch_transpose_max) that the kernel then
+// reads, or nullptr (it reads vol).  The same bits in every case.
 hipError_t launch_project(const DevGeom &g, const ProjLaunch &L, int model, bool ec,
-                          const float *vol, float *proj, unsigned *gmax, hipStream_t stream,
+                          const float *vol, float *proj, const unsigned *gmax, const float *vt, hipStream_t stream,
                           const double *stop = nullptr);
+hipError_t launch_transpose_max(const DevGeom &g, const float *vol, float *vt, unsigned *gmax, hipStream_t stream,
+                                const double *stop = nullptr);
 int64_t group_max_cells(const DevGeom &g);
 hipError_t launch_group_max(const DevGeom &g, const float *vol, unsigned *gmax, hipStream_t stream,
                             const double *stop = nullptr);
@@ -193,9 +213,22 @@ constexpr int64_t kStaticScratchWords = int64_t(1) << 18;
 hipError_t static_scratch(unsigned **out);
 // SiddonK reference projector: K x K rays per pixel, exact chord lengths.
 hipError_t launch_siddon(const DevGeom &g, int K, const float *vol, float *proj, hipStream_t s);
-// Fills a geometry's record table (every view, every column; pmax 4 or 8).
-hipError_t launch_record_table(const DevGeom &g, int pmax, float *rec, int *cnt, hipStream_t stream);
+// Fills the record table of g's views (every column; pmax 4 or 8; tt: TT
+// footprints).
+hipError_t launch_record_table(const DevGeom &g, int pmax, bool tt, float *rec, int *cnt, hipStream_t stream,
+                               const double *stop = nullptr);
+// part: the sums of a backprojection taken over several launches, each over
+// the next views of it (a multiple of kWaves views in all but the last):
+// back_part_floats(L) floats, read unless this is the first launch, written
+// (and vol left alone) unless it is the last.  The sums are then the bits of
+// one launch over all views.
+struct BackPart {
+    float *sums = nullptr;
+    bool first = true, last = true;
+};
+constexpr int64_t back_part_floats(const BackLaunch &L) { return (int64_t)L.items * kWaves * kBackPasses * L.gw * kWave; }
 hipError_t launch_backproject(const DevGeom &g, const BackLaunch &L, int model, bool ec,
-                              const float *proj, float *vol, hipStream_t stream, const double *stop = nullptr);
+                              const float *proj, float *vol, hipStream_t stream, const double *stop = nullptr,
+                              const BackPart &part = BackPart());
 
 }  // namespace cvp

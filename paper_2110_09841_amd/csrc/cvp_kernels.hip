@@ -37,6 +37,15 @@
 
 #include "cvp_internal.h"
 
+// The file is compiled in parts, in parallel: 0 projection, record tables and
+// scratch, 1 backprojection, 2 batched launches (all of them without
+// CVP_PART).
+#ifdef CVP_PART
+#define CVP_HAS(p) (CVP_PART == (p))
+#else
+#define CVP_HAS(p) 1
+#endif
+
 namespace cvp {
 namespace {
 
@@ -156,7 +165,8 @@ __device__ __forceinline__ Mom column_prefix(const DevGeom &G, const ViewGeom &V
 }
 
 // Record of one cut piece H_u for the FP32 voxel stage (12 floats):
-//  [0] u (int bits)  [1] W = A_u * b2 D_u / f       [2] Y0 hi   [3] Y0 lo
+//  [0] u and the fixed row counts (int bits)
+//  [1] W = A_u * b2 D_u / f                         [2] Y0 hi   [3] Y0 lo
 //  [4] beta hi       [5] beta lo   [6] beta          [7] rho = h/D (EC)
 //  [8] R^2 of the column centre (x1x2 part of r^2, relaxed form)
 //  [9] b2 D_u / f (mm of x3 per row)  [10] EC row margin factor
@@ -194,7 +204,6 @@ __device__ __forceinline__ void piece_record(const DevGeom &G, const ViewGeom &V
     const double bh = rint(beta * 1024.0) * (1.0 / 1024.0);
     const double p1 = C.xc1 + cx - V.s1, p2 = C.xc2 + cy - V.s2;   // cut centroid
     const double q1 = C.xc1 - V.s1, q2 = C.xc2 - V.s2;             // column centre
-    rec[0] = __int_as_float(u);
     rec[1] = (A > 1e-12 * G.a1 * G.a2) ? (float)(A * gmm) : 0.0f;
     rec[2] = (float)Y0h;
     rec[3] = (float)(Y0 - Y0h);
@@ -209,7 +218,21 @@ __device__ __forceinline__ void piece_record(const DevGeom &G, const ViewGeom &V
     const double rho32 = (double)rec[7];
     rec[10] = (float)(1.01 * rho32 / fmax(1.0 - rho32, 0.05));
     rec[11] = (float)(p1 * p1 + p2 * p2);
+    // rows the extent [Y, Y + beta] can touch, wherever it lies, widened on
+    // both sides by the box half-width at any boundary of the detector and
+    // by the FP32 rounding of Y (see fixed_start)
+    const double md = fmax(fmax(V.c2 + 0.5, G.N - 0.5 - V.c2), 0.0);
+    const double need0 = ceil(beta + 1.006), need1 = ceil(beta + 2.004 * rho32 * md + 1.006);
+    const int r0 = need0 <= G.rpad ? (int)need0 : 0;
+    const int r1 = need1 <= G.rpad && rho32 < 0.9 ? (int)need1 : 0;
+    rec[0] = __int_as_float(u | (r1 << 16) | (r0 << 20));
 }
+
+// Detector column and fixed row count (0: general row loop) of a record's
+// word 0.
+__device__ __forceinline__ int rec_col(int word) { return word & 0xffff; }
+template <bool EC>
+__device__ __forceinline__ int rec_rows(int word) { return EC ? (word >> 16) & 15 : (word >> 20) & 7; }
 
 // Record of the TT separable footprint (the footprint projector the paper
 // compares with, Sec. I and IV: Long, Fessler & Balter 2010) of column C at
@@ -355,6 +378,17 @@ __device__ __forceinline__ void lds_add_fixed(unsigned long long *p, float w)
     __hip_atomic_fetch_add(p, q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
+// The same for the product of a weight and a coefficient (already scaled),
+// taken in FP64 by the fused multiply-add that also rounds it.
+__device__ __forceinline__ void lds_add_fixed(unsigned long long *p, float w, double coef)
+{
+    const double d = fma((double)w, coef, 0x1.8p52);
+    const unsigned hi = (unsigned)__double2hiint(d) - 0x43380000u;
+    const unsigned lo = (unsigned)__double2loint(d);
+    const unsigned long long q = ((unsigned long long)hi << 32) | lo;
+    __hip_atomic_fetch_add(p, q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
 __device__ __forceinline__ double fixed_to_double(unsigned long long q)
 {
     return (double)(int)(unsigned)(q >> 32) * 0x1p32 + (double)(unsigned)q;
@@ -407,6 +441,136 @@ __device__ __forceinline__ void row_range(float Ytop, float beta, float mfac, fl
     vlo = max(vlo, 0);
     vhi = min(vhi, N - 1);
 }
+
+// Row weights with a fixed row count R (rec_rows): rows v0 .. v0 + R - 1, v0 =
+// floor(fixed_start - k beta), hold the whole extent and its box averages, so
+// only the R - 1 boundaries between them are evaluated.  With the face
+// offsets s1 = Ytop - t, s0 = Ybot - t of boundary (s0 - s1 = beta) the plain
+// share of the first row is med3(-s1, 0, beta) at its lower boundary, of the
+// last one med3(s0, 0, beta) at its upper one, and of a row between two
+// boundaries t, t + 1 max(min(s0, -s1', beta, 1), 0) (s1' at t + 1); Phi(t)
+// moves weight across each boundary.  Every share is one face offset or the
+// whole extent, so slivers keep their relative precision as in boundary.
+// There is no loop, row count or clipping per lane; rows beyond the detector
+// are spare rows of the band image or zero rows of the window.  The row loop
+// (sweep_rows) spends more on its set-up and on lanes waiting for the longest
+// of 64 than on the rows: a two-row piece takes 32 VALU instructions in the
+// projection (25 in the backprojection) instead of about 85.  Weights differ
+// from those of the row loop by rounding only.
+//
+// fixed_start: Y0 + 1/2 less the largest box half-width at a row boundary of
+// the detector (md = the largest |t - c2|) and 2.5e-3 for the FP32 rounding
+// of the sum (below 1.7e-3 for positions up to 8000 rows).
+template <bool EC>
+__device__ __forceinline__ float fixed_start(float Y0h, float Y0l, float rho, float md)
+{
+    return (Y0h + Y0l) + (EC ? fmaf(-rho, md, 0.4975f) : 0.4975f);
+}
+
+// Values of a piece that its voxels share.  The boundary v0 + 1/2 has the
+// face offset Yhm - v0 (exact on the 2^-10 grid) with Yhm the high part of
+// the top face less 1/2, and four times the box half-width |v0 r4 - k4|.
+struct FixedPiece {
+    float ys;            // fixed_start
+    float y0m, y0l;      // top face of voxel 0: high part - 1/2, low part
+    float bh, bl, beta;  // step per slice: high part, low part, whole
+    float m1;            // min(beta, 1)
+    float r4, k4;        // 4 rho, 4 rho (c2 - 1/2)
+};
+
+template <bool EC>
+__device__ __forceinline__ FixedPiece fixed_piece(float Y0h, float Y0l, float bh, float bl, float beta, float rho,
+                                                  float c2f, float md)
+{
+    FixedPiece P;
+    P.ys = fixed_start<EC>(Y0h, Y0l, rho, md);
+    P.y0m = Y0h - 0.5f;
+    P.y0l = Y0l;
+    P.bh = bh; P.bl = bl; P.beta = beta;
+    P.m1 = fminf(beta, 1.0f);
+    P.r4 = 4.0f * rho;
+    P.k4 = P.r4 * (c2f - 0.5f);
+    return P;
+}
+
+// w[j]: weight of row v0 + j of slice kf (times 1/r^2 at the cut centroid in
+// the exact form: zt, r8, r9).
+template <int R, bool EC, bool EXACT>
+__device__ __forceinline__ void fixed_rows(const FixedPiece &P, float v0, float kf, bool raw, float zt, float r8,
+                                           float r9, float *w)
+{
+    const float Yl = fmaf(-kf, P.bl, P.y0l), Ybl = Yl + P.bl;
+    float d = fmaf(-kf, P.bh, P.y0m) - v0, d0 = d + P.bh;
+    float s1[R + 1], s0[R + 1];
+#pragma unroll
+    for (int j = 1; j < R; ++j) {
+        s1[j] = d + Yl;
+        s0[j] = d0 + Ybl;
+        d -= 1.0f;
+        d0 -= 1.0f;
+    }
+    w[0] = __builtin_amdgcn_fmed3f(-s1[1], 0.0f, P.beta);
+#pragma unroll
+    for (int j = 1; j < R - 1; ++j) w[j] = fmaxf(fminf(fminf(s0[j], -s1[j + 1]), P.m1), 0.0f);
+    w[R - 1] = __builtin_amdgcn_fmed3f(s0[R - 1], 0.0f, P.beta);
+    if (EC) {
+        float e4 = fmaf(v0, P.r4, -P.k4);             // +-4e at the first boundary
+#pragma unroll
+        for (int j = 1; j < R; ++j) {
+            // with R <= 3 the box half-width is below 1, so p <= 1 (the
+            // output clamp of the subtraction); where e = 0 both p are 0
+            const float q0 = fmaf(fabsf(e4), 0.25f, -fabsf(s0[j])), q1 = fmaf(fabsf(e4), 0.25f, -fabsf(s1[j]));
+            const float p0 = R <= 3 ? __builtin_amdgcn_fmed3f(q0, 0.0f, 1.0f) : fmaxf(q0, 0.0f);
+            const float p1 = R <= 3 ? __builtin_amdgcn_fmed3f(q1, 0.0f, 1.0f) : fmaxf(q1, 0.0f);
+            const float phi = fmaf(p0, p0, -(p1 * p1)) * __builtin_amdgcn_rcpf(fmaxf(fabsf(e4), 1e-30f));
+            w[j - 1] -= phi;
+            w[j] += phi;
+            e4 += P.r4;
+        }
+    }
+    if (EXACT && !raw) {
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            const float lo = j == 0 ? 0.0f : fmaxf(0.0f, -s1[j]);
+            const float hi = j == R - 1 ? P.beta : fminf(P.beta, -s1[j + 1]);
+            const float mm = fminf(fmaxf(0.5f * (lo + hi), 0.0f), P.beta);
+            const float zb = fmaf(-mm, r9, zt);
+            w[j] *= __builtin_amdgcn_rcpf(fmaf(zb, zb, r8));
+        }
+    }
+}
+
+// Largest |t - c2| of the detector's row boundaries (fixed_start).
+__device__ __forceinline__ float detector_reach(float c2f, int N)
+{
+    return 1.001f * fmaxf(fmaxf(c2f + 0.5f, (float)N - 0.5f - c2f), 0.0f);
+}
+
+// Calls f with R = r as a compile-time constant (2 <= r <= kFixedRowsMax, the
+// same in every lane).
+template <class F>
+__device__ __forceinline__ void with_rows(int r, F &&f)
+{
+    switch (r) {
+    case 2: f(std::integral_constant<int, 2>{}); break;
+    case 3: f(std::integral_constant<int, 3>{}); break;
+    case 4: f(std::integral_constant<int, 4>{}); break;
+    case 5: f(std::integral_constant<int, 5>{}); break;
+    default: f(std::integral_constant<int, 6>{}); break;
+    }
+}
+
+// Keeps a uniform value in a vector register (an instruction reads only one
+// scalar one, so the compiler would copy it again for each use).
+__device__ __forceinline__ float in_vgpr(float x)
+{
+    asm("" : "+v"(x));
+    return x;
+}
+
+// N floats in consecutive registers; a uniform index selects one without
+// unrolling the loop over it.
+template <int N> struct FloatVec { typedef float type __attribute__((ext_vector_type(N))); };
 
 // Row weights of one voxel piece: rows [vlo, vhi] (already clipped) of the
 // unclipped range [vlo0, vhi0], added to the band column bcol.  The unclipped
@@ -590,10 +754,11 @@ __device__ __forceinline__ void build_records(const DevGeom &G, const ViewGeom &
 // arguments and operations are those of the kernels' own record stages
 // (u + 1/2 = (u + 1) - 1/2 exactly, no contraction), so the records are the
 // same bits and the kernels that read them give the same results.
-template <int PMAX>
+template <int PMAX, bool TT>
 __global__ void __launch_bounds__(kBlock)
-record_table_kernel(const DevGeom G, float *__restrict__ rec, int *__restrict__ cnt)
+record_table_kernel(const DevGeom G, float *__restrict__ rec, int *__restrict__ cnt, const double *__restrict__ stop)
 {
+    if (stop && *stop != 0.0) return;
     const int64_t ncols = (int64_t)G.n1 * G.n2;
     const int64_t idx = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (idx >= ncols * G.nviews) return;
@@ -607,15 +772,20 @@ record_table_kernel(const DevGeom G, float *__restrict__ rec, int *__restrict__ 
     const int n = min(max(ulast - ufirst + 1, 0), PMAX);
     cnt[idx] = n;
     float *out = rec + idx * PMAX * kRecFloats;
-    Mom lo = column_prefix(G, V, C, ufirst - 0.5);
+    Mom lo;
+    if (!TT) lo = column_prefix(G, V, C, ufirst - 0.5);
     for (int sl = 0; sl < n; ++sl) {
-        const Mom hi = column_prefix(G, V, C, (ufirst + sl) + 0.5);
         float r[kRecFloats];
-        piece_record<false, true>(G, V, C, ufirst + sl, lo, hi, r);
+        if constexpr (TT) {
+            tt_record(G, V, C, ufirst + sl, r);
+        } else {
+            const Mom hi = column_prefix(G, V, C, (ufirst + sl) + 0.5);
+            piece_record<false, true>(G, V, C, ufirst + sl, lo, hi, r);
+            lo = hi;
+        }
 #pragma unroll
         for (int e = 0; e < kRecFloats; e += 4)
             *reinterpret_cast<float4 *>(out + sl * kRecFloats + e) = make_float4(r[e], r[e + 1], r[e + 2], r[e + 3]);
-        lo = hi;
     }
 }
 
@@ -623,8 +793,10 @@ record_table_kernel(const DevGeom G, float *__restrict__ rec, int *__restrict__ 
 
 // One work item of the projection: detector-column band item / nviews of view
 // item % nviews.  smem holds the LDS layout described below.
-template <bool EXACT, bool EC, int PMAX, bool TT = false, bool TAB = false>
-__device__ __forceinline__ void project_item(const DevGeom &G, const int U, const int item,
+// VT: vol is the transposed copy of transpose_max_kernel ([n2][n1][n3]), else
+// the caller's volume ([n3][n2][n1]).
+template <bool EXACT, bool EC, int PMAX, bool TT, bool TAB, bool VT>
+__device__ __forceinline__ void project_item(const DevGeom &G, const int U, const int pad, const int item,
                                              float *smem, const float *__restrict__ vol,
                                              float *__restrict__ proj, const unsigned *__restrict__ gmax)
 {
@@ -633,11 +805,12 @@ __device__ __forceinline__ void project_item(const DevGeom &G, const int U, cons
     const int u0 = (item / G.nviews) * U;
     const int ub = min(u0 + U, G.M) - 1;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-    const int Npad = G.N | 1;
+    const int Npad = (G.N + 2 * pad) | 1;
     const int ngroups = (G.n1 + GW - 1) / GW;
 
-    // one fixed-point band image [U][Npad] shared by the four waves, then the
-    // row tables and a small reduction area
+    // one fixed-point band image [U][Npad] shared by the four waves (row v of
+    // a column at v + pad: spare rows for the fixed row counts at both ends),
+    // then the row tables and a small reduction area
     unsigned long long *bins = reinterpret_cast<unsigned long long *>(smem);
     int *rowStart = reinterpret_cast<int *>(bins + U * Npad);
     int *rowQ = rowStart + (G.n2 + 1);
@@ -709,8 +882,10 @@ __device__ __forceinline__ void project_item(const DevGeom &G, const int U, cons
     const int total = rowStart[G.n2];
 
     const float c2f = (float)V.c2;
+    const float md = detector_reach(c2f, G.N);
     const float a3f = (float)G.a3;
     const float zt0 = (float)(G.x3lo + G.a3 - V.s3);   // x3 of the top of voxel 0, minus s3
+    const float zc0 = zt0 - 0.5f * a3f;                // of its centre
     const bool raw = G.raw_volume != 0;
     const bool vec_rows = (G.n1 & 3) == 0 && (reinterpret_cast<uintptr_t>(vol) & 15) == 0;
 
@@ -755,7 +930,7 @@ __device__ __forceinline__ void project_item(const DevGeom &G, const int U, cons
             group(gi, j, i0);
             mxl = max(mxl, gmax[j * ngroups + i0 / GW]);
         }
-    } else {
+    } else if constexpr (!VT) {
         for (int gi = wave; gi < total; gi += kWaves) {
             int j, i0;
             group(gi, j, i0);
@@ -801,10 +976,10 @@ __device__ __forceinline__ void project_item(const DevGeom &G, const int U, cons
             const int c = lane & 15, slot = lane >> 4;
             const int i = i0 + c;
             if (i < G.n1) {
-                const size_t col = ((size_t)view * G.vstride * G.n2 + j) * G.n1 + i;
+                const size_t col = ((size_t)view * G.rtab_vs * G.n2 + j) * G.n1 + i;
                 const int nt = G.rtab_n[col];
                 const float *rc = G.rtab + col * G.rtab_pmax * kRecFloats;
-                const int uf = nt > 0 ? __float_as_int(rc[0]) : 0;
+                const int uf = nt > 0 ? rec_col(__float_as_int(rc[0])) : 0;
                 const int off = max(u0 - uf, 0);
                 ncol = min(max(min(nt, ub - uf + 1) - off, 0), PMAX);
 #pragma unroll
@@ -839,75 +1014,135 @@ __device__ __forceinline__ void project_item(const DevGeom &G, const int U, cons
         }
         if (__ballot(ncol > 0) == 0) continue;
         const bool full = vec_rows && (i0 + GW <= G.n1);
+        const unsigned cols = (unsigned)__ballot(ncol > 0) & 0xffffu;   // lanes 0..15: columns with pieces
 
-        // With cached records each lane takes KP slices (k and k + 64): one
-        // broadcast of a piece record then serves 64 KP voxels.
-        constexpr int KP = TAB ? 2 : 1;
-        for (int kc = 0; kc < G.n3; kc += kWave * KP) {
-            float mu[KP][GW];
-            float kf[KP], zt[KP], zc[KP];
-            bool kv[KP];
+        // A lane takes KH slices of a column (k, k + 64, ...), so a broadcast
+        // piece record serves 64 KH voxels.  From the transposed volume a
+        // column is one contiguous row of n3 values, loaded when its turn
+        // comes; from the caller's layout, where the 16 columns of a group
+        // share each 64-byte line, all of them are loaded at once (and fewer
+        // slices fit the registers).  The loops over columns, pieces and
+        // slices are not unrolled (the row-count variants would be repeated
+        // for each): their values are taken by uniform register indices.
+        constexpr int KH = VT ? 8 : 2, CW = VT ? 1 : GW;
+        for (int kc = 0; kc < G.n3; kc += kWave * KH) {
+            const int nh = min(KH, (G.n3 - kc + kWave - 1) / kWave);
+            const float kf0 = (float)(kc + lane);
+#pragma unroll 1
+            for (int cq = 0; cq < GW; cq += CW) {
+                if (VT && ((cols >> cq) & 1u) == 0) continue;
+                typename FloatVec<KH * CW>::type mu;
 #pragma unroll
-            for (int h = 0; h < KP; ++h) {
-                const int k = kc + h * kWave + lane;
-                kv[h] = k < G.n3;
-                load_mu(j, i0, k, full, mu[h]);
-                kf[h] = (float)k;
-                zt[h] = fmaf(kf[h], a3f, zt0);        // top of voxel k, relative to s3
-                zc[h] = zt[h] - 0.5f * a3f;           // centre of voxel k
-            }
-#pragma unroll
-            for (int c = 0; c < GW; ++c) {
-                const int np = __builtin_amdgcn_readlane(ncol, c);
-                if (np == 0) continue;
-                float base[KP];
-                bool any = false;
-#pragma unroll
-                for (int h = 0; h < KP; ++h) {
-                    base[h] = kv[h] ? mu[h][c] : 0.0f;
-                    any = any || base[h] != 0.0f;
-                }
-                if (__ballot(any) == 0) continue;
-                const float r8c = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(rq[0][8]), c));
-#pragma unroll
-                for (int h = 0; h < KP; ++h) {
-                    if (TT)   // the central ray's |r| (its min(a1/|r1|, a2/|r2|) is in the records)
-                        base[h] = base[h] * sqrtf(fmaf(zc[h], zc[h], r8c));
-                    else if (!EXACT && !raw)
-                        base[h] = base[h] * __builtin_amdgcn_rcpf(fmaf(zc[h], zc[h], r8c));
-                    base[h] = ldexpf(base[h], sc);
-                }
-                for (int p = 0; p < np; ++p) {
-                    const int src = c + 16 * (p & 3);
-                    float r[kRecFloats];
-                    if (PASSES == 1 || p < 4) {
-#pragma unroll
-                        for (int e = 0; e < kRecFloats; ++e)
-                            r[e] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(rq[0][e]), src));
+                for (int h = 0; h < KH; ++h) {
+                    const int k = kc + h * kWave + lane;
+                    if constexpr (VT) {
+                        if (h < nh) mu[h] = k < G.n3 ? vol[((size_t)j * G.n1 + i0 + cq) * G.n3 + k] : 0.0f;
                     } else {
+                        float t[GW];
+                        load_mu(j, i0, k, full, t);
 #pragma unroll
-                        for (int e = 0; e < kRecFloats; ++e)
-                            r[e] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(rq[PASSES - 1][e]), src));
+                        for (int c = 0; c < CW; ++c) mu[h * CW + c] = k < G.n3 ? t[c] : 0.0f;
                     }
-                    const int u = __float_as_int(r[0]);
-                    const float beta = r[6], rho = r[7];
-                    unsigned long long *bcol = bins + (u - u0) * Npad;
+                }
+#pragma unroll 1
+                for (int cc = 0; cc < CW; ++cc) {
+                    const int c = cq + cc;
+                    const int np = __builtin_amdgcn_readlane(ncol, c);
+                    if (np == 0) continue;
+                    // (16 wide: a uniform index into 8 or fewer is compiled to a chain of selects)
+                    typename FloatVec<16>::type base;
+                    unsigned any = 0u;
 #pragma unroll
-                    for (int h = 0; h < KP; ++h) {
-                        const float coef = base[h] * r[1];
-                        const float Yh = fmaf(-kf[h], r[4], r[2]);
-                        const float Yl = fmaf(-kf[h], r[5], r[3]);
-                        int vlo0, vhi0;
-                        row_range_unclipped<EC>(Yh + Yl, beta, r[10], c2f, vlo0, vhi0);
-                        if constexpr (TT) {
-                            float Ylu, Ybld, eu, ed;
-                            tt_ramps(Yh, Yl, r[5], beta, rho, c2f, Ylu, Ybld, eu, ed);
-                            sweep_rows_tt(vlo0, vhi0, max(vlo0, 0), min(vhi0, G.N - 1), Yh, Ylu, Yh + r[4], Ybld,
-                                          eu, ed, coef, bcol);
+                    for (int h = 0; h < KH; ++h) {
+                        if (h < nh) {
+                            base[h] = VT ? mu[h] : mu[h * CW + cc];
+                            any |= __float_as_uint(base[h]);
+                        }
+                    }
+                    if (__ballot((any << 1) != 0u) == 0) continue;
+                    if (TT || (!EXACT && !raw)) {
+                        const float r8c = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(rq[0][8]), c));
+#pragma unroll
+                        for (int h = 0; h < KH; ++h) {
+                            if (h < nh) {
+                                const float zc = fmaf(kf0 + (float)(h * kWave), a3f, zc0);   // voxel centre
+                                const float r2 = fmaf(zc, zc, r8c);
+                                // TT: the central ray's |r| (its min(a1/|r1|, a2/|r2|) is in the records)
+                                base[h] *= TT ? sqrtf(r2) : __builtin_amdgcn_rcpf(r2);
+                            }
+                        }
+                    }
+#pragma unroll 1
+                    for (int p = 0; p < np; ++p) {
+                        const int src = c + 16 * (p & 3);
+                        float r[kRecFloats];
+                        if (PASSES == 1 || p < 4) {
+#pragma unroll
+                            for (int e = 0; e < kRecFloats; ++e)
+                                r[e] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(rq[0][e]), src));
                         } else {
-                            // bottom face Y(k - 1): high part Yh + bh (exact on the 2^-10 grid), low part Yl + bl
-                            sweep_rows<EC, EXACT>(vlo0, vhi0, max(vlo0, 0), min(vhi0, G.N - 1), Yh, Yl, r[4],
-                                                  Yl + r[5], beta, rho, c2f, coef, raw, zt[h], r[11], r[9], bcol);
+#pragma unroll
+                            for (int e = 0; e < kRecFloats; ++e)
+                                r[e] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(rq[PASSES - 1][e]), src));
+                        }
+                        const int u = rec_col(__float_as_int(r[0]));
+                        const float beta = r[6], rho = r[7];
+                        unsigned long long *bcol = bins + (u - u0) * Npad + pad;
+                        const int rows = !TT && pad > 0 ? rec_rows<EC>(__float_as_int(r[0])) : 0;
+                        if (rows > 0) {
+                            const FixedPiece P = fixed_piece<EC>(r[2], in_vgpr(r[3]), r[4], r[5], beta, rho, c2f, md);
+                            const double W = ldexp((double)r[1], sc);
+                            // pieces with no row on the detector are left out (rows beyond its
+                            // edges fall into the spare rows); where every slice has one the
+                            // lanes need no test
+                            const float vtop = fmaf(-(float)(kc + nh * kWave - 1), beta, P.ys);
+                            const float vbot = fmaf(-(float)kc, beta, P.ys);
+                            const bool inside = __builtin_amdgcn_readfirstlane(
+                                (int)(vtop >= (float)(1 - rows) && vbot < (float)G.N));
+                            with_rows(rows, [&](auto tag) {
+                                constexpr int R = decltype(tag)::value;
+                                auto slices = [&](auto insideTag) {
+                                    float kf = kf0;
+#pragma unroll 1
+                                    for (int h = 0; h < nh; ++h, kf += (float)kWave) {
+                                        const float v0 = floorf(fmaf(-kf, beta, P.ys));
+                                        const int vi = (int)v0;
+                                        if (!decltype(insideTag)::value &&
+                                            (unsigned)(vi + (R - 1)) >= (unsigned)(G.N + (R - 1)))
+                                            continue;
+                                        const float zt = EXACT ? fmaf(kf, a3f, zt0) : 0.0f;
+                                        const double coef = (double)base[h] * W;
+                                        float w[R];
+                                        fixed_rows<R, EC, EXACT>(P, v0, kf, raw, zt, r[11], r[9], w);
+                                        unsigned long long *const q = bcol + vi;
+#pragma unroll
+                                        for (int e = 0; e < R; ++e) lds_add_fixed(q + e, w[e], coef);
+                                    }
+                                };
+                                if (inside) slices(std::true_type{});
+                                else slices(std::false_type{});
+                            });
+                            continue;
+                        }
+#pragma unroll 1
+                        for (int h = 0; h < nh; ++h) {
+                            const float kf = kf0 + (float)(h * kWave);
+                            const float zt = fmaf(kf, a3f, zt0);        // top of voxel k, relative to s3
+                            const float coef = ldexpf(base[h] * r[1], sc);
+                            const float Yh = fmaf(-kf, r[4], r[2]);
+                            const float Yl = fmaf(-kf, r[5], r[3]);
+                            int vlo0, vhi0;
+                            row_range_unclipped<EC>(Yh + Yl, beta, r[10], c2f, vlo0, vhi0);
+                            if constexpr (TT) {
+                                float Ylu, Ybld, eu, ed;
+                                tt_ramps(Yh, Yl, r[5], beta, rho, c2f, Ylu, Ybld, eu, ed);
+                                sweep_rows_tt(vlo0, vhi0, max(vlo0, 0), min(vhi0, G.N - 1), Yh, Ylu, Yh + r[4], Ybld,
+                                              eu, ed, coef, bcol);
+                            } else {
+                                // bottom face Y(k - 1): high part Yh + bh (exact on the 2^-10 grid), low part Yl + bl
+                                sweep_rows<EC, EXACT>(vlo0, vhi0, max(vlo0, 0), min(vhi0, G.N - 1), Yh, Yl, r[4],
+                                                      Yl + r[5], beta, rho, c2f, coef, raw, zt, r[11], r[9], bcol);
+                            }
                         }
                     }
                 }
@@ -922,7 +1157,7 @@ __device__ __forceinline__ void project_item(const DevGeom &G, const int U, cons
     for (int idx = tid; idx < Ub * G.N; idx += kBlock) {
         const int du = idx % Ub, v = idx / Ub;
         const int u = u0 + du;
-        float s = finite ? (float)ldexp(fixed_to_double(bins[du * Npad + v]), -sc) : __builtin_nanf("");
+        float s = finite ? (float)ldexp(fixed_to_double(bins[du * Npad + pad + v]), -sc) : __builtin_nanf("");
         if (G.sigma) s *= G.sigma[((size_t)view * G.vstride * G.sigma_views * G.N + v) * G.M + u];
         proj[((size_t)view * G.vstride * G.N + v) * G.M + u] = s;
     }
@@ -933,9 +1168,9 @@ __device__ __forceinline__ void project_item(const DevGeom &G, const int U, cons
 // SIMD); both ran about 20% faster at 512^3 x 248 views than at their
 // natural 190-220 VGPRs with 2 waves per SIMD, and the projection 3% faster
 // at 5 waves than at 4.
-template <bool EXACT, bool EC, int PMAX, bool TT = false, bool TAB = false>
+template <bool EXACT, bool EC, int PMAX, bool TT, bool TAB, bool VT>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5)))
-project_kernel(const DevGeom G, const int U, const int nbands, const float *__restrict__ vol,
+project_kernel(const DevGeom G, const int U, const int pad, const int nbands, const float *__restrict__ vol,
                float *__restrict__ proj, const unsigned *__restrict__ gmax, const double *__restrict__ stop)
 {
     extern __shared__ __align__(16) float smem[];
@@ -947,7 +1182,7 @@ project_kernel(const DevGeom G, const int U, const int nbands, const float *__re
     const int slot = blockIdx.x >> 3;
     const int band = (blockIdx.x & 7) + 8 * (slot / G.nviews);
     if (band >= nbands) return;
-    project_item<EXACT, EC, PMAX, TT, TAB>(G, U, band * G.nviews + slot % G.nviews, smem, vol, proj, gmax);
+    project_item<EXACT, EC, PMAX, TT, TAB, VT>(G, U, pad, band * G.nviews + slot % G.nviews, smem, vol, proj, gmax);
 }
 
 // gmax[j * ngroups + q] = the largest |mu| bit pattern over the columns
@@ -984,7 +1219,346 @@ group_max_kernel(const DevGeom G, const float *__restrict__ vol, unsigned *__res
     if (lane == 0) gmax[cell] = mxl;
 }
 
+// vt[(j n1 + i) n3 + k] = vol[(k n2 + j) n1 + i], and the group maxima of
+// group_max_kernel with it (the volume is read once for both): a workgroup
+// takes 64 columns of a row j and walks k in 64 x 64 tiles through LDS, so
+// both sides move whole 256-byte rows.  It replaces the projection's reads
+// of 64 bytes from each of 64 lines per group and slice block, half of every
+// line unused: 523 GB per launch at 512^3 x 248 views, against one pass over
+// the volume and its copy here.
+__global__ void __launch_bounds__(kBlock)
+transpose_max_kernel(const DevGeom G, const float *__restrict__ vol, float *__restrict__ vt,
+                     unsigned *__restrict__ gmax, const double *__restrict__ stop)
+{
+    if (stop && *stop != 0.0) return;
+    __shared__ float tile[kWave][kWave + 1];
+    const int nb = (G.n1 + kWave - 1) / kWave;
+    const int j = blockIdx.x / nb, i0 = (blockIdx.x - j * nb) * kWave;
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const int nc = min(kWave, G.n1 - i0);
+    unsigned mx = 0u;
+    for (int k0 = 0; k0 < G.n3; k0 += kWave) {
+        const int nk = min(kWave, G.n3 - k0);
+        float t[kWave / kWaves];
+#pragma unroll
+        for (int e = 0; e < kWave / kWaves; ++e) {
+            const int k = wave + e * kWaves;
+            t[e] = lane < nc && k < nk ? vol[((size_t)(k0 + k) * G.n2 + j) * G.n1 + i0 + lane] : 0.0f;
+        }
+        if (k0 > 0) __syncthreads();
+#pragma unroll
+        for (int e = 0; e < kWave / kWaves; ++e) {
+            mx = max(mx, __float_as_uint(t[e]) & 0x7fffffffu);
+            tile[wave + e * kWaves][lane] = t[e];
+        }
+        __syncthreads();
+        if (lane < nk) {
+#pragma unroll
+            for (int e = 0; e < kWave / kWaves; ++e) {
+                const int c = wave + e * kWaves;
+                if (c < nc) vt[((size_t)j * G.n1 + i0 + c) * G.n3 + k0 + lane] = tile[lane][c];
+            }
+        }
+    }
+    // the 16 columns of a group within each wave, then the four waves
+#pragma unroll
+    for (int off = 8; off > 0; off >>= 1) mx = max(mx, (unsigned)__shfl_xor((int)mx, off));
+    __shared__ unsigned red[kWaves][4];
+    if ((lane & 15) == 0) red[wave][lane >> 4] = mx;
+    __syncthreads();
+    const int ngroups = (G.n1 + 15) / 16, q = i0 / 16 + (int)threadIdx.x;
+    if (threadIdx.x < 4 && q < ngroups)
+        gmax[(size_t)j * ngroups + q] = max(max(red[0][threadIdx.x], red[1][threadIdx.x]),
+                                            max(red[2][threadIdx.x], red[3][threadIdx.x]));
+}
+
 // ------------------------------------------------------------ backprojection
+
+// Rows of the detector window that the voxels of a stack (slices k0 .. kmax)
+// need for one piece: [lo, hi] grows to hold them.  Fixed row counts: the
+// first rows, held within [-R, N], and R - 1 rows after them (rows off the
+// detector are zero rows of the window); else the piece's row ranges.
+template <bool EC, bool TT>
+__device__ __forceinline__ void window_rows(const float *r, int k0, int kmax, float c2f, float md, int N, int &lo,
+                                            int &hi)
+{
+    const int rows = TT ? 0 : rec_rows<EC>(__float_as_int(r[0]));
+    const float beta = r[6];
+    if (rows > 0) {
+        const float ys = fixed_start<EC>(r[2], r[3], r[7], md);
+        const int a = (int)floorf(fmaf(-(float)kmax, beta, ys)), b = (int)floorf(fmaf(-(float)k0, beta, ys));
+        lo = min(lo, min(max(a, -rows), N));
+        hi = max(hi, min(max(b, -rows), N) + rows - 1);
+        return;
+    }
+    const float mfac = r[10];
+    const float Ytop_hi = fmaf(-(float)kmax, r[4], r[2]) + fmaf(-(float)kmax, r[5], r[3]);
+    const float Ytop_lo = fmaf(-(float)k0, r[4], r[2]) + fmaf(-(float)k0, r[5], r[3]);
+    int a, b, a2, b2;
+    row_range<EC>(Ytop_hi, beta, mfac, c2f, N, a, b);
+    row_range<EC>(Ytop_lo, beta, mfac, c2f, N, a2, b2);
+    lo = min(lo, min(a, a2));
+    hi = max(hi, max(b, b2));
+}
+
+// Copies the detector window [wv0, wv1] x [wu0, wu0 + Wd) of one view, times
+// the pixel factor, to win[column][row - wv0] (row pitch Hp) with NT threads;
+// rows off the detector become zeros.  Threads cover 8, 16, 32 or 64 columns
+// (the power of two that holds Wd) of NT / that rows at a time and step down
+// the rows by constant offsets, four loads in flight; an element then costs
+// about 6 instructions at 60 to 70 % of the lanes (34 with a division per
+// element).  Returns whether this thread's values are all finite.
+template <int NT>
+__device__ __forceinline__ bool stage_window(float *win, const float *pv, const float *sgv, int wu0, int wv0, int wv1,
+                                             int Wd, int Hp, int N, int M, int t)
+{
+    const int lw = Wd <= 8 ? 3 : Wd <= 16 ? 4 : Wd <= 32 ? 5 : 6;
+    const int step = NT >> lw;                            // rows per pass
+    const int c = t & ((1 << lw) - 1), r = t >> lw;
+    const int va = max(wv0, 0), vb = min(wv1, N - 1);
+    float chk = 0.0f;
+    for (int uu = c; uu < Wd; uu += 1 << lw) {
+        unsigned off = (unsigned)((va + r) * M + wu0 + uu);
+        float *dst = win + uu * Hp + (va + r - wv0);
+        const unsigned dm = (unsigned)(step * M);
+        int v = va + r;
+        if (sgv) {
+            for (; v + 3 * step <= vb; v += 4 * step) {
+                float x[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[e] = pv[off + e * dm] * sgv[off + e * dm];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    dst[e * step] = x[e];
+                    chk = fmaf(x[e], 0.0f, chk);          // NaN once any value is not finite
+                }
+                off += 4 * dm;
+                dst += 4 * step;
+            }
+            for (; v <= vb; v += step) {
+                const float x = pv[off] * sgv[off];
+                *dst = x;
+                chk = fmaf(x, 0.0f, chk);
+                off += dm;
+                dst += step;
+            }
+        } else {
+            for (; v <= vb; v += step) {
+                const float x = pv[off];
+                *dst = x;
+                chk = fmaf(x, 0.0f, chk);
+                off += dm;
+                dst += step;
+            }
+        }
+        for (int z = wv0 + r; z < va; z += step) win[uu * Hp + (z - wv0)] = 0.0f;
+        for (int z = vb + 1 + r; z <= wv1; z += step) win[uu * Hp + (z - wv0)] = 0.0f;
+    }
+    return chk == 0.0f;
+}
+
+// An LDS address as one opaque value (the compiler would otherwise split the
+// constant part off and add it again for each lane).
+typedef __attribute__((address_space(3))) const float LdsFloat;
+__device__ __forceinline__ LdsFloat *lds_ptr(const float *p)
+{
+    int q = __builtin_amdgcn_readfirstlane((int)(unsigned)(uintptr_t)(LdsFloat *)p);   // the same in every lane
+    asm("" : "+s"(q));
+    return (LdsFloat *)(uintptr_t)(unsigned)q;
+}
+
+// One view as the gather of a backprojection sees it.
+struct BackView {
+    const float *pv, *sgv;      // projections and pixel factors of the view
+    int N, M;
+    int wu0, wv0, wv1, Hp;      // window
+    float c2f, md;
+    float zt0, a3f;             // x3 of the top of voxel 0 minus s3; slice height
+    bool raw;
+    bool fixed;                 // fixed row counts may be used (every staged value is finite)
+};
+
+// Row sum of one piece for one voxel of slice kf (lanes over k) by the row
+// loop, from the window (WIN, wcol: the piece's window column less wv0) or
+// global memory; the piece's coefficient is applied by the caller.
+template <bool EC, bool EXACT, bool TT, bool WIN>
+__device__ __forceinline__ float gather_rows(const BackView &B, const float4 &r0, const float4 &r1, const float4 &r2,
+                                             const int u, const float *wcol, const float kf, const bool kv)
+{
+    const float zt = fmaf(kf, B.a3f, B.zt0);
+    const float Yh = fmaf(-kf, r1.x, r0.z);
+    const float Yl = fmaf(-kf, r1.y, r0.w);
+    const float Ybh = Yh + r1.x, Ybl = Yl + r1.y;   // bottom face Y(k - 1), exact high part
+    const float beta = r1.z, rho = r1.w, rho4 = 4.0f * r1.w;
+    const float c2f = B.c2f;
+    // rows clipped to the detector and the window; as in the projection, Phi
+    // at the first and last boundaries of the unclipped range is exactly 0
+    int vlo0, vhi0;
+    row_range_unclipped<EC>(Yh + Yl, beta, r2.z, c2f, vlo0, vhi0);
+    const bool ends = !EC || rho < 0.9f;
+    const int vlo = max(max(vlo0, 0), B.wv0);
+    const int vhi = kv ? min(min(vhi0, B.N - 1), B.wv1) : vlo - 1;
+    if constexpr (TT) {
+        // the TT axial footprint's row integrals (Phi is exactly 0 at the
+        // ends of the unclipped range, computed or not)
+        float Ylu, Ybld, eu, ed;
+        tt_ramps(Yh, Yl, r1.y, beta, rho, c2f, Ylu, Ybld, eu, ed);
+        const float iu = __builtin_amdgcn_rcpf(fmaf(4.0f, eu, 1e-30f));
+        const float id = __builtin_amdgcn_rcpf(fmaf(4.0f, ed, 1e-30f));
+        const float tb = (float)vlo - 0.5f;
+        float d = Yh - tb, d0 = Ybh - tb;
+        float s1, mp, phip;
+        boundary_tt<true>(d, Ylu, d0, Ybld, eu, ed, iu, id, s1, mp, phip);
+        float psip = mp + phip, ap = 0.0f;
+        for (int v = vlo; v <= vhi; ++v) {
+            d -= 1.0f;
+            d0 -= 1.0f;
+            float mn, phin;
+            boundary_tt<true>(d, Ylu, d0, Ybld, eu, ed, iu, id, s1, mn, phin);
+            const float val = WIN ? wcol[v] : B.pv[(size_t)v * B.M + u];
+            ap = fmaf(psip - phin, val, ap);
+            psip = mn + phin;
+        }
+        return ap;
+    }
+    // boundaries as in sweep_rows; row weight m(t) + Phi(t) - Phi(t + 1)
+    const float tb = (float)vlo - 0.5f;
+    float d = Yh - tb;
+    float d0 = d + r1.x;                     // Ybh - tb, exact on the 2^-10 grid
+    float tc = tb - c2f;
+    float s1p, mp, phip;
+    if (vlo != vlo0 || !ends) boundary<EC>(d, Yl, d0, Ybl, tc, rho, rho4, s1p, mp, phip);
+    else boundary<false>(d, Yl, d0, Ybl, tc, rho, rho4, s1p, mp, phip);
+    float psip = mp + phip;
+    float ap = 0.0f;          // sum of row weight [1/r^2] val_v
+    auto row = [&](float val) {
+        d -= 1.0f;
+        d0 -= 1.0f;
+        tc += 1.0f;
+        float s1n, mn, phin;
+        boundary<EC>(d, Yl, d0, Ybl, tc, rho, rho4, s1n, mn, phin);
+        float w = psip - phin;
+        if (EXACT && !B.raw) {
+            float mm = 0.5f * (fmaxf(0.0f, -s1p) + fminf(beta, -s1n));
+            mm = fminf(fmaxf(mm, 0.0f), beta);
+            const float zb = fmaf(-mm, r2.y, zt);
+            w *= __builtin_amdgcn_rcpf(fmaf(zb, zb, r2.w));
+        }
+        ap = fmaf(w, val, ap);
+        psip = mn + phin;
+        s1p = s1n;
+    };
+    if (WIN) {
+        const float *const last = wcol + vhi;
+        for (const float *q = wcol + vlo; q < last; ++q) row(*q);
+        if (vlo <= vhi) {
+            // last row: Phi at the last boundary of the unclipped range is
+            // exactly 0
+            d -= 1.0f;
+            d0 -= 1.0f;
+            tc += 1.0f;
+            float s1n = d + Yl, phin = 0.0f;
+            if (vhi != vhi0 || !ends) {
+                float mn;
+                boundary<EC>(d, Yl, d0, Ybl, tc, rho, rho4, s1n, mn, phin);
+            }
+            float w = psip - phin;
+            if (EXACT && !B.raw) {
+                float mm = 0.5f * (fmaxf(0.0f, -s1p) + fminf(beta, -s1n));
+                mm = fminf(fmaxf(mm, 0.0f), beta);
+                const float zb = fmaf(-mm, r2.y, zt);
+                w *= __builtin_amdgcn_rcpf(fmaf(zb, zb, r2.w));
+            }
+            ap = fmaf(w, *last, ap);
+        }
+    } else {
+        for (int v = vlo; v <= vhi; ++v) {
+            const size_t off = (size_t)v * B.M + u;
+            float val = B.pv[off];
+            if (B.sgv) val *= B.sgv[off];
+            row(val);
+        }
+    }
+    return ap;
+}
+
+// The factor common to a voxel's pieces: 1/r^2 at its centre (relaxed form)
+// or the central ray's |r| (TT); 0 for a column without pieces (np = 0), whose
+// record holds nothing.
+template <bool EXACT, bool TT>
+__device__ __forceinline__ float column_factor(const BackView &B, const float *rc, int np, float kf)
+{
+    if (!TT && EXACT) return 1.0f;
+    const float zc = fmaf(kf, B.a3f, B.zt0) - 0.5f * B.a3f;
+    const float r2 = fmaf(zc, zc, rc[8]);
+    const float f = TT ? sqrtf(r2) : __builtin_amdgcn_rcpf(r2);
+    return np == 0 ? 0.0f : !TT && B.raw ? 1.0f : f;
+}
+
+// Sums a[NP] of the pieces of one column (np records at rc) for its voxels in
+// NP passes of 64 slices (kf, kv), without column_factor.  np and the records
+// are the same in every lane.
+template <bool EC, bool EXACT, bool TT, bool WIN, int NP>
+__device__ __forceinline__ void gather_column(const BackView &B, const float *rc, const int np, const float *win,
+                                              const float kf[NP], const bool kv[NP], float a[NP])
+{
+#pragma unroll
+    for (int ps = 0; ps < NP; ++ps) a[ps] = 0.0f;
+#pragma unroll 1
+    for (int p = 0; p < np; ++p) {
+        const float4 r0 = *reinterpret_cast<const float4 *>(rc + p * kRecFloats);
+        const float4 r1 = *reinterpret_cast<const float4 *>(rc + p * kRecFloats + 4);
+        const float4 r2 = *reinterpret_cast<const float4 *>(rc + p * kRecFloats + 8);
+        const int word = __builtin_amdgcn_readfirstlane(__float_as_int(r0.x));
+        const int u = rec_col(word);
+        const int rows = !TT && B.fixed ? rec_rows<EC>(word) : 0;
+        const float *wcol = win + (u - B.wu0) * B.Hp - B.wv0;
+        if (rows > 0) {
+            const FixedPiece P = fixed_piece<EC>(r0.z, r0.w, r1.x, r1.y, r1.z, r1.w, B.c2f, B.md);
+            LdsFloat *const wl = lds_ptr(WIN ? wcol : win);
+            with_rows(rows, [&](auto tag) {
+                constexpr int R = decltype(tag)::value;
+#pragma unroll
+                for (int ps = 0; ps < NP; ++ps) {
+                    const float k = kf[ps];
+                    // the window holds the rows of every slice (the position is monotone
+                    // in k), unless it ends R rows beyond the detector
+                    float v0 = floorf(fmaf(-k, r1.z, P.ys));
+                    if (WIN) v0 = __builtin_amdgcn_fmed3f(v0, (float)B.wv0, (float)(B.wv1 - (R - 1)));
+                    const int vi = (int)v0;
+                    const float zt = EXACT ? fmaf(k, B.a3f, B.zt0) : 0.0f;
+                    float w[R];
+                    fixed_rows<R, EC, EXACT>(P, v0, k, B.raw, zt, r2.w, r2.y, w);
+                    float val[R];
+#pragma unroll
+                    for (int e = 0; e < R; ++e) {
+                        if (WIN) {
+                            val[e] = wl[vi + e];
+                        } else {
+                            const bool on = kv[ps] && (unsigned)(vi + e) < (unsigned)B.N;
+                            const size_t off = (size_t)(on ? vi + e : 0) * B.M + u;
+                            val[e] = B.pv[off];
+                            if (B.sgv) val[e] *= B.sgv[off];
+                            if (!on) val[e] = 0.0f;
+                        }
+                    }
+                    float ap = w[0] * val[0];
+#pragma unroll
+                    for (int e = 1; e < R; ++e) ap = fmaf(w[e], val[e], ap);
+                    // a non-finite value (global reads; a window was checked) reaches
+                    // the voxels that the row loop gives it to
+                    if (!WIN && __ballot(!(fabsf(ap) < INFINITY)))
+                        ap = gather_rows<EC, EXACT, TT, WIN>(B, r0, r1, r2, u, wcol, k, kv[ps]);
+                    a[ps] = fmaf(r0.y, ap, a[ps]);
+                }
+            });
+            continue;
+        }
+#pragma unroll
+        for (int ps = 0; ps < NP; ++ps)
+            a[ps] = fmaf(r0.y, gather_rows<EC, EXACT, TT, WIN>(B, r0, r1, r2, u, wcol, kf[ps], kv[ps]), a[ps]);
+    }
+}
 
 // One work item of the backprojection: a stack of GW columns x 64 kp voxels
 // (kp = 1 or 2), gathered in kp 64-voxel passes that share each view's piece
@@ -994,7 +1568,7 @@ __device__ __forceinline__ void backproject_item(const DevGeom &G, const int ngr
                                                  const int nkchunks, const int kp, const int winCap,
                                                  const int item, float *smem,
                                                  const float *__restrict__ proj,
-                                                 float *__restrict__ vol)
+                                                 float *__restrict__ vol, const BackPart &part)
 {
     const int kch = item % nkchunks;
     const int t = item / nkchunks;
@@ -1021,11 +1595,17 @@ __device__ __forceinline__ void backproject_item(const DevGeom &G, const int ngr
     const float a3f = (float)G.a3;
     const bool raw = G.raw_volume != 0;
 
-    float acc[KP][GW];
+    typename FloatVec<GW>::type acc[KP];
 #pragma unroll
-    for (int ps = 0; ps < KP; ++ps)
+    for (int ps = 0; ps < KP; ++ps) acc[ps] = 0.0f;
+    // this wave's sums of the launches before (element (ps, c) of a lane)
+    float *const mine = part.sums + ((size_t)item * kWaves + wave) * KP * GW * kWave + lane;
+    if (!part.first) {
 #pragma unroll
-        for (int c = 0; c < GW; ++c) acc[ps][c] = 0.0f;
+        for (int ps = 0; ps < KP; ++ps)
+#pragma unroll
+            for (int c = 0; c < GW; ++c) acc[ps][c] = mine[(ps * GW + c) * kWave];
+    }
 
     for (int vb = wave; vb < G.nviews; vb += kWaves * RV) {
         if constexpr (TAB) {
@@ -1036,7 +1616,7 @@ __device__ __forceinline__ void backproject_item(const DevGeom &G, const int ngr
                 if (view >= G.nviews) break;
                 float *rv = rec + r * recView;
                 int *npv = reinterpret_cast<int *>(rv + GW * PMAX * kRecFloats);
-                const size_t col0 = ((size_t)view * G.vstride * G.n2 + j) * G.n1 + i0;
+                const size_t col0 = ((size_t)view * G.rtab_vs * G.n2 + j) * G.n1 + i0;
                 const int ncv = min(GW, G.n1 - i0);
                 const int tp = G.rtab_pmax;
                 const float4 *src = reinterpret_cast<const float4 *>(G.rtab + col0 * tp * kRecFloats);
@@ -1082,20 +1662,15 @@ __device__ __forceinline__ void backproject_item(const DevGeom &G, const int ngr
             const float *rv = rec + r * recView;
             int *npv = reinterpret_cast<int *>(const_cast<float *>(rv) + GW * PMAX * kRecFloats);
             const float c2f = (float)G.views[(size_t)(vb + r * kWaves) * G.vstride].c2;
-            int wu0 = 1 << 30, wu1 = -1, wv0 = 1 << 30, wv1 = -1;
+            const float md = detector_reach(c2f, G.N);
+            int wu0 = 1 << 30, wu1 = -1, wv0 = 1 << 30, wv1 = -(1 << 30);
             const int c = lane % GW, s0 = lane / GW;
             for (int s = s0; s < PMAX; s += kWave / GW) {
                 if (s < npv[c]) {
                     const float *r = rv + (c * PMAX + s) * kRecFloats;
-                    const int u = __float_as_int(r[0]);
-                    const float beta = r[6], mfac = r[10];
-                    const float Ytop_hi = fmaf(-(float)kmax, r[4], r[2]) + fmaf(-(float)kmax, r[5], r[3]);
-                    const float Ytop_lo = fmaf(-(float)k0, r[4], r[2]) + fmaf(-(float)k0, r[5], r[3]);
-                    int a, b, a2, b2;
-                    row_range<EC>(Ytop_hi, beta, mfac, c2f, G.N, a, b);
-                    row_range<EC>(Ytop_lo, beta, mfac, c2f, G.N, a2, b2);
+                    const int u = rec_col(__float_as_int(r[0]));
                     wu0 = min(wu0, u); wu1 = max(wu1, u);
-                    wv0 = min(wv0, min(a, a2)); wv1 = max(wv1, max(b, b2));
+                    window_rows<EC, TT>(r, k0, kmax, c2f, md, G.N, wv0, wv1);
                 }
             }
 #pragma unroll
@@ -1132,219 +1707,60 @@ __device__ __forceinline__ void backproject_item(const DevGeom &G, const int ngr
         if (r > 0) {
             wu0 = npc[GW]; wu1 = npc[GW + 1]; wv0 = npc[GW + 2]; wv1 = npc[GW + 3];
         }
-        if constexpr (TAB) {
-            // the window bounds are the same in every lane
-            wu0 = __builtin_amdgcn_readfirstlane(wu0);
-            wu1 = __builtin_amdgcn_readfirstlane(wu1);
-            wv0 = __builtin_amdgcn_readfirstlane(wv0);
-            wv1 = __builtin_amdgcn_readfirstlane(wv1);
-        }
-        if (wu1 < wu0 || wv1 < wv0) continue;
-        // one spare row each side absorbs FP32 rounding of intermediate k
-        wv0 = max(wv0 - 1, 0);
-        wv1 = min(wv1 + 1, G.N - 1);
+        // the window bounds are the same in every lane
+        wu0 = __builtin_amdgcn_readfirstlane(wu0);
+        wu1 = __builtin_amdgcn_readfirstlane(wu1);
+        wv0 = __builtin_amdgcn_readfirstlane(wv0);
+        wv1 = __builtin_amdgcn_readfirstlane(wv1);
+        if (wu1 < wu0 || wv1 < max(wv0, 0) || wv0 > G.N - 1) continue;   // no piece, or no row on the detector
+        // one spare row each side absorbs the FP32 rounding of the row loop's
+        // intermediate k
+        wv0 = max(wv0 - 1, -G.rpad);
+        wv1 = min(wv1 + 1, G.N - 1 + G.rpad);
         const int Wd = wu1 - wu0 + 1;
         const int H = wv1 - wv0 + 1;
         const int Hp = H | 1;
-        const float *pv = proj + (size_t)view * G.vstride * G.N * G.M;
+        BackView B;
+        B.pv = proj + (size_t)view * G.vstride * G.N * G.M;
+        B.sgv = sgv;
+        B.N = G.N; B.M = G.M;
+        B.wu0 = wu0; B.wv0 = wv0; B.wv1 = wv1; B.Hp = Hp;
+        B.c2f = c2f; B.md = detector_reach(c2f, G.N);
+        B.zt0 = (float)(G.x3lo + G.a3 - V.s3); B.a3f = a3f;
+        B.raw = raw;
 
         const bool useWin = Wd * Hp <= winCap;
-        if (useWin) {
-            for (int idx = lane; idx < Wd * H; idx += kWave) {
-                const int uu = idx % Wd, vv = idx / Wd;
-                const size_t off = (size_t)(wv0 + vv) * G.M + (wu0 + uu);
-                float val = pv[off];
-                if (sgv) val *= sgv[off];
-                win[uu * Hp + vv] = val;
-            }
-        }
+        B.fixed = true;
+        if (useWin)
+            B.fixed = __ballot(!stage_window<kWave>(win, B.pv, sgv, wu0, wv0, wv1, Wd, Hp, G.N, G.M, lane)) == 0;
         wave_sync();
 
-        // the gather, with the window read from LDS (WIN) or global memory.
-        // piece(): the row sum of one piece for one voxel (lanes over k),
-        // times the piece's coefficient by the caller.
+        // the gather, with the window read from LDS (WIN) or global memory;
+        // a piece record is read once for both passes
         auto gather = [&](auto winTag, auto npTag) {
-        constexpr bool WIN = decltype(winTag)::value;
-        constexpr int NP = decltype(npTag)::value;   // passes (a bound for the second form)
-        auto piece = [&](const float4 &r0, const float4 &r1, const float4 &r2, const int u, const float *wcol,
-                         const float kf, const float zt, const bool kv) -> float {
-            const float Yh = fmaf(-kf, r1.x, r0.z);
-            const float Yl = fmaf(-kf, r1.y, r0.w);
-            const float Ybh = Yh + r1.x, Ybl = Yl + r1.y;   // bottom face Y(k - 1), exact high part
-            const float beta = r1.z, rho = r1.w, rho4 = 4.0f * r1.w;
-            // rows clipped to the detector and the window; as in the
-            // projection, Phi at the first and last boundaries of the
-            // unclipped range is exactly 0
-            int vlo0, vhi0;
-            row_range_unclipped<EC>(Yh + Yl, beta, r2.z, c2f, vlo0, vhi0);
-            const bool ends = !EC || rho < 0.9f;
-            const int vlo = max(max(vlo0, 0), wv0);
-            const int vhi = kv ? min(min(vhi0, G.N - 1), wv1) : vlo - 1;
-            if constexpr (TT) {
-                // the TT axial footprint's row integrals (Phi is exactly 0
-                // at the ends of the unclipped range, computed or not)
-                float Ylu, Ybld, eu, ed;
-                tt_ramps(Yh, Yl, r1.y, beta, rho, c2f, Ylu, Ybld, eu, ed);
-                const float iu = __builtin_amdgcn_rcpf(fmaf(4.0f, eu, 1e-30f));
-                const float id = __builtin_amdgcn_rcpf(fmaf(4.0f, ed, 1e-30f));
-                const float tb = (float)vlo - 0.5f;
-                float d = Yh - tb, d0 = Ybh - tb;
-                float s1, mp, phip;
-                boundary_tt<true>(d, Ylu, d0, Ybld, eu, ed, iu, id, s1, mp, phip);
-                float psip = mp + phip, ap = 0.0f;
-                for (int v = vlo; v <= vhi; ++v) {
-                    d -= 1.0f;
-                    d0 -= 1.0f;
-                    float mn, phin;
-                    boundary_tt<true>(d, Ylu, d0, Ybld, eu, ed, iu, id, s1, mn, phin);
-                    const float val = WIN ? wcol[v] : pv[(size_t)v * G.M + u];
-                    ap = fmaf(psip - phin, val, ap);
-                    psip = mn + phin;
-                }
-                return ap;
-            }
-            // boundaries as in sweep_rows; row weight m(t) + Phi(t) - Phi(t + 1)
-            const float tb = (float)vlo - 0.5f;
-            float d = Yh - tb;
-            float d0 = d + r1.x;                     // Ybh - tb, exact on the 2^-10 grid
-            float tc = tb - c2f;
-            float s1p, mp, phip;
-            if (vlo != vlo0 || !ends) boundary<EC>(d, Yl, d0, Ybl, tc, rho, rho4, s1p, mp, phip);
-            else boundary<false>(d, Yl, d0, Ybl, tc, rho, rho4, s1p, mp, phip);
-            float psip = mp + phip;
-            float ap = 0.0f;          // sum of row weight [1/r^2] val_v
-            auto row = [&](float val) {
-                d -= 1.0f;
-                d0 -= 1.0f;
-                tc += 1.0f;
-                float s1n, mn, phin;
-                boundary<EC>(d, Yl, d0, Ybl, tc, rho, rho4, s1n, mn, phin);
-                float w = psip - phin;
-                if (EXACT && !raw) {
-                    float mm = 0.5f * (fmaxf(0.0f, -s1p) + fminf(beta, -s1n));
-                    mm = fminf(fmaxf(mm, 0.0f), beta);
-                    const float zb = fmaf(-mm, r2.y, zt);
-                    w *= __builtin_amdgcn_rcpf(fmaf(zb, zb, r2.w));
-                }
-                ap = fmaf(w, val, ap);
-                psip = mn + phin;
-                s1p = s1n;
-            };
-            if (WIN) {
-                const float *const last = wcol + vhi;
-                for (const float *q = wcol + vlo; q < last; ++q) row(*q);
-                if (vlo <= vhi) {
-                    // last row: Phi at the last boundary of the unclipped
-                    // range is exactly 0
-                    d -= 1.0f;
-                    d0 -= 1.0f;
-                    tc += 1.0f;
-                    float s1n = d + Yl, phin = 0.0f;
-                    if (vhi != vhi0 || !ends) {
-                        float mn;
-                        boundary<EC>(d, Yl, d0, Ybl, tc, rho, rho4, s1n, mn, phin);
-                    }
-                    float w = psip - phin;
-                    if (EXACT && !raw) {
-                        float mm = 0.5f * (fmaxf(0.0f, -s1p) + fminf(beta, -s1n));
-                        mm = fminf(fmaxf(mm, 0.0f), beta);
-                        const float zb = fmaf(-mm, r2.y, zt);
-                        w *= __builtin_amdgcn_rcpf(fmaf(zb, zb, r2.w));
-                    }
-                    ap = fmaf(w, *last, ap);
-                }
-            } else {
-                for (int v = vlo; v <= vhi; ++v) {
-                    const size_t off = (size_t)v * G.M + u;
-                    float val = pv[off];
-                    if (sgv) val *= sgv[off];
-                    row(val);
-                }
-            }
-            return ap;
-        };
-        auto record = [&](const float *rc, int p, float4 &r0, float4 &r1, float4 &r2) {
-            r0 = *reinterpret_cast<const float4 *>(rc + p * kRecFloats);
-            r1 = *reinterpret_cast<const float4 *>(rc + p * kRecFloats + 4);
-            r2 = *reinterpret_cast<const float4 *>(rc + p * kRecFloats + 8);
-        };
-        auto base_of = [&](const float *rc, float kf) {
-            const float zc = fmaf(kf, a3f, (float)(G.x3lo + G.a3 - V.s3)) - 0.5f * a3f;
-            float base = 1.0f;
-            if (TT) base = sqrtf(fmaf(zc, zc, rc[8]));
-            else if (!EXACT && !raw) base = __builtin_amdgcn_rcpf(fmaf(zc, zc, rc[8]));
-            return base;
-        };
-        if constexpr (TAB && NP > 1) {
-            // Each piece record is read once and serves the NP passes; the
-            // piece count, u and the window bounds are the same in every
-            // lane (scalar registers).  A voxel's pieces are summed in piece
-            // order, as below.  (With one pass the per-lane form below is
-            // faster.)
-            bool live[NP], kv[NP];
-            float kf[NP], zt[NP];
+            constexpr bool WIN = decltype(winTag)::value;
+            constexpr int NP = decltype(npTag)::value;
+            bool kv[NP];
+            float kf[NP];
 #pragma unroll
             for (int ps = 0; ps < NP; ++ps) {
-                live[ps] = k0 + ps * kWave < G.n3;   // uniform
                 const int k = k0 + ps * kWave + lane;
                 kv[ps] = k < G.n3;
-                kf[ps] = (float)k;
-                zt[ps] = fmaf(kf[ps], a3f, (float)(G.x3lo + G.a3 - V.s3));
+                kf[ps] = (float)min(k, G.n3 - 1);
             }
-#pragma unroll
+#pragma unroll 1
             for (int c = 0; c < GW; ++c) {
                 const int np = __builtin_amdgcn_readfirstlane(npc[c]);
-                if (np == 0) continue;
-                const float *rc = recv + c * PMAX * kRecFloats;
-                float base[NP], a[NP];
-#pragma unroll
-                for (int ps = 0; ps < NP; ++ps) {
-                    base[ps] = base_of(rc, kf[ps]);
-                    a[ps] = 0.0f;
-                }
-                for (int p = 0; p < np; ++p) {
-                    float4 r0, r1, r2;
-                    record(rc, p, r0, r1, r2);
-                    const int u = __builtin_amdgcn_readfirstlane(__float_as_int(r0.x));
-                    const float *wcol = win + (u - wu0) * Hp - wv0;
-#pragma unroll
-                    for (int ps = 0; ps < NP; ++ps)
-                        if (live[ps])
-                            a[ps] = fmaf(base[ps] * r0.y, piece(r0, r1, r2, u, wcol, kf[ps], zt[ps], kv[ps]), a[ps]);
-                }
+                float a[NP];   // (no branch around a column without pieces: it would copy every sum)
+                gather_column<EC, EXACT, TT, WIN, NP>(B, recv + c * PMAX * kRecFloats, np, win, kf, kv, a);
 #pragma unroll
                 for (int ps = 0; ps < NP; ++ps)
-                    if (live[ps]) acc[ps][c] += a[ps];
+                    acc[ps][c] = fmaf(column_factor<EXACT, TT>(B, recv + c * PMAX * kRecFloats, np, kf[ps]), a[ps], acc[ps][c]);
             }
-        } else {
-#pragma unroll
-            for (int ps = 0; ps < NP; ++ps) {
-                if (ps >= kp || k0 + ps * kWave >= G.n3) break;   // unused pass
-                const int k = k0 + ps * kWave + lane;
-                const bool kv = k < G.n3;
-                const float kf = (float)k;
-                const float zt = fmaf(kf, a3f, (float)(G.x3lo + G.a3 - V.s3));
-#pragma unroll
-                for (int c = 0; c < GW; ++c) {
-                    const int np = npc[c];
-                    if (np == 0) continue;
-                    const float *rc = recv + c * PMAX * kRecFloats;
-                    const float base = base_of(rc, kf);
-                    float a = 0.0f;
-                    for (int p = 0; p < np; ++p) {
-                        float4 r0, r1, r2;
-                        record(rc, p, r0, r1, r2);
-                        const int u = __float_as_int(r0.x);
-                        a = fmaf(base * r0.y, piece(r0, r1, r2, u, win + (u - wu0) * Hp - wv0, kf, zt, kv), a);
-                    }
-                    acc[ps][c] += a;
-                }
-            }
-        }
         };
         using P1 = std::integral_constant<int, 1>;
         using P2 = std::integral_constant<int, KP>;
-        if (TAB && kp == 1) {
+        if (kp == 1 || k0 + kWave >= G.n3) {
             if (useWin) gather(std::true_type{}, P1{});
             else gather(std::false_type{}, P1{});
         } else {
@@ -1353,6 +1769,14 @@ __device__ __forceinline__ void backproject_item(const DevGeom &G, const int ngr
         }
         wave_sync();
         }
+    }
+
+    if (!part.last) {
+#pragma unroll
+        for (int ps = 0; ps < KP; ++ps)
+#pragma unroll
+            for (int c = 0; c < GW; ++c) mine[(ps * GW + c) * kWave] = acc[ps][c];
+        return;
     }
 
     // Sum the four waves' partial sums in a fixed order; one store per voxel.
@@ -1376,16 +1800,16 @@ __device__ __forceinline__ void backproject_item(const DevGeom &G, const int ngr
 }
 
 template <bool EXACT, bool EC, int PMAX, int GW, bool TT = false, bool TAB = false>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3)))
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(TAB ? 4 : 3)))
 backproject_kernel(const DevGeom G, const int ngroups, const int nkchunks, const int kp, const int items,
                    const int chunk, const int winCap, const float *__restrict__ proj,
-                   float *__restrict__ vol, const double *__restrict__ stop)
+                   float *__restrict__ vol, const BackPart part, const double *__restrict__ stop)
 {
     extern __shared__ __align__(16) float smem[];
     if (stop && *stop != 0.0) return;
     const int item = (blockIdx.x & 7) * chunk + (blockIdx.x >> 3);
     if (item >= items) return;
-    backproject_item<EXACT, EC, PMAX, GW, TT, TAB>(G, ngroups, nkchunks, kp, winCap, item, smem, proj, vol);
+    backproject_item<EXACT, EC, PMAX, GW, TT, TAB>(G, ngroups, nkchunks, kp, winCap, item, smem, proj, vol, part);
 }
 
 // The backprojection with one detector window per workgroup (cached records
@@ -1401,7 +1825,7 @@ template <bool EXACT, bool EC, int PMAX, int GW>
 __device__ __forceinline__ void backproject_shared_item(const DevGeom &G, const int ngroups, const int nkchunks,
                                                         const int kp, const int winCap, const int item,
                                                         float *smem, const float *__restrict__ proj,
-                                                        float *__restrict__ vol)
+                                                        float *__restrict__ vol, const BackPart &part)
 {
     constexpr int KP = kBackPasses;
     constexpr int CPW = GW / kWaves;                 // columns per wave
@@ -1425,13 +1849,17 @@ __device__ __forceinline__ void backproject_shared_item(const DevGeom &G, const 
     int *bnd = npv + GW;
     float *win = rec + ((GW * PMAX * kRecFloats + GW + 16 + 3) / 4) * 4;
 
-    float acc[4][KP][CPW];
+    // sums of view class cl and column cc at cl CPW + cc
+    typename FloatVec<4 * CPW>::type acc[KP];
 #pragma unroll
-    for (int cl = 0; cl < 4; ++cl)
+    for (int ps = 0; ps < KP; ++ps) acc[ps] = 0.0f;
+    float *const mine = part.sums + ((size_t)item * kWaves + wave) * KP * GW * kWave + lane;
+    if (!part.first) {
 #pragma unroll
         for (int ps = 0; ps < KP; ++ps)
 #pragma unroll
-            for (int c = 0; c < CPW; ++c) acc[cl][ps][c] = 0.0f;
+            for (int c = 0; c < GW; ++c) acc[ps][c] = mine[(ps * GW + c) * kWave];
+    }
 
     for (int view = 0; view < G.nviews; ++view) {
         const int cl = view & 3;
@@ -1439,7 +1867,7 @@ __device__ __forceinline__ void backproject_shared_item(const DevGeom &G, const 
         const float c2f = (float)V.c2;
         // the view's records of the stack
         {
-            const size_t col0 = ((size_t)view * G.vstride * G.n2 + j) * G.n1 + i0;
+            const size_t col0 = ((size_t)view * G.rtab_vs * G.n2 + j) * G.n1 + i0;
             const int tp = G.rtab_pmax;
             const float4 *src = reinterpret_cast<const float4 *>(G.rtab + col0 * tp * kRecFloats);
             constexpr int F4 = kRecFloats / 4;
@@ -1453,21 +1881,12 @@ __device__ __forceinline__ void backproject_shared_item(const DevGeom &G, const 
         // the window: columns of all pieces, rows from the chunk's top voxel
         // (smallest chi2) to its bottom voxel
         {
-            int wu0 = 1 << 30, wu1 = -1, wv0 = 1 << 30, wv1 = -1;
+            int wu0 = 1 << 30, wu1 = -1, wv0 = 1 << 30, wv1 = -(1 << 30);
             const int c = tid % GW, sl = tid / GW;
             if (sl < PMAX && sl < npv[c]) {
                 const float *r = rec + (c * PMAX + sl) * kRecFloats;
-                const int u = __float_as_int(r[0]);
-                const float beta = r[6], mfac = r[10];
-                const float Ytop_hi = fmaf(-(float)kmax, r[4], r[2]) + fmaf(-(float)kmax, r[5], r[3]);
-                const float Ytop_lo = fmaf(-(float)k0, r[4], r[2]) + fmaf(-(float)k0, r[5], r[3]);
-                int a, b, a2, b2;
-                row_range<EC>(Ytop_hi, beta, mfac, c2f, G.N, a, b);
-                row_range<EC>(Ytop_lo, beta, mfac, c2f, G.N, a2, b2);
-                wu0 = u;
-                wu1 = u;
-                wv0 = min(a, a2);
-                wv1 = max(b, b2);
+                wu0 = wu1 = rec_col(__float_as_int(r[0]));
+                window_rows<EC, false>(r, k0, kmax, c2f, detector_reach(c2f, G.N), G.N, wv0, wv1);
             }
 #pragma unroll
             for (int off = 32; off > 0; off >>= 1) {
@@ -1496,131 +1915,74 @@ __device__ __forceinline__ void backproject_shared_item(const DevGeom &G, const 
         wu1 = __builtin_amdgcn_readfirstlane(wu1);
         wv0 = __builtin_amdgcn_readfirstlane(wv0);
         wv1 = __builtin_amdgcn_readfirstlane(wv1);
-        if (wu1 < wu0 || wv1 < wv0) {      // no piece in this view
+        if (wu1 < wu0 || wv1 < max(wv0, 0) || wv0 > G.N - 1) {      // no piece, or no row on the detector
             __syncthreads();
             continue;
         }
-        // one spare row each side absorbs FP32 rounding of intermediate k
-        wv0 = max(wv0 - 1, 0);
-        wv1 = min(wv1 + 1, G.N - 1);
+        // one spare row each side absorbs the FP32 rounding of the row loop's
+        // intermediate k
+        wv0 = max(wv0 - 1, -G.rpad);
+        wv1 = min(wv1 + 1, G.N - 1 + G.rpad);
         const int Wd = wu1 - wu0 + 1;
         const int H = wv1 - wv0 + 1;
         const int Hp = H | 1;
-        const float *pv = proj + (size_t)view * G.vstride * G.N * G.M;
-        const float *sgv = G.sigma ? G.sigma + (size_t)view * G.vstride * G.sigma_views * G.N * G.M : nullptr;
+        BackView B;
+        B.pv = proj + (size_t)view * G.vstride * G.N * G.M;
+        B.sgv = G.sigma ? G.sigma + (size_t)view * G.vstride * G.sigma_views * G.N * G.M : nullptr;
+        B.N = G.N; B.M = G.M;
+        B.wu0 = wu0; B.wv0 = wv0; B.wv1 = wv1; B.Hp = Hp;
+        B.c2f = c2f; B.md = detector_reach(c2f, G.N);
+        B.zt0 = (float)(G.x3lo + G.a3 - V.s3); B.a3f = a3f;
+        B.raw = raw;
         const bool useWin = Wd * Hp <= winCap;
-        if (useWin) {
-            for (int idx = tid; idx < Wd * H; idx += kBlock) {
-                const int uu = idx % Wd, vv = idx / Wd;
-                const size_t off = (size_t)(wv0 + vv) * G.M + (wu0 + uu);
-                float val = pv[off];
-                if (sgv) val *= sgv[off];
-                win[uu * Hp + vv] = val;
-            }
-        }
-        __syncthreads();
+        B.fixed = true;
+        if (useWin)
+            B.fixed = __syncthreads_and(stage_window<kBlock>(win, B.pv, B.sgv, wu0, wv0, wv1, Wd, Hp, G.N, G.M, tid));
+        else
+            __syncthreads();
 
-        auto gather = [&](auto winTag) {
+        auto gather = [&](auto winTag, auto npTag) {
             constexpr bool WIN = decltype(winTag)::value;
+            constexpr int NP = decltype(npTag)::value;
+            bool kv[NP];
+            float kf[NP];
 #pragma unroll
-            for (int ps = 0; ps < KP; ++ps) {
-                if (ps >= kp || k0 + ps * kWave >= G.n3) break;   // unused pass
+            for (int ps = 0; ps < NP; ++ps) {
                 const int k = k0 + ps * kWave + lane;
-                const bool kv = k < G.n3;
-                const float kf = (float)k;
-                const float zt = fmaf(kf, a3f, (float)(G.x3lo + G.a3 - V.s3));
-                const float zc = zt - 0.5f * a3f;
+                kv[ps] = k < G.n3;
+                kf[ps] = (float)min(k, G.n3 - 1);
+            }
+#pragma unroll 1
+            for (int cc = 0; cc < CPW; ++cc) {
+                const int c = wave * CPW + cc;
+                const int np = __builtin_amdgcn_readfirstlane(npv[c]);
+                float a[NP];
+                gather_column<EC, EXACT, false, WIN, NP>(B, rec + c * PMAX * kRecFloats, np, win, kf, kv, a);
 #pragma unroll
-                for (int cc = 0; cc < CPW; ++cc) {
-                    const int c = wave * CPW + cc;
-                    const int np = npv[c];
-                    if (np == 0) continue;
-                    const float *rc = rec + c * PMAX * kRecFloats;
-                    float base = 1.0f;
-                    if (!EXACT && !raw) base = __builtin_amdgcn_rcpf(fmaf(zc, zc, rc[8]));
-                    float a = 0.0f;
-                    for (int p = 0; p < np; ++p) {
-                        const float4 r0 = *reinterpret_cast<const float4 *>(rc + p * kRecFloats);
-                        const float4 r1 = *reinterpret_cast<const float4 *>(rc + p * kRecFloats + 4);
-                        const float4 r2 = *reinterpret_cast<const float4 *>(rc + p * kRecFloats + 8);
-                        const int u = __float_as_int(r0.x);
-                        const float Yh = fmaf(-kf, r1.x, r0.z);
-                        const float Yl = fmaf(-kf, r1.y, r0.w);
-                        const float Ybl = Yl + r1.y;
-                        const float beta = r1.z, rho = r1.w, rho4 = 4.0f * r1.w;
-                        int vlo0, vhi0;
-                        row_range_unclipped<EC>(Yh + Yl, beta, r2.z, c2f, vlo0, vhi0);
-                        const bool ends = !EC || rho < 0.9f;
-                        const int vlo = max(max(vlo0, 0), wv0);
-                        const int vhi = kv ? min(min(vhi0, G.N - 1), wv1) : vlo - 1;
-                        const float *wcol = win + (u - wu0) * Hp - wv0;
-                        const float tb = (float)vlo - 0.5f;
-                        float d = Yh - tb;
-                        float d0 = d + r1.x;         // Ybh - tb, exact on the 2^-10 grid
-                        float tc = tb - c2f;
-                        float s1p, mp, phip;
-                        if (vlo != vlo0 || !ends) boundary<EC>(d, Yl, d0, Ybl, tc, rho, rho4, s1p, mp, phip);
-                        else boundary<false>(d, Yl, d0, Ybl, tc, rho, rho4, s1p, mp, phip);
-                        float psip = mp + phip;
-                        float ap = 0.0f;
-                        auto row = [&](float val) {
-                            d -= 1.0f;
-                            d0 -= 1.0f;
-                            tc += 1.0f;
-                            float s1n, mn, phin;
-                            boundary<EC>(d, Yl, d0, Ybl, tc, rho, rho4, s1n, mn, phin);
-                            float w = psip - phin;
-                            if (EXACT && !raw) {
-                                float mm = 0.5f * (fmaxf(0.0f, -s1p) + fminf(beta, -s1n));
-                                mm = fminf(fmaxf(mm, 0.0f), beta);
-                                const float zb = fmaf(-mm, r2.y, zt);
-                                w *= __builtin_amdgcn_rcpf(fmaf(zb, zb, r2.w));
-                            }
-                            ap = fmaf(w, val, ap);
-                            psip = mn + phin;
-                            s1p = s1n;
-                        };
-                        if (WIN) {
-                            const float *const last = wcol + vhi;
-                            for (const float *qq = wcol + vlo; qq < last; ++qq) row(*qq);
-                            if (vlo <= vhi) {
-                                d -= 1.0f;
-                                d0 -= 1.0f;
-                                tc += 1.0f;
-                                float s1n = d + Yl, phin = 0.0f;
-                                if (vhi != vhi0 || !ends) {
-                                    float mn;
-                                    boundary<EC>(d, Yl, d0, Ybl, tc, rho, rho4, s1n, mn, phin);
-                                }
-                                float w = psip - phin;
-                                if (EXACT && !raw) {
-                                    float mm = 0.5f * (fmaxf(0.0f, -s1p) + fminf(beta, -s1n));
-                                    mm = fminf(fmaxf(mm, 0.0f), beta);
-                                    const float zb = fmaf(-mm, r2.y, zt);
-                                    w *= __builtin_amdgcn_rcpf(fmaf(zb, zb, r2.w));
-                                }
-                                ap = fmaf(w, *last, ap);
-                            }
-                        } else {
-                            for (int v = vlo; v <= vhi; ++v) {
-                                const size_t off = (size_t)v * G.M + u;
-                                float val = pv[off];
-                                if (sgv) val *= sgv[off];
-                                row(val);
-                            }
-                        }
-                        a = fmaf(base * r0.y, ap, a);
-                    }
-                    // the partial sum of view class cl (a uniform index)
-#pragma unroll
-                    for (int ccl = 0; ccl < 4; ++ccl)
-                        if (ccl == cl) acc[ccl][ps][cc] += a;
+                for (int ps = 0; ps < NP; ++ps) {
+                    const float f = column_factor<EXACT, false>(B, rec + c * PMAX * kRecFloats, np, kf[ps]);
+                    acc[ps][cl * CPW + cc] = fmaf(f, a[ps], acc[ps][cl * CPW + cc]);
                 }
             }
         };
-        if (useWin) gather(std::true_type{});
-        else gather(std::false_type{});
+        using P1 = std::integral_constant<int, 1>;
+        using P2 = std::integral_constant<int, KP>;
+        if (kp == 1 || k0 + kWave >= G.n3) {
+            if (useWin) gather(std::true_type{}, P1{});
+            else gather(std::false_type{}, P1{});
+        } else {
+            if (useWin) gather(std::true_type{}, P2{});
+            else gather(std::false_type{}, P2{});
+        }
         __syncthreads();                   // the next view reuses the records and the window
+    }
+
+    if (!part.last) {
+#pragma unroll
+        for (int ps = 0; ps < KP; ++ps)
+#pragma unroll
+            for (int c = 0; c < GW; ++c) mine[(ps * GW + c) * kWave] = acc[ps][c];
+        return;
     }
 
     // ((c0 + c1) + c2) + c3 per voxel, one store each
@@ -1631,25 +1993,25 @@ __device__ __forceinline__ void backproject_shared_item(const DevGeom &G, const 
 #pragma unroll
         for (int cc = 0; cc < CPW; ++cc) {
             const int i = i0 + wave * CPW + cc;
-            float sum = acc[0][ps][cc];
+            float sum = acc[ps][cc];
 #pragma unroll
-            for (int w = 1; w < 4; ++w) sum += acc[w][ps][cc];
+            for (int w = 1; w < 4; ++w) sum += acc[ps][w * CPW + cc];
             if (k < G.n3 && i < G.n1) vol[((size_t)k * G.n2 + j) * G.n1 + i] = sum;
         }
     }
 }
 
 template <bool EXACT, bool EC, int PMAX, int GW>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3)))
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4)))
 backproject_shared_kernel(const DevGeom G, const int ngroups, const int nkchunks, const int kp, const int items,
                           const int chunk, const int winCap, const float *__restrict__ proj,
-                          float *__restrict__ vol, const double *__restrict__ stop)
+                          float *__restrict__ vol, const BackPart part, const double *__restrict__ stop)
 {
     extern __shared__ __align__(16) float smem[];
     if (stop && *stop != 0.0) return;
     const int item = (blockIdx.x & 7) * chunk + (blockIdx.x >> 3);
     if (item >= items) return;
-    backproject_shared_item<EXACT, EC, PMAX, GW>(G, ngroups, nkchunks, kp, winCap, item, smem, proj, vol);
+    backproject_shared_item<EXACT, EC, PMAX, GW>(G, ngroups, nkchunks, kp, winCap, item, smem, proj, vol, part);
 }
 
 // ------------------------------------------------------------ batched, persistent
@@ -1671,7 +2033,7 @@ __device__ __forceinline__ bool next_item(const BatchTable &T, int *counter, int
     return true;
 }
 
-template <bool EXACT, bool EC, bool TAB = false>
+template <bool EXACT, bool EC, bool TAB, bool VT>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5)))
 project_batched_kernel(const BatchProblem *__restrict__ probs, const BatchTable *__restrict__ T,
                        int *counter)
@@ -1682,9 +2044,9 @@ project_batched_kernel(const BatchProblem *__restrict__ probs, const BatchTable 
         const BatchProblem &P = probs[p];
         if (P.stop && *P.stop != 0.0) continue;
         if (P.pmax <= 4)
-            project_item<EXACT, EC, 4, false, TAB>(P.G, P.U, local, smem, P.in, P.out, P.gmax);
+            project_item<EXACT, EC, 4, false, TAB, VT>(P.G, P.U, P.pad, local, smem, VT ? P.vt : P.in, P.out, P.gmax);
         else
-            project_item<EXACT, EC, 8, false, TAB>(P.G, P.U, local, smem, P.in, P.out, P.gmax);
+            project_item<EXACT, EC, 8, false, TAB, VT>(P.G, P.U, P.pad, local, smem, VT ? P.vt : P.in, P.out, P.gmax);
     }
 }
 
@@ -1696,7 +2058,7 @@ project_batched_kernel(const BatchProblem *__restrict__ probs, const BatchTable 
 // single variant of the gather (its registers fit like the single-problem
 // kernel's; one kernel inlining every variant spilled).
 template <bool EXACT, bool EC, int PMAX, int GW, bool TAB = false>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3)))
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(TAB ? 4 : 3)))
 backproject_batched_kernel(const BatchProblem *__restrict__ probs, const BatchTable *__restrict__ T,
                            int *counter)
 {
@@ -1706,7 +2068,7 @@ backproject_batched_kernel(const BatchProblem *__restrict__ probs, const BatchTa
         const BatchProblem &P = probs[p];
         if (P.stop && *P.stop != 0.0) continue;
         backproject_item<EXACT, EC, PMAX, GW, false, TAB>(P.G, P.ngroups, P.nkchunks, P.kp, P.win_cap, local, smem,
-                                                         P.in, P.out);
+                                                         P.in, P.out, BackPart());
     }
 }
 
@@ -1728,52 +2090,52 @@ __global__ void batch_setup(BatchProblem *probs, const BatchIO io, int *counter)
     *counter = 0;
 }
 
+template <bool EXACT, bool EC, int PMAX, bool TT, bool TAB>
+hipError_t launch_p_vt(const DevGeom &g, const ProjLaunch &L, const float *vol, float *proj, const unsigned *gmax,
+                       const float *vt, hipStream_t s, const double *stop)
+{
+    const dim3 grid(8 * L.chunk), block(kBlock);
+    if (vt)
+        hipLaunchKernelGGL((project_kernel<EXACT, EC, PMAX, TT, TAB, true>), grid, block, L.lds, s, g, L.U, L.pad,
+                           L.nbands, vt, proj, gmax, stop);
+    else
+        hipLaunchKernelGGL((project_kernel<EXACT, EC, PMAX, TT, TAB, false>), grid, block, L.lds, s, g, L.U, L.pad,
+                           L.nbands, vol, proj, gmax, stop);
+    return hipGetLastError();
+}
+
 template <bool EXACT, bool EC, bool TT = false>
 hipError_t launch_p(const DevGeom &g, const ProjLaunch &L, const float *vol, float *proj,
-                    unsigned *gmax, hipStream_t s, const double *stop)
+                    const unsigned *gmax, const float *vt, hipStream_t s, const double *stop)
 {
-    if (gmax) {
-        hipError_t e = launch_group_max(g, vol, gmax, s, stop);
-        if (e != hipSuccess) return e;
-    }
-    const dim3 grid(8 * L.chunk), block(kBlock);
-    if (!TT && g.rtab) {
-        // the geometry's cached records
+    if (!gmax) vt = nullptr;   // the wedge scan reads the caller's layout
+    if (g.rtab) {
+        // a table of records (of the projector model launched)
         if (g.rtab_pmax != (L.pmax <= 4 ? 4 : 8)) return hipErrorInvalidValue;
-        if (L.pmax <= 4)
-            hipLaunchKernelGGL((project_kernel<EXACT, EC, 4, false, true>), grid, block, L.lds, s, g, L.U, L.nbands,
-                               vol, proj, gmax, stop);
-        else
-            hipLaunchKernelGGL((project_kernel<EXACT, EC, 8, false, true>), grid, block, L.lds, s, g, L.U, L.nbands,
-                               vol, proj, gmax, stop);
-        return hipGetLastError();
+        if (L.pmax <= 4) return launch_p_vt<EXACT, EC, 4, TT, true>(g, L, vol, proj, gmax, vt, s, stop);
+        return launch_p_vt<EXACT, EC, 8, TT, true>(g, L, vol, proj, gmax, vt, s, stop);
     }
-    if (L.pmax <= 4)
-        hipLaunchKernelGGL((project_kernel<EXACT, EC, 4, TT>), grid, block, L.lds, s, g, L.U, L.nbands, vol, proj,
-                           gmax, stop);
-    else
-        hipLaunchKernelGGL((project_kernel<EXACT, EC, 8, TT>), grid, block, L.lds, s, g, L.U, L.nbands, vol, proj,
-                           gmax, stop);
-    return hipGetLastError();
+    if (L.pmax <= 4) return launch_p_vt<EXACT, EC, 4, TT, false>(g, L, vol, proj, gmax, vt, s, stop);
+    return launch_p_vt<EXACT, EC, 8, TT, false>(g, L, vol, proj, gmax, vt, s, stop);
 }
 
 template <bool EXACT, bool EC, int PMAX, bool TT = false, bool TAB = false>
 hipError_t launch_bp_gw(const DevGeom &g, const BackLaunch &L, const float *proj, float *vol,
-                        hipStream_t s, const double *stop)
+                        hipStream_t s, const double *stop, const BackPart &part)
 {
     const dim3 grid(8 * L.chunk), block(kBlock);
     switch (L.gw) {
     case 16:
         hipLaunchKernelGGL((backproject_kernel<EXACT, EC, PMAX, 16, TT, TAB>), grid, block, L.lds, s, g,
-                           L.ngroups, L.nkchunks, L.kp, L.items, L.chunk, L.win_cap, proj, vol, stop);
+                           L.ngroups, L.nkchunks, L.kp, L.items, L.chunk, L.win_cap, proj, vol, part, stop);
         break;
     case 8:
         hipLaunchKernelGGL((backproject_kernel<EXACT, EC, PMAX, 8, TT, TAB>), grid, block, L.lds, s, g,
-                           L.ngroups, L.nkchunks, L.kp, L.items, L.chunk, L.win_cap, proj, vol, stop);
+                           L.ngroups, L.nkchunks, L.kp, L.items, L.chunk, L.win_cap, proj, vol, part, stop);
         break;
     default:
         hipLaunchKernelGGL((backproject_kernel<EXACT, EC, PMAX, 4, TT, TAB>), grid, block, L.lds, s, g,
-                           L.ngroups, L.nkchunks, L.kp, L.items, L.chunk, L.win_cap, proj, vol, stop);
+                           L.ngroups, L.nkchunks, L.kp, L.items, L.chunk, L.win_cap, proj, vol, part, stop);
         break;
     }
     return hipGetLastError();
@@ -1781,90 +2143,81 @@ hipError_t launch_bp_gw(const DevGeom &g, const BackLaunch &L, const float *proj
 
 template <bool EXACT, bool EC, int PMAX>
 hipError_t launch_bp_shared(const DevGeom &g, const BackLaunch &L, const float *proj, float *vol,
-                            hipStream_t s, const double *stop)
+                            hipStream_t s, const double *stop, const BackPart &part)
 {
     const dim3 grid(8 * L.chunk), block(kBlock);
     switch (L.gw) {
     case 16:
         hipLaunchKernelGGL((backproject_shared_kernel<EXACT, EC, PMAX, 16>), grid, block, L.lds, s, g, L.ngroups,
-                           L.nkchunks, L.kp, L.items, L.chunk, L.win_cap, proj, vol, stop);
+                           L.nkchunks, L.kp, L.items, L.chunk, L.win_cap, proj, vol, part, stop);
         break;
     case 8:
         hipLaunchKernelGGL((backproject_shared_kernel<EXACT, EC, PMAX, 8>), grid, block, L.lds, s, g, L.ngroups,
-                           L.nkchunks, L.kp, L.items, L.chunk, L.win_cap, proj, vol, stop);
+                           L.nkchunks, L.kp, L.items, L.chunk, L.win_cap, proj, vol, part, stop);
         break;
     default:
-        hipLaunchKernelGGL((backproject_shared_kernel<EXACT, EC, PMAX, 4>), grid, block, L.lds, s, g, L.ngroups,
-                           L.nkchunks, L.kp, L.items, L.chunk, L.win_cap, proj, vol, stop);
-        break;
+        return hipErrorInvalidValue;   // plans give a shared window to stacks of 8 or 16 columns only
     }
     return hipGetLastError();
 }
 
 template <bool EXACT, bool EC, bool TT = false>
 hipError_t launch_bp(const DevGeom &g, const BackLaunch &L, const float *proj, float *vol,
-                     hipStream_t s, const double *stop)
+                     hipStream_t s, const double *stop, const BackPart &part)
 {
-    if (!TT && g.rtab) {
-        // the geometry's cached records (the plan L was made for these kernels)
+    if (g.rtab) {
+        // a table of records (the plan L was made for these kernels)
         if (L.pmax > 8 || g.rtab_pmax != (L.pmax <= 4 ? 4 : 8)) return hipErrorInvalidValue;
         if (L.shared) {
-            if (L.pmax <= 4) return launch_bp_shared<EXACT, EC, 4>(g, L, proj, vol, s, stop);
-            return launch_bp_shared<EXACT, EC, 8>(g, L, proj, vol, s, stop);
+            if (TT) return hipErrorInvalidValue;
+            if (L.pmax <= 4) return launch_bp_shared<EXACT, EC, 4>(g, L, proj, vol, s, stop, part);
+            return launch_bp_shared<EXACT, EC, 8>(g, L, proj, vol, s, stop, part);
         }
-        if (L.pmax <= 4) return launch_bp_gw<EXACT, EC, 4, false, true>(g, L, proj, vol, s, stop);
-        return launch_bp_gw<EXACT, EC, 8, false, true>(g, L, proj, vol, s, stop);
+        if (L.pmax <= 4) return launch_bp_gw<EXACT, EC, 4, TT, true>(g, L, proj, vol, s, stop, part);
+        return launch_bp_gw<EXACT, EC, 8, TT, true>(g, L, proj, vol, s, stop, part);
     }
-    if (L.pmax <= 4) return launch_bp_gw<EXACT, EC, 4, TT>(g, L, proj, vol, s, stop);
-    if (L.pmax <= 8) return launch_bp_gw<EXACT, EC, 8, TT>(g, L, proj, vol, s, stop);
+    if (L.pmax <= 4) return launch_bp_gw<EXACT, EC, 4, TT>(g, L, proj, vol, s, stop, part);
+    if (L.pmax <= 8) return launch_bp_gw<EXACT, EC, 8, TT>(g, L, proj, vol, s, stop, part);
     // wide footprints: 4-column stacks only
     if (L.gw != 4) return hipErrorInvalidValue;
     hipLaunchKernelGGL((backproject_kernel<EXACT, EC, kPmaxWide, 4, TT>), dim3(8 * L.chunk), dim3(kBlock), L.lds, s, g,
-                       L.ngroups, L.nkchunks, L.kp, L.items, L.chunk, L.win_cap, proj, vol, stop);
+                       L.ngroups, L.nkchunks, L.kp, L.items, L.chunk, L.win_cap, proj, vol, part, stop);
     return hipGetLastError();
 }
 
-template <bool EXACT, bool EC, int PMAX, bool TT = false, bool TAB = false>
-hipError_t set_lds_one(size_t n)
+hipError_t allow_lds(const void *fn, size_t n)
 {
-    hipError_t e = hipFuncSetAttribute((const void *)project_kernel<EXACT, EC, PMAX, TT, TAB>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)n);
-    if (e == hipSuccess)
-        e = hipFuncSetAttribute((const void *)backproject_kernel<EXACT, EC, PMAX, 16, TT, TAB>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)n);
-    if (e == hipSuccess)
-        e = hipFuncSetAttribute((const void *)backproject_kernel<EXACT, EC, PMAX, 8, TT, TAB>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)n);
-    if (e == hipSuccess)
-        e = hipFuncSetAttribute((const void *)backproject_kernel<EXACT, EC, PMAX, 4, TT, TAB>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)n);
-    if constexpr (TAB && !TT) {
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute((const void *)backproject_shared_kernel<EXACT, EC, PMAX, 16>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)n);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute((const void *)backproject_shared_kernel<EXACT, EC, PMAX, 8>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)n);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute((const void *)backproject_shared_kernel<EXACT, EC, PMAX, 4>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)n);
-    }
+    return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)n);
+}
+
+}  // namespace
+
+// Calls f<EXACT, EC> for the four forms of the cutting voxel projector until
+// one fails.
+template <class F>
+hipError_t each_form(F &&f)
+{
+    using T = std::true_type;
+    using N = std::false_type;
+    hipError_t e = f(T{}, T{});
+    if (e == hipSuccess) e = f(T{}, N{});
+    if (e == hipSuccess) e = f(N{}, T{});
+    if (e == hipSuccess) e = f(N{}, N{});
     return e;
 }
 
-template <bool EXACT, bool EC, bool TT = false>
-hipError_t set_lds_wide(size_t n)
-{
-    return hipFuncSetAttribute((const void *)backproject_kernel<EXACT, EC, kPmaxWide, 4, TT>,
-                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)n);
-}
-
+#if CVP_HAS(2)
+namespace {
 template <bool EXACT, bool EC, bool TAB>
-hipError_t launch_pb(BatchProblem *probs, const BatchTable *tab, int *counter, int grid, size_t lds,
+hipError_t launch_pb(BatchProblem *probs, const BatchTable *tab, int *counter, int grid, size_t lds, bool vt,
                      hipStream_t s)
 {
-    hipLaunchKernelGGL((project_batched_kernel<EXACT, EC, TAB>), dim3(grid), dim3(kBlock), lds, s, probs, tab,
-                       counter);
+    if (vt)
+        hipLaunchKernelGGL((project_batched_kernel<EXACT, EC, TAB, true>), dim3(grid), dim3(kBlock), lds, s, probs, tab,
+                           counter);
+    else
+        hipLaunchKernelGGL((project_batched_kernel<EXACT, EC, TAB, false>), dim3(grid), dim3(kBlock), lds, s, probs, tab,
+                           counter);
     return hipGetLastError();
 }
 
@@ -1892,39 +2245,15 @@ hipError_t launch_bb(BatchProblem *probs, const BatchTable *tab, int *counter, i
                      : launch_bb_p<EXACT, EC, 8, TAB>(probs, tab, counter, grid, lds, gw, s);
 }
 
-template <bool EXACT, bool EC, int PMAX, bool TAB>
-hipError_t set_lds_batched_back(size_t n)
-{
-    hipError_t e = hipFuncSetAttribute((const void *)backproject_batched_kernel<EXACT, EC, PMAX, 16, TAB>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)n);
-    if (e == hipSuccess)
-        e = hipFuncSetAttribute((const void *)backproject_batched_kernel<EXACT, EC, PMAX, 8, TAB>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)n);
-    if (e == hipSuccess)
-        e = hipFuncSetAttribute((const void *)backproject_batched_kernel<EXACT, EC, PMAX, 4, TAB>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)n);
-    return e;
-}
-
-template <bool EXACT, bool EC, bool TAB>
-hipError_t set_lds_batched(size_t n)
-{
-    hipError_t e = hipFuncSetAttribute((const void *)project_batched_kernel<EXACT, EC, TAB>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)n);
-    if (e == hipSuccess) e = set_lds_batched_back<EXACT, EC, 4, TAB>(n);
-    if (e == hipSuccess) e = set_lds_batched_back<EXACT, EC, 8, TAB>(n);
-    return e;
-}
-
 template <bool TAB>
 hipError_t launch_batched_t(bool backward, BatchProblem *probs, const BatchTable *tab, int *counter, bool exact,
-                            bool ec, int grid, size_t lds, int gw, int pmax, hipStream_t s)
+                            bool ec, int grid, size_t lds, int gw, int pmax, bool vt, hipStream_t s)
 {
     if (!backward) {
-        if (exact) return ec ? launch_pb<true, true, TAB>(probs, tab, counter, grid, lds, s)
-                             : launch_pb<true, false, TAB>(probs, tab, counter, grid, lds, s);
-        return ec ? launch_pb<false, true, TAB>(probs, tab, counter, grid, lds, s)
-                  : launch_pb<false, false, TAB>(probs, tab, counter, grid, lds, s);
+        if (exact) return ec ? launch_pb<true, true, TAB>(probs, tab, counter, grid, lds, vt, s)
+                             : launch_pb<true, false, TAB>(probs, tab, counter, grid, lds, vt, s);
+        return ec ? launch_pb<false, true, TAB>(probs, tab, counter, grid, lds, vt, s)
+                  : launch_pb<false, false, TAB>(probs, tab, counter, grid, lds, vt, s);
     }
     if (exact) return ec ? launch_bb<true, true, TAB>(probs, tab, counter, grid, lds, gw, pmax, s)
                          : launch_bb<true, false, TAB>(probs, tab, counter, grid, lds, gw, pmax, s);
@@ -1941,10 +2270,11 @@ const void *back_batched_fn(int gw)
 }
 
 template <bool TAB>
-int blocks_per_cu_t(bool backward, size_t lds, int gw, int pmax)
+int blocks_per_cu_t(bool backward, size_t lds, int gw, int pmax, bool vt)
 {
     int nb = 0;
-    const void *fn = !backward ? (const void *)project_batched_kernel<false, true, TAB>
+    const void *fn = !backward ? (vt ? (const void *)project_batched_kernel<false, true, TAB, true>
+                                     : (const void *)project_batched_kernel<false, true, TAB, false>)
                                : pmax <= 4 ? back_batched_fn<4, TAB>(gw) : back_batched_fn<8, TAB>(gw);
     hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, kBlock, lds);
     if (e != hipSuccess || nb < 1) nb = 1;
@@ -1955,69 +2285,98 @@ int blocks_per_cu_t(bool backward, size_t lds, int gw, int pmax)
 
 hipError_t launch_batched(bool backward, BatchProblem *probs, const BatchTable *tab, int *counter,
                           const BatchIO &io, bool exact, bool ec, int grid, size_t lds, int gw, int pmax, bool cached,
-                          hipStream_t s)
+                          bool vt, hipStream_t s)
 {
     hipLaunchKernelGGL(batch_setup, dim3(1), dim3(64), 0, s, probs, io, counter);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return cached ? launch_batched_t<true>(backward, probs, tab, counter, exact, ec, grid, lds, gw, pmax, s)
-                  : launch_batched_t<false>(backward, probs, tab, counter, exact, ec, grid, lds, gw, pmax, s);
+    return cached ? launch_batched_t<true>(backward, probs, tab, counter, exact, ec, grid, lds, gw, pmax, vt, s)
+                  : launch_batched_t<false>(backward, probs, tab, counter, exact, ec, grid, lds, gw, pmax, vt, s);
 }
 
 // Workgroups of a persistent batched kernel that fit on one CU at this LDS size.
-int batched_blocks_per_cu(bool backward, size_t lds, int gw, int pmax, bool cached)
+int batched_blocks_per_cu(bool backward, size_t lds, int gw, int pmax, bool cached, bool vt)
 {
-    return cached ? blocks_per_cu_t<true>(backward, lds, gw, pmax) : blocks_per_cu_t<false>(backward, lds, gw, pmax);
+    return cached ? blocks_per_cu_t<true>(backward, lds, gw, pmax, vt)
+                  : blocks_per_cu_t<false>(backward, lds, gw, pmax, vt);
+}
+
+template <int PMAX, bool TAB>
+static hipError_t allow_batched_back(size_t n)
+{
+    return each_form([&](auto x, auto c) {
+        constexpr bool X = decltype(x)::value, C = decltype(c)::value;
+        hipError_t r = allow_lds((const void *)backproject_batched_kernel<X, C, PMAX, 16, TAB>, n);
+        if (r == hipSuccess) r = allow_lds((const void *)backproject_batched_kernel<X, C, PMAX, 8, TAB>, n);
+        if (r == hipSuccess) r = allow_lds((const void *)backproject_batched_kernel<X, C, PMAX, 4, TAB>, n);
+        return r;
+    });
+}
+
+hipError_t configure_batched_lds(size_t n)
+{
+    hipError_t e = each_form([&](auto x, auto c) {
+        constexpr bool X = decltype(x)::value, C = decltype(c)::value;
+        hipError_t r = allow_lds((const void *)project_batched_kernel<X, C, false, false>, n);
+        if (r == hipSuccess) r = allow_lds((const void *)project_batched_kernel<X, C, false, true>, n);
+        if (r == hipSuccess) r = allow_lds((const void *)project_batched_kernel<X, C, true, false>, n);
+        if (r == hipSuccess) r = allow_lds((const void *)project_batched_kernel<X, C, true, true>, n);
+        return r;
+    });
+    if (e == hipSuccess) e = allow_batched_back<4, false>(n);
+    if (e == hipSuccess) e = allow_batched_back<8, false>(n);
+    if (e == hipSuccess) e = allow_batched_back<4, true>(n);
+    if (e == hipSuccess) e = allow_batched_back<8, true>(n);
+    return e;
+}
+#endif
+
+#if CVP_HAS(0)
+template <bool EXACT, bool EC, int PMAX, bool TT, bool TAB>
+hipError_t allow_project(size_t n)
+{
+    hipError_t e = allow_lds((const void *)project_kernel<EXACT, EC, PMAX, TT, TAB, false>, n);
+    if (e == hipSuccess) e = allow_lds((const void *)project_kernel<EXACT, EC, PMAX, TT, TAB, true>, n);
+    return e;
 }
 
 // Allow the dynamic LDS sizes chosen by the host (above the 64 KB default).
-hipError_t configure_kernel_lds(size_t max_lds, size_t max_lds_batched)
+hipError_t configure_project_lds(size_t n)
 {
-    hipError_t e = hipSuccess;
-    if (e == hipSuccess) e = set_lds_one<true, true, 4>(max_lds);
-    if (e == hipSuccess) e = set_lds_one<true, false, 4>(max_lds);
-    if (e == hipSuccess) e = set_lds_one<false, true, 4>(max_lds);
-    if (e == hipSuccess) e = set_lds_one<false, false, 4>(max_lds);
-    if (e == hipSuccess) e = set_lds_one<true, true, 8>(max_lds);
-    if (e == hipSuccess) e = set_lds_one<true, false, 8>(max_lds);
-    if (e == hipSuccess) e = set_lds_one<false, true, 8>(max_lds);
-    if (e == hipSuccess) e = set_lds_one<false, false, 8>(max_lds);
-    if (e == hipSuccess) e = set_lds_wide<true, true>(max_lds);
-    if (e == hipSuccess) e = set_lds_wide<true, false>(max_lds);
-    if (e == hipSuccess) e = set_lds_wide<false, true>(max_lds);
-    if (e == hipSuccess) e = set_lds_wide<false, false>(max_lds);
-    if (e == hipSuccess) e = set_lds_one<false, true, 4, true>(max_lds);
-    if (e == hipSuccess) e = set_lds_one<false, true, 8, true>(max_lds);
-    if (e == hipSuccess) e = set_lds_wide<false, true, true>(max_lds);
-    if (e == hipSuccess) e = set_lds_one<true, true, 4, false, true>(max_lds);
-    if (e == hipSuccess) e = set_lds_one<true, false, 4, false, true>(max_lds);
-    if (e == hipSuccess) e = set_lds_one<false, true, 4, false, true>(max_lds);
-    if (e == hipSuccess) e = set_lds_one<false, false, 4, false, true>(max_lds);
-    if (e == hipSuccess) e = set_lds_one<true, true, 8, false, true>(max_lds);
-    if (e == hipSuccess) e = set_lds_one<true, false, 8, false, true>(max_lds);
-    if (e == hipSuccess) e = set_lds_one<false, true, 8, false, true>(max_lds);
-    if (e == hipSuccess) e = set_lds_one<false, false, 8, false, true>(max_lds);
-    if (e == hipSuccess) e = set_lds_batched<true, true, false>(max_lds_batched);
-    if (e == hipSuccess) e = set_lds_batched<true, false, false>(max_lds_batched);
-    if (e == hipSuccess) e = set_lds_batched<false, true, false>(max_lds_batched);
-    if (e == hipSuccess) e = set_lds_batched<false, false, false>(max_lds_batched);
-    if (e == hipSuccess) e = set_lds_batched<true, true, true>(max_lds_batched);
-    if (e == hipSuccess) e = set_lds_batched<true, false, true>(max_lds_batched);
-    if (e == hipSuccess) e = set_lds_batched<false, true, true>(max_lds_batched);
-    if (e == hipSuccess) e = set_lds_batched<false, false, true>(max_lds_batched);
+    hipError_t e = each_form([&](auto x, auto c) {
+        constexpr bool X = decltype(x)::value, C = decltype(c)::value;
+        hipError_t r = allow_project<X, C, 4, false, false>(n);
+        if (r == hipSuccess) r = allow_project<X, C, 8, false, false>(n);
+        if (r == hipSuccess) r = allow_project<X, C, 4, false, true>(n);
+        if (r == hipSuccess) r = allow_project<X, C, 8, false, true>(n);
+        return r;
+    });
+    if (e == hipSuccess) e = allow_project<false, true, 4, true, false>(n);
+    if (e == hipSuccess) e = allow_project<false, true, 8, true, false>(n);
+    if (e == hipSuccess) e = allow_project<false, true, 4, true, true>(n);
+    if (e == hipSuccess) e = allow_project<false, true, 8, true, true>(n);
     return e;
 }
 
 hipError_t launch_project(const DevGeom &g, const ProjLaunch &L, int model, bool ec,
-                          const float *vol, float *proj, unsigned *gmax, hipStream_t stream, const double *stop)
+                          const float *vol, float *proj, const unsigned *gmax, const float *vt, hipStream_t stream,
+                          const double *stop)
 {
     // TT: its ramps need the row margins of the EC instantiations
-    if (model == kModelTT) return launch_p<false, true, true>(g, L, vol, proj, gmax, stream, stop);
+    if (model == kModelTT) return launch_p<false, true, true>(g, L, vol, proj, gmax, vt, stream, stop);
     const bool exact = model == kModelExact;
-    if (exact) return ec ? launch_p<true, true>(g, L, vol, proj, gmax, stream, stop)
-                         : launch_p<true, false>(g, L, vol, proj, gmax, stream, stop);
-    return ec ? launch_p<false, true>(g, L, vol, proj, gmax, stream, stop)
-              : launch_p<false, false>(g, L, vol, proj, gmax, stream, stop);
+    if (exact) return ec ? launch_p<true, true>(g, L, vol, proj, gmax, vt, stream, stop)
+                         : launch_p<true, false>(g, L, vol, proj, gmax, vt, stream, stop);
+    return ec ? launch_p<false, true>(g, L, vol, proj, gmax, vt, stream, stop)
+              : launch_p<false, false>(g, L, vol, proj, gmax, vt, stream, stop);
+}
+
+hipError_t launch_transpose_max(const DevGeom &g, const float *vol, float *vt, unsigned *gmax, hipStream_t stream,
+                                const double *stop)
+{
+    hipLaunchKernelGGL(transpose_max_kernel, dim3((unsigned)(g.n2 * ((g.n1 + kWave - 1) / kWave))), dim3(kBlock), 0,
+                       stream, g, vol, vt, gmax, stop);
+    return hipGetLastError();
 }
 
 int64_t group_max_cells(const DevGeom &g)
@@ -2034,16 +2393,15 @@ hipError_t launch_group_max(const DevGeom &g, const float *vol, unsigned *gmax, 
     return hipGetLastError();
 }
 
-hipError_t launch_record_table(const DevGeom &g, int pmax, float *rec, int *cnt, hipStream_t stream)
+hipError_t launch_record_table(const DevGeom &g, int pmax, bool tt, float *rec, int *cnt, hipStream_t stream,
+                               const double *stop)
 {
     const int64_t n = (int64_t)g.n1 * g.n2 * g.nviews;
     const dim3 grid((unsigned)((n + kBlock - 1) / kBlock)), block(kBlock);
-    if (pmax == 4)
-        hipLaunchKernelGGL(record_table_kernel<4>, grid, block, 0, stream, g, rec, cnt);
-    else if (pmax == 8)
-        hipLaunchKernelGGL(record_table_kernel<8>, grid, block, 0, stream, g, rec, cnt);
-    else
-        return hipErrorInvalidValue;
+    if (pmax != 4 && pmax != 8) return hipErrorInvalidValue;
+    const auto fn = tt ? (pmax == 4 ? record_table_kernel<4, true> : record_table_kernel<8, true>)
+                       : (pmax == 4 ? record_table_kernel<4, false> : record_table_kernel<8, false>);
+    hipLaunchKernelGGL(fn, grid, block, 0, stream, g, rec, cnt, stop);
     return hipGetLastError();
 }
 
@@ -2079,15 +2437,56 @@ hipError_t static_scratch(unsigned **out)
     return hipSuccess;
 }
 
-hipError_t launch_backproject(const DevGeom &g, const BackLaunch &L, int model, bool ec,
-                              const float *proj, float *vol, hipStream_t stream, const double *stop)
+#endif
+
+#if CVP_HAS(1)
+template <bool EXACT, bool EC, int PMAX, bool TT, bool TAB>
+hipError_t allow_backproject(size_t n)
 {
-    if (model == kModelTT) return launch_bp<false, true, true>(g, L, proj, vol, stream, stop);
-    const bool exact = model == kModelExact;
-    if (exact) return ec ? launch_bp<true, true>(g, L, proj, vol, stream, stop)
-                         : launch_bp<true, false>(g, L, proj, vol, stream, stop);
-    return ec ? launch_bp<false, true>(g, L, proj, vol, stream, stop)
-              : launch_bp<false, false>(g, L, proj, vol, stream, stop);
+    if constexpr (PMAX == kPmaxWide) {
+        return allow_lds((const void *)backproject_kernel<EXACT, EC, PMAX, 4, TT, TAB>, n);
+    } else {
+        hipError_t e = allow_lds((const void *)backproject_kernel<EXACT, EC, PMAX, 16, TT, TAB>, n);
+        if (e == hipSuccess) e = allow_lds((const void *)backproject_kernel<EXACT, EC, PMAX, 8, TT, TAB>, n);
+        if (e == hipSuccess) e = allow_lds((const void *)backproject_kernel<EXACT, EC, PMAX, 4, TT, TAB>, n);
+        if constexpr (TAB && !TT) {
+            if (e == hipSuccess) e = allow_lds((const void *)backproject_shared_kernel<EXACT, EC, PMAX, 16>, n);
+            if (e == hipSuccess) e = allow_lds((const void *)backproject_shared_kernel<EXACT, EC, PMAX, 8>, n);
+        }
+        return e;
+    }
 }
+
+hipError_t configure_backproject_lds(size_t n)
+{
+    hipError_t e = each_form([&](auto x, auto c) {
+        constexpr bool X = decltype(x)::value, C = decltype(c)::value;
+        hipError_t r = allow_backproject<X, C, 4, false, false>(n);
+        if (r == hipSuccess) r = allow_backproject<X, C, 8, false, false>(n);
+        if (r == hipSuccess) r = allow_backproject<X, C, kPmaxWide, false, false>(n);
+        if (r == hipSuccess) r = allow_backproject<X, C, 4, false, true>(n);
+        if (r == hipSuccess) r = allow_backproject<X, C, 8, false, true>(n);
+        return r;
+    });
+    if (e == hipSuccess) e = allow_backproject<false, true, 4, true, false>(n);
+    if (e == hipSuccess) e = allow_backproject<false, true, 8, true, false>(n);
+    if (e == hipSuccess) e = allow_backproject<false, true, kPmaxWide, true, false>(n);
+    if (e == hipSuccess) e = allow_backproject<false, true, 4, true, true>(n);
+    if (e == hipSuccess) e = allow_backproject<false, true, 8, true, true>(n);
+    return e;
+}
+
+hipError_t launch_backproject(const DevGeom &g, const BackLaunch &L, int model, bool ec,
+                              const float *proj, float *vol, hipStream_t stream, const double *stop, const BackPart &part)
+{
+    if (model == kModelTT) return launch_bp<false, true, true>(g, L, proj, vol, stream, stop, part);
+    const bool exact = model == kModelExact;
+    if (exact) return ec ? launch_bp<true, true>(g, L, proj, vol, stream, stop, part)
+                         : launch_bp<true, false>(g, L, proj, vol, stream, stop, part);
+    return ec ? launch_bp<false, true>(g, L, proj, vol, stream, stop, part)
+              : launch_bp<false, false>(g, L, proj, vol, stream, stop, part);
+}
+
+#endif
 
 }  // namespace cvp

@@ -141,19 +141,38 @@ def _stream():
     return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
 
 
+def operator_scratch(geom, o, device, project=True, backproject=True):
+    """Scratch for the operators of ``geom`` with the options ``o`` (an
+    _lib.OptionsC) from torch's caching allocator, on
+    the current stream (cvp_operator_workspace_size): the whole of it, or as
+    much as the free memory holds (down to nothing for a backprojection, the
+    per-group maxima for a projection); the results do not depend on it."""
+    p, b = ctypes.c_int64(), ctypes.c_int64()
+    _lib.check(_lib.lib().cvp_operator_workspace_size(geom.handle, ctypes.byref(o), ctypes.byref(p),
+                                                      ctypes.byref(b)))
+    want = max(p.value if project else 0, b.value if backproject else 0)
+    least = 4 * geom.project_work_words if project else 0
+    while want > least:
+        try:
+            return torch.empty(want, dtype=torch.uint8, device=device)
+        except torch.OutOfMemoryError:
+            want //= 4
+    return torch.empty(least, dtype=torch.uint8, device=device)
+
+
 def project(x, geom: Geometry, opts: Options = Options(), out=None):
     """b = A x (overwrites ``out`` if given).  Runs cvp_project_ws with its
-    small scratch (the per-group maxima of |x|) from torch's caching
-    allocator on the current stream."""
+    scratch (see operator_scratch) from torch's caching allocator on the
+    current stream."""
     _check_tensor(x, geom.vol_shape, "x")
     if out is None:
         out = torch.empty(geom.proj_shape, dtype=torch.float32, device=x.device)
     _check_tensor(out, geom.proj_shape, "out")
-    work = torch.empty(geom.project_work_words, dtype=torch.int32, device=x.device)
     o = opts.c()
+    work = operator_scratch(geom, o, x.device, backproject=False)
     _lib.check(_lib.lib().cvp_project_ws(geom.handle, ctypes.byref(o), ctypes.c_void_p(x.data_ptr()),
                                          ctypes.c_void_p(out.data_ptr()), ctypes.c_void_p(work.data_ptr()),
-                                         4 * work.numel(), _stream()))
+                                         work.numel(), _stream()))
     return out
 
 
@@ -170,14 +189,17 @@ def project_siddon(x, geom: Geometry, K: int, out=None):
 
 
 def backproject(b, geom: Geometry, opts: Options = Options(), out=None):
-    """x = A^T b (overwrites ``out`` if given)."""
+    """x = A^T b (overwrites ``out`` if given).  Runs cvp_backproject_ws with
+    scratch from torch's caching allocator (see operator_scratch)."""
     _check_tensor(b, geom.proj_shape, "b")
     if out is None:
         out = torch.empty(geom.vol_shape, dtype=torch.float32, device=b.device)
     _check_tensor(out, geom.vol_shape, "out")
     o = opts.c()
-    _lib.check(_lib.lib().cvp_backproject(geom.handle, ctypes.byref(o), ctypes.c_void_p(b.data_ptr()),
-                                          ctypes.c_void_p(out.data_ptr()), _stream()))
+    work = operator_scratch(geom, o, b.device, project=False)
+    _lib.check(_lib.lib().cvp_backproject_ws(geom.handle, ctypes.byref(o), ctypes.c_void_p(b.data_ptr()),
+                                             ctypes.c_void_p(out.data_ptr()), ctypes.c_void_p(work.data_ptr()),
+                                             work.numel(), _stream()))
     return out
 
 

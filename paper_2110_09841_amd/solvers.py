@@ -10,7 +10,7 @@ import ctypes
 import torch
 
 from . import _lib
-from .cvp import Geometry, Options, _check_tensor, _stream
+from .cvp import Geometry, Options, _check_tensor, _stream, operator_scratch
 
 LSQR_SCALARS = 16
 HISTORY = 4096
@@ -26,10 +26,10 @@ def project_views(x, geom: Geometry, view0, view_stride, n_views, out, opts: Opt
     views of ``out`` are left untouched."""
     _check_tensor(x, geom.vol_shape, "x")
     _check_tensor(out, geom.proj_shape, "out")
-    work = torch.empty(geom.project_work_words, dtype=torch.int32, device=x.device)
     o = opts.c()
+    work = operator_scratch(geom, o, x.device, backproject=False)
     _lib.check(_lib.lib().cvp_project_views(geom.handle, ctypes.byref(o), _vp(x), _vp(out), int(view0),
-                                            int(view_stride), int(n_views), _vp(work), 4 * work.numel(),
+                                            int(view_stride), int(n_views), _vp(work), work.numel(),
                                             _stream()))
     return out
 
@@ -42,8 +42,9 @@ def backproject_views(b, geom: Geometry, view0, view_stride, n_views, out=None, 
         out = torch.empty(geom.vol_shape, dtype=torch.float32, device=b.device)
     _check_tensor(out, geom.vol_shape, "out")
     o = opts.c()
-    _lib.check(_lib.lib().cvp_backproject_views(geom.handle, ctypes.byref(o), _vp(b), _vp(out), int(view0),
-                                                int(view_stride), int(n_views), _stream()))
+    work = operator_scratch(geom, o, b.device, project=False)
+    _lib.check(_lib.lib().cvp_backproject_views_ws(geom.handle, ctypes.byref(o), _vp(b), _vp(out), int(view0),
+                                                   int(view_stride), int(n_views), _vp(work), work.numel(), _stream()))
     return out
 
 
@@ -83,19 +84,20 @@ class LSQR(_Captured):
         _lib.check(_lib.lib().cvp_lsqr_workspace_size(geom.n_voxels, self.u.numel(), ctypes.byref(nbytes)))
         self.work = torch.zeros(nbytes.value // 8, dtype=torch.float64, device=dev)
         self._o = opts.c()
+        self.scratch = operator_scratch(geom, self._o, dev)
 
     def _ptrs(self):
         return [_vp(t) for t in (self.x, self.u, self.v, self.w, self.q, self.s, self.work)]
 
     def start(self):
         x, u, v, w, q, s, wk = self._ptrs()
-        _lib.check(_lib.lib().cvp_lsqr_start(self.geom.handle, ctypes.byref(self._o), _vp(self.b), x, u, v, w, q, s,
-                                             wk, _stream()))
+        _lib.check(_lib.lib().cvp_lsqr_start_ws(self.geom.handle, ctypes.byref(self._o), _vp(self.b), x, u, v, w, q, s,
+                                                wk, _vp(self.scratch), self.scratch.numel(), _stream()))
 
     def iterate(self, n: int):
         x, u, v, w, q, s, wk = self._ptrs()
-        _lib.check(_lib.lib().cvp_lsqr_iterate(self.geom.handle, ctypes.byref(self._o), int(n), x, u, v, w, q, s,
-                                               wk, _stream()))
+        _lib.check(_lib.lib().cvp_lsqr_iterate_ws(self.geom.handle, ctypes.byref(self._o), int(n), x, u, v, w, q, s,
+                                                  wk, _vp(self.scratch), self.scratch.numel(), _stream()))
 
     def iterations(self):
         return int(self.work[6].item())
@@ -125,14 +127,16 @@ class OSSART(_Captured):
         self.q = torch.empty(geom.proj_shape, dtype=torch.float32, device=dev)
         self.z = torch.empty(geom.vol_shape, dtype=torch.float32, device=dev)
         self._o = opts.c()
+        self.scratch = operator_scratch(geom, self._o, dev)
 
     def setup(self):
-        _lib.check(_lib.lib().cvp_sart_setup(self.geom.handle, ctypes.byref(self._o), self.T, _vp(self.rowsum),
-                                             _vp(self.colsum), _vp(self.q), _stream()))
+        _lib.check(_lib.lib().cvp_sart_setup_ws(self.geom.handle, ctypes.byref(self._o), self.T, _vp(self.rowsum),
+                                                _vp(self.colsum), _vp(self.q), _vp(self.scratch),
+                                                self.scratch.numel(), _stream()))
 
     def iterate(self, n_sweeps: int):
-        _lib.check(_lib.lib().cvp_sart_iterate(self.geom.handle, ctypes.byref(self._o), self.T, int(n_sweeps),
-                                               ctypes.c_float(self.lam), int(self.nonneg), _vp(self.b), _vp(self.x),
-                                               _vp(self.rowsum), _vp(self.colsum), _vp(self.q), _vp(self.z),
-                                               _stream()))
+        _lib.check(_lib.lib().cvp_sart_iterate_ws(self.geom.handle, ctypes.byref(self._o), self.T, int(n_sweeps),
+                                                  ctypes.c_float(self.lam), int(self.nonneg), _vp(self.b),
+                                                  _vp(self.x), _vp(self.rowsum), _vp(self.colsum), _vp(self.q),
+                                                  _vp(self.z), _vp(self.scratch), self.scratch.numel(), _stream()))
 
