@@ -53,6 +53,7 @@ struct cvp_geometry {
     double wone_tt = 0.0, wsum_tt = 0.0;   // fixed-point bounds of the TT projector's weights
     cvp::BackLaunch blc{};           // backprojection plan of the kernels that read a table of records
     cvp::BackLaunch blt{};           // the same without a shared window (TT footprints)
+    int band_set = 0;                // projection band width set by the caller (0: default)
     int bp_wpc = 0;                  // requested workgroups per CU of that plan (0: default)
     int bp_shared = 0;               // requested one window per workgroup in that plan
     float *d_rtab = nullptr;         // cached piece records (cvp_geometry_cache_records)
@@ -106,8 +107,8 @@ size_t project_lds_bytes(int U, int N, int n2, int pmax)
 {
     const size_t npad = (size_t)(N | 1);
     (void)pmax;   // piece records live in registers
-    // 64-bit band image, row tables, prefix-sum scratch, per-wave maxima
-    return (size_t)U * npad * 8 + (size_t)(2 * n2 + 1 + kBlock + kWaves) * 4 + 16;
+    // 64-bit band image, row tables, prefix sums and maxima per wave
+    return (size_t)U * npad * 8 + (size_t)(2 * n2 + 1 + 2 * kWaves) * 4 + 16;
 }
 
 size_t backproject_lds_bytes(int gw, int pmax, int winCap)
@@ -117,13 +118,28 @@ size_t backproject_lds_bytes(int gw, int pmax, int winCap)
     return kWaves * waveFloats * 4;
 }
 
+// Default projection plans.  Band widths measured (transposed volume, records
+// kept; A x in us): 64^3 x 32 views, 96 columns: U = 1, 2, 8, 32: 154, 152,
+// 355, 996; 80x80x72 x 8 views, 128 columns: U = 1, 2, 8: 128, 175, 519;
+// 107x93x131 x 75 views, 181 columns: U = 1, 3, 8, 22: 1309, 1004, 1051, 2300;
+// 128^3 x 180 views, 256 columns: U = 3, 8, 13: 3051, 2723, 3000; 256^3 x 360
+// views, 512 columns: U = 4, 8, 9, 16 (ms): 46.7, 43.1, 46.0, 54.4; 512^3 x 248
+// views: U = 4, 6, 8 (ms): 85.6, 83.9, 99 (6 fills the LDS budget).
+constexpr int kBandMost = 8;
+constexpr int64_t kItemsLeast = 3 * 1280;
+// Volumes up to 64 MiB take their work items in plain order (views of a band
+// next to each other, round robin over the XCDs): 3 to 14 % faster than bands
+// by XCD on those workloads, which leaves XCDs idle when bands are few; at
+// 512^3, where the wedges of a band share an XCD's L2, 1 % slower.
+constexpr int64_t kLinearVolume = int64_t(64) << 20;
+
 // Projection: bands of U detector columns (a 64-bit band image of U x N and
 // the row tables in LDS).  force_u = 0: U as large as the default LDS budget
-// (five workgroups per compute unit) allows; otherwise U = force_u if its LDS
-// fits one workgroup.
-static bool plan_projection_pad(int N, int n2, int M, int nviews, int pmax, int force_u, int pad, ProjLaunch &L)
+// (five workgroups per compute unit) and the rules above allow; otherwise U =
+// force_u if its LDS fits one workgroup.
+static bool plan_projection_pad(const DevGeom &G, int nviews, int pmax, int force_u, int pad, ProjLaunch &L)
 {
-    N += 2 * pad;
+    const int N = G.N + 2 * pad, n2 = G.n2, M = G.M;
     // A work item keeps at most pmax pieces per column, and a column's pieces
     // inside a band of U detector columns are at most U; pmax = 8 with U <= 8
     // therefore serves footprints of any width.
@@ -136,7 +152,11 @@ static bool plan_projection_pad(int N, int n2, int M, int nviews, int pmax, int 
         // as wide as the default budget allows; a single column may use more
         if (fixed + perU > kLdsMax) return false;
         U = fixed + perU <= kLdsBudget ? (int)((kLdsBudget - fixed) / perU) : 1;
-        U = std::max(1, std::min(U, umax));
+        U = std::max(1, std::min(U, kBandMost));
+        // narrower bands while there are too few workgroups to keep the GPU's
+        // 256 compute units x 5 busy three times over: an item's columns are
+        // walked one after another, so few wide bands leave the chip idle
+        while (U > 1 && (int64_t)((M + U - 1) / U) * nviews < kItemsLeast) --U;
     } else if (U > umax || project_lds_bytes(U, N, n2, pmax) > kLdsMax) {
         return false;
     }
@@ -146,6 +166,7 @@ static bool plan_projection_pad(int N, int n2, int M, int nviews, int pmax, int 
     L.chunk = nviews * ((L.nbands + 7) / 8);   // work items per XCD (bands interleaved over XCDs)
     L.pmax = pmax;
     L.pad = pad;
+    L.linear = (int64_t)G.n1 * G.n2 * G.n3 * (int64_t)sizeof(float) <= kLinearVolume;
     L.lds = project_lds_bytes(U, N, n2, pmax);
     return true;
 }
@@ -154,8 +175,7 @@ static bool plan_projection_pad(int N, int n2, int M, int nviews, int pmax, int 
 // (pieces then take the general row loop) where only that fits the LDS.
 bool plan_projection(const DevGeom &G, int nviews, int pmax, int force_u, ProjLaunch &L)
 {
-    return plan_projection_pad(G.N, G.n2, G.M, nviews, pmax, force_u, G.rpad, L) ||
-           plan_projection_pad(G.N, G.n2, G.M, nviews, pmax, force_u, 0, L);
+    return plan_projection_pad(G, nviews, pmax, force_u, G.rpad, L) || plan_projection_pad(G, nviews, pmax, force_u, 0, L);
 }
 
 // Backprojection: stacks of GW columns x 64 kp voxels; the largest stack whose
@@ -693,6 +713,7 @@ cvp_status cvp_geometry_set_launch(cvp_geometry *g, const cvp_launch *in)
             blc = bl;
     }
     g->pl = pl;
+    g->band_set = u;
     g->bl = bl;
     g->blc = blc;
     g->bp_wpc = wpc;
@@ -1683,7 +1704,7 @@ cvp_status cvp_sart_iterate_ws(const cvp_geometry *g, const cvp_options *o, int3
             const int cnt = subset_count(V, n_subsets, t);
             view_subset(g, t, n_subsets, cnt, Gt, off);
             cvp::ProjLaunch pl{};
-            cvp::plan_projection(G, cnt, g->pmax, g->pl.U, pl);
+            cvp::plan_projection(G, cnt, g->pmax, g->band_set, pl);   // bands for this many views
             // q_t = A_t x (z is free: it holds the per-group maxima)
             e = run_project(g, Gt, pl, ex, ec, d_x, d_q + off, (unsigned *)d_z, op_work, op_bytes, sm);
             if (e == hipSuccess)

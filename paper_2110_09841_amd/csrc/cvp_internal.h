@@ -89,6 +89,7 @@ struct ProjLaunch {
     int nbands;
     int items;       // nbands * nviews
     int chunk;       // work-item slots per XCD (grid = 8 * chunk)
+    int linear;      // 1: work items in order over the whole GPU instead of bands by XCD
     int pmax;        // 4 or 8 (8 with U <= 8 for wider footprints)
     int pad;         // spare rows at each end of a band column (the geometry's rpad, or 0 if they do not fit)
     size_t lds;      // dynamic LDS bytes

@@ -815,7 +815,7 @@ __device__ __forceinline__ void project_item(const DevGeom &G, const int U, cons
     int *rowStart = reinterpret_cast<int *>(bins + U * Npad);
     int *rowQ = rowStart + (G.n2 + 1);
     int *part = rowQ + G.n2;
-    unsigned *red = reinterpret_cast<unsigned *>(part + kBlock);
+    unsigned *red = reinterpret_cast<unsigned *>(part + kWaves);
 
     for (int idx = tid; idx < U * Npad; idx += kBlock) bins[idx] = 0ull;
 
@@ -835,41 +835,50 @@ __device__ __forceinline__ void project_item(const DevGeom &G, const int U, cons
             const int j = tid * rows_per + r;
             if (j >= G.n2) break;
             const float y0 = (float)(G.x2lo + j * G.a2 - V.s2), y1 = y0 + (float)G.a2;
+            // chi1 at the two corners of a group edge (consecutive groups share it)
+            auto edge = [&](int i, float &mn, float &mx) {
+                const float x = (float)(G.x1lo + i * G.a1 - V.s1);
+                const float c0 = fb * (e1x * x + e1y * y0) * __builtin_amdgcn_rcpf(dx * x + dy * y0);
+                const float c1 = fb * (e1x * x + e1y * y1) * __builtin_amdgcn_rcpf(dx * x + dy * y1);
+                mn = (float)V.c1 + fminf(c0, c1);
+                mx = (float)V.c1 + fmaxf(c0, c1);
+            };
             int qa = -1, qb = -2;
+            float mn0, mx0;
+            edge(0, mn0, mx0);
             for (int q = 0; q < ngroups; ++q) {
-                const float x0 = (float)(G.x1lo + q * GW * G.a1 - V.s1);
-                const float x1 = (float)(G.x1lo + min((q + 1) * GW, G.n1) * G.a1 - V.s1);
-                float mn = 1e30f, mx = -1e30f;
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const float px = (k & 1) ? x1 : x0, py = (k & 2) ? y1 : y0;
-                    const float ch = (float)V.c1 + fb * (e1x * px + e1y * py) / (dx * px + dy * py);
-                    mn = fminf(mn, ch);
-                    mx = fmaxf(mx, ch);
-                }
-                if (mx >= lo_t && mn <= hi_t) {
+                float mn1, mx1;
+                edge(min((q + 1) * GW, G.n1), mn1, mx1);
+                if (fmaxf(mx0, mx1) >= lo_t && fminf(mn0, mn1) <= hi_t) {
                     if (qa < 0) qa = q;
                     qb = q;
                 }
+                mn0 = mn1;
+                mx0 = mx1;
             }
             rowQ[j] = qa;
             const int cnt = qa >= 0 ? qb - qa + 1 : 0;
             rowStart[j] = cnt;   // counts for now
             local += cnt;
         }
-        part[tid] = local;
-        __syncthreads();
-        if (tid == 0) {
-            int acc = 0;
-            for (int t = 0; t < kBlock; ++t) {
-                const int v = part[t];
-                part[t] = acc;
-                acc += v;
-            }
-            rowStart[G.n2] = acc;
+        // exclusive prefix sums over the threads: within the waves, then
+        // across them
+        int acc = local;
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+            const int t = __shfl_up(acc, off);
+            if (lane >= off) acc += t;
         }
+        if (lane == kWave - 1) part[wave] = acc;
         __syncthreads();
-        int acc = part[tid];
+        int before = 0, sum = 0;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+            if (w < wave) before += part[w];
+            sum += part[w];
+        }
+        if (tid == 0) rowStart[G.n2] = sum;
+        acc += before - local;
         for (int r = 0; r < rows_per; ++r) {
             const int j = tid * rows_per + r;
             if (j >= G.n2) break;
@@ -1170,7 +1179,8 @@ __device__ __forceinline__ void project_item(const DevGeom &G, const int U, cons
 // at 5 waves than at 4.
 template <bool EXACT, bool EC, int PMAX, bool TT, bool TAB, bool VT>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5)))
-project_kernel(const DevGeom G, const int U, const int pad, const int nbands, const float *__restrict__ vol,
+project_kernel(const DevGeom G, const int U, const int pad, const int nbands, const int linear,
+               const float *__restrict__ vol,
                float *__restrict__ proj, const unsigned *__restrict__ gmax, const double *__restrict__ stop)
 {
     extern __shared__ __align__(16) float smem[];
@@ -1179,10 +1189,14 @@ project_kernel(const DevGeom G, const int U, const int pad, const int nbands, co
     // x + 16, ..., each for all views in order: the costly central bands are
     // spread over all XCDs, and the workgroups an XCD runs at a time share a
     // band and neighbouring views, so their wedges overlap in its L2.
-    const int slot = blockIdx.x >> 3;
-    const int band = (blockIdx.x & 7) + 8 * (slot / G.nviews);
-    if (band >= nbands) return;
-    project_item<EXACT, EC, PMAX, TT, TAB, VT>(G, U, pad, band * G.nviews + slot % G.nviews, smem, vol, proj, gmax);
+    int item = blockIdx.x;
+    if (!linear) {
+        const int slot = blockIdx.x >> 3;
+        const int band = (blockIdx.x & 7) + 8 * (slot / G.nviews);
+        item = band * G.nviews + slot % G.nviews;
+    }
+    if (item >= nbands * G.nviews) return;
+    project_item<EXACT, EC, PMAX, TT, TAB, VT>(G, U, pad, item, smem, vol, proj, gmax);
 }
 
 // gmax[j * ngroups + q] = the largest |mu| bit pattern over the columns
@@ -2094,13 +2108,13 @@ template <bool EXACT, bool EC, int PMAX, bool TT, bool TAB>
 hipError_t launch_p_vt(const DevGeom &g, const ProjLaunch &L, const float *vol, float *proj, const unsigned *gmax,
                        const float *vt, hipStream_t s, const double *stop)
 {
-    const dim3 grid(8 * L.chunk), block(kBlock);
+    const dim3 grid(L.linear ? L.items : 8 * L.chunk), block(kBlock);
     if (vt)
         hipLaunchKernelGGL((project_kernel<EXACT, EC, PMAX, TT, TAB, true>), grid, block, L.lds, s, g, L.U, L.pad,
-                           L.nbands, vt, proj, gmax, stop);
+                           L.nbands, L.linear, vt, proj, gmax, stop);
     else
         hipLaunchKernelGGL((project_kernel<EXACT, EC, PMAX, TT, TAB, false>), grid, block, L.lds, s, g, L.U, L.pad,
-                           L.nbands, vol, proj, gmax, stop);
+                           L.nbands, L.linear, vol, proj, gmax, stop);
     return hipGetLastError();
 }
 
