@@ -183,8 +183,9 @@ cvp_status cvp_project_ws(const cvp_geometry *g, const cvp_options *opts,
 /*
  * Scratch with which the operators run fastest: with project_bytes of it
  * cvp_project_ws and cvp_project_views also copy the volume to [n2][n1][n3]
- * order and read the copy column by column, and both directions make the
- * cut-piece records of their views in one pass before the operator kernel
+ * order and read the copy column by column, the backprojection copies the
+ * scaled projections to [views][cols][rows] order (the backprojection fields
+ * of the launch plan do not apply then), and both directions make the cut-piece records of their views in one pass before the operator kernel
  * instead of in every workgroup (unless the geometry caches them for opts, see
  * cvp_geometry_cache_records; at most 8 GiB of records at a time, views
  * beyond that in further launches).  Every work size an entry point accepts
@@ -274,9 +275,10 @@ cvp_status cvp_backproject_views_ws(const cvp_geometry *g, const cvp_options *op
  * backprojection).  The per-call pointer setup and the counter reset are one
  * tiny kernel on the same stream, so a batched call can be graph-captured.
  * n: 1..32 geometries on the same device; the batch keeps pointers to them
- * (they must outlive it) and owns its device tables: room for a transposed
- * copy of every volume and the members' cut-piece records, each up to 8 GiB
- * (above that, or when the memory is not there, the launches do without).
+ * (they must outlive it) and owns its device tables: room for transposed
+ * copies of every volume and every projection array, and the members'
+ * cut-piece records, each up to 32 GiB in all (above that, or when the memory
+ * is not there, the launches do without).
  * When every member has cached records (cvp_geometry_cache_records) at
  * cvp_batch_create, the batched kernels read those instead of tables of the
  * batch; a call after a member's table was freed or rebuilt then returns

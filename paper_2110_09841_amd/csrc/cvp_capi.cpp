@@ -52,7 +52,7 @@ struct cvp_geometry {
     int pmax = 4;                    // pieces per column the kernels keep (4, 8 or kPmaxWide)
     double wone_tt = 0.0, wsum_tt = 0.0;   // fixed-point bounds of the TT projector's weights
     cvp::BackLaunch blc{};           // backprojection plan of the kernels that read a table of records
-    cvp::BackLaunch blt{};           // the same without a shared window (TT footprints)
+    cvp::DirectLaunch bld{};         // backprojection plan of the launches from a transposed copy
     int band_set = 0;                // projection band width set by the caller (0: default)
     int bp_wpc = 0;                  // requested workgroups per CU of that plan (0: default)
     int bp_shared = 0;               // requested one window per workgroup in that plan
@@ -348,6 +348,25 @@ struct Circular {
     double D, f, b1, b2, c1, c2, rmax;
 };
 
+// The plan of the launches from a transposed copy of the projections: as many
+// 64-slice passes per stack as the volume has, up to kDirectPasses, spread
+// evenly (each piece record then serves them all, with as many loads in
+// flight); fewer while the launch has less than one workgroup per slot of the
+// GPU (256 compute units x 4).
+static cvp::DirectLaunch direct_plan(const cvp::DevGeom &G, int pmax)
+{
+    cvp::DirectLaunch L{};
+    const int passes = (G.n3 + 63) / 64;
+    int chunks = (passes + cvp::kDirectPasses - 1) / cvp::kDirectPasses;
+    L.ngroups = (G.n1 + cvp::kDirectCols - 1) / cvp::kDirectCols;
+    while (chunks < passes && (int64_t)G.n2 * L.ngroups * chunks < 1024) ++chunks;
+    L.kp = (passes + chunks - 1) / chunks;
+    L.nkchunks = (G.n3 + 64 * L.kp - 1) / (64 * L.kp);
+    L.items = G.n2 * L.ngroups * L.nkchunks;
+    L.pmax = pmax;
+    return L;
+}
+
 // The backprojection plan of the cached-record kernels: the in-kernel plan's
 // stack shape when it fits their smaller LDS budget, else their default.
 static void replan_backprojection(cvp_geometry *g)
@@ -359,11 +378,7 @@ static void replan_backprojection(cvp_geometry *g)
         g->blc = bl;
     else
         g->blc = g->bl;
-    g->blt = g->blc;
-    if (g->blc.shared && !cvp::plan_backprojection(g->base, g->pmax, g->zabs, g->Dmin, g->blc.gw, g->blc.kp, g->blt, true, 0,
-                                                   g->bp_wpc, false) &&
-        !cvp::plan_backprojection(g->base, g->pmax, g->zabs, g->Dmin, 0, 0, g->blt, true, 0, g->bp_wpc, false))
-        g->blt.gw = 0;     // none: the footprints are made in the kernel
+    g->bld = direct_plan(g->base, g->pmax);
 }
 
 // Builds the device tables and launch plans from per-view frames.  circ:
@@ -718,10 +733,6 @@ cvp_status cvp_geometry_set_launch(cvp_geometry *g, const cvp_launch *in)
     g->blc = blc;
     g->bp_wpc = wpc;
     g->bp_shared = shw;
-    g->blt = blc;
-    if (blc.shared && !cvp::plan_backprojection(G, g->pmax, g->zabs, g->Dmin, blc.gw, blc.kp, g->blt, true, 0, wpc, false) &&
-        !cvp::plan_backprojection(G, g->pmax, g->zabs, g->Dmin, 0, 0, g->blt, true, 0, wpc, false))
-        g->blt.gw = 0;
     return ok();
 }
 
@@ -832,7 +843,8 @@ static cvp_status prepare(const cvp_geometry *g, const cvp_options *o, const voi
 //
 // With scratch a call lays out in it what its kernels read faster than what
 // they would make themselves: the transposed volume with its group maxima
-// (projection), and the cut-piece records of a run of views, made by one pass
+// (projection) or the transposed, scaled projections (backprojection), and
+// the cut-piece records of a run of views, made by one pass
 // before the operator kernel of those views (unless the geometry keeps all
 // records).  In the operator kernels that FP64 stage is repeated by every
 // band or stack that meets a column and takes the registers of one to two
@@ -845,6 +857,8 @@ static int64_t gmax_bytes(const cvp_geometry *g) { return cvp::group_max_cells(g
 // launched in several pieces, each still thousands of workgroups (12.7 GB of
 // records at 512^3 x 248 views: two pieces).
 constexpr int64_t kTableBytes = int64_t(8) << 30;
+// A batch holds tables and copies for its members up to this many bytes each.
+constexpr int64_t kBatchBytes = int64_t(32) << 30;
 
 // Records of one view: rows padded to 256 bytes (records, counts).
 struct TableSize { int64_t rec, cnt; };
@@ -899,12 +913,19 @@ struct Scratch {
 // Whether an operator call makes records in its scratch.
 static bool makes_records(const cvp_geometry *g, const cvp::DevGeom &G) { return !G.rtab && g->pmax <= 8; }
 
-// Views [q, q + c) of the launch G, reading the records at rec / cnt.
+// Views [q, q + c) of the launch G, reading the records at rec / cnt (nullptr:
+// the table of G).
 static void launch_views(const cvp_geometry *g, cvp::DevGeom &G, int q, int c, float *rec, int *cnt)
 {
     G.views += (int64_t)q * G.vstride;
     G.nviews = c;
     if (G.sigma && G.sigma_views) G.sigma += (int64_t)q * G.vstride * G.N * G.M;
+    if (!rec) {
+        const int64_t cols = (int64_t)q * G.rtab_vs * G.n2 * G.n1;
+        G.rtab += cols * G.rtab_pmax * cvp::kRecFloats;
+        G.rtab_n += cols;
+        return;
+    }
     G.rtab = rec;
     G.rtab_n = cnt;
     G.rtab_pmax = g->pmax;
@@ -954,36 +975,58 @@ static int64_t project_full_bytes(const cvp_geometry *g, bool records)
     return n;
 }
 
+// Scratch of a backprojection over `views` views: the transposed projections
+// with their flags, and the records unless the geometry keeps them.
+static int64_t copy_bytes(const cvp_geometry *g, int64_t views)
+{
+    return align256(cvp::copy_floats(g->base, views) * (int64_t)sizeof(float)) +
+           align256(cvp::copy_flags(g->base, views) * (int64_t)sizeof(int));
+}
+static int64_t back_bytes(const cvp_geometry *g, bool records, int64_t views)
+{
+    return copy_bytes(g, views) + (records ? table_bytes(g, views) : 0);
+}
+static int back_views(const cvp_geometry *g, bool records, int64_t bytes, int views)
+{
+    if (bytes >= back_bytes(g, records, views)) return views;
+    const int64_t n = bytes > 0 ? bytes / back_bytes(g, records, 1) : 0;   // at most an underestimate (padding)
+    return (int)(n / cvp::kWaves * cvp::kWaves);
+}
+
 // x = A^T b over the views of G.
 static hipError_t run_backproject(const cvp_geometry *g, const cvp::DevGeom &G, int model, bool ec, const float *proj,
                                   float *vol, void *work, int64_t work_bytes, hipStream_t s,
                                   const double *stop = nullptr)
 {
-    const cvp::BackLaunch &bl = model == cvp::kModelTT ? g->blt : g->blc;
-    if (makes_records(g, G) && bl.gw > 0) {
+    const bool records = makes_records(g, G);
+    if (g->pmax <= 8) {
         Scratch w(work, work_bytes);
-        int step = table_views(g, w.n, G.nviews, cvp::kWaves);
+        int step = back_views(g, records, w.n, G.nviews);
         cvp::BackPart part;
         if (step < G.nviews) {
             // several launches: the running sums wait in the scratch too
-            part.sums = static_cast<float *>(w.take(cvp::back_part_floats(bl) * (int64_t)sizeof(float)));
-            step = part.sums ? table_views(g, w.n, G.nviews, cvp::kWaves) : 0;
+            part.sums = static_cast<float *>(w.take(cvp::back_part_floats(g->bld) * (int64_t)sizeof(float)));
+            step = part.sums ? back_views(g, records, w.n, G.nviews) : 0;
             if (step >= 8) step = even_views(G.nviews, step, cvp::kWaves);
         }
         if (step >= std::min(G.nviews, 8)) {
-            const TableSize ts = table_size(g, step);
-            float *rec = reinterpret_cast<float *>(w.p);
-            int *cnt = reinterpret_cast<int *>(w.p + ts.rec);
+            cvp::BackCopy copy;
+            copy.pad = G.rpad;
+            copy.pt = static_cast<float *>(w.take(cvp::copy_floats(G, step) * (int64_t)sizeof(float)));
+            copy.bad = static_cast<int *>(w.take(cvp::copy_flags(G, step) * (int64_t)sizeof(int)));
+            float *rec = records ? static_cast<float *>(w.take(table_size(g, step).rec)) : nullptr;
+            int *cnt = records ? static_cast<int *>(w.take(table_size(g, step).cnt)) : nullptr;
             hipError_t e = hipSuccess;
             for (int q = 0; q < G.nviews && e == hipSuccess; q += step) {
                 cvp::DevGeom Gq = G;
-                launch_views(g, Gq, q, std::min(step, G.nviews - q), rec, cnt);
+                const int c = std::min(step, G.nviews - q);
+                launch_views(g, Gq, q, c, rec, cnt);
                 part.first = q == 0;
                 part.last = q + step >= G.nviews;
-                e = cvp::launch_record_table(Gq, g->pmax, model == cvp::kModelTT, rec, cnt, s, stop);
+                if (records) e = cvp::launch_record_table(Gq, g->pmax, model == cvp::kModelTT, rec, cnt, s, stop);
                 if (e == hipSuccess)
-                    e = cvp::launch_backproject(Gq, bl, model, ec, proj + (int64_t)q * G.vstride * G.N * G.M, vol, s,
-                                                stop, part);
+                    e = cvp::launch_transpose_projections(Gq, proj + (int64_t)q * G.vstride * G.N * G.M, copy, s, stop);
+                if (e == hipSuccess) e = cvp::launch_backproject_direct(Gq, g->bld, model, ec, copy, vol, s, stop, part);
             }
             return e;
         }
@@ -993,11 +1036,10 @@ static hipError_t run_backproject(const cvp_geometry *g, const cvp::DevGeom &G, 
 
 static int64_t backproject_full_bytes(const cvp_geometry *g, bool records)
 {
-    if (!records) return 0;
-    const int64_t all = table_bytes(g, g->base.nviews), most = std::max(kTableBytes, table_bytes(g, 8));
+    if (g->pmax > 8) return 0;
+    const int64_t all = back_bytes(g, records, g->base.nviews), most = std::max(kTableBytes, back_bytes(g, records, 8));
     if (all <= most) return all + 256;
-    const int64_t part = std::max(cvp::back_part_floats(g->blc), cvp::back_part_floats(g->blt));
-    return most + align256(part * (int64_t)sizeof(float)) + 256;
+    return most + align256(cvp::back_part_floats(g->bld) * (int64_t)sizeof(float)) + 256;
 }
 
 cvp_status cvp_operator_workspace_size(const cvp_geometry *g, const cvp_options *o, int64_t *project_bytes,
@@ -1194,18 +1236,20 @@ struct cvp_batch {
     std::vector<const cvp_geometry *> geoms;
     cvp::BatchProblem *d_probs = nullptr;
     cvp::BatchTable *d_ptab = nullptr;
-    // backprojection groups g = 3 p + w: piece stride 4 (p = 0) or 8 (p = 1),
-    // stack width 16, 8, 4 (w = 0, 1, 2)
-    cvp::BatchTable *d_btab[6] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
+    // backprojection groups g = 4 p + w: piece stride 4 (p = 0) or 8 (p = 1),
+    // stack width 16, 8, 4 (w = 0, 1, 2) or from transposed copies (w = 3)
+    cvp::BatchTable *d_btab[8] = {};
     int *d_counter = nullptr;         // [0] projection, [1 + g] backprojection group g
     std::vector<unsigned *> d_gmax;   // per problem: per-group maxima of the volume
     std::vector<float *> vts;         // per problem: its transposed volume (nullptr: none)
-    size_t plds = 0, blds[6] = {0, 0, 0, 0, 0, 0};
-    int pgrid = 0, bgrid[6] = {0, 0, 0, 0, 0, 0};
+    size_t plds = 0, blds[8] = {};
+    int pgrid = 0, bgrid[8] = {};
     bool cached = false;                  // every member reads a table of records
     std::vector<const float *> rtabs;     // the geometries' tables captured at creation (empty: the batch's own)
     std::vector<void *> d_own;            // the batch's own tables and transposed volumes
     bool vt = false;                      // the projection reads transposed volumes
+    bool direct = false;                  // the backprojection reads transposed copies
+    std::vector<cvp::BackCopy> copies;    // per problem
 };
 
 extern "C" {
@@ -1244,7 +1288,7 @@ cvp_status cvp_batch_create(const cvp_geometry *const *geoms, int32_t n, cvp_bat
     b->device = geoms[0]->device;
     b->geoms.assign(geoms, geoms + n);
     // With every member's records cached the batched kernels read those; else
-    // the batch makes tables of its own for all of them, up to kTableBytes
+    // the batch makes tables of its own for all of them, up to kBatchBytes
     // (launches on a larger batch make their records in the kernels).
     bool own = false;
     b->cached = true;
@@ -1254,7 +1298,7 @@ cvp_status cvp_batch_create(const cvp_geometry *const *geoms, int32_t n, cvp_bat
     if (!b->cached) {
         int64_t total = 0;
         for (int q = 0; q < n; ++q) total += table_bytes(geoms[q], geoms[q]->base.nviews);
-        own = total <= kTableBytes;
+        own = total <= kBatchBytes;
         for (int q = 0; q < n && own; ++q) {
             const cvp_geometry *g = geoms[q];
             void *t = nullptr;
@@ -1283,6 +1327,24 @@ cvp_status cvp_batch_create(const cvp_geometry *const *geoms, int32_t n, cvp_bat
     static const int kGw[3] = {16, 8, 4};
     std::vector<cvp::BackLaunch> bls(n);
     std::vector<int> grp(n);
+    // transposed copies of the projections for the members' backprojections
+    // from their tables (the copies are filled per call)
+    b->copies.assign(n, cvp::BackCopy());
+    int64_t copies = 0;
+    for (int q = 0; q < n; ++q) copies += copy_bytes(geoms[q], geoms[q]->base.nviews);
+    b->direct = b->cached && copies <= kBatchBytes;
+    for (int q = 0; q < n && b->direct; ++q) {
+        const cvp_geometry *g = geoms[q];
+        void *t = nullptr;
+        b->direct = hipMalloc(&t, copy_bytes(g, g->base.nviews)) == hipSuccess;
+        if (!b->direct) break;
+        b->d_own.push_back(t);
+        b->copies[q].pt = static_cast<float *>(t);
+        b->copies[q].bad = reinterpret_cast<int *>(
+            static_cast<char *>(t) + align256(cvp::copy_floats(g->base, g->base.nviews) * (int64_t)sizeof(float)));
+        b->copies[q].pad = g->base.rpad;
+    }
+    if (!b->direct) (void)hipGetLastError();
     for (int q = 0; q < n; ++q) {
         // the member's own stack width, else the next narrower one whose
         // 8-piece records fit
@@ -1291,8 +1353,8 @@ cvp_status cvp_batch_create(const cvp_geometry *const *geoms, int32_t n, cvp_bat
         for (int gi = 0; gi < 3 && !planned; ++gi) {
             if (kGw[gi] > geoms[q]->bl.gw) continue;
             planned = cvp::plan_backprojection(geoms[q]->base, pm, geoms[q]->zabs, geoms[q]->Dmin, kGw[gi], 0, bls[q],
-                                               b->cached, cvp::kBatchStaticLds, geoms[q]->bp_wpc);
-            grp[q] = (pm == 4 ? 0 : 3) + gi;
+                                               false, cvp::kBatchStaticLds);
+            grp[q] = (pm == 4 ? 0 : 4) + (b->direct ? 3 : gi);
         }
         if (!planned) {
             cvp_batch_destroy(b);
@@ -1316,7 +1378,9 @@ cvp_status cvp_batch_create(const cvp_geometry *const *geoms, int32_t n, cvp_bat
         P.pitems = pl.items;
         P.ngroups = bl.ngroups;
         P.nkchunks = bl.nkchunks;
-        P.bitems = bl.items;
+        P.bitems = b->direct ? g->bld.items : bl.items;
+        P.direct = g->bld;
+        P.copy = b->copies[q];
         P.in = nullptr;
         P.out = nullptr;
         P.gmax = nullptr;   // set below
@@ -1330,7 +1394,7 @@ cvp_status cvp_batch_create(const cvp_geometry *const *geoms, int32_t n, cvp_bat
             if (!own) b->rtabs.push_back(g->d_rtab);
         }
         b->plds = std::max(b->plds, pl.lds);
-        b->blds[grp[q]] = std::max(b->blds[grp[q]], bl.lds);
+        b->blds[grp[q]] = std::max(b->blds[grp[q]], b->direct ? cvp::back_direct_lds(bl.pmax) : bl.lds);
         pcost[q] = (double)g->nvox / pl.nbands;           // voxels per band (all k)
         bcost[q] = (double)g->base.nviews;                // views per voxel stack
     }
@@ -1354,24 +1418,24 @@ cvp_status cvp_batch_create(const cvp_geometry *const *geoms, int32_t n, cvp_bat
     hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, b->device);
     if (e == hipSuccess) e = hipMalloc((void **)&b->d_probs, n * sizeof(cvp::BatchProblem));
     if (e == hipSuccess) e = hipMalloc((void **)&b->d_ptab, sizeof(cvp::BatchTable));
-    if (e == hipSuccess) e = hipMalloc((void **)&b->d_counter, 7 * sizeof(int));
-    for (int gi = 0; gi < 6 && e == hipSuccess; ++gi) {
+    if (e == hipSuccess) e = hipMalloc((void **)&b->d_counter, 9 * sizeof(int));
+    for (int gi = 0; gi < 8 && e == hipSuccess; ++gi) {
         if (b->blds[gi] == 0) continue;   // no member with this stride and width
         const cvp::BatchTable bt = table(bcost, true, gi);
         e = hipMalloc((void **)&b->d_btab[gi], sizeof(cvp::BatchTable));
         if (e == hipSuccess) e = hipMemcpy(b->d_btab[gi], &bt, sizeof(bt), hipMemcpyHostToDevice);
-        b->bgrid[gi] = cus * cvp::batched_blocks_per_cu(true, b->blds[gi], kGw[gi % 3], gi < 3 ? 4 : 8, b->cached,
-                                                        b->vt);
+        b->bgrid[gi] = cus * cvp::batched_blocks_per_cu(true, b->blds[gi], gi % 4 < 3 ? kGw[gi % 4] : 0, gi < 4 ? 4 : 8,
+                                                        b->cached, b->vt);
     }
     b->d_gmax.assign(n, nullptr);
     for (int q = 0; q < n && e == hipSuccess; ++q) {
         e = hipMalloc((void **)&b->d_gmax[q], cvp::group_max_cells(probs[q].G) * sizeof(unsigned));
         probs[q].gmax = b->d_gmax[q];
     }
-    // room for the members' transposed volumes (up to kTableBytes)
+    // room for the members' transposed volumes
     int64_t volumes = 0;
     for (int q = 0; q < n; ++q) volumes += geoms[q]->nvox * (int64_t)sizeof(float);
-    b->vt = e == hipSuccess && volumes <= kTableBytes;
+    b->vt = e == hipSuccess && volumes <= kBatchBytes;
     for (int q = 0; q < n && b->vt; ++q) {
         void *t = nullptr;
         b->vt = hipMalloc(&t, geoms[q]->nvox * sizeof(float)) == hipSuccess;
@@ -1429,11 +1493,16 @@ static cvp_status batched(const cvp_batch *b, const cvp_options *o, const float 
                                 b->cached, b->vt, (hipStream_t)stream);
     } else {
         static const int kGw[3] = {16, 8, 4};
-        for (int gi = 0; gi < 6 && e == hipSuccess; ++gi)
+        for (int q = 0; q < b->n && b->direct && e == hipSuccess; ++q) {
+            cvp::DevGeom G = b->geoms[q]->base;
+            G.sigma = io.sigma[q];
+            e = cvp::launch_transpose_projections(G, ins[q], b->copies[q], (hipStream_t)stream, io.stop[q]);
+        }
+        for (int gi = 0; gi < 8 && e == hipSuccess; ++gi)
             if (b->d_btab[gi])
                 e = cvp::launch_batched(true, b->d_probs, b->d_btab[gi], b->d_counter + 1 + gi, io, ex, ec,
-                                        b->bgrid[gi], b->blds[gi], kGw[gi % 3], gi < 3 ? 4 : 8, b->cached,
-                                        b->vt, (hipStream_t)stream);
+                                        b->bgrid[gi], b->blds[gi], gi % 4 < 3 ? kGw[gi % 4] : 0, gi < 4 ? 4 : 8,
+                                        b->cached, b->vt, (hipStream_t)stream);
     }
     if (e != hipSuccess) return device_fail(e, "batched launch");
     return ok();

@@ -20,6 +20,9 @@ constexpr int back_rec_floats(int gw, int pmax) { return gw * pmax * kRecFloats 
 constexpr int back_views_per_pass(int gw, int pmax) { return 64 / (gw * (pmax < 64 / gw ? pmax : 64 / gw)); }
 constexpr float kYQuantumInv = 1024.0f;
 constexpr int kBackPasses = 2;        // most 64-voxel passes per backprojection stack
+// the launches from a transposed copy (no window limits them): columns and
+// most passes per stack
+constexpr int kDirectCols = 4, kDirectPasses = 4;
 constexpr int kPmaxWide = 64;         // pieces per column of the wide-footprint backprojection
 
 // Projector models of launch_project / launch_backproject: the cutting voxel
@@ -109,6 +112,23 @@ struct BackLaunch {
     int shared;      // 1: one detector window per workgroup (cached records only)
 };
 
+// A backprojection from a transposed copy of the projections: stacks of
+// kDirectCols columns x 64 kp slices.
+struct DirectLaunch {
+    int kp;
+    int ngroups, nkchunks;
+    int items;
+    int pmax;        // 4 or 8
+};
+
+// The transposed, scaled projections of a launch's views (with `pad` zero
+// rows on both sides) and the flags of their non-finite blocks.
+struct BackCopy {
+    float *pt = nullptr;
+    int *bad = nullptr;
+    int pad = 0;
+};
+
 // Batched, persistent launches over up to kMaxBatch problems.
 constexpr int kMaxBatch = 32;
 
@@ -128,6 +148,8 @@ struct BatchProblem {        // device table entry (one per problem)
     float *out;
     unsigned *gmax;          // the problem's per-group maxima (owned by the batch)
     float *vt;               // its transposed volume (owned by the batch), or nullptr
+    DirectLaunch direct;     // backprojection from its transposed copy (owned by the batch),
+    BackCopy copy;           // where the batch has copies
     const double *stop;      // set per call: the problem's work items are skipped while *stop != 0
 };
 
@@ -146,8 +168,9 @@ struct BatchIO {             // per call, by value
     const double *stop[kMaxBatch];   // per problem, or nullptr
 };
 
-// gw, pmax: the backprojection launch's stack width (16, 8 or 4) and piece
-// stride (4 or 8); cached: every member reads a table of records; vt: the
+// gw, pmax: the backprojection launch's stack width (16, 8 or 4, records made
+// in the kernel; 0: from the transposed copies and tables) and piece stride
+// (4 or 8); cached: the projection reads tables of records; vt: the
 // projection reads the members' transposed volumes
 hipError_t launch_batched(bool backward, BatchProblem *probs, const BatchTable *tab, int *counter,
                           const BatchIO &io, bool exact, bool ec, int grid, size_t lds, int gw, int pmax, bool cached,
@@ -227,9 +250,25 @@ struct BackPart {
     float *sums = nullptr;
     bool first = true, last = true;
 };
-constexpr int64_t back_part_floats(const BackLaunch &L) { return (int64_t)L.items * kWaves * kBackPasses * L.gw * kWave; }
+constexpr int64_t copy_floats(const DevGeom &g, int64_t views) { return views * g.M * (g.N + 2 * (int64_t)g.rpad); }
+constexpr int64_t copy_flags(const DevGeom &g, int64_t views) { return views * ((g.M + kWave - 1) / kWave); }
+// LDS of backproject_direct_kernel: the waves' records, or their sums at the end
+constexpr size_t back_direct_lds(int pmax)
+{
+    const size_t rec = (size_t)kWaves * back_views_per_pass(kDirectCols, pmax) * back_rec_floats(kDirectCols, pmax);
+    const size_t red = (size_t)kWaves * kDirectCols * kWave;
+    return 4 * (rec > red ? rec : red);
+}
+hipError_t launch_transpose_projections(const DevGeom &g, const float *proj, const BackCopy &copy, hipStream_t stream,
+                                        const double *stop = nullptr);
+// From the copy and a table of records.
+hipError_t launch_backproject_direct(const DevGeom &g, const DirectLaunch &L, int model, bool ec, const BackCopy &copy,
+                                     float *vol, hipStream_t stream, const double *stop, const BackPart &part);
+constexpr int64_t back_part_floats(const DirectLaunch &L)
+{
+    return (int64_t)L.items * kWaves * kDirectPasses * kDirectCols * kWave;
+}
 hipError_t launch_backproject(const DevGeom &g, const BackLaunch &L, int model, bool ec,
-                              const float *proj, float *vol, hipStream_t stream, const double *stop = nullptr,
-                              const BackPart &part = BackPart());
+                              const float *proj, float *vol, hipStream_t stream, const double *stop = nullptr);
 
 }  // namespace cvp

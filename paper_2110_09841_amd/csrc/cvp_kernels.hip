@@ -1381,6 +1381,22 @@ __device__ __forceinline__ LdsFloat *lds_ptr(const float *p)
     return (LdsFloat *)(uintptr_t)(unsigned)q;
 }
 
+// Where a gather reads projection values: the window in LDS, the caller's
+// projections, or the transposed copy of transpose_projections_kernel.
+constexpr int kFromWindow = 0, kFromCaller = 1, kFromCopy = 2;
+
+// R consecutive floats at byte offset off of base (the same in every lane).
+template <int R>
+__device__ __forceinline__ void load_rows(const float *base, unsigned off, float *val)
+{
+    constexpr int N = R > 4 ? 4 : R;
+    typedef float vec __attribute__((ext_vector_type(N), aligned(4)));
+    const vec v = *reinterpret_cast<const vec *>(reinterpret_cast<const char *>(base) + off);
+#pragma unroll
+    for (int e = 0; e < N; ++e) val[e] = v[e];
+    if constexpr (R > 4) load_rows<R - 4>(base, off + 16u, val + 4);
+}
+
 // One view as the gather of a backprojection sees it.
 struct BackView {
     const float *pv, *sgv;      // projections and pixel factors of the view
@@ -1393,12 +1409,13 @@ struct BackView {
 };
 
 // Row sum of one piece for one voxel of slice kf (lanes over k) by the row
-// loop, from the window (WIN, wcol: the piece's window column less wv0) or
-// global memory; the piece's coefficient is applied by the caller.
-template <bool EC, bool EXACT, bool TT, bool WIN>
+// loop, from the window or the copy (wcol: the piece's column at row 0) or
+// the caller's projections; the piece's coefficient is applied by the caller.
+template <bool EC, bool EXACT, bool TT, int SRC>
 __device__ __forceinline__ float gather_rows(const BackView &B, const float4 &r0, const float4 &r1, const float4 &r2,
                                              const int u, const float *wcol, const float kf, const bool kv)
 {
+    constexpr bool WIN = SRC != kFromCaller;
     const float zt = fmaf(kf, B.a3f, B.zt0);
     const float Yh = fmaf(-kf, r1.x, r0.z);
     const float Yl = fmaf(-kf, r1.y, r0.w);
@@ -1512,7 +1529,7 @@ __device__ __forceinline__ float column_factor(const BackView &B, const float *r
 // Sums a[NP] of the pieces of one column (np records at rc) for its voxels in
 // NP passes of 64 slices (kf, kv), without column_factor.  np and the records
 // are the same in every lane.
-template <bool EC, bool EXACT, bool TT, bool WIN, int NP>
+template <bool EC, bool EXACT, bool TT, int SRC, int NP>
 __device__ __forceinline__ void gather_column(const BackView &B, const float *rc, const int np, const float *win,
                                               const float kf[NP], const bool kv[NP], float a[NP])
 {
@@ -1526,43 +1543,48 @@ __device__ __forceinline__ void gather_column(const BackView &B, const float *rc
         const int word = __builtin_amdgcn_readfirstlane(__float_as_int(r0.x));
         const int u = rec_col(word);
         const int rows = !TT && B.fixed ? rec_rows<EC>(word) : 0;
-        const float *wcol = win + (u - B.wu0) * B.Hp - B.wv0;
+        // (copy: wu0 = 0, wv0 = minus the spare rows before row 0)
+        const float *wcol = win + (SRC == kFromCopy ? (size_t)u * B.Hp : (u - B.wu0) * B.Hp) - B.wv0;
         if (rows > 0) {
             const FixedPiece P = fixed_piece<EC>(r0.z, r0.w, r1.x, r1.y, r1.z, r1.w, B.c2f, B.md);
-            LdsFloat *const wl = lds_ptr(WIN ? wcol : win);
+            LdsFloat *const wl = SRC == kFromWindow ? lds_ptr(wcol) : nullptr;
             with_rows(rows, [&](auto tag) {
                 constexpr int R = decltype(tag)::value;
 #pragma unroll
                 for (int ps = 0; ps < NP; ++ps) {
                     const float k = kf[ps];
                     // the window holds the rows of every slice (the position is monotone
-                    // in k), unless it ends R rows beyond the detector
+                    // in k), unless it ends R rows beyond the detector like the copy
                     float v0 = floorf(fmaf(-k, r1.z, P.ys));
-                    if (WIN) v0 = __builtin_amdgcn_fmed3f(v0, (float)B.wv0, (float)(B.wv1 - (R - 1)));
+                    if (SRC != kFromCaller) v0 = __builtin_amdgcn_fmed3f(v0, (float)B.wv0, (float)(B.wv1 - (R - 1)));
                     const int vi = (int)v0;
                     const float zt = EXACT ? fmaf(k, B.a3f, B.zt0) : 0.0f;
                     float w[R];
                     fixed_rows<R, EC, EXACT>(P, v0, k, B.raw, zt, r2.w, r2.y, w);
                     float val[R];
+                    if constexpr (SRC == kFromCopy) {
+                        load_rows<R>(wcol + B.wv0, (unsigned)(vi - B.wv0) * 4u, val);
+                    } else {
 #pragma unroll
-                    for (int e = 0; e < R; ++e) {
-                        if (WIN) {
-                            val[e] = wl[vi + e];
-                        } else {
-                            const bool on = kv[ps] && (unsigned)(vi + e) < (unsigned)B.N;
-                            const size_t off = (size_t)(on ? vi + e : 0) * B.M + u;
-                            val[e] = B.pv[off];
-                            if (B.sgv) val[e] *= B.sgv[off];
-                            if (!on) val[e] = 0.0f;
+                        for (int e = 0; e < R; ++e) {
+                            if (SRC == kFromWindow) {
+                                val[e] = wl[vi + e];
+                            } else {
+                                const bool on = kv[ps] && (unsigned)(vi + e) < (unsigned)B.N;
+                                const size_t off = (size_t)(on ? vi + e : 0) * B.M + u;
+                                val[e] = B.pv[off];
+                                if (B.sgv) val[e] *= B.sgv[off];
+                                if (!on) val[e] = 0.0f;
+                            }
                         }
                     }
                     float ap = w[0] * val[0];
 #pragma unroll
                     for (int e = 1; e < R; ++e) ap = fmaf(w[e], val[e], ap);
-                    // a non-finite value (global reads; a window was checked) reaches
-                    // the voxels that the row loop gives it to
-                    if (!WIN && __ballot(!(fabsf(ap) < INFINITY)))
-                        ap = gather_rows<EC, EXACT, TT, WIN>(B, r0, r1, r2, u, wcol, k, kv[ps]);
+                    // a non-finite value (caller's projections; window and copy were
+                    // checked) reaches the voxels that the row loop gives it to
+                    if (SRC == kFromCaller && __ballot(!(fabsf(ap) < INFINITY)))
+                        ap = gather_rows<EC, EXACT, TT, SRC>(B, r0, r1, r2, u, wcol, k, kv[ps]);
                     a[ps] = fmaf(r0.y, ap, a[ps]);
                 }
             });
@@ -1570,7 +1592,27 @@ __device__ __forceinline__ void gather_column(const BackView &B, const float *rc
         }
 #pragma unroll
         for (int ps = 0; ps < NP; ++ps)
-            a[ps] = fmaf(r0.y, gather_rows<EC, EXACT, TT, WIN>(B, r0, r1, r2, u, wcol, kf[ps], kv[ps]), a[ps]);
+            a[ps] = fmaf(r0.y, gather_rows<EC, EXACT, TT, SRC>(B, r0, r1, r2, u, wcol, kf[ps], kv[ps]), a[ps]);
+    }
+}
+
+// A wave's copies of the table's records of the stack of GW columns from i0
+// of row j, for RV of its views (vb, vb + kWaves, ...), into LDS.
+template <int PMAX, int GW, int RV>
+__device__ __forceinline__ void stack_records(const DevGeom &G, int i0, int j, int vb, float *rec, int lane)
+{
+#pragma unroll
+    for (int r = 0; r < RV; ++r) {
+        const int view = vb + r * kWaves;
+        if (view >= G.nviews) break;
+        float *rv = rec + r * back_rec_floats(GW, PMAX);
+        int *npv = reinterpret_cast<int *>(rv + GW * PMAX * kRecFloats);
+        const size_t col0 = ((size_t)view * G.rtab_vs * G.n2 + j) * G.n1 + i0;
+        const int ncv = min(GW, G.n1 - i0);
+        // one contiguous block (the table has PMAX slots per column)
+        const float4 *src = reinterpret_cast<const float4 *>(G.rtab + col0 * PMAX * kRecFloats);
+        for (int q4 = lane; q4 < ncv * PMAX * kRecFloats / 4; q4 += kWave) reinterpret_cast<float4 *>(rv)[q4] = src[q4];
+        if (lane < GW) npv[lane] = lane < ncv ? G.rtab_n[col0 + lane] : 0;
     }
 }
 
@@ -1582,7 +1624,7 @@ __device__ __forceinline__ void backproject_item(const DevGeom &G, const int ngr
                                                  const int nkchunks, const int kp, const int winCap,
                                                  const int item, float *smem,
                                                  const float *__restrict__ proj,
-                                                 float *__restrict__ vol, const BackPart &part)
+                                                 float *__restrict__ vol)
 {
     const int kch = item % nkchunks;
     const int t = item / nkchunks;
@@ -1612,42 +1654,10 @@ __device__ __forceinline__ void backproject_item(const DevGeom &G, const int ngr
     typename FloatVec<GW>::type acc[KP];
 #pragma unroll
     for (int ps = 0; ps < KP; ++ps) acc[ps] = 0.0f;
-    // this wave's sums of the launches before (element (ps, c) of a lane)
-    float *const mine = part.sums + ((size_t)item * kWaves + wave) * KP * GW * kWave + lane;
-    if (!part.first) {
-#pragma unroll
-        for (int ps = 0; ps < KP; ++ps)
-#pragma unroll
-            for (int c = 0; c < GW; ++c) acc[ps][c] = mine[(ps * GW + c) * kWave];
-    }
 
     for (int vb = wave; vb < G.nviews; vb += kWaves * RV) {
         if constexpr (TAB) {
-            // the geometry's records of the stack, view by view, into LDS
-#pragma unroll
-            for (int r = 0; r < RV; ++r) {
-                const int view = vb + r * kWaves;
-                if (view >= G.nviews) break;
-                float *rv = rec + r * recView;
-                int *npv = reinterpret_cast<int *>(rv + GW * PMAX * kRecFloats);
-                const size_t col0 = ((size_t)view * G.rtab_vs * G.n2 + j) * G.n1 + i0;
-                const int ncv = min(GW, G.n1 - i0);
-                const int tp = G.rtab_pmax;
-                const float4 *src = reinterpret_cast<const float4 *>(G.rtab + col0 * tp * kRecFloats);
-                if (tp == PMAX) {
-                    // one contiguous block
-                    for (int q4 = lane; q4 < ncv * PMAX * kRecFloats / 4; q4 += kWave)
-                        reinterpret_cast<float4 *>(rv)[q4] = src[q4];
-                } else {
-                    // a table of tp <= PMAX slots per column (batched launches keep PMAX = 8)
-                    constexpr int F4 = kRecFloats / 4;
-                    for (int q4 = lane; q4 < ncv * tp * F4; q4 += kWave) {
-                        const int cs = q4 / F4, c = cs / tp, sl = cs - c * tp;
-                        reinterpret_cast<float4 *>(rv)[(c * PMAX + sl) * F4 + (q4 - cs * F4)] = src[q4];
-                    }
-                }
-                if (lane < GW) npv[lane] = lane < ncv ? G.rtab_n[col0 + lane] : 0;
-            }
+            stack_records<PMAX, GW, RV>(G, i0, j, vb, rec, lane);
         } else {
             // The accumulators wait in the (idle) window area while the FP64
             // record stage, the kernel's register peak, runs.
@@ -1752,7 +1762,7 @@ __device__ __forceinline__ void backproject_item(const DevGeom &G, const int ngr
         // the gather, with the window read from LDS (WIN) or global memory;
         // a piece record is read once for both passes
         auto gather = [&](auto winTag, auto npTag) {
-            constexpr bool WIN = decltype(winTag)::value;
+            constexpr int SRC = decltype(winTag)::value ? kFromWindow : kFromCaller;
             constexpr int NP = decltype(npTag)::value;
             bool kv[NP];
             float kf[NP];
@@ -1766,7 +1776,7 @@ __device__ __forceinline__ void backproject_item(const DevGeom &G, const int ngr
             for (int c = 0; c < GW; ++c) {
                 const int np = __builtin_amdgcn_readfirstlane(npc[c]);
                 float a[NP];   // (no branch around a column without pieces: it would copy every sum)
-                gather_column<EC, EXACT, TT, WIN, NP>(B, recv + c * PMAX * kRecFloats, np, win, kf, kv, a);
+                gather_column<EC, EXACT, TT, SRC, NP>(B, recv + c * PMAX * kRecFloats, np, win, kf, kv, a);
 #pragma unroll
                 for (int ps = 0; ps < NP; ++ps)
                     acc[ps][c] = fmaf(column_factor<EXACT, TT>(B, recv + c * PMAX * kRecFloats, np, kf[ps]), a[ps], acc[ps][c]);
@@ -1783,14 +1793,6 @@ __device__ __forceinline__ void backproject_item(const DevGeom &G, const int ngr
         }
         wave_sync();
         }
-    }
-
-    if (!part.last) {
-#pragma unroll
-        for (int ps = 0; ps < KP; ++ps)
-#pragma unroll
-            for (int c = 0; c < GW; ++c) mine[(ps * GW + c) * kWave] = acc[ps][c];
-        return;
     }
 
     // Sum the four waves' partial sums in a fixed order; one store per voxel.
@@ -1817,13 +1819,195 @@ template <bool EXACT, bool EC, int PMAX, int GW, bool TT = false, bool TAB = fal
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(TAB ? 4 : 3)))
 backproject_kernel(const DevGeom G, const int ngroups, const int nkchunks, const int kp, const int items,
                    const int chunk, const int winCap, const float *__restrict__ proj,
-                   float *__restrict__ vol, const BackPart part, const double *__restrict__ stop)
+                   float *__restrict__ vol, const double *__restrict__ stop)
 {
     extern __shared__ __align__(16) float smem[];
     if (stop && *stop != 0.0) return;
     const int item = (blockIdx.x & 7) * chunk + (blockIdx.x >> 3);
     if (item >= items) return;
-    backproject_item<EXACT, EC, PMAX, GW, TT, TAB>(G, ngroups, nkchunks, kp, winCap, item, smem, proj, vol, part);
+    backproject_item<EXACT, EC, PMAX, GW, TT, TAB>(G, ngroups, nkchunks, kp, winCap, item, smem, proj, vol);
+}
+
+// pt[view][u][pad + v] = proj[view][v][u] sigma[v][u] with `pad` zero rows on
+// both sides of the detector rows (pitch np = N + 2 pad floats), for the
+// views of G; bad[view][block] = 1 if a value is not finite.  A workgroup
+// takes 64 columns of a view and walks the rows in 64 x 64 tiles through LDS.
+__global__ void __launch_bounds__(kBlock)
+transpose_projections_kernel(const DevGeom G, const int pad, const float *__restrict__ proj, float *__restrict__ pt,
+                             int *__restrict__ bad, const double *__restrict__ stop)
+{
+    if (stop && *stop != 0.0) return;
+    __shared__ float tile[kWave][kWave + 1];
+    const int nb = (G.M + kWave - 1) / kWave, np = G.N + 2 * pad;
+    const int view = blockIdx.x / nb, u0 = (blockIdx.x - view * nb) * kWave;
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const int nc = min(kWave, G.M - u0);
+    const float *pv = proj + (size_t)view * G.vstride * G.N * G.M;
+    const float *sgv = G.sigma ? G.sigma + (size_t)view * G.vstride * G.sigma_views * G.N * G.M : nullptr;
+    float *out = pt + ((size_t)view * G.M + u0) * np;
+    float chk = 0.0f;
+    for (int v0 = 0; v0 < np; v0 += kWave) {
+        float t[kWave / kWaves];
+#pragma unroll
+        for (int e = 0; e < kWave / kWaves; ++e) {
+            const int v = v0 + wave + e * kWaves - pad;
+            t[e] = 0.0f;
+            if (lane < nc && (unsigned)v < (unsigned)G.N) {
+                const size_t off = (size_t)v * G.M + u0 + lane;
+                t[e] = sgv ? pv[off] * sgv[off] : pv[off];
+            }
+            chk = fmaf(t[e], 0.0f, chk);                  // NaN once any value is not finite
+        }
+        if (v0 > 0) __syncthreads();
+#pragma unroll
+        for (int e = 0; e < kWave / kWaves; ++e) tile[wave + e * kWaves][lane] = t[e];
+        __syncthreads();
+        if (v0 + lane < np) {
+#pragma unroll
+            for (int e = 0; e < kWave / kWaves; ++e) {
+                const int c = wave + e * kWaves;
+                if (c < nc) out[(size_t)c * np + v0 + lane] = tile[lane][c];
+            }
+        }
+    }
+    const int any = __syncthreads_or(!(chk == 0.0f));
+    if (threadIdx.x == 0) bad[(size_t)view * nb + u0 / kWave] = any;
+}
+
+// The backprojection from a transposed copy of the scaled projections
+// (transpose_projections_kernel; records from a table): the rows of a piece
+// are consecutive in it, so the lanes of a wave (slices k, beta rows apart)
+// read neighbouring addresses and one load takes all rows of a piece.  No
+// window is staged (2000 elements per stack and view at 512^3 x 248 views, a
+// fifth of the windowed kernel's instructions, whose stacks must also keep
+// their windows within LDS); a stack's columns overlap in L1.  Views, sums
+// and arithmetic are those of backproject_item: the same bits.
+template <bool EXACT, bool EC, int PMAX, bool TT>
+__device__ __forceinline__ void backproject_direct_item(const DevGeom &G, const int ngroups, const int nkchunks,
+                                                        const int kp, const int item, float *smem,
+                                                        const BackCopy &copy, float *__restrict__ vol,
+                                                        const BackPart &part)
+{
+    const int kch = item % nkchunks;
+    const int t = item / nkchunks;
+    const int q = t % ngroups;
+    const int j = t / ngroups;
+    constexpr int GW = kDirectCols, KP = kDirectPasses;
+    const int i0 = q * GW;
+    const int k0 = kch * kWave * kp;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    constexpr int LPV = GW * (PMAX < kWave / GW ? PMAX : kWave / GW);
+    constexpr int RV = kWave / LPV;
+    constexpr int recView = back_rec_floats(GW, PMAX);
+    float *rec = smem + wave * (RV * recView);
+
+    float acc[GW * KP];                                   // column c, pass ps at c KP + ps
+#pragma unroll
+    for (int e = 0; e < GW * KP; ++e) acc[e] = 0.0f;
+    float *const mine = part.sums + ((size_t)item * kWaves + wave) * KP * GW * kWave + lane;
+    if (!part.first) {
+#pragma unroll
+        for (int e = 0; e < GW * KP; ++e) acc[e] = mine[e * kWave];
+    }
+
+    const int passes = min(kp, (G.n3 - k0 + kWave - 1) / kWave);   // with slices in them
+    const int nb = (G.M + kWave - 1) / kWave;
+    for (int vb = wave; vb < G.nviews; vb += kWaves * RV) {
+        wave_sync();                       // the records of the views before are no longer read
+        stack_records<PMAX, GW, RV>(G, i0, j, vb, rec, lane);
+        wave_sync();
+#pragma unroll 1
+        for (int r = 0; r < RV; ++r) {
+            const int view = vb + r * kWaves;
+            if (view >= G.nviews) break;
+            const ViewGeom V = G.views[(size_t)view * G.vstride];
+            const float *recv = rec + r * recView;
+            const int *npc = reinterpret_cast<const int *>(recv + GW * PMAX * kRecFloats);
+            BackView B;
+            B.pv = B.sgv = nullptr;
+            B.N = G.N; B.M = G.M;
+            B.wu0 = 0; B.wv0 = -copy.pad; B.wv1 = G.N - 1 + copy.pad; B.Hp = G.N + 2 * copy.pad;
+            B.c2f = (float)V.c2; B.md = detector_reach(B.c2f, G.N);
+            B.zt0 = (float)(G.x3lo + G.a3 - V.s3); B.a3f = (float)G.a3;
+            B.raw = G.raw_volume != 0;
+            int bad = 0;
+            for (int b = lane; b < nb; b += kWave) bad |= copy.bad[(size_t)view * nb + b];
+            B.fixed = __ballot(bad != 0) == 0;
+            const float *base = copy.pt + (size_t)view * G.M * B.Hp;
+            // NP passes of 64 slices from pass ps0 on share each piece record
+            auto gather = [&](auto ps0Tag, auto npTag) {
+                constexpr int PS0 = decltype(ps0Tag)::value, NP = decltype(npTag)::value;
+                if constexpr (PS0 + NP <= KP) {
+                    bool kv[NP];
+                    float kf[NP];
+#pragma unroll
+                    for (int ps = 0; ps < NP; ++ps) {
+                        const int k = k0 + (PS0 + ps) * kWave + lane;
+                        kv[ps] = k < G.n3;
+                        kf[ps] = (float)min(k, G.n3 - 1);
+                    }
+#pragma unroll
+                    for (int c = 0; c < GW; ++c) {
+                        const float *rc = recv + c * PMAX * kRecFloats;
+                        const int np = __builtin_amdgcn_readfirstlane(npc[c]);
+                        float a[NP];
+                        gather_column<EC, EXACT, TT, kFromCopy, NP>(B, rc, np, base, kf, kv, a);
+#pragma unroll
+                        for (int ps = 0; ps < NP; ++ps)
+                            acc[c * KP + PS0 + ps] =
+                                fmaf(column_factor<EXACT, TT>(B, rc, np, kf[ps]), a[ps], acc[c * KP + PS0 + ps]);
+                    }
+                }
+            };
+            using std::integral_constant;
+            using N0 = integral_constant<int, 0>;
+            using N1 = integral_constant<int, 1>;
+            using N2 = integral_constant<int, 2>;
+            if (passes == 4) gather(N0{}, integral_constant<int, 4>{});
+            else if (passes >= 2) gather(N0{}, N2{});
+            else gather(N0{}, N1{});
+            if (passes == 3) gather(N2{}, N1{});
+        }
+    }
+    if (!part.last) {
+#pragma unroll
+        for (int e = 0; e < GW * KP; ++e) mine[e * kWave] = acc[e];
+        return;
+    }
+
+    // Sum the four waves' partial sums in a fixed order; one store per voxel.
+    float *red = smem;   // [kWaves][GW][kWave], aliases the records
+#pragma unroll
+    for (int ps = 0; ps < KP; ++ps) {
+        if (ps >= kp) break;
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < GW; ++c) red[(wave * GW + c) * kWave + lane] = acc[c * KP + ps];
+        __syncthreads();
+        const int k = k0 + ps * kWave + lane;
+        for (int c = wave; c < GW; c += kWaves) {
+            const int i = i0 + c;
+            float s = red[(0 * GW + c) * kWave + lane];
+#pragma unroll
+            for (int w = 1; w < kWaves; ++w) s += red[(w * GW + c) * kWave + lane];
+            if (k < G.n3 && i < G.n1) vol[((size_t)k * G.n2 + j) * G.n1 + i] = s;
+        }
+    }
+}
+
+template <bool EXACT, bool EC, int PMAX, bool TT>
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4)))
+backproject_direct_kernel(const DevGeom G, const int ngroups, const int nkchunks, const int kp, const int items,
+                          const BackCopy copy, float *__restrict__ vol, const BackPart part,
+                          const double *__restrict__ stop)
+{
+    extern __shared__ __align__(16) float smem[];
+    if (stop && *stop != 0.0) return;
+    // XCD x (workgroups go to the 8 round robin) takes a contiguous run of items
+    const int item = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    if (item >= items) return;
+    backproject_direct_item<EXACT, EC, PMAX, TT>(G, ngroups, nkchunks, kp, item, smem, copy, vol, part);
 }
 
 // The backprojection with one detector window per workgroup (cached records
@@ -1839,7 +2023,7 @@ template <bool EXACT, bool EC, int PMAX, int GW>
 __device__ __forceinline__ void backproject_shared_item(const DevGeom &G, const int ngroups, const int nkchunks,
                                                         const int kp, const int winCap, const int item,
                                                         float *smem, const float *__restrict__ proj,
-                                                        float *__restrict__ vol, const BackPart &part)
+                                                        float *__restrict__ vol)
 {
     constexpr int KP = kBackPasses;
     constexpr int CPW = GW / kWaves;                 // columns per wave
@@ -1867,13 +2051,6 @@ __device__ __forceinline__ void backproject_shared_item(const DevGeom &G, const 
     typename FloatVec<4 * CPW>::type acc[KP];
 #pragma unroll
     for (int ps = 0; ps < KP; ++ps) acc[ps] = 0.0f;
-    float *const mine = part.sums + ((size_t)item * kWaves + wave) * KP * GW * kWave + lane;
-    if (!part.first) {
-#pragma unroll
-        for (int ps = 0; ps < KP; ++ps)
-#pragma unroll
-            for (int c = 0; c < GW; ++c) acc[ps][c] = mine[(ps * GW + c) * kWave];
-    }
 
     for (int view = 0; view < G.nviews; ++view) {
         const int cl = view & 3;
@@ -1956,7 +2133,7 @@ __device__ __forceinline__ void backproject_shared_item(const DevGeom &G, const 
             __syncthreads();
 
         auto gather = [&](auto winTag, auto npTag) {
-            constexpr bool WIN = decltype(winTag)::value;
+            constexpr int SRC = decltype(winTag)::value ? kFromWindow : kFromCaller;
             constexpr int NP = decltype(npTag)::value;
             bool kv[NP];
             float kf[NP];
@@ -1971,7 +2148,7 @@ __device__ __forceinline__ void backproject_shared_item(const DevGeom &G, const 
                 const int c = wave * CPW + cc;
                 const int np = __builtin_amdgcn_readfirstlane(npv[c]);
                 float a[NP];
-                gather_column<EC, EXACT, false, WIN, NP>(B, rec + c * PMAX * kRecFloats, np, win, kf, kv, a);
+                gather_column<EC, EXACT, false, SRC, NP>(B, rec + c * PMAX * kRecFloats, np, win, kf, kv, a);
 #pragma unroll
                 for (int ps = 0; ps < NP; ++ps) {
                     const float f = column_factor<EXACT, false>(B, rec + c * PMAX * kRecFloats, np, kf[ps]);
@@ -1989,14 +2166,6 @@ __device__ __forceinline__ void backproject_shared_item(const DevGeom &G, const 
             else gather(std::false_type{}, P2{});
         }
         __syncthreads();                   // the next view reuses the records and the window
-    }
-
-    if (!part.last) {
-#pragma unroll
-        for (int ps = 0; ps < KP; ++ps)
-#pragma unroll
-            for (int c = 0; c < GW; ++c) mine[(ps * GW + c) * kWave] = acc[ps][c];
-        return;
     }
 
     // ((c0 + c1) + c2) + c3 per voxel, one store each
@@ -2019,13 +2188,13 @@ template <bool EXACT, bool EC, int PMAX, int GW>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4)))
 backproject_shared_kernel(const DevGeom G, const int ngroups, const int nkchunks, const int kp, const int items,
                           const int chunk, const int winCap, const float *__restrict__ proj,
-                          float *__restrict__ vol, const BackPart part, const double *__restrict__ stop)
+                          float *__restrict__ vol, const double *__restrict__ stop)
 {
     extern __shared__ __align__(16) float smem[];
     if (stop && *stop != 0.0) return;
     const int item = (blockIdx.x & 7) * chunk + (blockIdx.x >> 3);
     if (item >= items) return;
-    backproject_shared_item<EXACT, EC, PMAX, GW>(G, ngroups, nkchunks, kp, winCap, item, smem, proj, vol, part);
+    backproject_shared_item<EXACT, EC, PMAX, GW>(G, ngroups, nkchunks, kp, winCap, item, smem, proj, vol);
 }
 
 // ------------------------------------------------------------ batched, persistent
@@ -2071,8 +2240,8 @@ project_batched_kernel(const BatchProblem *__restrict__ probs, const BatchTable 
 // equals its own single-problem launch bitwise, and each kernel holds a
 // single variant of the gather (its registers fit like the single-problem
 // kernel's; one kernel inlining every variant spilled).
-template <bool EXACT, bool EC, int PMAX, int GW, bool TAB = false>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(TAB ? 4 : 3)))
+template <bool EXACT, bool EC, int PMAX, int GW>
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3)))
 backproject_batched_kernel(const BatchProblem *__restrict__ probs, const BatchTable *__restrict__ T,
                            int *counter)
 {
@@ -2081,8 +2250,24 @@ backproject_batched_kernel(const BatchProblem *__restrict__ probs, const BatchTa
     while (next_item(*T, counter, p, local)) {
         const BatchProblem &P = probs[p];
         if (P.stop && *P.stop != 0.0) continue;
-        backproject_item<EXACT, EC, PMAX, GW, false, TAB>(P.G, P.ngroups, P.nkchunks, P.kp, P.win_cap, local, smem,
-                                                         P.in, P.out, BackPart());
+        backproject_item<EXACT, EC, PMAX, GW, false, false>(P.G, P.ngroups, P.nkchunks, P.kp, P.win_cap, local, smem,
+                                                         P.in, P.out);
+    }
+}
+
+// The same from the members' transposed copies and tables of records: one
+// launch per piece stride.
+template <bool EXACT, bool EC, int PMAX>
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4)))
+backproject_direct_batched_kernel(const BatchProblem *__restrict__ probs, const BatchTable *__restrict__ T, int *counter)
+{
+    extern __shared__ __align__(16) float smem[];
+    int p, local;
+    while (next_item(*T, counter, p, local)) {
+        const BatchProblem &P = probs[p];
+        if (P.stop && *P.stop != 0.0) continue;
+        backproject_direct_item<EXACT, EC, PMAX, false>(P.G, P.direct.ngroups, P.direct.nkchunks, P.direct.kp, local, smem,
+                                                        P.copy, P.out, BackPart());
     }
 }
 
@@ -2135,21 +2320,21 @@ hipError_t launch_p(const DevGeom &g, const ProjLaunch &L, const float *vol, flo
 
 template <bool EXACT, bool EC, int PMAX, bool TT = false, bool TAB = false>
 hipError_t launch_bp_gw(const DevGeom &g, const BackLaunch &L, const float *proj, float *vol,
-                        hipStream_t s, const double *stop, const BackPart &part)
+                        hipStream_t s, const double *stop)
 {
     const dim3 grid(8 * L.chunk), block(kBlock);
     switch (L.gw) {
     case 16:
         hipLaunchKernelGGL((backproject_kernel<EXACT, EC, PMAX, 16, TT, TAB>), grid, block, L.lds, s, g,
-                           L.ngroups, L.nkchunks, L.kp, L.items, L.chunk, L.win_cap, proj, vol, part, stop);
+                           L.ngroups, L.nkchunks, L.kp, L.items, L.chunk, L.win_cap, proj, vol, stop);
         break;
     case 8:
         hipLaunchKernelGGL((backproject_kernel<EXACT, EC, PMAX, 8, TT, TAB>), grid, block, L.lds, s, g,
-                           L.ngroups, L.nkchunks, L.kp, L.items, L.chunk, L.win_cap, proj, vol, part, stop);
+                           L.ngroups, L.nkchunks, L.kp, L.items, L.chunk, L.win_cap, proj, vol, stop);
         break;
     default:
         hipLaunchKernelGGL((backproject_kernel<EXACT, EC, PMAX, 4, TT, TAB>), grid, block, L.lds, s, g,
-                           L.ngroups, L.nkchunks, L.kp, L.items, L.chunk, L.win_cap, proj, vol, part, stop);
+                           L.ngroups, L.nkchunks, L.kp, L.items, L.chunk, L.win_cap, proj, vol, stop);
         break;
     }
     return hipGetLastError();
@@ -2157,17 +2342,17 @@ hipError_t launch_bp_gw(const DevGeom &g, const BackLaunch &L, const float *proj
 
 template <bool EXACT, bool EC, int PMAX>
 hipError_t launch_bp_shared(const DevGeom &g, const BackLaunch &L, const float *proj, float *vol,
-                            hipStream_t s, const double *stop, const BackPart &part)
+                            hipStream_t s, const double *stop)
 {
     const dim3 grid(8 * L.chunk), block(kBlock);
     switch (L.gw) {
     case 16:
         hipLaunchKernelGGL((backproject_shared_kernel<EXACT, EC, PMAX, 16>), grid, block, L.lds, s, g, L.ngroups,
-                           L.nkchunks, L.kp, L.items, L.chunk, L.win_cap, proj, vol, part, stop);
+                           L.nkchunks, L.kp, L.items, L.chunk, L.win_cap, proj, vol, stop);
         break;
     case 8:
         hipLaunchKernelGGL((backproject_shared_kernel<EXACT, EC, PMAX, 8>), grid, block, L.lds, s, g, L.ngroups,
-                           L.nkchunks, L.kp, L.items, L.chunk, L.win_cap, proj, vol, part, stop);
+                           L.nkchunks, L.kp, L.items, L.chunk, L.win_cap, proj, vol, stop);
         break;
     default:
         return hipErrorInvalidValue;   // plans give a shared window to stacks of 8 or 16 columns only
@@ -2177,25 +2362,25 @@ hipError_t launch_bp_shared(const DevGeom &g, const BackLaunch &L, const float *
 
 template <bool EXACT, bool EC, bool TT = false>
 hipError_t launch_bp(const DevGeom &g, const BackLaunch &L, const float *proj, float *vol,
-                     hipStream_t s, const double *stop, const BackPart &part)
+                     hipStream_t s, const double *stop)
 {
     if (g.rtab) {
         // a table of records (the plan L was made for these kernels)
         if (L.pmax > 8 || g.rtab_pmax != (L.pmax <= 4 ? 4 : 8)) return hipErrorInvalidValue;
         if (L.shared) {
             if (TT) return hipErrorInvalidValue;
-            if (L.pmax <= 4) return launch_bp_shared<EXACT, EC, 4>(g, L, proj, vol, s, stop, part);
-            return launch_bp_shared<EXACT, EC, 8>(g, L, proj, vol, s, stop, part);
+            if (L.pmax <= 4) return launch_bp_shared<EXACT, EC, 4>(g, L, proj, vol, s, stop);
+            return launch_bp_shared<EXACT, EC, 8>(g, L, proj, vol, s, stop);
         }
-        if (L.pmax <= 4) return launch_bp_gw<EXACT, EC, 4, TT, true>(g, L, proj, vol, s, stop, part);
-        return launch_bp_gw<EXACT, EC, 8, TT, true>(g, L, proj, vol, s, stop, part);
+        if (L.pmax <= 4) return launch_bp_gw<EXACT, EC, 4, TT, true>(g, L, proj, vol, s, stop);
+        return launch_bp_gw<EXACT, EC, 8, TT, true>(g, L, proj, vol, s, stop);
     }
-    if (L.pmax <= 4) return launch_bp_gw<EXACT, EC, 4, TT>(g, L, proj, vol, s, stop, part);
-    if (L.pmax <= 8) return launch_bp_gw<EXACT, EC, 8, TT>(g, L, proj, vol, s, stop, part);
+    if (L.pmax <= 4) return launch_bp_gw<EXACT, EC, 4, TT>(g, L, proj, vol, s, stop);
+    if (L.pmax <= 8) return launch_bp_gw<EXACT, EC, 8, TT>(g, L, proj, vol, s, stop);
     // wide footprints: 4-column stacks only
     if (L.gw != 4) return hipErrorInvalidValue;
     hipLaunchKernelGGL((backproject_kernel<EXACT, EC, kPmaxWide, 4, TT>), dim3(8 * L.chunk), dim3(kBlock), L.lds, s, g,
-                       L.ngroups, L.nkchunks, L.kp, L.items, L.chunk, L.win_cap, proj, vol, part, stop);
+                       L.ngroups, L.nkchunks, L.kp, L.items, L.chunk, L.win_cap, proj, vol, stop);
     return hipGetLastError();
 }
 
@@ -2235,66 +2420,45 @@ hipError_t launch_pb(BatchProblem *probs, const BatchTable *tab, int *counter, i
     return hipGetLastError();
 }
 
-template <bool EXACT, bool EC, int PMAX, bool TAB>
-hipError_t launch_bb_p(BatchProblem *probs, const BatchTable *tab, int *counter, int grid, size_t lds, int gw,
-                       hipStream_t s)
+template <bool EXACT, bool EC, int PMAX>
+hipError_t launch_bb(BatchProblem *probs, const BatchTable *tab, int *counter, int grid, size_t lds, int gw,
+                     hipStream_t s)
 {
-    if (gw == 16)
-        hipLaunchKernelGGL((backproject_batched_kernel<EXACT, EC, PMAX, 16, TAB>), dim3(grid), dim3(kBlock), lds, s,
-                           probs, tab, counter);
-    else if (gw == 8)
-        hipLaunchKernelGGL((backproject_batched_kernel<EXACT, EC, PMAX, 8, TAB>), dim3(grid), dim3(kBlock), lds, s,
-                           probs, tab, counter);
-    else
-        hipLaunchKernelGGL((backproject_batched_kernel<EXACT, EC, PMAX, 4, TAB>), dim3(grid), dim3(kBlock), lds, s,
-                           probs, tab, counter);
+    const auto fn = gw == 0 ? backproject_direct_batched_kernel<EXACT, EC, PMAX>
+                    : gw == 16 ? backproject_batched_kernel<EXACT, EC, PMAX, 16>
+                    : gw == 8 ? backproject_batched_kernel<EXACT, EC, PMAX, 8>
+                              : backproject_batched_kernel<EXACT, EC, PMAX, 4>;
+    hipLaunchKernelGGL(fn, dim3(grid), dim3(kBlock), lds, s, probs, tab, counter);
     return hipGetLastError();
 }
 
-template <bool EXACT, bool EC, bool TAB>
-hipError_t launch_bb(BatchProblem *probs, const BatchTable *tab, int *counter, int grid, size_t lds, int gw, int pmax,
-                     hipStream_t s)
+template <bool EXACT, bool EC>
+hipError_t launch_batched_form(bool backward, BatchProblem *probs, const BatchTable *tab, int *counter, int grid,
+                               size_t lds, int gw, int pmax, bool cached, bool vt, hipStream_t s)
 {
-    return pmax <= 4 ? launch_bb_p<EXACT, EC, 4, TAB>(probs, tab, counter, grid, lds, gw, s)
-                     : launch_bb_p<EXACT, EC, 8, TAB>(probs, tab, counter, grid, lds, gw, s);
+    if (!backward)
+        return cached ? launch_pb<EXACT, EC, true>(probs, tab, counter, grid, lds, vt, s)
+                      : launch_pb<EXACT, EC, false>(probs, tab, counter, grid, lds, vt, s);
+    return pmax <= 4 ? launch_bb<EXACT, EC, 4>(probs, tab, counter, grid, lds, gw, s)
+                     : launch_bb<EXACT, EC, 8>(probs, tab, counter, grid, lds, gw, s);
 }
 
-template <bool TAB>
-hipError_t launch_batched_t(bool backward, BatchProblem *probs, const BatchTable *tab, int *counter, bool exact,
-                            bool ec, int grid, size_t lds, int gw, int pmax, bool vt, hipStream_t s)
-{
-    if (!backward) {
-        if (exact) return ec ? launch_pb<true, true, TAB>(probs, tab, counter, grid, lds, vt, s)
-                             : launch_pb<true, false, TAB>(probs, tab, counter, grid, lds, vt, s);
-        return ec ? launch_pb<false, true, TAB>(probs, tab, counter, grid, lds, vt, s)
-                  : launch_pb<false, false, TAB>(probs, tab, counter, grid, lds, vt, s);
-    }
-    if (exact) return ec ? launch_bb<true, true, TAB>(probs, tab, counter, grid, lds, gw, pmax, s)
-                         : launch_bb<true, false, TAB>(probs, tab, counter, grid, lds, gw, pmax, s);
-    return ec ? launch_bb<false, true, TAB>(probs, tab, counter, grid, lds, gw, pmax, s)
-              : launch_bb<false, false, TAB>(probs, tab, counter, grid, lds, gw, pmax, s);
-}
-
-template <int PMAX, bool TAB>
+template <int PMAX>
 const void *back_batched_fn(int gw)
 {
-    if (gw == 16) return (const void *)backproject_batched_kernel<false, true, PMAX, 16, TAB>;
-    if (gw == 8) return (const void *)backproject_batched_kernel<false, true, PMAX, 8, TAB>;
-    return (const void *)backproject_batched_kernel<false, true, PMAX, 4, TAB>;
+    if (gw == 0) return (const void *)backproject_direct_batched_kernel<false, true, PMAX>;
+    if (gw == 16) return (const void *)backproject_batched_kernel<false, true, PMAX, 16>;
+    if (gw == 8) return (const void *)backproject_batched_kernel<false, true, PMAX, 8>;
+    return (const void *)backproject_batched_kernel<false, true, PMAX, 4>;
 }
 
-template <bool TAB>
-int blocks_per_cu_t(bool backward, size_t lds, int gw, int pmax, bool vt)
+const void *project_batched_fn(bool cached, bool vt)
 {
-    int nb = 0;
-    const void *fn = !backward ? (vt ? (const void *)project_batched_kernel<false, true, TAB, true>
-                                     : (const void *)project_batched_kernel<false, true, TAB, false>)
-                               : pmax <= 4 ? back_batched_fn<4, TAB>(gw) : back_batched_fn<8, TAB>(gw);
-    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, kBlock, lds);
-    if (e != hipSuccess || nb < 1) nb = 1;
-    return nb;
+    if (cached) return vt ? (const void *)project_batched_kernel<false, true, true, true>
+                          : (const void *)project_batched_kernel<false, true, true, false>;
+    return vt ? (const void *)project_batched_kernel<false, true, false, true>
+              : (const void *)project_batched_kernel<false, true, false, false>;
 }
-
 }  // namespace
 
 hipError_t launch_batched(bool backward, BatchProblem *probs, const BatchTable *tab, int *counter,
@@ -2304,25 +2468,30 @@ hipError_t launch_batched(bool backward, BatchProblem *probs, const BatchTable *
     hipLaunchKernelGGL(batch_setup, dim3(1), dim3(64), 0, s, probs, io, counter);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return cached ? launch_batched_t<true>(backward, probs, tab, counter, exact, ec, grid, lds, gw, pmax, vt, s)
-                  : launch_batched_t<false>(backward, probs, tab, counter, exact, ec, grid, lds, gw, pmax, vt, s);
+    if (exact) return ec ? launch_batched_form<true, true>(backward, probs, tab, counter, grid, lds, gw, pmax, cached, vt, s)
+                         : launch_batched_form<true, false>(backward, probs, tab, counter, grid, lds, gw, pmax, cached, vt, s);
+    return ec ? launch_batched_form<false, true>(backward, probs, tab, counter, grid, lds, gw, pmax, cached, vt, s)
+              : launch_batched_form<false, false>(backward, probs, tab, counter, grid, lds, gw, pmax, cached, vt, s);
 }
 
 // Workgroups of a persistent batched kernel that fit on one CU at this LDS size.
 int batched_blocks_per_cu(bool backward, size_t lds, int gw, int pmax, bool cached, bool vt)
 {
-    return cached ? blocks_per_cu_t<true>(backward, lds, gw, pmax, vt)
-                  : blocks_per_cu_t<false>(backward, lds, gw, pmax, vt);
+    int nb = 0;
+    const void *fn = !backward ? project_batched_fn(cached, vt) : pmax <= 4 ? back_batched_fn<4>(gw) : back_batched_fn<8>(gw);
+    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, kBlock, lds);
+    if (e != hipSuccess || nb < 1) nb = 1;
+    return nb;
 }
 
-template <int PMAX, bool TAB>
+template <int PMAX>
 static hipError_t allow_batched_back(size_t n)
 {
     return each_form([&](auto x, auto c) {
         constexpr bool X = decltype(x)::value, C = decltype(c)::value;
-        hipError_t r = allow_lds((const void *)backproject_batched_kernel<X, C, PMAX, 16, TAB>, n);
-        if (r == hipSuccess) r = allow_lds((const void *)backproject_batched_kernel<X, C, PMAX, 8, TAB>, n);
-        if (r == hipSuccess) r = allow_lds((const void *)backproject_batched_kernel<X, C, PMAX, 4, TAB>, n);
+        hipError_t r = allow_lds((const void *)backproject_batched_kernel<X, C, PMAX, 16>, n);
+        if (r == hipSuccess) r = allow_lds((const void *)backproject_batched_kernel<X, C, PMAX, 8>, n);
+        if (r == hipSuccess) r = allow_lds((const void *)backproject_batched_kernel<X, C, PMAX, 4>, n);
         return r;
     });
 }
@@ -2337,10 +2506,8 @@ hipError_t configure_batched_lds(size_t n)
         if (r == hipSuccess) r = allow_lds((const void *)project_batched_kernel<X, C, true, true>, n);
         return r;
     });
-    if (e == hipSuccess) e = allow_batched_back<4, false>(n);
-    if (e == hipSuccess) e = allow_batched_back<8, false>(n);
-    if (e == hipSuccess) e = allow_batched_back<4, true>(n);
-    if (e == hipSuccess) e = allow_batched_back<8, true>(n);
+    if (e == hipSuccess) e = allow_batched_back<4>(n);
+    if (e == hipSuccess) e = allow_batched_back<8>(n);
     return e;
 }
 #endif
@@ -2490,15 +2657,45 @@ hipError_t configure_backproject_lds(size_t n)
     return e;
 }
 
-hipError_t launch_backproject(const DevGeom &g, const BackLaunch &L, int model, bool ec,
-                              const float *proj, float *vol, hipStream_t stream, const double *stop, const BackPart &part)
+hipError_t launch_transpose_projections(const DevGeom &g, const float *proj, const BackCopy &copy, hipStream_t stream,
+                                        const double *stop)
 {
-    if (model == kModelTT) return launch_bp<false, true, true>(g, L, proj, vol, stream, stop, part);
+    const int64_t blocks = (int64_t)g.nviews * ((g.M + kWave - 1) / kWave);
+    hipLaunchKernelGGL(transpose_projections_kernel, dim3((unsigned)blocks), dim3(kBlock), 0, stream, g, copy.pad, proj,
+                       copy.pt, copy.bad, stop);
+    return hipGetLastError();
+}
+
+template <bool EXACT, bool EC, bool TT = false>
+static hipError_t launch_direct(const DevGeom &g, const DirectLaunch &L, const BackCopy &copy, float *vol, hipStream_t s,
+                                const double *stop, const BackPart &part)
+{
+    if (!g.rtab || g.rtab_pmax != L.pmax) return hipErrorInvalidValue;
+    const auto fn = L.pmax <= 4 ? backproject_direct_kernel<EXACT, EC, 4, TT> : backproject_direct_kernel<EXACT, EC, 8, TT>;
+    hipLaunchKernelGGL(fn, dim3((L.items + 7) / 8 * 8), dim3(kBlock), back_direct_lds(L.pmax), s, g, L.ngroups, L.nkchunks,
+                       L.kp, L.items, copy, vol, part, stop);
+    return hipGetLastError();
+}
+
+hipError_t launch_backproject_direct(const DevGeom &g, const DirectLaunch &L, int model, bool ec, const BackCopy &copy,
+                                     float *vol, hipStream_t stream, const double *stop, const BackPart &part)
+{
+    if (model == kModelTT) return launch_direct<false, true, true>(g, L, copy, vol, stream, stop, part);
+    if (model == kModelExact) return ec ? launch_direct<true, true>(g, L, copy, vol, stream, stop, part)
+                                        : launch_direct<true, false>(g, L, copy, vol, stream, stop, part);
+    return ec ? launch_direct<false, true>(g, L, copy, vol, stream, stop, part)
+              : launch_direct<false, false>(g, L, copy, vol, stream, stop, part);
+}
+
+hipError_t launch_backproject(const DevGeom &g, const BackLaunch &L, int model, bool ec,
+                              const float *proj, float *vol, hipStream_t stream, const double *stop)
+{
+    if (model == kModelTT) return launch_bp<false, true, true>(g, L, proj, vol, stream, stop);
     const bool exact = model == kModelExact;
-    if (exact) return ec ? launch_bp<true, true>(g, L, proj, vol, stream, stop, part)
-                         : launch_bp<true, false>(g, L, proj, vol, stream, stop, part);
-    return ec ? launch_bp<false, true>(g, L, proj, vol, stream, stop, part)
-              : launch_bp<false, false>(g, L, proj, vol, stream, stop, part);
+    if (exact) return ec ? launch_bp<true, true>(g, L, proj, vol, stream, stop)
+                         : launch_bp<true, false>(g, L, proj, vol, stream, stop);
+    return ec ? launch_bp<false, true>(g, L, proj, vol, stream, stop)
+              : launch_bp<false, false>(g, L, proj, vol, stream, stop);
 }
 
 #endif
