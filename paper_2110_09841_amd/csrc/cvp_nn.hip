@@ -14,8 +14,8 @@
 // (weights stored [tap][co][ci]).  The 16x16 FP32 result has row 4*(l/16)+e,
 // column l%16 in element e of lane l.
 // conv3d backward-weight reduces over voxels: D[co][ci] = sum_v dY[v][co] X[v+off][ci],
-// with dY and the shifted X rows staged transposed in LDS so that the 8
-// consecutive voxels of a lane are one 16-byte LDS read.
+// with dY and X staged in LDS as they lie in memory and the voxels of a lane
+// gathered by the transposing LDS read.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -309,134 +309,245 @@ conv3d_lds_kernel(const Act in, const __bf16 *__restrict__ wt, const float *__re
     }
 }
 
-// Backward-weight partials: for the taps (dz, dy) = tap9 and all three dx,
-// and a chunk of `rows` (d, h) rows, part[chunk][tap][co][ci] =
-// sum over the chunk's voxels of dY[v][co] * X[v + off][ci].  Per 64-voxel
-// segment, dY and the three dx-shifted X rows are staged transposed in LDS
-// as [channel][voxel pair]: a thread loads 8 channels of two neighbouring
-// voxels (two 16-byte loads) and writes 8 words each holding the channel's
-// two BF16 values, so the writes of a wave are consecutive words.  A lane's
-// MFMA fragment (8 consecutive voxels of one channel) is then one 16-byte
-// LDS read; the row pitch of 36 words keeps those reads conflict free.
-// Wave w owns the 16x16 (co, ci) tiles w, w + 4, ...
+// Backward-weight partials: part[chunk][tap][co][ci] = sum over the chunk's
+// voxels v of dY[v][co] X[v + off(tap)][ci].  A chunk is a set of units, a unit
+// a column of tiles of TY x 32 voxels marched along d: the LDS holds three
+// slices of X with their halo and one of dY, both as they lie in memory (16
+// channels of a voxel are 32 bytes), so every step of the march loads one new
+// slice for all 27 taps, and loads it while the taps of the last are summed.
+// The contraction runs over voxels, that is across the rows of that layout:
+// the transposing LDS read gives each lane 4 consecutive voxels of one
+// channel, and with voxels 16 j + 4 g + e in element e of lane group g the 64
+// lanes of a read touch 512 consecutive bytes whatever the tap, so a shift by
+// a tap is an offset and no bank conflicts arise.  The 27 taps are split over
+// the waves (7, 7, 7, 6); 64 output channels are two workgroups.
+// With 16 output channels an X fragment feeds one MFMA and the LDS bandwidth
+// bounds the inner loop; with 64 input channels (one wave per SIMD, 480
+// registers) the latency of staging does.  With the reduction 25 us at 16 ->
+// 16 channels, 64 x 72 x 88 (134 with 64 rows per workgroup, one (dz, dy) each
+// and voxel pairs transposed by hand on the way into the LDS), 58 us at 64 ->
+// 32, 48 x 50 x 66 (262).
+template <int CI>
+constexpr int wgrad_rows() { return CI == 16 ? 8 : CI == 32 ? 4 : 2; }
+
 template <int CO, int CI>
-__global__ void __launch_bounds__(256)
-conv3d_wgrad_kernel(const Act x, const Act dy, int rows_per_chunk, float *__restrict__ part)
+constexpr int wgrad_lds_bytes()
 {
-    constexpr int MT = CO / 16, NT = CI / 16;
-    constexpr int TILES = MT * NT;                 // 16x16 tiles per tap
-    constexpr int PER_WAVE = (TILES + 3) / 4;
-    constexpr int PITCH = 36;                      // words per channel row (32 voxel pairs + pad)
-    __shared__ __align__(16) unsigned sdy[CO * PITCH];
-    __shared__ __align__(16) unsigned sx[3 * CI * PITCH];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int tap9 = blockIdx.y;                   // (dz, dy) in 0..8
-    const int dz = tap9 / 3 - 1, dyo = tap9 % 3 - 1;
-    const int chunk = blockIdx.x;
-    const int nrows = x.D * x.H;
-    const int r0 = chunk * rows_per_chunk;
-    const int r1 = min(r0 + rows_per_chunk, nrows);
-    const int segs = (x.W + 63) / 64;
+    return (3 * (wgrad_rows<CI>() + 2) * 34 * CI + wgrad_rows<CI>() * 32 * (CO < 32 ? CO : 32)) * 2;
+}
 
-    f32x4 acc[3][PER_WAVE];
-#pragma unroll
-    for (int t = 0; t < 3; ++t)
-#pragma unroll
-        for (int q = 0; q < PER_WAVE; ++q) acc[t][q] = f32x4{0.f, 0.f, 0.f, 0.f};
+struct WgradPlan {
+    int chunks;          // partial sums, one workgroup each (two for 64 output channels)
+    int units;           // tile columns x runs of slices
+    int run;             // slices per unit
+    int ytiles, segs;    // tiles along y and x
+};
 
-    // 8 channels of voxel w of a row (zero outside [0, W) or when !ok)
-    auto load8 = [](const Act &a, size_t rowbase, int w, int c0, bool ok) {
-        if (ok && w >= 0 && w < a.W)
-            return *reinterpret_cast<const bf16x8 *>(a.p + (rowbase + w) * a.stride + c0);
-        return zero8();
-    };
-    auto pack = [](__bf16 lo, __bf16 hi) {
-        return (unsigned)__builtin_bit_cast(unsigned short, lo) | ((unsigned)__builtin_bit_cast(unsigned short, hi) << 16);
-    };
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
-    for (int rr = r0; rr < r1; ++rr) {
-        const int d = rr / x.H, h = rr % x.H;
-        const int z = d + dz, y = h + dyo;
-        const bool zy = z >= 0 && z < x.D && y >= 0 && y < x.H;
-        const size_t dyrow = ((size_t)d * dy.H + h) * dy.W;
-        const size_t xrow = ((size_t)z * x.H + y) * x.W;
-        for (int seg = 0; seg < segs; ++seg) {
-            const int w0 = seg * 64;
-            __syncthreads();
-            // dY: tasks (pair m, channel group g)
-            for (int task = threadIdx.x; task < 32 * (CO / 8); task += 256) {
-                const int m = task & 31, g = task >> 5;
-                const int wa = w0 + 2 * m;
-                const bf16x8 a = load8(dy, dyrow, wa, 8 * g, true);
-                const bf16x8 b = load8(dy, dyrow, wa + 1, 8 * g, true);
+__device__ __forceinline__ s16x4 read_voxels4(const unsigned char *p)
+{
+    return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)p);
+}
+
+__device__ __forceinline__ bf16x8 join(s16x4 lo, s16x4 hi)
+{
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+// The q-th tap of a wave: two of the nine (dz, dy) with their three dx, and
+// one dx of the ninth (the fourth wave repeats one and drops it).
+__device__ __forceinline__ int wgrad_tap(int wave, int q)
+{
+    return q < 6 ? (2 * wave + q / 3) * 3 + q % 3 : 24 + min(wave, 2);
+}
+
+template <int CO, int CI>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((CO < 32 ? 1 : 2) * CI / 16 > 4 ? 1 : 2)))
+conv3d_wgrad_kernel(const Act x, const Act dy, const WgradPlan P, float *__restrict__ part)
+{
+    constexpr int COB = CO < 32 ? CO : 32;         // output channels of this workgroup
+    constexpr int MT = COB / 16, NT = CI / 16;
+    constexpr int TY = wgrad_rows<CI>(), XW = 34;
+    constexpr int TAPS = 7;                        // per wave
+    constexpr int XV = (TY + 2) * XW, DV = TY * 32;        // voxels of a staged slice
+    constexpr int XT = XV * (CI / 8), DT = DV * (COB / 8); // 16-byte loads of a staged slice
+    constexpr int NX = (XT + 255) / 256, ND = (DT + 255) / 256;
+    constexpr int SLICE = XV * CI * 2;             // bytes
+    extern __shared__ __align__(16) unsigned char tile[];
+    unsigned char *const sdy = tile + 3 * SLICE;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int co0 = blockIdx.y * COB;
+
+    f32x4 acc[TAPS][MT][NT];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) sdy[(8 * g + e) * PITCH + m] = pack(a[e], b[e]);
+    for (int q = 0; q < TAPS; ++q)
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+            for (int n = 0; n < NT; ++n) acc[q][m][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    for (int unit = blockIdx.x; unit < P.units; unit += P.chunks) {
+        const int seg = unit % P.segs, ty = unit / P.segs % P.ytiles, run = unit / P.segs / P.ytiles;
+        const int w0 = seg * 32, h0 = ty * TY;
+        const int d0 = run * P.run, d1 = min(d0 + P.run, x.D);
+        const int rows = min(TY, x.H - h0);
+
+        bf16x8 px[NX], pd[ND];
+        auto load_x = [&](int z) {
+#pragma unroll
+            for (int i = 0; i < NX; ++i) {
+                const int idx = threadIdx.x + 256 * i;
+                const int v = idx / (CI / 8), c8 = idx % (CI / 8);
+                const int xx = w0 - 1 + v % XW, y = h0 - 1 + v / XW;
+                px[i] = zero8();
+                if (idx < XT && (unsigned)xx < (unsigned)x.W && (unsigned)y < (unsigned)x.H && (unsigned)z < (unsigned)x.D)
+                    px[i] = *reinterpret_cast<const bf16x8 *>(x.p + (((size_t)z * x.H + y) * x.W + xx) * x.stride + c8 * 8);
             }
-            // X, three dx shifts: tasks (pair m, channel group g, shift t)
-            for (int task = threadIdx.x; task < 3 * 32 * (CI / 8); task += 256) {
-                const int m = task & 31, g = (task >> 5) % (CI / 8), t = task / (32 * (CI / 8));
-                const int va = 2 * m, wa = w0 + va + t - 1;
-                const bf16x8 a = load8(x, xrow, wa, 8 * g, zy && w0 + va < x.W);
-                const bf16x8 b = load8(x, xrow, wa + 1, 8 * g, zy && w0 + va + 1 < x.W);
+        };
+        auto store_x = [&](int slot) {
 #pragma unroll
-                for (int e = 0; e < 8; ++e) sx[(t * CI + 8 * g + e) * PITCH + m] = pack(a[e], b[e]);
+            for (int i = 0; i < NX; ++i) {
+                const int idx = threadIdx.x + 256 * i;
+                const int v = idx / (CI / 8), c8 = idx % (CI / 8);
+                if (idx < XT)
+                    *reinterpret_cast<bf16x8 *>(tile + slot * SLICE + ((c8 / 2) * XV + v) * 32 + (c8 & 1) * 16) = px[i];
             }
-            __syncthreads();
-            // K = 64 voxels = 2 MFMA steps of 32; lane reads voxels v0 .. v0+7
+        };
+        auto load_dy = [&](int d) {
 #pragma unroll
-            for (int ks = 0; ks < 2; ++ks) {
-                const int p0 = ks * 16 + (lane >> 4) * 4;          // first voxel pair
-#pragma unroll
-                for (int q = 0; q < PER_WAVE; ++q) {
-                    const int tile = wave + 4 * q;
-                    if (tile < TILES) {
-                        const int mt = tile / NT, nt = tile % NT;
-                        const bf16x8 a = *reinterpret_cast<const bf16x8 *>(&sdy[(mt * 16 + (lane & 15)) * PITCH + p0]);
-#pragma unroll
-                        for (int t = 0; t < 3; ++t) {
-                            const bf16x8 b =
-                                *reinterpret_cast<const bf16x8 *>(&sx[(t * CI + nt * 16 + (lane & 15)) * PITCH + p0]);
-                            acc[t][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[t][q], 0, 0, 0);
-                        }
-                    }
-                }
+            for (int i = 0; i < ND; ++i) {
+                const int idx = threadIdx.x + 256 * i;
+                const int v = idx / (COB / 8), c8 = idx % (COB / 8);
+                const int xx = w0 + v % 32, r = v / 32;
+                pd[i] = zero8();
+                if (idx < DT && r < rows && xx < dy.W)
+                    pd[i] = *reinterpret_cast<const bf16x8 *>(dy.p + (((size_t)d * dy.H + h0 + r) * dy.W + xx) * dy.stride +
+                                                              co0 + c8 * 8);
             }
-        }
-    }
-    // part layout: [chunk][27][CO][CI]; tap = tap9 * 3 + (dx + 1)
+        };
+        auto store_dy = [&]() {
 #pragma unroll
-    for (int q = 0; q < PER_WAVE; ++q) {
-        const int tile = wave + 4 * q;
-        if (tile >= TILES) continue;
-        const int mt = tile / NT, nt = tile % NT;
+            for (int i = 0; i < ND; ++i) {
+                const int idx = threadIdx.x + 256 * i;
+                const int v = idx / (COB / 8), c8 = idx % (COB / 8);
+                if (idx < DT) *reinterpret_cast<bf16x8 *>(sdy + ((c8 / 2) * DV + v) * 32 + (c8 & 1) * 16) = pd[i];
+            }
+        };
+
+        // voxels 16 j + 4 g + e past the end of the row: X[v - 1] of the first
+        // of them is a voxel of the row and must not meet the zero dY beyond
+        // it (an infinite X would give NaN); the other taps read zeros there
+        s16x4 keep[2], keep6[2];
 #pragma unroll
-        for (int t = 0; t < 3; ++t) {
-            float *dst = part + (((size_t)chunk * 27 + tap9 * 3 + t) * CO) * CI;
+        for (int j = 0; j < 2; ++j)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const int co = mt * 16 + (lane >> 4) * 4 + e;
-                const int ci = nt * 16 + (lane & 15);
-                dst[co * CI + ci] = acc[t][q][e];
+                keep[j][e] = 16 * j + 4 * (lane >> 4) + e < x.W - w0 ? -1 : 0;
+                keep6[j][e] = wave == 0 ? keep[j][e] : -1;
             }
+
+        // the taps of one slice, whose X slices d - 1, d, d + 1 are in slots
+        // b, b + 1, b + 2 (mod 3)
+        auto sum = [&](int b) {
+            const unsigned char *src[TAPS];
+#pragma unroll
+            for (int q = 0; q < TAPS; ++q) {
+                const int tap = wgrad_tap(wave, q);
+                int slot = b + tap / 9;
+                slot = slot >= 3 ? slot - 3 : slot;
+                src[q] = tile + slot * SLICE + ((tap / 3 % 3) * XW + tap % 3) * 32 + lane * 8;
+            }
+#pragma unroll 1
+            for (int r = 0; r < rows; ++r) {
+                bf16x8 a[MT];
+#pragma unroll
+                for (int m = 0; m < MT; ++m) {
+                    const unsigned char *p = sdy + (m * DV + r * 32) * 32 + lane * 8;
+                    a[m] = join(read_voxels4(p), read_voxels4(p + 512));
+                }
+#pragma unroll
+                for (int q = 0; q < TAPS; ++q)
+#pragma unroll
+                    for (int n = 0; n < NT; ++n) {
+                        const unsigned char *p = src[q] + (n * XV + r * XW) * 32;
+                        s16x4 lo = read_voxels4(p), hi = read_voxels4(p + 512);
+                        if (q == 0 || q == 3) {
+                            lo &= keep[0];
+                            hi &= keep[1];
+                        } else if (q == 6) {
+                            lo &= keep6[0];
+                            hi &= keep6[1];
+                        }
+                        const bf16x8 c = join(lo, hi);
+#pragma unroll
+                        for (int m = 0; m < MT; ++m)
+                            acc[q][m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[m], c, acc[q][m][n], 0, 0, 0);
+                    }
+            }
+        };
+
+        __syncthreads();                           // the unit before is done with the tiles
+        load_x(d0 - 1);
+        store_x(0);
+        load_x(d0);
+        store_x(1);
+        load_x(d0 + 1);
+        load_dy(d0);
+        int b = 0;
+        for (int d = d0; d < d1; ++d) {
+            __syncthreads();
+            store_x(b == 0 ? 2 : b - 1);
+            store_dy();
+            __syncthreads();
+            if (d + 1 < d1) {
+                load_x(d + 2);
+                load_dy(d + 1);
+            }
+            sum(b);
+            b = b == 2 ? 0 : b + 1;
         }
+    }
+#pragma unroll
+    for (int q = 0; q < TAPS; ++q) {
+        if (q == 6 && wave == 3) continue;
+        const int tap = wgrad_tap(wave, q);
+        float *dst = part + ((size_t)blockIdx.x * 27 + tap) * CO * CI;
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+            for (int n = 0; n < NT; ++n)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    dst[(co0 + m * 16 + (lane >> 4) * 4 + e) * CI + n * 16 + (lane & 15)] = acc[q][m][n][e];
     }
 }
 
 // out[i] = sum over chunks of part[chunk][i], i < n.  A block takes 64
-// consecutive i; wave w sums the chunks c = w, w + 4, ... in order and the
-// four wave sums are added in a fixed order (deterministic).
-__global__ void reduce_chunks(const float *__restrict__ part, int chunks, int64_t n, float *__restrict__ out)
+// consecutive i; wave w of its 16 sums the chunks c = w, w + 16, ... in order
+// and the wave sums are added in a fixed order (deterministic).
+__global__ void __launch_bounds__(1024) reduce_chunks(const float *__restrict__ part, int chunks, int64_t n,
+                                                      float *__restrict__ out)
 {
-    __shared__ float red[4][64];
+    __shared__ float red[16][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     for (int64_t base = (int64_t)blockIdx.x * 64; base < n; base += (int64_t)gridDim.x * 64) {
         const int64_t i = base + lane;
         float s = 0.0f;
-        if (i < n)
-            for (int c = wave; c < chunks; c += 4) s += part[(size_t)c * n + i];
+        if (i < n) {
+#pragma unroll 8
+            for (int c = wave; c < chunks; c += 16) s += part[(size_t)c * n + i];
+        }
         red[wave][lane] = s;
         __syncthreads();
-        if (wave == 0 && i < n) out[i] = ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
+        if (wave == 0 && i < n) {
+            float t = red[0][lane];
+#pragma unroll
+            for (int w = 1; w < 16; ++w) t += red[w][lane];
+            out[i] = t;
+        }
         __syncthreads();
     }
 }
@@ -764,6 +875,13 @@ bool valid(const cvp_nn_tensor *t)
 
 cvp_status st(hipError_t e) { return e == hipSuccess ? CVP_OK : CVP_E_DEVICE; }
 
+// Bounds of the weight gradient's partial sums: two workgroups per CU, and 57
+// MB.  Measured with the reduction, microseconds at (16 -> 16, 64 x 72 x 88),
+// (32 -> 16, the same) and (64 -> 32, 48 x 50 x 66): 25, 42, 58; with at most
+// 256 chunks 34, 58, 58; with 28 MB 25, 42, 89; with 113 MB 25, 42, 71.
+constexpr int64_t kWgradChunks = 512;
+constexpr int64_t kWgradFloats = int64_t(2) * 64 * 64 * 27 * 64;
+
 int grid_for(int64_t n) { return (int)((n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096); }
 
 // The LDS-tiled convolutions take more than the default 64 KB of dynamic LDS
@@ -843,12 +961,21 @@ cvp_status cvp_nn_conv3d(const cvp_nn_tensor *in, const void *weight, const floa
     return st(hipGetLastError());
 }
 
+// Partial sums of the weight gradient that fill the GPU.
+static int64_t wgrad_chunks_wanted(int64_t n)
+{
+    return std::max<int64_t>(1, std::min<int64_t>(kWgradChunks, kWgradFloats / n));
+}
+
+// the smallest workspace taken: one partial sum per 64 rows
+static int64_t wgrad_chunks_least(const cvp_nn_tensor *x) { return ((int64_t)x->d * x->h + 63) / 64; }
+
 cvp_status cvp_nn_wgrad_workspace(const cvp_nn_tensor *x, const cvp_nn_tensor *dy, int64_t *floats)
 {
     if (!x || !dy || !floats) return CVP_E_INVALID;
-    const int rows = x->d * x->h;
-    const int chunks = (rows + 63) / 64;
-    *floats = (int64_t)chunks * 27 * dy->channels * x->channels;
+    const int64_t n = (int64_t)27 * dy->channels * x->channels;
+    const int64_t least = wgrad_chunks_least(x);
+    *floats = (n > 0 ? std::max(least, wgrad_chunks_wanted(n)) : least) * n;
     return CVP_OK;
 }
 
@@ -856,15 +983,40 @@ cvp_status cvp_nn_conv3d_wgrad(const cvp_nn_tensor *x, const cvp_nn_tensor *dy, 
                                int64_t work_floats, void *stream)
 {
     if (!valid(x) || !valid(dy) || !dw || !work) return CVP_E_INVALID;
-    int64_t need = 0;
-    cvp_nn_wgrad_workspace(x, dy, &need);
-    if (work_floats < need) return CVP_E_INVALID;
-    const cvpnn::Act a = act(x), g = act(dy);
-    const int rows = x->d * x->h, rpc = 64, chunks = (rows + rpc - 1) / rpc;
-    const dim3 grid(chunks, 9), block(256);
-    hipStream_t s = (hipStream_t)stream;
     const int co = dy->channels, ci = x->channels;
-#define WG(CO_, CI_) hipLaunchKernelGGL((cvpnn::conv3d_wgrad_kernel<CO_, CI_>), grid, block, 0, s, a, g, rpc, work)
+    const int64_t n = (int64_t)27 * co * ci;
+    if (work_floats < wgrad_chunks_least(x) * n) return CVP_E_INVALID;
+    const cvpnn::Act a = act(x), g = act(dy);
+    hipStream_t s = (hipStream_t)stream;
+    // the run length whose longest chunk is shortest: a unit costs its slices
+    // and the two more that its first needs
+    const int64_t cap = std::min(work_floats / n, wgrad_chunks_wanted(n));
+    const int ty = ci == 16 ? cvpnn::wgrad_rows<16>() : ci == 32 ? cvpnn::wgrad_rows<32>() : cvpnn::wgrad_rows<64>();
+    cvpnn::WgradPlan p;
+    p.ytiles = (x->h + ty - 1) / ty;
+    p.segs = (x->w + 31) / 32;
+    const int64_t columns = (int64_t)p.ytiles * p.segs;
+    if (columns * x->d > INT32_MAX / 2) return CVP_E_UNSUPPORTED;
+    int64_t best = INT64_MAX;
+    for (int run = 1; run <= x->d; ++run) {
+        const int64_t units = columns * ((x->d + run - 1) / run), chunks = std::min(cap, units);
+        const int64_t cost = (units + chunks - 1) / chunks * (run + 2);
+        if (cost < best) {
+            best = cost;
+            p.run = run;
+            p.units = (int)units;
+            p.chunks = (int)chunks;
+        }
+    }
+#define WG(CO_, CI_)                                                                                            \
+    do {                                                                                                        \
+        static const hipError_t ready = hipFuncSetAttribute(                                                    \
+            reinterpret_cast<const void *>(cvpnn::conv3d_wgrad_kernel<CO_, CI_>),                               \
+            hipFuncAttributeMaxDynamicSharedMemorySize, cvpnn::wgrad_lds_bytes<CO_, CI_>());                    \
+        if (ready != hipSuccess) return st(ready);                                                              \
+        hipLaunchKernelGGL((cvpnn::conv3d_wgrad_kernel<CO_, CI_>), dim3(p.chunks, CO_ > 32 ? CO_ / 32 : 1),     \
+                           dim3(256), (cvpnn::wgrad_lds_bytes<CO_, CI_>()), s, a, g, p, work);                  \
+    } while (0)
     if (co == 16 && ci == 16) WG(16, 16);
     else if (co == 16 && ci == 32) WG(16, 32);
     else if (co == 32 && ci == 16) WG(32, 16);
@@ -875,8 +1027,7 @@ cvp_status cvp_nn_conv3d_wgrad(const cvp_nn_tensor *x, const cvp_nn_tensor *dy, 
     else if (co == 16 && ci == 64) WG(16, 64);
     else return CVP_E_UNSUPPORTED;
 #undef WG
-    const int64_t n = (int64_t)27 * co * ci;
-    hipLaunchKernelGGL(cvpnn::reduce_chunks, dim3(grid_for(4 * n)), dim3(256), 0, s, work, chunks, n, dw);
+    hipLaunchKernelGGL(cvpnn::reduce_chunks, dim3(grid_for(4 * n)), dim3(1024), 0, s, work, p.chunks, n, dw);
     return st(hipGetLastError());
 }
 
@@ -889,7 +1040,7 @@ cvp_status cvp_nn_channel_sum(const cvp_nn_tensor *a, float *out, float *work, i
     if (work_floats < (int64_t)chunks * a->channels) return CVP_E_INVALID;
     hipStream_t s = (hipStream_t)stream;
     hipLaunchKernelGGL(cvpnn::channel_sum_partials, dim3(chunks), dim3(256), 0, s, act(a), rpc, work);
-    hipLaunchKernelGGL(cvpnn::reduce_chunks, dim3(1), dim3(256), 0, s, work, chunks, (int64_t)a->channels, out);
+    hipLaunchKernelGGL(cvpnn::reduce_chunks, dim3(1), dim3(1024), 0, s, work, chunks, (int64_t)a->channels, out);
     return st(hipGetLastError());
 }
 
@@ -989,7 +1140,7 @@ cvp_status cvp_nn_head_bwd(const cvp_nn_tensor *h, const float *w, const float *
     if (work_floats < (int64_t)blocks * 17) return CVP_E_INVALID;
     hipStream_t s = (hipStream_t)stream;
     hipLaunchKernelGGL(cvpnn::head_bwd, dim3(blocks), dim3(256), 0, s, act(h), w, g, 1.0f / scale, act(dh), per, work);
-    hipLaunchKernelGGL(cvpnn::reduce_chunks, dim3(1), dim3(256), 0, s, work, blocks, (int64_t)17, dwb);
+    hipLaunchKernelGGL(cvpnn::reduce_chunks, dim3(1), dim3(1024), 0, s, work, blocks, (int64_t)17, dwb);
     return st(hipGetLastError());
 }
 
