@@ -24,6 +24,7 @@
 namespace cvpnn {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
+typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
 struct Act {             // a channels-last BF16 tensor (or channel slice)
@@ -119,194 +120,215 @@ conv3d_kernel(const Act in, const __bf16 *__restrict__ wt, const float *__restri
     }
 }
 
-// The same convolution with the input channel count CI a compile-time power
-// of two (16, 32 or 64), for volumes whose element count fits 32 bits: a
-// lane's tap and channel follow from shifts, the tap's offsets from
-// divisions by constants, and the addresses from 32-bit voxel indices.  The
-// arithmetic (k order, MFMA sequence, epilogue) is that of conv3d_kernel, so
-// the results are the same bits.
-template <int CO, int CI>
-__global__ void __launch_bounds__(256)
-conv3d_kernel_c(const Act in, const __bf16 *__restrict__ wt, const float *__restrict__ bias, Act out, int relu,
-                int flip)
+// The same convolution for 16, 32 or 64 input channels and volumes whose
+// element count fits 32 bits.  A workgroup marches tiles of up to 8 x 32
+// voxels along d: the LDS holds three slices of the input with their halo
+// (zeros outside the volume), each step loads one new slice while the last is
+// computed, and the weights of 16 NT output channels stay in a wave's
+// registers for the whole march, so the inner loop is LDS reads at constant
+// offsets and MFMAs.  A wave computes two rows (four tiles of 16 voxels) at a
+// time; with more than 16 NT output channels the waves split the channels and
+// then the rows.  The weights are the first MFMA operand, which puts four
+// consecutive output channels of a voxel in a lane: one 8-byte store.  Per
+// element the k order and the MFMA sequence are those of conv3d_kernel: the
+// results are the same bits.  The LDS bandwidth (one fragment per NT MFMAs)
+// bounds the inner loop with 64 input channels, with 16 output channels memory
+// nearly does: 16 -> 16, 32 -> 16 at 128^3, 64 -> 32 at 64^3 and 64 -> 64 at
+// 32^3 take 43, 71, 44 and 19 us; with a workgroup per tile of 4 x 64 voxels,
+// all three slices staged by each and the weights fetched at each k step, 85,
+// 184, 141 and 35 us.  (Sharing the fragments between four output rows halves
+// the LDS reads, but the shorter chains of independent MFMAs and the registers
+// cost more: 66, 51 and 20 us for the last three.)
+constexpr int kMarchRows = 8, kMarchX = 34;
+constexpr unsigned kOutside = 0xFFFFFF00u;      // beyond a buffer of at most kMarchElems elements, 255 bytes further too
+constexpr int64_t kMarchElems = (int64_t(1) << 31) - 256;
+
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+template <int CI>
+constexpr int march_lds_bytes() { return 3 * (kMarchRows + 2) * kMarchX * CI * 2; }
+
+struct MarchPlan {
+    int units;           // tile columns x runs of slices
+    int run;             // slices per unit
+    int rows;            // rows per tile: 2, 4 or 8
+    int ytiles, segs;    // tiles along y and x
+};
+
+template <int CO, int CI, int NT, bool FLIP>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CI * NT == 16 ? 3 : CI * NT == 32 ? 2 : 1)))
+conv3d_march_kernel(const Act in, const __bf16 *__restrict__ wt, const float *__restrict__ bias, const Act out, int relu,
+                    const MarchPlan P)
 {
-    constexpr int NT = CO / 16;
     constexpr int KSTEPS = (27 * CI + 31) / 32;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int segs = (in.W + 63) / 64;
-    const int row = blockIdx.x * 4 + wave;           // (d, h, segment)
-    if (row >= in.D * in.H * segs) return;
-    const int seg = row % segs;
-    const int dh = row / segs;
-    const int d = dh / in.H, h = dh % in.H;
-    const int w0 = seg * 64;
-
-    f32x4 acc[4][NT];
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int n = 0; n < NT; ++n) acc[r][n] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    const int i16 = lane & 15;
-    const int kg = lane >> 4;        // which group of 8 k within the 32
-#pragma unroll 2
-    for (int ks = 0; ks < KSTEPS; ++ks) {
-        const int k = ks * 32 + kg * 8;
-        const int tap = k / CI;
-        const int ci = k % CI;
-        const bool tv = tap < 27;
-        const int tp = flip ? 26 - tap : tap;
-        const int dz = tp / 9 - 1, dy = (tp / 3) % 3 - 1, dx = tp % 3 - 1;
-        const int z = d + dz, y = h + dy;
-        const bool zy = tv && (unsigned)z < (unsigned)in.D && (unsigned)y < (unsigned)in.H;
-        const int base = (z * in.H + y) * in.W + w0 + i16 + dx;   // voxel index of row tile 0
-        bf16x8 a[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int x = w0 + r * 16 + i16 + dx;
-            if (zy && (unsigned)x < (unsigned)in.W)
-                a[r] = *reinterpret_cast<const bf16x8 *>(in.p + (base + r * 16) * in.stride + ci);
-            else
-                a[r] = zero8();
-        }
-#pragma unroll
-        for (int n = 0; n < NT; ++n) {
-            const int co = n * 16 + i16;
-            bf16x8 b = tv ? *reinterpret_cast<const bf16x8 *>(wt + (tap * CO + co) * CI + ci) : zero8();
-#pragma unroll
-            for (int r = 0; r < 4; ++r) acc[r][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[r], b, acc[r][n], 0, 0, 0);
-        }
-    }
-#pragma unroll
-    for (int n = 0; n < NT; ++n) {
-        const int co = n * 16 + i16;
-        const float bv = bias ? bias[co] : 0.0f;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int x = w0 + r * 16 + (lane >> 4) * 4 + e;
-                if (x < out.W) {
-                    float v = acc[r][n][e] + bv;
-                    if (relu) v = fmaxf(v, 0.0f);
-                    out.p[((d * out.H + h) * out.W + x) * out.stride + co] = (__bf16)v;
-                }
-            }
-        }
-    }
-}
-
-// The same convolution with the workgroup's input tile staged in LDS: a
-// workgroup computes 16 RX voxels (RX = 4 or 2 row tiles per wave) of 4
-// consecutive rows h0..h0+3 of slice d (one row per wave) and first copies the
-// (16 RX + 2) x 6 x 3 input voxels those outputs read (zeros outside the
-// volume) into LDS, so each of the 27
-// taps' A fragments is an LDS read instead of a gather from global memory
-// (every input voxel was fetched 27 times through L1).  The k order, MFMA
-// sequence and epilogue are those of conv3d_kernel: the results are the same
-// bits.  RX = 4 with 16 or 32 input channels (38 or 76 KB of LDS), RX = 2
-// with 64 (78 KB).
-constexpr int kTileY = 6, kTileZ = 3;
-
-template <int CI, int RX>
-constexpr int conv_tile_bytes() { return kTileZ * kTileY * (RX * 16 + 2) * CI * 2; }
-
-// LDS holds 4 (16 input channels) or 2 (32) workgroups per CU: the register
-// budget of that occupancy lets the scheduler keep more fragments in flight.
-template <int CO, int CI, int RX>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(conv_tile_bytes<CI, RX>() <= 40960 ? 4 : 2)))
-conv3d_lds_kernel(const Act in, const __bf16 *__restrict__ wt, const float *__restrict__ bias, Act out, int relu,
-                  int flip)
-{
-    constexpr int NT = CO / 16;
-    constexpr int KSTEPS = (27 * CI + 31) / 32;
-    constexpr int C8 = CI / 8;                       // 16-byte chunks per voxel
+    constexpr int WN = CO / (16 * NT), WR = 4 / WN;        // waves over channels and over rows
+    constexpr int C8 = CI / 8;
+    constexpr int XV = (kMarchRows + 2) * kMarchX;         // voxels of a staged slice
+    constexpr int SLICE = XV * CI * 2;
+    constexpr int NX = (XV * C8 + 255) / 256;
     extern __shared__ __align__(16) unsigned char tile[];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    constexpr int kTileX = RX * 16 + 2;
-    const int segs = (in.W + RX * 16 - 1) / (RX * 16), quads = (in.H + 3) / 4;
-    int blk = blockIdx.x;
-    const int seg = blk % segs;
-    blk /= segs;
-    const int h0 = (blk % quads) * 4;
-    const int d = blk / quads;
-    const int w0 = seg * RX * 16;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int i16 = lane & 15, kg = lane >> 4;
+    const int cow = wave % WN * NT * 16;                   // first output channel of this wave
 
-    // stage the input tile, voxel v = (zz, yy, xx) = (d - 1 + zz, h0 - 1 + yy,
-    // w0 - 1 + xx), as [8-channel chunk][voxel][16 bytes]: the 16 lanes of a
-    // fragment read consecutive 16-byte slots (no LDS bank conflicts)
-    constexpr int NV = kTileZ * kTileY * kTileX;
-    constexpr int NCH = NV * C8;
-    for (int idx = threadIdx.x; idx < NCH; idx += 256) {
-        const int c8 = idx / NV, v = idx % NV;
-        const int xx = v % kTileX, t = v / kTileX;
-        const int yy = t % kTileY, zz = t / kTileY;
-        const int x = w0 - 1 + xx, y = h0 - 1 + yy, z = d - 1 + zz;
-        bf16x8 val = zero8();
-        if ((unsigned)x < (unsigned)in.W && (unsigned)y < (unsigned)in.H && (unsigned)z < (unsigned)in.D)
-            val = *reinterpret_cast<const bf16x8 *>(in.p + ((z * in.H + y) * in.W + x) * in.stride + c8 * 8);
-        *reinterpret_cast<bf16x8 *>(tile + idx * 16) = val;
-    }
-    __syncthreads();
-    const int h = h0 + wave;
-    if (h >= in.H) return;                           // no barrier follows
-
-    f32x4 acc[RX][NT];
-#pragma unroll
-    for (int r = 0; r < RX; ++r)
-#pragma unroll
-        for (int n = 0; n < NT; ++n) acc[r][n] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    const int i16 = lane & 15;
-    const int kg = lane >> 4;        // which group of 8 k within the 32
-    // fragments of k step ks: A from the tile, B (weights) from global memory
-    auto load = [&](int ks, bf16x8 a[RX], bf16x8 b[NT]) {
-        const int k = ks * 32 + kg * 8;
-        const int tap = k / CI;
-        const int ci = k % CI;
-        const bool tv = tap < 27;
-        const int tp = flip ? 26 - tap : tap;
-        const int dz = tp / 9 - 1, dy = (tp / 3) % 3 - 1, dx = tp % 3 - 1;
-        // tile voxel of row tile 0: (dz + 1, wave + dy + 1, i16 + dx + 1)
-        const unsigned char *src =
-            tile + ((ci / 8) * NV + ((dz + 1) * kTileY + wave + dy + 1) * kTileX + i16 + dx + 1) * 16;
-#pragma unroll
-        for (int r = 0; r < RX; ++r) a[r] = tv ? *reinterpret_cast<const bf16x8 *>(src + r * 16 * 16) : zero8();
-#pragma unroll
-        for (int n = 0; n < NT; ++n)
-            b[n] = tv ? *reinterpret_cast<const bf16x8 *>(wt + (tap * CO + n * 16 + i16) * CI + ci) : zero8();
-    };
-    // the k loop unrolled, with the next step's fragments loaded before this
-    // step's MFMAs (two register sets)
-    bf16x8 fa[2][RX], fb[2][NT];
-    load(0, fa[0], fb[0]);
+    // weights of k step ks: k = 32 ks + 8 kg .. + 7 of channel cow + 16 n + i16
+    bf16x8 w[KSTEPS][NT];
 #pragma unroll
     for (int ks = 0; ks < KSTEPS; ++ks) {
-        const int c = ks & 1;
-        if (ks + 1 < KSTEPS) load(ks + 1, fa[c ^ 1], fb[c ^ 1]);
+        const int k = ks * 32 + kg * 8, tap = k / CI, ci = k % CI;
 #pragma unroll
         for (int n = 0; n < NT; ++n)
-#pragma unroll
-            for (int r = 0; r < RX; ++r)
-                acc[r][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[c][r], fb[c][n], acc[r][n], 0, 0, 0);
+            w[ks][n] = tap < 27 ? *reinterpret_cast<const bf16x8 *>(wt + (tap * CO + cow + 16 * n + i16) * CI + ci) : zero8();
     }
+    f32x4 bv[NT];
 #pragma unroll
-    for (int n = 0; n < NT; ++n) {
-        const int co = n * 16 + i16;
-        const float bv = bias ? bias[co] : 0.0f;
+    for (int n = 0; n < NT; ++n)
 #pragma unroll
-        for (int r = 0; r < RX; ++r) {
+        for (int e = 0; e < 4; ++e) bv[n][e] = bias ? bias[cow + 16 * n + 4 * kg + e] : 0.0f;
+
+    // Buffer accesses: an offset outside reads zeros and stores nothing, so
+    // the loads and stores need no branches (a branch makes the compiler wait
+    // for all of them at once).  The results of a pass are stored when the
+    // next begins: the wait for a slice's loads, in order of issue, would
+    // otherwise wait for the stores just issued as well.
+    const int nvox = in.D * in.H * in.W;
+    const __amdgpu_buffer_rsrc_t src_buf =
+        __builtin_amdgcn_make_buffer_rsrc(in.p, 0, (unsigned)((nvox - 1) * in.stride + CI) * 2u, 0x00027000);
+    const __amdgpu_buffer_rsrc_t dst_buf =
+        __builtin_amdgcn_make_buffer_rsrc(out.p, 0, (unsigned)((nvox - 1) * out.stride + CO) * 2u, 0x00027000);
+    u32x2 res[4][NT];
+    unsigned res_at[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int x = w0 + r * 16 + (lane >> 4) * 4 + e;
-                if (x < out.W) {
-                    float v = acc[r][n][e] + bv;
-                    if (relu) v = fmaxf(v, 0.0f);
-                    out.p[((d * out.H + h) * out.W + x) * out.stride + co] = (__bf16)v;
+    for (int t = 0; t < 4; ++t) {
+        res_at[t] = kOutside;
+#pragma unroll
+        for (int n = 0; n < NT; ++n) res[t][n] = u32x2{0, 0};
+    }
+    auto flush = [&] {
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int n = 0; n < NT; ++n)
+                __builtin_amdgcn_raw_buffer_store_b64(res[t][n], dst_buf, res_at[t], n * 32, 0);
+    };
+
+    for (int unit = blockIdx.x; unit < P.units; unit += gridDim.x) {
+        const int seg = unit % P.segs, ty = unit / P.segs % P.ytiles, run = unit / P.segs / P.ytiles;
+        const int w0 = seg * 32, h0 = ty * P.rows;
+        const int d0 = run * P.run, d1 = min(d0 + P.run, in.D);
+        const int rows = min(P.rows, in.H - h0);
+
+        // a slice: 16-byte slots [8-channel chunk][voxel], so that the 16
+        // lanes of a fragment read consecutive slots
+        u32x4 px[NX];
+        unsigned at[NX];                                   // of the thread's slots in slice 0
+#pragma unroll
+        for (int i = 0; i < NX; ++i) {
+            const int idx = threadIdx.x + 256 * i;
+            const int v = idx / C8, c8 = idx % C8;
+            const int r = v / kMarchX, x = w0 - 1 + v % kMarchX, y = h0 - 1 + r;
+            const bool ok = r < P.rows + 2 && (unsigned)x < (unsigned)in.W && (unsigned)y < (unsigned)in.H;
+            at[i] = ok ? (unsigned)((y * in.W + x) * in.stride + c8 * 8) * 2u : kOutside;
+        }
+        auto load = [&](int z) {
+            const unsigned zo = (unsigned)(z * in.H * in.W) * (unsigned)in.stride * 2u;
+#pragma unroll
+            for (int i = 0; i < NX; ++i)
+                px[i] = __builtin_amdgcn_raw_buffer_load_b128(
+                    src_buf, (unsigned)z < (unsigned)in.D && at[i] != kOutside ? at[i] + zo : kOutside, 0, 0);
+        };
+        auto store = [&](int slot) {
+#pragma unroll
+            for (int i = 0; i < NX; ++i) {
+                const int idx = threadIdx.x + 256 * i;
+                if (idx < XV * C8)
+                    *reinterpret_cast<u32x4 *>(tile + slot * SLICE + (idx % C8 * XV + idx / C8) * 16) = px[i];
+            }
+        };
+
+        __syncthreads();                                   // the unit before is done with the tiles
+        load(d0 - 1);
+        store(0);
+        load(d0);
+        store(1);
+        load(d0 + 1);
+        int b = 0;                                         // slot of slice d - 1
+        for (int d = d0; d < d1; ++d) {
+            __syncthreads();
+            store(b == 0 ? 2 : b - 1);
+            __syncthreads();
+            if (d + 1 < d1) load(d + 2);
+
+            // lane's offsets of the three slices; with 16 input channels two
+            // taps share a k step and the offset is that of the lane's tap
+            int slot[3];
+#pragma unroll
+            for (int z = 0; z < 3; ++z) slot[z] = (b + z >= 3 ? b + z - 3 : b + z) * SLICE;
+            constexpr int NO = CI == 16 ? KSTEPS : 3;
+            int off[NO];
+#pragma unroll
+            for (int o = 0; o < NO; ++o) {
+                if (CI == 16) {
+                    const int t0 = FLIP ? 26 - 2 * o : 2 * o, t1 = o == 13 ? t0 : FLIP ? t0 - 1 : t0 + 1;
+                    const int o0 = slot[t0 / 9] + (t0 / 3 % 3 * kMarchX + t0 % 3) * 16;
+                    const int o1 = slot[t1 / 9] + (t1 / 3 % 3 * kMarchX + t1 % 3) * 16;
+                    off[o] = (kg & 2 ? o1 : o0) + ((kg & 1) * XV + i16) * 16;
+                } else {
+                    off[o] = slot[o] + (kg * XV + i16) * 16;
                 }
             }
+            for (int r = wave / WN * 2; r < rows; r += 2 * WR) {
+                flush();
+                f32x4 acc[4][NT];
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+#pragma unroll
+                    for (int n = 0; n < NT; ++n) acc[t][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+                const unsigned char *row = tile + r * kMarchX * 16;
+#pragma unroll
+                for (int ks = 0; ks < KSTEPS; ++ks) {
+                    const unsigned char *src;
+                    if (CI == 16) {
+                        src = row + off[ks];
+                    } else {
+                        const int tap = ks * 32 / CI, tp = FLIP ? 26 - tap : tap;
+                        src = row + off[tp / 9] + (tp / 3 % 3 * kMarchX + tp % 3) * 16 + ks * 32 % CI / 8 * XV * 16;
+                    }
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {          // tile t: row t / 2, voxels 16 (t % 2) ..
+                        bf16x8 a = *reinterpret_cast<const bf16x8 *>(src + (t / 2 * kMarchX + t % 2 * 16) * 16);
+                        if (CI == 16 && ks == KSTEPS - 1 && (kg & 2)) a = zero8();     // no 28th tap
+#pragma unroll
+                        for (int n = 0; n < NT; ++n)
+                            acc[t][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[ks][n], a, acc[t][n], 0, 0, 0);
+                    }
+                }
+                // lane: voxel i16 of the tile, channels 4 kg .. + 3
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const int x = w0 + t % 2 * 16 + i16, y = h0 + r + t / 2;
+                    res_at[t] = x < out.W && r + t / 2 < rows
+                                    ? (unsigned)(((d * out.H + y) * out.W + x) * out.stride + cow + 4 * kg) * 2u
+                                    : kOutside;
+#pragma unroll
+                    for (int n = 0; n < NT; ++n) {
+                        bf16x4 o;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            float v = acc[t][n][e] + bv[n][e];
+                            if (relu) v = fmaxf(v, 0.0f);
+                            o[e] = (__bf16)v;
+                        }
+                        res[t][n] = __builtin_bit_cast(u32x2, o);
+                    }
+                }
+            }
+            b = b == 2 ? 0 : b + 1;
         }
     }
+    flush();
 }
 
 // Backward-weight partials: part[chunk][tap][co][ci] = sum over the chunk's
@@ -884,24 +906,55 @@ constexpr int64_t kWgradFloats = int64_t(2) * 64 * 64 * 27 * 64;
 
 int grid_for(int64_t n) { return (int)((n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096); }
 
-// The LDS-tiled convolutions take more than the default 64 KB of dynamic LDS
-// (32 or 64 input channels: 76 or 78 KB); allowed once per process.
-hipError_t conv_lds_setup()
+// A convolution marched along d: the tile height and the run length whose
+// busiest workgroup is done first.  A unit takes the weights' load, its slices
+// and the two more that its first needs; a slice takes its matrix work or its
+// loads, whichever is longer (cycles of a CU).
+template <int CO, int CI, int NT>
+cvpnn::MarchPlan march_plan(const cvpnn::Act &a, int &blocks)
 {
-    static hipError_t done = [] {
-        hipError_t e = hipSuccess;
-#define ALLOW(CO_, CI_, RX_)                                                                                 \
-        if (e == hipSuccess)                                                                                 \
-            e = hipFuncSetAttribute(reinterpret_cast<const void *>(cvpnn::conv3d_lds_kernel<CO_, CI_, RX_>), \
-                                    hipFuncAttributeMaxDynamicSharedMemorySize,                              \
-                                    cvpnn::conv_tile_bytes<CI_, RX_>());
-        ALLOW(16, 16, 4) ALLOW(16, 32, 4) ALLOW(32, 16, 4) ALLOW(32, 32, 4) ALLOW(64, 32, 4)
-        ALLOW(16, 16, 2) ALLOW(16, 32, 2) ALLOW(16, 64, 2) ALLOW(32, 16, 2) ALLOW(32, 32, 2) ALLOW(32, 64, 2)
-        ALLOW(64, 32, 2) ALLOW(64, 64, 2)
-#undef ALLOW
-        return e;
-    }();
-    return done;
+    constexpr int per_cu = CI * NT == 16 ? 3 : CI * NT == 32 ? 2 : 1;
+    constexpr int steps = (27 * CI + 31) / 32, WR = 4 / (CO / (16 * NT));
+    cvpnn::MarchPlan best{};
+    double least = 0.0;
+    for (int rows = 2; rows <= cvpnn::kMarchRows; rows *= 2) {
+        cvpnn::MarchPlan p;
+        p.rows = rows;
+        p.ytiles = (a.H + rows - 1) / rows;
+        p.segs = (a.W + 31) / 32;
+        const int passes = (rows / 2 + WR - 1) / WR;
+        const double work = passes * steps * 4 * NT * 16.0 * (NT == 1 ? 2 : 1) * (per_cu > 1 ? per_cu / 1.5 : 1.0) + 600;
+        const double load = (rows + 2) * 34.0 * CI * 2 / 24 * per_cu + 800;
+        for (int run = 1; run <= a.D; ++run) {
+            const int64_t units = (int64_t)p.ytiles * p.segs * ((a.D + run - 1) / run);
+            if (units > INT32_MAX / 2) continue;
+            const int64_t slots = std::min<int64_t>(units, 256 * per_cu);
+            const double cost = (double)((units + slots - 1) / slots) * (run * std::max(work, load) + 2 * load) +
+                                steps * NT * 16.0 * 4 * per_cu;
+            if (least == 0.0 || cost < least) {
+                least = cost;
+                p.run = run;
+                p.units = (int)units;
+                best = p;
+                blocks = (int)slots;
+            }
+        }
+    }
+    return best;
+}
+
+template <int CO, int CI, int NT, bool FLIP>
+hipError_t launch_march(const cvpnn::Act &a, const __bf16 *w, const float *bias, const cvpnn::Act &o, int relu, hipStream_t s)
+{
+    static const hipError_t ready =
+        hipFuncSetAttribute(reinterpret_cast<const void *>(cvpnn::conv3d_march_kernel<CO, CI, NT, FLIP>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, cvpnn::march_lds_bytes<CI>());
+    if (ready != hipSuccess) return ready;
+    int blocks = 0;
+    const cvpnn::MarchPlan p = march_plan<CO, CI, NT>(a, blocks);
+    hipLaunchKernelGGL((cvpnn::conv3d_march_kernel<CO, CI, NT, FLIP>), dim3(blocks), dim3(256),
+                       (cvpnn::march_lds_bytes<CI>()), s, a, w, bias, o, relu, p);
+    return hipGetLastError();
 }
 
 }  // namespace
@@ -918,46 +971,26 @@ cvp_status cvp_nn_conv3d(const cvp_nn_tensor *in, const void *weight, const floa
     const dim3 grid((rows + 3) / 4), block(256);
     hipStream_t s = (hipStream_t)stream;
     const __bf16 *w = reinterpret_cast<const __bf16 *>(weight);
-    // channel counts 16, 32, 64 and 32-bit element offsets: the specialised kernel
+    // channel counts 16, 32, 64 and 32-bit byte offsets: the marching kernel,
+    // with the weights of 32 output channels in a wave where they fit its
+    // registers (with 64 input channels 432 of 512 would be taken)
     const int64_t elems = (int64_t)in->d * in->h * in->w * std::max(in->stride, out->stride);
     const int ci = in->channels, co = out->channels;
-    const bool spec = elems < (int64_t(1) << 31) && (ci == 16 || ci == 32 || ci == 64);
-#define CONVC(CO_, CI_) hipLaunchKernelGGL((cvpnn::conv3d_kernel_c<CO_, CI_>), grid, block, 0, s, a, w, bias, o, relu, flip)
-    // the LDS-tiled kernel (4 rows of a slice per workgroup): 64-voxel rows
-    // with 16 or 32 input channels, 32-voxel rows with 64 (a 78 KB tile; at
-    // 32^3 with 32 channels the 64-voxel rows were faster, 35 against 49 us)
-    const int rx = ci == 64 ? 2 : 4;
-    const dim3 lgrid(in->d * ((in->h + 3) / 4) * ((in->w + rx * 16 - 1) / (rx * 16)));
-#define CONVL(CO_, CI_, RX_) hipLaunchKernelGGL((cvpnn::conv3d_lds_kernel<CO_, CI_, RX_>), lgrid, block, \
-                                                (cvpnn::conv_tile_bytes<CI_, RX_>()), s, a, w, bias, o, relu, flip)
-    if (spec) {
-        const hipError_t e = conv_lds_setup();
-        if (e != hipSuccess) return st(e);
+    const bool spec = elems <= cvpnn::kMarchElems && (ci == 16 || ci == 32 || ci == 64);
+#define MARCH(CO_, CI_, NT_)                                                                \
+    if (spec && co == CO_ && ci == CI_)                                                     \
+        return st(flip ? launch_march<CO_, CI_, NT_, true>(a, w, bias, o, relu, s)          \
+                       : launch_march<CO_, CI_, NT_, false>(a, w, bias, o, relu, s));
+    MARCH(16, 16, 1) MARCH(16, 32, 1) MARCH(16, 64, 1)
+    MARCH(32, 16, 2) MARCH(32, 32, 2) MARCH(32, 64, 1)
+    MARCH(64, 16, 2) MARCH(64, 32, 2) MARCH(64, 64, 1)
+#undef MARCH
+    switch (co) {
+    case 16: hipLaunchKernelGGL(cvpnn::conv3d_kernel<16>, grid, block, 0, s, a, w, bias, o, relu, flip); break;
+    case 32: hipLaunchKernelGGL(cvpnn::conv3d_kernel<32>, grid, block, 0, s, a, w, bias, o, relu, flip); break;
+    case 64: hipLaunchKernelGGL(cvpnn::conv3d_kernel<64>, grid, block, 0, s, a, w, bias, o, relu, flip); break;
+    default: return CVP_E_UNSUPPORTED;
     }
-    if (spec && co == 64 && ci == 16) CONVC(64, 16);   // the LDS kernel's registers would spill
-    else if (spec && rx == 4 && co == 16 && ci == 16) CONVL(16, 16, 4);
-    else if (spec && rx == 4 && co == 16 && ci == 32) CONVL(16, 32, 4);
-    else if (spec && rx == 4 && co == 32 && ci == 16) CONVL(32, 16, 4);
-    else if (spec && rx == 4 && co == 32 && ci == 32) CONVL(32, 32, 4);
-    else if (spec && rx == 4 && co == 64 && ci == 32) CONVL(64, 32, 4);
-    else if (spec && co == 16 && ci == 16) CONVL(16, 16, 2);
-    else if (spec && co == 16 && ci == 32) CONVL(16, 32, 2);
-    else if (spec && co == 16 && ci == 64) CONVL(16, 64, 2);
-    else if (spec && co == 32 && ci == 16) CONVL(32, 16, 2);
-    else if (spec && co == 32 && ci == 32) CONVL(32, 32, 2);
-    else if (spec && co == 32 && ci == 64) CONVL(32, 64, 2);
-    else if (spec && co == 64 && ci == 32) CONVL(64, 32, 2);
-    else if (spec && co == 64 && ci == 64) CONVL(64, 64, 2);
-    else {
-        switch (co) {
-        case 16: hipLaunchKernelGGL(cvpnn::conv3d_kernel<16>, grid, block, 0, s, a, w, bias, o, relu, flip); break;
-        case 32: hipLaunchKernelGGL(cvpnn::conv3d_kernel<32>, grid, block, 0, s, a, w, bias, o, relu, flip); break;
-        case 64: hipLaunchKernelGGL(cvpnn::conv3d_kernel<64>, grid, block, 0, s, a, w, bias, o, relu, flip); break;
-        default: return CVP_E_UNSUPPORTED;
-        }
-    }
-#undef CONVC
-#undef CONVL
     return st(hipGetLastError());
 }
 

@@ -1,4 +1,4 @@
-"""Weight gradient of the 3x3x3 convolution: tile edges, channel pairs,
+"""The 3x3x3 convolution and its weight gradient: tile edges, channel pairs,
 workspace sizes.  The inputs are small whole numbers, whose products and sums
 FP32 holds exactly, so the results are compared for equality."""
 import ctypes
@@ -67,4 +67,45 @@ def test_infinite_input_at_the_row_end_meets_no_padding():
     bad = ~torch.isfinite(dw[12:15].cpu())          # dz = dy = 0, dx = -1, 0, 1
     want = torch.zeros_like(bad)
     want[1:, :, 3] = True                           # dY at 19 (dx = 0) and at 18 (dx = 1)
+    assert torch.equal(bad, want)
+
+
+@pytest.mark.parametrize("co", [16, 32, 64])
+@pytest.mark.parametrize("ci", [16, 32, 64])
+@pytest.mark.parametrize("shape", [(1, 1, 1), (3, 9, 16), (5, 17, 33), (2, 8, 66), (70, 5, 31)])
+@pytest.mark.parametrize("flip", [0, 1])
+def test_convolution_is_exact_for_whole_numbers(co, ci, shape, flip):
+    """Input and output are channel slices; the channels beside the output
+    keep their values."""
+    D, H, W = shape
+    x, w = ints(shape + (ci + 8,), 6), ints((27, co, ci), 7)
+    bias = None if flip else ints((co,), 8).float()
+    y = torch.full(shape + (co + 24,), 3.0, dtype=torch.bfloat16, device="cuda")
+    U._check(U.lib().cvp_nn_conv3d(ctypes.byref(U.desc(x, 8, ci)), U._p(w), U._p(bias), ctypes.byref(U.desc(y, 16, co)),
+                                   1 - flip, flip, U._s()))
+    xp = torch.zeros(D + 2, H + 2, W + 2, ci, dtype=torch.float64)
+    xp[1:-1, 1:-1, 1:-1] = x[..., 8:].double().cpu()
+    ref = torch.zeros(D, H, W, co, dtype=torch.float64)
+    for t in range(27):
+        m = 26 - t if flip else t
+        ref += xp[m // 9:m // 9 + D, m // 3 % 3:m // 3 % 3 + H, m % 3:m % 3 + W] @ w[t].double().cpu().t()
+    if not flip:
+        ref = (ref + bias.double().cpu()).clamp(min=0)
+    y = y.cpu()
+    assert torch.equal(y[..., 16:16 + co], ref.float().to(torch.bfloat16))
+    assert (y[..., :16] == 3).all() and (y[..., 16 + co:] == 3).all()
+
+
+@pytest.mark.parametrize("flip", [0, 1])
+def test_infinite_weight_and_input_stay_local(flip):
+    """16 input channels: the last k step holds one tap; an infinite voxel
+    reaches its 27 neighbours and no others."""
+    x = torch.ones((5, 6, 40, 16), dtype=torch.bfloat16, device="cuda")
+    x[2, 3, 20, 5] = float("inf")
+    w = torch.ones((27, 16, 16), dtype=torch.bfloat16, device="cuda")
+    y = torch.empty_like(x)
+    U._check(U.lib().cvp_nn_conv3d(ctypes.byref(U.desc(x)), U._p(w), None, ctypes.byref(U.desc(y)), 0, flip, U._s()))
+    bad = ~torch.isfinite(y.cpu())
+    want = torch.zeros_like(bad)
+    want[1:4, 2:5, 19:22] = True
     assert torch.equal(bad, want)
