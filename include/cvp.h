@@ -464,6 +464,23 @@ cvp_status cvp_nn_conv3d(const cvp_nn_tensor *in, const void *weight, const floa
 cvp_status cvp_nn_wgrad_workspace(const cvp_nn_tensor *x, const cvp_nn_tensor *dy, int64_t *floats);
 cvp_status cvp_nn_conv3d_wgrad(const cvp_nn_tensor *x, const cvp_nn_tensor *dy, float *dw, float *work,
                                int64_t work_floats, void *stream);
+/* The same with the bias gradient db[dy->channels] = sum of dY over voxels;
+ * the workspace holds dy->channels floats more for every 64 rows (d, h). */
+cvp_status cvp_nn_conv3d_wgrad_bias(const cvp_nn_tensor *x, const cvp_nn_tensor *dy, float *dw, float *db, float *work,
+                                    int64_t work_floats, void *stream);
+/* The backward passes below set the gradient they write to 0 where `keep`,
+ * the post-ReLU tensor it belongs to, is not positive: what the plain call
+ * followed by cvp_nn_relu_mask gives.  conv3d_bwd_masked is cvp_nn_conv3d with
+ * flip and no bias, avgpool2_bwd_add adds the pooling's gradient to g first,
+ * and the head masks with its own input h. */
+cvp_status cvp_nn_conv3d_bwd_masked(const cvp_nn_tensor *dy, const void *weight_t, const cvp_nn_tensor *keep,
+                                    const cvp_nn_tensor *dx, void *stream);
+cvp_status cvp_nn_avgpool2_bwd_add(const cvp_nn_tensor *dout, const cvp_nn_tensor *keep, const cvp_nn_tensor *g,
+                                   void *stream);
+cvp_status cvp_nn_upsample2_bwd_masked(const cvp_nn_tensor *dout, const cvp_nn_tensor *keep, const cvp_nn_tensor *din,
+                                       void *stream);
+cvp_status cvp_nn_head_bwd_masked(const cvp_nn_tensor *h, const float *w, const float *g, float scale,
+                                  const cvp_nn_tensor *dh, float *dwb, float *work, int64_t work_floats, void *stream);
 /* out[c] = sum_v a[v][c] (bias gradient); work >= ceil(d*h/16) * channels floats */
 cvp_status cvp_nn_channel_sum(const cvp_nn_tensor *a, float *out, float *work, int64_t work_floats,
                               void *stream);

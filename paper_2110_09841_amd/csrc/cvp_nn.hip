@@ -130,6 +130,7 @@ conv3d_kernel(const Act in, const __bf16 *__restrict__ wt, const float *__restri
 // time; with more than 16 NT output channels the waves split the channels and
 // then the rows.  The weights are the first MFMA operand, which puts four
 // consecutive output channels of a voxel in a lane: one 8-byte store.  Per
+// MASK: the result becomes 0 where `keep` (a post-ReLU output) is not positive.  Per
 // element the k order and the MFMA sequence are those of conv3d_kernel: the
 // results are the same bits.  The LDS bandwidth (one fragment per NT MFMAs)
 // bounds the inner loop with 64 input channels, with 16 output channels memory
@@ -156,10 +157,10 @@ struct MarchPlan {
     int ytiles, segs;    // tiles along y and x
 };
 
-template <int CO, int CI, int NT, bool FLIP>
+template <int CO, int CI, int NT, bool FLIP, bool MASK>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CI * NT == 16 ? 3 : CI * NT == 32 ? 2 : 1)))
-conv3d_march_kernel(const Act in, const __bf16 *__restrict__ wt, const float *__restrict__ bias, const Act out, int relu,
-                    const MarchPlan P)
+conv3d_march_kernel(const Act in, const __bf16 *__restrict__ wt, const float *__restrict__ bias, const Act out,
+                    const Act keep, int relu, const MarchPlan P)
 {
     constexpr int KSTEPS = (27 * CI + 31) / 32;
     constexpr int WN = CO / (16 * NT), WR = 4 / WN;        // waves over channels and over rows
@@ -198,6 +199,8 @@ conv3d_march_kernel(const Act in, const __bf16 *__restrict__ wt, const float *__
         __builtin_amdgcn_make_buffer_rsrc(in.p, 0, (unsigned)((nvox - 1) * in.stride + CI) * 2u, 0x00027000);
     const __amdgpu_buffer_rsrc_t dst_buf =
         __builtin_amdgcn_make_buffer_rsrc(out.p, 0, (unsigned)((nvox - 1) * out.stride + CO) * 2u, 0x00027000);
+    const __amdgpu_buffer_rsrc_t keep_buf = __builtin_amdgcn_make_buffer_rsrc(
+        MASK ? keep.p : out.p, 0, MASK ? (unsigned)((nvox - 1) * keep.stride + CO) * 2u : 0u, 0x00027000);
     u32x2 res[4][NT];
     unsigned res_at[4];
 #pragma unroll
@@ -281,6 +284,19 @@ conv3d_march_kernel(const Act in, const __bf16 *__restrict__ wt, const float *__
             }
             for (int r = wave / WN * 2; r < rows; r += 2 * WR) {
                 flush();
+                u32x2 kept[4][NT];                         // read ahead of the pass
+                if constexpr (MASK) {
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        const int x = w0 + t % 2 * 16 + i16, y = h0 + r + t / 2;
+                        const unsigned at = x < out.W && r + t / 2 < rows
+                                                ? (unsigned)(((d * out.H + y) * out.W + x) * keep.stride + cow + 4 * kg) * 2u
+                                                : kOutside;
+#pragma unroll
+                        for (int n = 0; n < NT; ++n)
+                            kept[t][n] = __builtin_amdgcn_raw_buffer_load_b64(keep_buf, at, n * 32, 0);
+                    }
+                }
                 f32x4 acc[4][NT];
 #pragma unroll
                 for (int t = 0; t < 4; ++t)
@@ -321,6 +337,12 @@ conv3d_march_kernel(const Act in, const __bf16 *__restrict__ wt, const float *__
                             if (relu) v = fmaxf(v, 0.0f);
                             o[e] = (__bf16)v;
                         }
+                        if constexpr (MASK) {
+                            const bf16x4 m = __builtin_bit_cast(bf16x4, kept[t][n]);
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                if (!((float)m[e] > 0.0f)) o[e] = (__bf16)0.0f;
+                        }
                         res[t][n] = __builtin_bit_cast(u32x2, o);
                     }
                 }
@@ -342,7 +364,8 @@ conv3d_march_kernel(const Act in, const __bf16 *__restrict__ wt, const float *__
 // channel, and with voxels 16 j + 4 g + e in element e of lane group g the 64
 // lanes of a read touch 512 consecutive bytes whatever the tap, so a shift by
 // a tap is an offset and no bank conflicts arise.  The 27 taps are split over
-// the waves (7, 7, 7, 6); 64 output channels are two workgroups.
+// the waves (7, 7, 7, 6); 64 output channels are two workgroups.  With `bias`
+// a partial sum ends with the CO sums of dY, added as it is staged.
 // With 16 output channels an X fragment feeds one MFMA and the LDS bandwidth
 // bounds the inner loop; with 64 input channels (one wave per SIMD, 480
 // registers) the latency of staging does.  With the reduction 25 us at 16 ->
@@ -387,7 +410,7 @@ __device__ __forceinline__ int wgrad_tap(int wave, int q)
 
 template <int CO, int CI>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((CO < 32 ? 1 : 2) * CI / 16 > 4 ? 1 : 2)))
-conv3d_wgrad_kernel(const Act x, const Act dy, const WgradPlan P, float *__restrict__ part)
+conv3d_wgrad_kernel(const Act x, const Act dy, const WgradPlan P, int bias, float *__restrict__ part)
 {
     constexpr int COB = CO < 32 ? CO : 32;         // output channels of this workgroup
     constexpr int MT = COB / 16, NT = CI / 16;
@@ -410,6 +433,10 @@ conv3d_wgrad_kernel(const Act x, const Act dy, const WgradPlan P, float *__restr
         for (int m = 0; m < MT; ++m)
 #pragma unroll
             for (int n = 0; n < NT; ++n) acc[q][m][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    float bsum[8];                                 // channels 8 (thread % (COB / 8)) ..
+#pragma unroll
+    for (int e = 0; e < 8; ++e) bsum[e] = 0.0f;
 
     for (int unit = blockIdx.x; unit < P.units; unit += P.chunks) {
         const int seg = unit % P.segs, ty = unit / P.segs % P.ytiles, run = unit / P.segs / P.ytiles;
@@ -456,6 +483,8 @@ conv3d_wgrad_kernel(const Act x, const Act dy, const WgradPlan P, float *__restr
                 const int idx = threadIdx.x + 256 * i;
                 const int v = idx / (COB / 8), c8 = idx % (COB / 8);
                 if (idx < DT) *reinterpret_cast<bf16x8 *>(sdy + ((c8 / 2) * DV + v) * 32 + (c8 & 1) * 16) = pd[i];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) bsum[e] += (float)pd[i][e];
             }
         };
 
@@ -532,11 +561,24 @@ conv3d_wgrad_kernel(const Act x, const Act dy, const WgradPlan P, float *__restr
             b = b == 2 ? 0 : b + 1;
         }
     }
+    const size_t stride = (size_t)27 * CO * CI + (bias ? CO : 0);
+    if (bias) {
+        __syncthreads();
+        float *red = reinterpret_cast<float *>(tile);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) red[threadIdx.x * 8 + e] = bsum[e];
+        __syncthreads();
+        if (threadIdx.x < COB) {
+            float t = 0.0f;
+            for (int k = threadIdx.x / 8; k < 256; k += COB / 8) t += red[k * 8 + threadIdx.x % 8];
+            part[blockIdx.x * stride + (size_t)27 * CO * CI + co0 + threadIdx.x] = t;
+        }
+    }
 #pragma unroll
     for (int q = 0; q < TAPS; ++q) {
         if (q == 6 && wave == 3) continue;
         const int tap = wgrad_tap(wave, q);
-        float *dst = part + ((size_t)blockIdx.x * 27 + tap) * CO * CI;
+        float *dst = part + blockIdx.x * stride + (size_t)tap * CO * CI;
 #pragma unroll
         for (int m = 0; m < MT; ++m)
 #pragma unroll
@@ -549,9 +591,10 @@ conv3d_wgrad_kernel(const Act x, const Act dy, const WgradPlan P, float *__restr
 
 // out[i] = sum over chunks of part[chunk][i], i < n.  A block takes 64
 // consecutive i; wave w of its 16 sums the chunks c = w, w + 16, ... in order
-// and the wave sums are added in a fixed order (deterministic).
+// and the wave sums are added in a fixed order (deterministic).  The sums from
+// index n1 on go to out2.
 __global__ void __launch_bounds__(1024) reduce_chunks(const float *__restrict__ part, int chunks, int64_t n,
-                                                      float *__restrict__ out)
+                                                      float *__restrict__ out, int64_t n1, float *__restrict__ out2)
 {
     __shared__ float red[16][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -568,7 +611,7 @@ __global__ void __launch_bounds__(1024) reduce_chunks(const float *__restrict__ 
             float t = red[0][lane];
 #pragma unroll
             for (int w = 1; w < 16; ++w) t += red[w][lane];
-            out[i] = t;
+            (i < n1 ? out[i] : out2[i - n1]) = t;
         }
         __syncthreads();
     }
@@ -628,6 +671,15 @@ __device__ __forceinline__ size_t voxel_at(const Act &t, int z, int y, int x)
     return (((size_t)z * t.H + y) * t.W + x) * t.stride;
 }
 
+// g where y > 0, else 0
+__device__ __forceinline__ bf16x8 mask8(bf16x8 g, const bf16x8 y)
+{
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+        if (!((float)y[e] > 0.0f)) g[e] = (__bf16)0.0f;
+    return g;
+}
+
 // dY *= (Y > 0) in place (ReLU backward; Y is the post-ReLU output)
 template <typename I>
 __global__ void relu_mask(Act dy, const Act y)
@@ -637,12 +689,9 @@ __global__ void relu_mask(Act dy, const Act y)
     for (I i = (I)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (I)gridDim.x * blockDim.x) {
         const I v = i / C8;
         const int c = (int)(i % C8) * 8;
-        bf16x8 g = *reinterpret_cast<const bf16x8 *>(dy.p + (size_t)v * dy.stride + c);
+        const bf16x8 g = *reinterpret_cast<const bf16x8 *>(dy.p + (size_t)v * dy.stride + c);
         const bf16x8 q = *reinterpret_cast<const bf16x8 *>(y.p + (size_t)v * y.stride + c);
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-            if (!((float)q[e] > 0.0f)) g[e] = (__bf16)0.0f;
-        *reinterpret_cast<bf16x8 *>(dy.p + (size_t)v * dy.stride + c) = g;
+        *reinterpret_cast<bf16x8 *>(dy.p + (size_t)v * dy.stride + c) = mask8(g, q);
     }
 }
 
@@ -689,6 +738,27 @@ __global__ void avgpool2_bwd(const Act dout, Act din)
     }
 }
 
+// Where a tensor feeds a pooling and a skip connection: g = (g + dout(parent)
+// / 8) where keep > 0, else 0; each addend and the sum rounded to BF16 as by
+// avgpool2_bwd and add_kernel.
+template <typename I>
+__global__ void avgpool2_bwd_add(const Act dout, const Act keep, Act g)
+{
+    const int C8 = g.C / 8;
+    const I n = (I)g.D * g.H * g.W * C8;
+    for (I i = (I)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (I)gridDim.x * blockDim.x) {
+        int c, x, y, z;
+        chunk_coords<I>(i, C8, g.W, g.H, c, x, y, z);
+        const bf16x8 p = *reinterpret_cast<const bf16x8 *>(dout.p + voxel_at(dout, z / 2, y / 2, x / 2) + c);
+        bf16x8 *const at = reinterpret_cast<bf16x8 *>(g.p + voxel_at(g, z, y, x) + c);
+        const bf16x8 q = *at;
+        bf16x8 o;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[e] = (__bf16)((float)q[e] + (float)(__bf16)(0.125f * (float)p[e]));
+        *at = mask8(o, *reinterpret_cast<const bf16x8 *>(keep.p + voxel_at(keep, z, y, x) + c));
+    }
+}
+
 // nearest 2x upsampling: out (2D,2H,2W) from in
 template <typename I>
 __global__ void upsample2(const Act in, Act out)
@@ -703,9 +773,10 @@ __global__ void upsample2(const Act in, Act out)
     }
 }
 
-// backward of upsample2: din = sum of the 8 children of dout
+// backward of upsample2: din = sum of the 8 children of dout, 0 where keep (if
+// given) is not positive
 template <typename I>
-__global__ void upsample2_bwd(const Act dout, Act din)
+__global__ void upsample2_bwd(const Act dout, Act din, const Act keep)
 {
     const int C8 = din.C / 8;
     const I n = (I)din.D * din.H * din.W * C8;
@@ -725,6 +796,7 @@ __global__ void upsample2_bwd(const Act dout, Act din)
         bf16x8 o;
 #pragma unroll
         for (int e = 0; e < 8; ++e) o[e] = (__bf16)s[e];
+        if (keep.p) o = mask8(o, *reinterpret_cast<const bf16x8 *>(keep.p + voxel_at(keep, z, y, x) + c));
         *reinterpret_cast<bf16x8 *>(din.p + voxel_at(din, z, y, x) + c) = o;
     }
 }
@@ -779,9 +851,10 @@ __global__ void head_fwd(const Act h, const float *__restrict__ w, const float *
     }
 }
 
-// Head backward: dh[v][c] = w[c] g[v] / scale (BF16), partial sums for dw, db
+// Head backward: dh[v][c] = w[c] g[v] / scale (BF16), with `relu` 0 where
+// h[v][c] is not positive; partial sums for dw, db
 __global__ void head_bwd(const Act h, const float *__restrict__ w, const float *__restrict__ g,
-                         float inv_scale, Act dh, int64_t per_block, float *__restrict__ part)
+                         float inv_scale, Act dh, int64_t per_block, int relu, float *__restrict__ part)
 {
     __shared__ float sh[17][256];
     const int64_t n = (int64_t)h.D * h.H * h.W;
@@ -801,15 +874,23 @@ __global__ void head_bwd(const Act h, const float *__restrict__ w, const float *
                 acc[c8 + e] = fmaf((float)q[e], gv, acc[c8 + e]);
                 o[e] = (__bf16)(w[c8 + e] * gv);
             }
-            *reinterpret_cast<bf16x8 *>(dh.p + v * dh.stride + c8) = o;
+            *reinterpret_cast<bf16x8 *>(dh.p + v * dh.stride + c8) = relu ? mask8(o, q) : o;
         }
         acc[16] += gv;
     }
     for (int c = 0; c < 17; ++c) sh[c][threadIdx.x] = acc[c];
     __syncthreads();
+    // 15 threads a channel, then their sums
+    const int c = threadIdx.x / 15, k = threadIdx.x % 15;
+    float s = 0.0f;
+    if (threadIdx.x < 255)
+        for (int t = k; t < 256; t += 15) s += sh[c][t];
+    __syncthreads();
+    if (threadIdx.x < 255) sh[c][k] = s;
+    __syncthreads();
     if (threadIdx.x < 17) {
         float s = 0.0f;
-        for (int t = 0; t < (int)blockDim.x; ++t) s += sh[threadIdx.x][t];
+        for (int t = 0; t < 15; ++t) s += sh[threadIdx.x][t];
         part[(size_t)blockIdx.x * 17 + threadIdx.x] = s;
     }
 }
@@ -825,6 +906,17 @@ __global__ void transpose_weights(const __bf16 *__restrict__ w, __bf16 *__restri
     }
 }
 
+// sh[0] = the sum of v over the 256 threads of a block, in a fixed order
+__device__ __forceinline__ void block_sum_f64(double *sh, double v)
+{
+    sh[threadIdx.x] = v;
+    __syncthreads();
+    for (int h = 128; h > 0; h >>= 1) {
+        if ((int)threadIdx.x < h) sh[threadIdx.x] += sh[threadIdx.x + h];
+        __syncthreads();
+    }
+}
+
 // MSE: grad = 2 (a - b) / n, partial sums of (a - b)^2 (FP64)
 __global__ void mse_kernel(const float *__restrict__ a, const float *__restrict__ b, int64_t n,
                            float *__restrict__ grad, double *__restrict__ part)
@@ -837,22 +929,17 @@ __global__ void mse_kernel(const float *__restrict__ a, const float *__restrict_
         grad[i] = sc * dlt;
         acc += (double)dlt * dlt;
     }
-    sh[threadIdx.x] = acc;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double s = 0.0;
-        for (int t = 0; t < (int)blockDim.x; ++t) s += sh[t];
-        part[blockIdx.x] = s;
-    }
+    block_sum_f64(sh, acc);
+    if (threadIdx.x == 0) part[blockIdx.x] = sh[0];
 }
 
 __global__ void sum_partials_f64(const double *__restrict__ part, int n, double scale, double *__restrict__ out)
 {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        double s = 0.0;
-        for (int i = 0; i < n; ++i) s += part[i];
-        *out = s * scale;
-    }
+    __shared__ double sh[256];
+    double s = 0.0;
+    for (int i = threadIdx.x; i < n; i += 256) s += part[i];
+    block_sum_f64(sh, s);
+    if (threadIdx.x == 0) *out = sh[0] * scale;
 }
 
 // Adam on FP32 master weights, with a BF16 copy for the kernels (optional)
@@ -943,18 +1030,55 @@ cvpnn::MarchPlan march_plan(const cvpnn::Act &a, int &blocks)
     return best;
 }
 
-template <int CO, int CI, int NT, bool FLIP>
-hipError_t launch_march(const cvpnn::Act &a, const __bf16 *w, const float *bias, const cvpnn::Act &o, int relu, hipStream_t s)
+template <int CO, int CI, int NT, bool FLIP, bool MASK>
+hipError_t launch_march(const cvpnn::Act &a, const __bf16 *w, const float *bias, const cvpnn::Act &o, const cvpnn::Act &keep,
+                        int relu, hipStream_t s)
 {
     static const hipError_t ready =
-        hipFuncSetAttribute(reinterpret_cast<const void *>(cvpnn::conv3d_march_kernel<CO, CI, NT, FLIP>),
+        hipFuncSetAttribute(reinterpret_cast<const void *>(cvpnn::conv3d_march_kernel<CO, CI, NT, FLIP, MASK>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, cvpnn::march_lds_bytes<CI>());
     if (ready != hipSuccess) return ready;
     int blocks = 0;
     const cvpnn::MarchPlan p = march_plan<CO, CI, NT>(a, blocks);
-    hipLaunchKernelGGL((cvpnn::conv3d_march_kernel<CO, CI, NT, FLIP>), dim3(blocks), dim3(256),
-                       (cvpnn::march_lds_bytes<CI>()), s, a, w, bias, o, relu, p);
+    hipLaunchKernelGGL((cvpnn::conv3d_march_kernel<CO, CI, NT, FLIP, MASK>), dim3(blocks), dim3(256),
+                       (cvpnn::march_lds_bytes<CI>()), s, a, w, bias, o, keep, relu, p);
     return hipGetLastError();
+}
+
+bool same_grid(const cvp_nn_tensor *a, const cvp_nn_tensor *b) { return a->d == b->d && a->h == b->h && a->w == b->w; }
+
+// keep: 0, or the post-ReLU tensor that masks the result (flip set, then)
+cvp_status convolve(const cvp_nn_tensor *in, const void *weight, const float *bias, const cvp_nn_tensor *out,
+                    const cvp_nn_tensor *keep, int relu, int flip, void *stream)
+{
+    const cvpnn::Act a = act(in), o = act(out), k = keep ? act(keep) : cvpnn::Act{};
+    hipStream_t s = (hipStream_t)stream;
+    const __bf16 *w = reinterpret_cast<const __bf16 *>(weight);
+    // channel counts 16, 32, 64 and 32-bit byte offsets: the marching kernel,
+    // with the weights of 32 output channels in a wave where they fit its
+    // registers (with 64 input channels 432 of 512 would be taken)
+    const int64_t elems = (int64_t)in->d * in->h * in->w * std::max(std::max(in->stride, out->stride), k.stride);
+    const int ci = in->channels, co = out->channels;
+    const bool spec = elems <= cvpnn::kMarchElems && (ci == 16 || ci == 32 || ci == 64);
+#define MARCH(CO_, CI_, NT_)                                                                       \
+    if (spec && co == CO_ && ci == CI_)                                                            \
+        return st(keep   ? launch_march<CO_, CI_, NT_, true, true>(a, w, bias, o, k, relu, s)      \
+                  : flip ? launch_march<CO_, CI_, NT_, true, false>(a, w, bias, o, k, relu, s)     \
+                         : launch_march<CO_, CI_, NT_, false, false>(a, w, bias, o, k, relu, s));
+    MARCH(16, 16, 1) MARCH(16, 32, 1) MARCH(16, 64, 1)
+    MARCH(32, 16, 2) MARCH(32, 32, 2) MARCH(32, 64, 1)
+    MARCH(64, 16, 2) MARCH(64, 32, 2) MARCH(64, 64, 1)
+#undef MARCH
+    const int rows = in->d * in->h * ((in->w + 63) / 64);
+    const dim3 grid((rows + 3) / 4), block(256);
+    switch (co) {
+    case 16: hipLaunchKernelGGL(cvpnn::conv3d_kernel<16>, grid, block, 0, s, a, w, bias, o, relu, flip); break;
+    case 32: hipLaunchKernelGGL(cvpnn::conv3d_kernel<32>, grid, block, 0, s, a, w, bias, o, relu, flip); break;
+    case 64: hipLaunchKernelGGL(cvpnn::conv3d_kernel<64>, grid, block, 0, s, a, w, bias, o, relu, flip); break;
+    default: return CVP_E_UNSUPPORTED;
+    }
+    const hipError_t e = hipGetLastError();
+    return e != hipSuccess || !keep ? st(e) : cvp_nn_relu_mask(out, keep, stream);
 }
 
 }  // namespace
@@ -966,32 +1090,15 @@ cvp_status cvp_nn_conv3d(const cvp_nn_tensor *in, const void *weight, const floa
 {
     if (!valid(in) || !valid(out) || !weight) return CVP_E_INVALID;
     if (in->d != out->d || in->h != out->h || in->w != out->w) return CVP_E_INVALID;
-    const cvpnn::Act a = act(in), o = act(out);
-    const int rows = in->d * in->h * ((in->w + 63) / 64);
-    const dim3 grid((rows + 3) / 4), block(256);
-    hipStream_t s = (hipStream_t)stream;
-    const __bf16 *w = reinterpret_cast<const __bf16 *>(weight);
-    // channel counts 16, 32, 64 and 32-bit byte offsets: the marching kernel,
-    // with the weights of 32 output channels in a wave where they fit its
-    // registers (with 64 input channels 432 of 512 would be taken)
-    const int64_t elems = (int64_t)in->d * in->h * in->w * std::max(in->stride, out->stride);
-    const int ci = in->channels, co = out->channels;
-    const bool spec = elems <= cvpnn::kMarchElems && (ci == 16 || ci == 32 || ci == 64);
-#define MARCH(CO_, CI_, NT_)                                                                \
-    if (spec && co == CO_ && ci == CI_)                                                     \
-        return st(flip ? launch_march<CO_, CI_, NT_, true>(a, w, bias, o, relu, s)          \
-                       : launch_march<CO_, CI_, NT_, false>(a, w, bias, o, relu, s));
-    MARCH(16, 16, 1) MARCH(16, 32, 1) MARCH(16, 64, 1)
-    MARCH(32, 16, 2) MARCH(32, 32, 2) MARCH(32, 64, 1)
-    MARCH(64, 16, 2) MARCH(64, 32, 2) MARCH(64, 64, 1)
-#undef MARCH
-    switch (co) {
-    case 16: hipLaunchKernelGGL(cvpnn::conv3d_kernel<16>, grid, block, 0, s, a, w, bias, o, relu, flip); break;
-    case 32: hipLaunchKernelGGL(cvpnn::conv3d_kernel<32>, grid, block, 0, s, a, w, bias, o, relu, flip); break;
-    case 64: hipLaunchKernelGGL(cvpnn::conv3d_kernel<64>, grid, block, 0, s, a, w, bias, o, relu, flip); break;
-    default: return CVP_E_UNSUPPORTED;
-    }
-    return st(hipGetLastError());
+    return convolve(in, weight, bias, out, nullptr, relu, flip, stream);
+}
+
+cvp_status cvp_nn_conv3d_bwd_masked(const cvp_nn_tensor *dy, const void *weight_t, const cvp_nn_tensor *keep,
+                                    const cvp_nn_tensor *dx, void *stream)
+{
+    if (!valid(dy) || !valid(dx) || !valid(keep) || !weight_t) return CVP_E_INVALID;
+    if (!same_grid(dy, dx) || !same_grid(dx, keep) || keep->channels != dx->channels) return CVP_E_INVALID;
+    return convolve(dy, weight_t, nullptr, dx, keep, 0, 1, stream);
 }
 
 // Partial sums of the weight gradient that fill the GPU.
@@ -1012,18 +1119,19 @@ cvp_status cvp_nn_wgrad_workspace(const cvp_nn_tensor *x, const cvp_nn_tensor *d
     return CVP_OK;
 }
 
-cvp_status cvp_nn_conv3d_wgrad(const cvp_nn_tensor *x, const cvp_nn_tensor *dy, float *dw, float *work,
-                               int64_t work_floats, void *stream)
+// db: 0, or the bias gradient as well
+static cvp_status wgrad(const cvp_nn_tensor *x, const cvp_nn_tensor *dy, float *dw, float *db, float *work,
+                        int64_t work_floats, void *stream)
 {
     if (!valid(x) || !valid(dy) || !dw || !work) return CVP_E_INVALID;
     const int co = dy->channels, ci = x->channels;
-    const int64_t n = (int64_t)27 * co * ci;
+    const int64_t nw = (int64_t)27 * co * ci, n = nw + (db ? co : 0);
     if (work_floats < wgrad_chunks_least(x) * n) return CVP_E_INVALID;
     const cvpnn::Act a = act(x), g = act(dy);
     hipStream_t s = (hipStream_t)stream;
     // the run length whose longest chunk is shortest: a unit costs its slices
     // and the two more that its first needs
-    const int64_t cap = std::min(work_floats / n, wgrad_chunks_wanted(n));
+    const int64_t cap = std::min(work_floats / n, wgrad_chunks_wanted(nw));
     const int ty = ci == 16 ? cvpnn::wgrad_rows<16>() : ci == 32 ? cvpnn::wgrad_rows<32>() : cvpnn::wgrad_rows<64>();
     cvpnn::WgradPlan p;
     p.ytiles = (x->h + ty - 1) / ty;
@@ -1048,7 +1156,7 @@ cvp_status cvp_nn_conv3d_wgrad(const cvp_nn_tensor *x, const cvp_nn_tensor *dy, 
             hipFuncAttributeMaxDynamicSharedMemorySize, cvpnn::wgrad_lds_bytes<CO_, CI_>());                    \
         if (ready != hipSuccess) return st(ready);                                                              \
         hipLaunchKernelGGL((cvpnn::conv3d_wgrad_kernel<CO_, CI_>), dim3(p.chunks, CO_ > 32 ? CO_ / 32 : 1),     \
-                           dim3(256), (cvpnn::wgrad_lds_bytes<CO_, CI_>()), s, a, g, p, work);                  \
+                           dim3(256), (cvpnn::wgrad_lds_bytes<CO_, CI_>()), s, a, g, p, db ? 1 : 0, work);                  \
     } while (0)
     if (co == 16 && ci == 16) WG(16, 16);
     else if (co == 16 && ci == 32) WG(16, 32);
@@ -1060,8 +1168,21 @@ cvp_status cvp_nn_conv3d_wgrad(const cvp_nn_tensor *x, const cvp_nn_tensor *dy, 
     else if (co == 16 && ci == 64) WG(16, 64);
     else return CVP_E_UNSUPPORTED;
 #undef WG
-    hipLaunchKernelGGL(cvpnn::reduce_chunks, dim3(grid_for(4 * n)), dim3(1024), 0, s, work, p.chunks, n, dw);
+    hipLaunchKernelGGL(cvpnn::reduce_chunks, dim3(grid_for(4 * n)), dim3(1024), 0, s, work, p.chunks, n, dw, nw, db);
     return st(hipGetLastError());
+}
+
+cvp_status cvp_nn_conv3d_wgrad(const cvp_nn_tensor *x, const cvp_nn_tensor *dy, float *dw, float *work,
+                               int64_t work_floats, void *stream)
+{
+    return wgrad(x, dy, dw, nullptr, work, work_floats, stream);
+}
+
+cvp_status cvp_nn_conv3d_wgrad_bias(const cvp_nn_tensor *x, const cvp_nn_tensor *dy, float *dw, float *db, float *work,
+                                    int64_t work_floats, void *stream)
+{
+    if (!db) return CVP_E_INVALID;
+    return wgrad(x, dy, dw, db, work, work_floats, stream);
 }
 
 cvp_status cvp_nn_channel_sum(const cvp_nn_tensor *a, float *out, float *work, int64_t work_floats,
@@ -1073,7 +1194,8 @@ cvp_status cvp_nn_channel_sum(const cvp_nn_tensor *a, float *out, float *work, i
     if (work_floats < (int64_t)chunks * a->channels) return CVP_E_INVALID;
     hipStream_t s = (hipStream_t)stream;
     hipLaunchKernelGGL(cvpnn::channel_sum_partials, dim3(chunks), dim3(256), 0, s, act(a), rpc, work);
-    hipLaunchKernelGGL(cvpnn::reduce_chunks, dim3(1), dim3(1024), 0, s, work, chunks, (int64_t)a->channels, out);
+    hipLaunchKernelGGL(cvpnn::reduce_chunks, dim3(1), dim3(1024), 0, s, work, chunks, (int64_t)a->channels, out,
+                       (int64_t)a->channels, nullptr);
     return st(hipGetLastError());
 }
 
@@ -1089,7 +1211,8 @@ cvp_status cvp_nn_relu_mask(const cvp_nn_tensor *dy, const cvp_nn_tensor *y, voi
     return st(hipGetLastError());
 }
 
-static cvp_status resample(int kind, const cvp_nn_tensor *a, const cvp_nn_tensor *b, void *stream)
+static cvp_status resample(int kind, const cvp_nn_tensor *a, const cvp_nn_tensor *b, void *stream,
+                           const cvp_nn_tensor *keep = nullptr)
 {
     if (!valid(a) || !valid(b) || a->channels != b->channels) return CVP_E_INVALID;
     hipStream_t s = (hipStream_t)stream;
@@ -1100,16 +1223,19 @@ static cvp_status resample(int kind, const cvp_nn_tensor *a, const cvp_nn_tensor
     const int64_t nb = (int64_t)big->d * big->h * big->w * big->channels / 8;
     const int64_t ns = nb / 8;
     const bool i32 = nb < (int64_t(1) << 31);
-#define RS(K, N)                                                                                      \
-    do {                                                                                              \
-        if (i32) hipLaunchKernelGGL(cvpnn::K<int>, dim3(grid_for(N)), dim3(256), 0, s, act(a), act(b)); \
-        else hipLaunchKernelGGL(cvpnn::K<int64_t>, dim3(grid_for(N)), dim3(256), 0, s, act(a), act(b)); \
+#define RS(K, N, ...)                                                                                       \
+    do {                                                                                                    \
+        if (i32) hipLaunchKernelGGL(cvpnn::K<int>, dim3(grid_for(N)), dim3(256), 0, s, act(a), __VA_ARGS__); \
+        else hipLaunchKernelGGL(cvpnn::K<int64_t>, dim3(grid_for(N)), dim3(256), 0, s, act(a), __VA_ARGS__); \
     } while (0)
     switch (kind) {
-    case 0: RS(avgpool2, ns); break;
-    case 1: RS(avgpool2_bwd, nb); break;
-    case 2: RS(upsample2, nb); break;
-    default: RS(upsample2_bwd, ns); break;
+    case 0: RS(avgpool2, ns, act(b)); break;
+    case 1:
+        if (keep) RS(avgpool2_bwd_add, nb, act(keep), act(b));
+        else RS(avgpool2_bwd, nb, act(b));
+        break;
+    case 2: RS(upsample2, nb, act(b)); break;
+    default: RS(upsample2_bwd, ns, act(b), keep ? act(keep) : cvpnn::Act{}); break;
     }
 #undef RS
     return st(hipGetLastError());
@@ -1119,6 +1245,19 @@ cvp_status cvp_nn_avgpool2(const cvp_nn_tensor *in, const cvp_nn_tensor *out, vo
 cvp_status cvp_nn_avgpool2_bwd(const cvp_nn_tensor *dout, const cvp_nn_tensor *din, void *stream) { return resample(1, dout, din, stream); }
 cvp_status cvp_nn_upsample2(const cvp_nn_tensor *in, const cvp_nn_tensor *out, void *stream) { return resample(2, in, out, stream); }
 cvp_status cvp_nn_upsample2_bwd(const cvp_nn_tensor *dout, const cvp_nn_tensor *din, void *stream) { return resample(3, dout, din, stream); }
+
+cvp_status cvp_nn_avgpool2_bwd_add(const cvp_nn_tensor *dout, const cvp_nn_tensor *keep, const cvp_nn_tensor *g, void *stream)
+{
+    if (!valid(keep) || !valid(g) || !same_grid(keep, g) || keep->channels != g->channels) return CVP_E_INVALID;
+    return resample(1, dout, g, stream, keep);
+}
+
+cvp_status cvp_nn_upsample2_bwd_masked(const cvp_nn_tensor *dout, const cvp_nn_tensor *keep, const cvp_nn_tensor *din,
+                                       void *stream)
+{
+    if (!valid(keep) || !valid(din) || !same_grid(keep, din) || keep->channels != din->channels) return CVP_E_INVALID;
+    return resample(3, dout, din, stream, keep);
+}
 
 cvp_status cvp_nn_add(const cvp_nn_tensor *a, const cvp_nn_tensor *b, const cvp_nn_tensor *out, void *stream)
 {
@@ -1162,8 +1301,8 @@ cvp_status cvp_nn_head(const cvp_nn_tensor *h, const float *w, const float *b, c
     return st(hipGetLastError());
 }
 
-cvp_status cvp_nn_head_bwd(const cvp_nn_tensor *h, const float *w, const float *g, float scale,
-                           const cvp_nn_tensor *dh, float *dwb /*17*/, float *work, int64_t work_floats,
+static cvp_status head_bwd(const cvp_nn_tensor *h, const float *w, const float *g, float scale,
+                           const cvp_nn_tensor *dh, float *dwb /*17*/, float *work, int64_t work_floats, int relu,
                            void *stream)
 {
     if (!valid(h) || !valid(dh) || h->channels > 16 || !w || !g || !dwb || !work || !(scale > 0)) return CVP_E_INVALID;
@@ -1172,9 +1311,22 @@ cvp_status cvp_nn_head_bwd(const cvp_nn_tensor *h, const float *w, const float *
     const int blocks = (int)((n + per - 1) / per);
     if (work_floats < (int64_t)blocks * 17) return CVP_E_INVALID;
     hipStream_t s = (hipStream_t)stream;
-    hipLaunchKernelGGL(cvpnn::head_bwd, dim3(blocks), dim3(256), 0, s, act(h), w, g, 1.0f / scale, act(dh), per, work);
-    hipLaunchKernelGGL(cvpnn::reduce_chunks, dim3(1), dim3(1024), 0, s, work, blocks, (int64_t)17, dwb);
+    hipLaunchKernelGGL(cvpnn::head_bwd, dim3(blocks), dim3(256), 0, s, act(h), w, g, 1.0f / scale, act(dh), per, relu,
+                       work);
+    hipLaunchKernelGGL(cvpnn::reduce_chunks, dim3(1), dim3(1024), 0, s, work, blocks, (int64_t)17, dwb, (int64_t)17, nullptr);
     return st(hipGetLastError());
+}
+
+cvp_status cvp_nn_head_bwd(const cvp_nn_tensor *h, const float *w, const float *g, float scale,
+                           const cvp_nn_tensor *dh, float *dwb, float *work, int64_t work_floats, void *stream)
+{
+    return head_bwd(h, w, g, scale, dh, dwb, work, work_floats, 0, stream);
+}
+
+cvp_status cvp_nn_head_bwd_masked(const cvp_nn_tensor *h, const float *w, const float *g, float scale,
+                                  const cvp_nn_tensor *dh, float *dwb, float *work, int64_t work_floats, void *stream)
+{
+    return head_bwd(h, w, g, scale, dh, dwb, work, work_floats, 1, stream);
 }
 
 cvp_status cvp_nn_mse(const float *a, const float *b, int64_t n, float *grad, double *loss, double *work,
@@ -1183,7 +1335,7 @@ cvp_status cvp_nn_mse(const float *a, const float *b, int64_t n, float *grad, do
     if (!a || !b || !grad || !loss || !work || n <= 0 || work_doubles < 1024) return CVP_E_INVALID;
     hipStream_t s = (hipStream_t)stream;
     hipLaunchKernelGGL(cvpnn::mse_kernel, dim3(1024), dim3(256), 0, s, a, b, n, grad, work);
-    hipLaunchKernelGGL(cvpnn::sum_partials_f64, dim3(1), dim3(64), 0, s, work, 1024, 1.0 / (double)n, loss);
+    hipLaunchKernelGGL(cvpnn::sum_partials_f64, dim3(1), dim3(256), 0, s, work, 1024, 1.0 / (double)n, loss);
     return st(hipGetLastError());
 }
 

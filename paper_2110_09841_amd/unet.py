@@ -36,6 +36,15 @@ _SIGS = {
     "cvp_nn_wgrad_workspace": [ctypes.POINTER(NNTensor), ctypes.POINTER(NNTensor), ctypes.POINTER(ctypes.c_int64)],
     "cvp_nn_conv3d_wgrad": [ctypes.POINTER(NNTensor), ctypes.POINTER(NNTensor), ctypes.c_void_p, ctypes.c_void_p,
                             ctypes.c_int64, ctypes.c_void_p],
+    "cvp_nn_conv3d_wgrad_bias": [ctypes.POINTER(NNTensor), ctypes.POINTER(NNTensor), ctypes.c_void_p, ctypes.c_void_p,
+                                 ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p],
+    "cvp_nn_conv3d_bwd_masked": [ctypes.POINTER(NNTensor), ctypes.c_void_p, ctypes.POINTER(NNTensor),
+                                 ctypes.POINTER(NNTensor), ctypes.c_void_p],
+    "cvp_nn_avgpool2_bwd_add": [ctypes.POINTER(NNTensor)] * 3 + [ctypes.c_void_p],
+    "cvp_nn_upsample2_bwd_masked": [ctypes.POINTER(NNTensor)] * 3 + [ctypes.c_void_p],
+    "cvp_nn_head_bwd_masked": [ctypes.POINTER(NNTensor), ctypes.c_void_p, ctypes.c_void_p, ctypes.c_float,
+                               ctypes.POINTER(NNTensor), ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int64,
+                               ctypes.c_void_p],
     "cvp_nn_channel_sum": [ctypes.POINTER(NNTensor), ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p],
     "cvp_nn_relu_mask": [ctypes.POINTER(NNTensor), ctypes.POINTER(NNTensor), ctypes.c_void_p],
     "cvp_nn_avgpool2": [ctypes.POINTER(NNTensor), ctypes.POINTER(NNTensor), ctypes.c_void_p],
@@ -216,44 +225,49 @@ class UNet:
         return self.x0
 
     # -------------------------------------------------------------- backward
-    def _conv_bwd(self, name, x_desc, y_desc, gy_desc, gx_desc):
-        """Given dL/dy (post-ReLU, in gy), fill the parameter gradients and,
-        if gx_desc is not None, dL/dx."""
+    def _conv_bwd(self, name, x_desc, gy_desc, gx_desc, masked=True):
+        """Given dL/d(pre-ReLU output) in gy, fill the parameter gradients and,
+        if gx_desc is not None, dL/dx; masked: x is itself a ReLU's output and
+        gx becomes the gradient before that ReLU."""
         c, L = self.convs[name], lib()
-        _check(L.cvp_nn_relu_mask(ctypes.byref(gy_desc), ctypes.byref(y_desc), _s()))
-        _check(L.cvp_nn_conv3d_wgrad(ctypes.byref(x_desc), ctypes.byref(gy_desc), _p(c.gw), _p(self.work),
-                                     self.work.numel(), _s()))
-        _check(L.cvp_nn_channel_sum(ctypes.byref(gy_desc), _p(c.gb), _p(self.work), self.work.numel(), _s()))
-        if gx_desc is not None:
+        _check(L.cvp_nn_conv3d_wgrad_bias(ctypes.byref(x_desc), ctypes.byref(gy_desc), _p(c.gw), _p(c.gb),
+                                          _p(self.work), self.work.numel(), _s()))
+        if gx_desc is not None and masked:
+            _check(L.cvp_nn_conv3d_bwd_masked(ctypes.byref(gy_desc), _p(c.wt), ctypes.byref(x_desc),
+                                              ctypes.byref(gx_desc), _s()))
+        elif gx_desc is not None:
             _check(L.cvp_nn_conv3d(ctypes.byref(gy_desc), _p(c.wt), None, ctypes.byref(gx_desc), 0, 1, _s()))
 
     def backward(self, gx0):
-        """Back-propagate dL/dx0 (FP32 volume) to all parameters."""
+        """Back-propagate dL/dx0 (FP32 volume) to all parameters.  Every tensor
+        of self.g is the gradient before the ReLU of its activation (up1, up2,
+        p1 and p2 have none)."""
         a, g, L = self.a, self.g, lib()
-        _check(L.cvp_nn_head_bwd(ctypes.byref(desc(a["d1b"])), _p(self.hw), _p(gx0), ctypes.c_float(INPUT_SCALE),
-                                 ctypes.byref(desc(g["d1b"])), _p(self.ghead), _p(self.work), self.work.numel(), _s()))
-        self._conv_bwd("d1b", desc(a["d1a"]), desc(a["d1b"]), desc(g["d1b"]), desc(g["d1a"]))
-        self._conv_bwd("d1a", desc(a["cat1"]), desc(a["d1a"]), desc(g["d1a"]), desc(g["cat1"]))
+        _check(L.cvp_nn_head_bwd_masked(ctypes.byref(desc(a["d1b"])), _p(self.hw), _p(gx0),
+                                        ctypes.c_float(INPUT_SCALE), ctypes.byref(desc(g["d1b"])), _p(self.ghead),
+                                        _p(self.work), self.work.numel(), _s()))
+        self._conv_bwd("d1b", desc(a["d1a"]), desc(g["d1b"]), desc(g["d1a"]))
+        self._conv_bwd("d1a", desc(a["cat1"]), desc(g["d1a"]), desc(g["cat1"]))
         # cat1 = [u1 out | skip 1]
-        self._conv_bwd("u1", desc(a["up1"]), desc(a["cat1"], 0, 16), desc(g["cat1"], 0, 16), desc(g["up1"]))
-        _check(L.cvp_nn_upsample2_bwd(ctypes.byref(desc(g["up1"])), ctypes.byref(desc(g["d2b"])), _s()))
-        self._conv_bwd("d2b", desc(a["d2a"]), desc(a["d2b"]), desc(g["d2b"]), desc(g["d2a"]))
-        self._conv_bwd("d2a", desc(a["cat2"]), desc(a["d2a"]), desc(g["d2a"]), desc(g["cat2"]))
-        self._conv_bwd("u2", desc(a["up2"]), desc(a["cat2"], 0, 32), desc(g["cat2"], 0, 32), desc(g["up2"]))
-        _check(L.cvp_nn_upsample2_bwd(ctypes.byref(desc(g["up2"])), ctypes.byref(desc(g["c3b"])), _s()))
-        self._conv_bwd("c3b", desc(a["c3a"]), desc(a["c3b"]), desc(g["c3b"]), desc(g["c3a"]))
-        self._conv_bwd("c3a", desc(a["p2"]), desc(a["c3a"]), desc(g["c3a"]), desc(g["p2"]))
+        self._conv_bwd("u1", desc(a["up1"]), desc(g["cat1"], 0, 16), desc(g["up1"]), masked=False)
+        _check(L.cvp_nn_upsample2_bwd_masked(ctypes.byref(desc(g["up1"])), ctypes.byref(desc(a["d2b"])),
+                                             ctypes.byref(desc(g["d2b"])), _s()))
+        self._conv_bwd("d2b", desc(a["d2a"]), desc(g["d2b"]), desc(g["d2a"]))
+        self._conv_bwd("d2a", desc(a["cat2"]), desc(g["d2a"]), desc(g["cat2"]))
+        self._conv_bwd("u2", desc(a["up2"]), desc(g["cat2"], 0, 32), desc(g["up2"]), masked=False)
+        _check(L.cvp_nn_upsample2_bwd_masked(ctypes.byref(desc(g["up2"])), ctypes.byref(desc(a["c3b"])),
+                                             ctypes.byref(desc(g["c3b"])), _s()))
+        self._conv_bwd("c3b", desc(a["c3a"]), desc(g["c3b"]), desc(g["c3a"]))
+        self._conv_bwd("c3a", desc(a["p2"]), desc(g["c3a"]), desc(g["p2"]), masked=False)
         # skip 2 receives the concat slice plus the pooled path
-        _check(L.cvp_nn_avgpool2_bwd(ctypes.byref(desc(g["p2"])), ctypes.byref(desc(g["up2"], 0, 32)), _s()))
-        _check(L.cvp_nn_add(ctypes.byref(desc(g["cat2"], 32, 32)), ctypes.byref(desc(g["up2"], 0, 32)),
-                            ctypes.byref(desc(g["cat2"], 32, 32)), _s()))
-        self._conv_bwd("c2b", desc(a["c2a"]), desc(a["cat2"], 32, 32), desc(g["cat2"], 32, 32), desc(g["c2a"]))
-        self._conv_bwd("c2a", desc(a["p1"]), desc(a["c2a"]), desc(g["c2a"]), desc(g["p1"]))
-        _check(L.cvp_nn_avgpool2_bwd(ctypes.byref(desc(g["p1"])), ctypes.byref(desc(g["up1"], 0, 16)), _s()))
-        _check(L.cvp_nn_add(ctypes.byref(desc(g["cat1"], 16, 16)), ctypes.byref(desc(g["up1"], 0, 16)),
-                            ctypes.byref(desc(g["cat1"], 16, 16)), _s()))
-        self._conv_bwd("c1b", desc(a["c1a"]), desc(a["cat1"], 16, 16), desc(g["cat1"], 16, 16), desc(g["c1a"]))
-        self._conv_bwd("c1a", desc(a["in"]), desc(a["c1a"]), desc(g["c1a"]), None)
+        _check(L.cvp_nn_avgpool2_bwd_add(ctypes.byref(desc(g["p2"])), ctypes.byref(desc(a["cat2"], 32, 32)),
+                                         ctypes.byref(desc(g["cat2"], 32, 32)), _s()))
+        self._conv_bwd("c2b", desc(a["c2a"]), desc(g["cat2"], 32, 32), desc(g["c2a"]))
+        self._conv_bwd("c2a", desc(a["p1"]), desc(g["c2a"]), desc(g["p1"]), masked=False)
+        _check(L.cvp_nn_avgpool2_bwd_add(ctypes.byref(desc(g["p1"])), ctypes.byref(desc(a["cat1"], 16, 16)),
+                                         ctypes.byref(desc(g["cat1"], 16, 16)), _s()))
+        self._conv_bwd("c1b", desc(a["c1a"]), desc(g["cat1"], 16, 16), desc(g["c1a"]))
+        self._conv_bwd("c1a", desc(a["in"]), desc(g["c1a"]), None)
 
     def mse(self, x0, target):
         """loss = mean (x0 - target)^2 (device FP64); fills self.gx0."""

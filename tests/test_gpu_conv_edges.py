@@ -109,3 +109,67 @@ def test_infinite_weight_and_input_stay_local(flip):
     want = torch.zeros_like(bad)
     want[1:4, 2:5, 19:22] = True
     assert torch.equal(bad, want)
+
+
+def same_bits(a, b):
+    return torch.equal(a.view(torch.int16), b.view(torch.int16))
+
+
+@pytest.mark.parametrize("ci,co", [(16, 16), (16, 32), (32, 16), (32, 32), (32, 64), (64, 32), (64, 64), (24, 16)])
+@pytest.mark.parametrize("shape", [(1, 1, 1), (5, 17, 33), (2, 8, 66)])
+def test_masked_backward_equals_convolution_and_mask(ci, co, shape):
+    L, gen = U.lib(), torch.Generator().manual_seed(9)
+    dy = torch.randn(shape + (ci,), generator=gen).to(torch.bfloat16).cuda()
+    w = torch.randn((27, co, ci), generator=gen).to(torch.bfloat16).cuda()
+    keep = torch.randn(shape + (co + 8,), generator=gen).clamp(min=0).to(torch.bfloat16).cuda()
+    a, b = (torch.full(shape + (co + 8,), 3.0, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    k = U.desc(keep, 0, co)
+    U._check(L.cvp_nn_conv3d(ctypes.byref(U.desc(dy)), U._p(w), None, ctypes.byref(U.desc(a, 8, co)), 0, 1, U._s()))
+    U._check(L.cvp_nn_relu_mask(ctypes.byref(U.desc(a, 8, co)), ctypes.byref(k), U._s()))
+    U._check(L.cvp_nn_conv3d_bwd_masked(ctypes.byref(U.desc(dy)), U._p(w), ctypes.byref(k),
+                                        ctypes.byref(U.desc(b, 8, co)), U._s()))
+    assert same_bits(a, b)
+
+
+@pytest.mark.parametrize("co,ci", [(16, 16), (32, 64), (64, 32)])
+@pytest.mark.parametrize("shape", [(1, 1, 1), (5, 17, 33), (70, 5, 31)])
+def test_bias_gradient_beside_the_weights(co, ci, shape):
+    L = U.lib()
+    x, g = ints(shape + (ci,), 1), ints(shape + (co,), 2)
+    dw, db = torch.empty((27, co, ci), device="cuda"), torch.empty(co, device="cuda")
+    least = (shape[0] * shape[1] + 63) // 64 * (27 * co * ci + co)
+    for floats in (least, 20 * least):
+        work = torch.full((floats,), float("nan"), device="cuda")
+        U._check(L.cvp_nn_conv3d_wgrad_bias(ctypes.byref(U.desc(x)), ctypes.byref(U.desc(g)), U._p(dw), U._p(db),
+                                            U._p(work), floats, U._s()))
+        assert torch.equal(dw.cpu(), reference(x, g))
+        assert torch.equal(db.cpu(), g.float().sum((0, 1, 2)).cpu())
+
+
+def test_masked_upsampling_pooling_and_head():
+    L, gen = U.lib(), torch.Generator().manual_seed(10)
+    rnd = lambda s: torch.randn(s, generator=gen).to(torch.bfloat16).cuda()
+    fine, coarse = (6, 4, 10), (3, 2, 5)
+    gf, kc = rnd(fine + (16,)), rnd(coarse + (16,)).clamp(min=0)
+    a, b = torch.empty_like(kc), torch.empty_like(kc)
+    U._check(L.cvp_nn_upsample2_bwd(ctypes.byref(U.desc(gf)), ctypes.byref(U.desc(a)), U._s()))
+    U._check(L.cvp_nn_relu_mask(ctypes.byref(U.desc(a)), ctypes.byref(U.desc(kc)), U._s()))
+    U._check(L.cvp_nn_upsample2_bwd_masked(ctypes.byref(U.desc(gf)), ctypes.byref(U.desc(kc)), ctypes.byref(U.desc(b)),
+                                           U._s()))
+    assert same_bits(a, b)
+    gc, kf = rnd(coarse + (16,)), rnd(fine + (16,)).clamp(min=0)
+    a, b, t = gf.clone(), gf.clone(), torch.empty_like(gf)
+    U._check(L.cvp_nn_avgpool2_bwd(ctypes.byref(U.desc(gc)), ctypes.byref(U.desc(t)), U._s()))
+    U._check(L.cvp_nn_add(ctypes.byref(U.desc(a)), ctypes.byref(U.desc(t)), ctypes.byref(U.desc(a)), U._s()))
+    U._check(L.cvp_nn_relu_mask(ctypes.byref(U.desc(a)), ctypes.byref(U.desc(kf)), U._s()))
+    U._check(L.cvp_nn_avgpool2_bwd_add(ctypes.byref(U.desc(gc)), ctypes.byref(U.desc(kf)), ctypes.byref(U.desc(b)), U._s()))
+    assert same_bits(a, b)
+    w, gx = torch.randn(16, generator=gen).cuda(), torch.randn(fine, generator=gen).cuda()
+    work = torch.empty(4096, device="cuda")
+    d1, d2 = torch.empty(17, device="cuda"), torch.empty(17, device="cuda")
+    U._check(L.cvp_nn_head_bwd(ctypes.byref(U.desc(kf)), U._p(w), U._p(gx), ctypes.c_float(2.0), ctypes.byref(U.desc(a)),
+                               U._p(d1), U._p(work), 4096, U._s()))
+    U._check(L.cvp_nn_relu_mask(ctypes.byref(U.desc(a)), ctypes.byref(U.desc(kf)), U._s()))
+    U._check(L.cvp_nn_head_bwd_masked(ctypes.byref(U.desc(kf)), U._p(w), U._p(gx), ctypes.c_float(2.0),
+                                      ctypes.byref(U.desc(b)), U._p(d2), U._p(work), 4096, U._s()))
+    assert same_bits(a, b) and torch.equal(d1, d2)
