@@ -1030,10 +1030,10 @@ __device__ __forceinline__ void project_item(const DevGeom &G, const int U, cons
         // column is one contiguous row of n3 values, loaded when its turn
         // comes; from the caller's layout, where the 16 columns of a group
         // share each 64-byte line, all of them are loaded at once (and fewer
-        // slices fit the registers).  The loops over columns, pieces and
+        // slices fit the registers: two, or one beside the FP64 stage).  The loops over columns, pieces and
         // slices are not unrolled (the row-count variants would be repeated
         // for each): their values are taken by uniform register indices.
-        constexpr int KH = VT ? 8 : 2, CW = VT ? 1 : GW;
+        constexpr int KH = VT ? 8 : TAB ? 2 : 1, CW = VT ? 1 : GW;
         for (int kc = 0; kc < G.n3; kc += kWave * KH) {
             const int nh = min(KH, (G.n3 - kc + kWave - 1) / kWave);
             const float kf0 = (float)(kc + lane);
@@ -1172,13 +1172,14 @@ __device__ __forceinline__ void project_item(const DevGeom &G, const int U, cons
     }
 }
 
-// Register budgets: the projection is held to 96 VGPRs (5 waves per SIMD,
-// spills outside the voxel loop) and the backprojection to 168 (3 waves per
-// SIMD); both ran about 20% faster at 512^3 x 248 views than at their
-// natural 190-220 VGPRs with 2 waves per SIMD, and the projection 3% faster
-// at 5 waves than at 4.
+// Register budgets: the projection is held to 96 VGPRs (5 waves per SIMD; the
+// kernels that make their records spill in the FP64 stage) and the window
+// backprojection without a table to 168 (3 waves per SIMD); both ran about 20%
+// faster at 512^3 x 248 views than at their natural 190-220 VGPRs with 2 waves
+// per SIMD.  With a table but the caller's layout, two slices of 16 columns
+// take 4 waves per SIMD (at 5 they spill inside the voxel loop).
 template <bool EXACT, bool EC, int PMAX, bool TT, bool TAB, bool VT>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5)))
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(TAB && !VT ? 4 : 5)))
 project_kernel(const DevGeom G, const int U, const int pad, const int nbands, const int linear,
                const float *__restrict__ vol,
                float *__restrict__ proj, const unsigned *__restrict__ gmax, const double *__restrict__ stop)
@@ -1528,8 +1529,9 @@ __device__ __forceinline__ float column_factor(const BackView &B, const float *r
 
 // Sums a[NP] of the pieces of one column (np records at rc) for its voxels in
 // NP passes of 64 slices (kf, kv), without column_factor.  np and the records
-// are the same in every lane.
-template <bool EC, bool EXACT, bool TT, int SRC, int NP>
+// are the same in every lane.  FIXED: use the row counts (footprints of more
+// than 8 columns are of voxels many rows high, too).
+template <bool EC, bool EXACT, bool TT, int SRC, int NP, bool FIXED = true>
 __device__ __forceinline__ void gather_column(const BackView &B, const float *rc, const int np, const float *win,
                                               const float kf[NP], const bool kv[NP], float a[NP])
 {
@@ -1542,7 +1544,7 @@ __device__ __forceinline__ void gather_column(const BackView &B, const float *rc
         const float4 r2 = *reinterpret_cast<const float4 *>(rc + p * kRecFloats + 8);
         const int word = __builtin_amdgcn_readfirstlane(__float_as_int(r0.x));
         const int u = rec_col(word);
-        const int rows = !TT && B.fixed ? rec_rows<EC>(word) : 0;
+        const int rows = FIXED && !TT && B.fixed ? rec_rows<EC>(word) : 0;
         // (copy: wu0 = 0, wv0 = minus the spare rows before row 0)
         const float *wcol = win + (SRC == kFromCopy ? (size_t)u * B.Hp : (u - B.wu0) * B.Hp) - B.wv0;
         if (rows > 0) {
@@ -1776,7 +1778,7 @@ __device__ __forceinline__ void backproject_item(const DevGeom &G, const int ngr
             for (int c = 0; c < GW; ++c) {
                 const int np = __builtin_amdgcn_readfirstlane(npc[c]);
                 float a[NP];   // (no branch around a column without pieces: it would copy every sum)
-                gather_column<EC, EXACT, TT, SRC, NP>(B, recv + c * PMAX * kRecFloats, np, win, kf, kv, a);
+                gather_column<EC, EXACT, TT, SRC, NP, (PMAX <= 8)>(B, recv + c * PMAX * kRecFloats, np, win, kf, kv, a);
 #pragma unroll
                 for (int ps = 0; ps < NP; ++ps)
                     acc[ps][c] = fmaf(column_factor<EXACT, TT>(B, recv + c * PMAX * kRecFloats, np, kf[ps]), a[ps], acc[ps][c]);
@@ -2294,12 +2296,15 @@ hipError_t launch_p_vt(const DevGeom &g, const ProjLaunch &L, const float *vol, 
                        const float *vt, hipStream_t s, const double *stop)
 {
     const dim3 grid(L.linear ? L.items : 8 * L.chunk), block(kBlock);
-    if (vt)
-        hipLaunchKernelGGL((project_kernel<EXACT, EC, PMAX, TT, TAB, true>), grid, block, L.lds, s, g, L.U, L.pad,
-                           L.nbands, L.linear, vt, proj, gmax, stop);
-    else
-        hipLaunchKernelGGL((project_kernel<EXACT, EC, PMAX, TT, TAB, false>), grid, block, L.lds, s, g, L.U, L.pad,
-                           L.nbands, L.linear, vol, proj, gmax, stop);
+    if constexpr (TAB) {       // (the kernels without a table read the caller's layout only)
+        if (vt) {
+            hipLaunchKernelGGL((project_kernel<EXACT, EC, PMAX, TT, TAB, true>), grid, block, L.lds, s, g, L.U, L.pad,
+                               L.nbands, L.linear, vt, proj, gmax, stop);
+            return hipGetLastError();
+        }
+    }
+    hipLaunchKernelGGL((project_kernel<EXACT, EC, PMAX, TT, TAB, false>), grid, block, L.lds, s, g, L.U, L.pad,
+                       L.nbands, L.linear, vol, proj, gmax, stop);
     return hipGetLastError();
 }
 
@@ -2411,12 +2416,15 @@ template <bool EXACT, bool EC, bool TAB>
 hipError_t launch_pb(BatchProblem *probs, const BatchTable *tab, int *counter, int grid, size_t lds, bool vt,
                      hipStream_t s)
 {
-    if (vt)
-        hipLaunchKernelGGL((project_batched_kernel<EXACT, EC, TAB, true>), dim3(grid), dim3(kBlock), lds, s, probs, tab,
-                           counter);
-    else
-        hipLaunchKernelGGL((project_batched_kernel<EXACT, EC, TAB, false>), dim3(grid), dim3(kBlock), lds, s, probs, tab,
-                           counter);
+    if constexpr (TAB) {
+        if (vt) {
+            hipLaunchKernelGGL((project_batched_kernel<EXACT, EC, TAB, true>), dim3(grid), dim3(kBlock), lds, s, probs,
+                               tab, counter);
+            return hipGetLastError();
+        }
+    }
+    hipLaunchKernelGGL((project_batched_kernel<EXACT, EC, TAB, false>), dim3(grid), dim3(kBlock), lds, s, probs, tab,
+                       counter);
     return hipGetLastError();
 }
 
@@ -2456,8 +2464,7 @@ const void *project_batched_fn(bool cached, bool vt)
 {
     if (cached) return vt ? (const void *)project_batched_kernel<false, true, true, true>
                           : (const void *)project_batched_kernel<false, true, true, false>;
-    return vt ? (const void *)project_batched_kernel<false, true, false, true>
-              : (const void *)project_batched_kernel<false, true, false, false>;
+    return (const void *)project_batched_kernel<false, true, false, false>;
 }
 }  // namespace
 
@@ -2501,7 +2508,6 @@ hipError_t configure_batched_lds(size_t n)
     hipError_t e = each_form([&](auto x, auto c) {
         constexpr bool X = decltype(x)::value, C = decltype(c)::value;
         hipError_t r = allow_lds((const void *)project_batched_kernel<X, C, false, false>, n);
-        if (r == hipSuccess) r = allow_lds((const void *)project_batched_kernel<X, C, false, true>, n);
         if (r == hipSuccess) r = allow_lds((const void *)project_batched_kernel<X, C, true, false>, n);
         if (r == hipSuccess) r = allow_lds((const void *)project_batched_kernel<X, C, true, true>, n);
         return r;
@@ -2517,7 +2523,8 @@ template <bool EXACT, bool EC, int PMAX, bool TT, bool TAB>
 hipError_t allow_project(size_t n)
 {
     hipError_t e = allow_lds((const void *)project_kernel<EXACT, EC, PMAX, TT, TAB, false>, n);
-    if (e == hipSuccess) e = allow_lds((const void *)project_kernel<EXACT, EC, PMAX, TT, TAB, true>, n);
+    if constexpr (TAB)
+        if (e == hipSuccess) e = allow_lds((const void *)project_kernel<EXACT, EC, PMAX, TT, TAB, true>, n);
     return e;
 }
 
