@@ -954,8 +954,14 @@ static hipError_t run_project(const cvp_geometry *g, const cvp::DevGeom &G, cons
         if (v && makes_records(g, G)) most = table_views(g, t.n, G.nviews, 1);
         if (most < std::min(G.nviews, 8)) most = 0;
         if (v && (G.rtab || most > 0)) {
-            vt = v;
             w = t;
+            // For two slices per lane (and TT's one) the kernel on the caller's
+            // layout, which loads a group's 16 columns at once, is the faster:
+            // relaxed at 128^3, 120 views 2.19 against 2.29 ms, 512 x 512 x
+            // 128, 180 views 31.1 against 34.3, TT there 37 against 47; but
+            // exact at 64^3, 64 views 0.48 against 0.42, relaxed at 256^3,
+            // 120 views 8.7 against 8.1.
+            if (G.n3 > 128 || (G.n3 <= 64 && model != cvp::kModelTT)) vt = v;
         }
     }
     hipError_t e = hipSuccess;
