@@ -460,12 +460,14 @@ typedef struct {
 cvp_status cvp_nn_conv3d(const cvp_nn_tensor *in, const void *weight, const float *bias,
                          const cvp_nn_tensor *out, int32_t relu, int32_t flip, void *stream);
 /* dW[tap][co][ci] = sum_v dY[v][co] X[v + off(tap)][ci] (FP32), via per-chunk
- * partials in work (cvp_nn_wgrad_workspace floats) and a fixed-order sum. */
+ * partials in work and a fixed-order sum.  cvp_nn_wgrad_workspace: floats of
+ * work for this call and for cvp_nn_conv3d_wgrad_bias; less is taken down to
+ * one partial sum (27 Cout Cin floats) for every 64 rows (d, h). */
 cvp_status cvp_nn_wgrad_workspace(const cvp_nn_tensor *x, const cvp_nn_tensor *dy, int64_t *floats);
 cvp_status cvp_nn_conv3d_wgrad(const cvp_nn_tensor *x, const cvp_nn_tensor *dy, float *dw, float *work,
                                int64_t work_floats, void *stream);
 /* The same with the bias gradient db[dy->channels] = sum of dY over voxels;
- * the workspace holds dy->channels floats more for every 64 rows (d, h). */
+ * a partial sum then takes dy->channels floats more. */
 cvp_status cvp_nn_conv3d_wgrad_bias(const cvp_nn_tensor *x, const cvp_nn_tensor *dy, float *dw, float *db, float *work,
                                     int64_t work_floats, void *stream);
 /* The backward passes below set the gradient they write to 0 where `keep`,

@@ -1101,21 +1101,31 @@ cvp_status cvp_nn_conv3d_bwd_masked(const cvp_nn_tensor *dy, const void *weight_
     return convolve(dy, weight_t, nullptr, dx, keep, 0, 1, stream);
 }
 
-// Partial sums of the weight gradient that fill the GPU.
-static int64_t wgrad_chunks_wanted(int64_t n)
+// Partial sums of the weight gradient that fill the GPU (nw floats each).
+static int64_t wgrad_chunks_wanted(int64_t nw)
 {
-    return std::max<int64_t>(1, std::min<int64_t>(kWgradChunks, kWgradFloats / n));
+    return std::max<int64_t>(1, std::min<int64_t>(kWgradChunks, kWgradFloats / nw));
 }
 
 // the smallest workspace taken: one partial sum per 64 rows
 static int64_t wgrad_chunks_least(const cvp_nn_tensor *x) { return ((int64_t)x->d * x->h + 63) / 64; }
 
+// rows of a tile and tiles of a slice
+static int wgrad_tile_rows(int ci) { return ci == 16 ? cvpnn::wgrad_rows<16>() : ci == 32 ? cvpnn::wgrad_rows<32>() : cvpnn::wgrad_rows<64>(); }
+static int64_t wgrad_columns(const cvp_nn_tensor *x)
+{
+    const int ty = wgrad_tile_rows(x->channels);
+    return (int64_t)((x->h + ty - 1) / ty) * ((x->w + 31) / 32);
+}
+
 cvp_status cvp_nn_wgrad_workspace(const cvp_nn_tensor *x, const cvp_nn_tensor *dy, int64_t *floats)
 {
     if (!x || !dy || !floats) return CVP_E_INVALID;
-    const int64_t n = (int64_t)27 * dy->channels * x->channels;
+    const int64_t nw = (int64_t)27 * dy->channels * x->channels;
     const int64_t least = wgrad_chunks_least(x);
-    *floats = (n > 0 ? std::max(least, wgrad_chunks_wanted(n)) : least) * n;
+    // no more partial sums than there are tiles; each with the bias gradient's
+    const int64_t chunks = nw > 0 ? std::max(least, std::min(wgrad_chunks_wanted(nw), wgrad_columns(x) * x->d)) : least;
+    *floats = chunks * (nw + dy->channels);
     return CVP_OK;
 }
 
@@ -1132,11 +1142,10 @@ static cvp_status wgrad(const cvp_nn_tensor *x, const cvp_nn_tensor *dy, float *
     // the run length whose longest chunk is shortest: a unit costs its slices
     // and the two more that its first needs
     const int64_t cap = std::min(work_floats / n, wgrad_chunks_wanted(nw));
-    const int ty = ci == 16 ? cvpnn::wgrad_rows<16>() : ci == 32 ? cvpnn::wgrad_rows<32>() : cvpnn::wgrad_rows<64>();
     cvpnn::WgradPlan p;
-    p.ytiles = (x->h + ty - 1) / ty;
+    p.ytiles = (x->h + wgrad_tile_rows(ci) - 1) / wgrad_tile_rows(ci);
     p.segs = (x->w + 31) / 32;
-    const int64_t columns = (int64_t)p.ytiles * p.segs;
+    const int64_t columns = wgrad_columns(x);
     if (columns * x->d > INT32_MAX / 2) return CVP_E_UNSUPPORTED;
     int64_t best = INT64_MAX;
     for (int run = 1; run <= x->d; ++run) {

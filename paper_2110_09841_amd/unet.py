@@ -152,6 +152,19 @@ def forward_bound_seconds(shape, peak_flops=2.5e15, peak_bytes=8e12):
     return t
 
 
+def work_floats(shape):
+    """Floats of scratch that the backward pass takes: the most that a layer's
+    weight and bias gradients ask for, or the head's partial sums."""
+    worst = 17 * -(-shape[0] * shape[1] * shape[2] // 4096)
+    n = ctypes.c_int64()
+    for _, ci, co, s in LAYERS:
+        grid = [v // s for v in shape]
+        x, dy = (NNTensor(None, *grid, c, c) for c in (ci, co))
+        _check(lib().cvp_nn_wgrad_workspace(ctypes.byref(x), ctypes.byref(dy), ctypes.byref(n)))
+        worst = max(worst, n.value)
+    return worst
+
+
 class UNet:
     def __init__(self, shape, seed=0, device="cuda"):
         D, H, W = shape
@@ -179,16 +192,7 @@ class UNet:
         self.g = {k: torch.empty_like(v) for k, v in self.a.items()}
         self.gx0 = torch.empty(self.shape, dtype=torch.float32, device=device)
         self.x0 = torch.empty(self.shape, dtype=torch.float32, device=device)
-        worst = 0
-        L = lib()
-        for xi, gi in (("in", "c1a"), ("cat1", "d1a")):
-            n = ctypes.c_int64()
-            L.cvp_nn_wgrad_workspace(ctypes.byref(desc(self.a[xi])), ctypes.byref(desc(self.a[gi])), ctypes.byref(n))
-            worst = max(worst, n.value)
-        n = ctypes.c_int64()
-        L.cvp_nn_wgrad_workspace(ctypes.byref(desc(self.a["p2"])), ctypes.byref(desc(self.a["c3a"])), ctypes.byref(n))
-        worst = max(worst, n.value, 64 * 64 * 27 * 64)
-        self.work = torch.empty(worst + 4096, dtype=torch.float32, device=device)
+        self.work = torch.empty(work_floats(self.shape), dtype=torch.float32, device=device)
         self.work64 = torch.empty(1024, dtype=torch.float64, device=device)
         self.loss = torch.zeros(1, dtype=torch.float64, device=device)
         self.step_count = 0
