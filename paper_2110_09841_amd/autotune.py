@@ -5,9 +5,13 @@ item, which also sets how many workgroups share a compute unit through their
 LDS footprint) and the backprojection for each stack width and number of
 64-voxel passes per stack, on seeded random
 data of the geometry's own shape, with HIP events on the current stream, and
-keeps the fastest of each.  Results can be cached in a JSON file keyed by the
-geometry and the options, so a later process reuses them without timing.
+keeps the fastest of each.  The backprojection is timed without scratch: with
+it, voxels of up to 8 detector columns take the kernel that reads a transposed
+copy of the projections, and the plan has no field for that one.  Results can
+be cached in a JSON file keyed by the geometry, the options and whether the
+geometry keeps its records, so a later process reuses them without timing.
 """
+import ctypes
 import hashlib
 import json
 import os
@@ -16,11 +20,12 @@ import numpy as np
 import torch
 
 from . import _lib
-from .cvp import Geometry, Options, backproject, project
+from .cvp import Geometry, Options, _stream, project
 
 DEFAULT_BANDS = (4, 6, 8, 9, 10, 12, 16, 19, 24, 32)
 DEFAULT_STACKS = (16, 8, 4)
 DEFAULT_PASSES = (2, 1)
+PLANS = 2          # of the stored plans: 1 were timed with scratch
 
 
 def _key(geom: Geometry, opts: Options):
@@ -33,9 +38,16 @@ def _key(geom: Geometry, opts: Options):
         "sid": p["sid_mm"], "sdd": p["sdd_mm"],
         "angles": hashlib.sha1(np.asarray(p["angles_rad"], dtype=np.float64).tobytes()).hexdigest(),
         "variant": opts.variant, "ec": bool(opts.ec), "scaling": opts.scaling,
+        "plans": PLANS, "records_cached": bool(geom.records_cached),
         "device": torch.cuda.get_device_name(geom.device),
     }, sort_keys=True)
     return hashlib.sha1(blob.encode()).hexdigest()
+
+
+def _backproject(b, geom: Geometry, o, out):
+    """x = A^T b without scratch, by the kernels that the plan describes."""
+    _lib.check(_lib.lib().cvp_backproject(geom.handle, ctypes.byref(o), ctypes.c_void_p(b.data_ptr()),
+                                          ctypes.c_void_p(out.data_ptr()), _stream()))
 
 
 def _time(fn, reps):
@@ -70,6 +82,7 @@ def autotune(geom: Geometry, opts: Options, bands=DEFAULT_BANDS, stacks=DEFAULT_
     b = torch.rand(geom.proj_shape, generator=g, device=geom.device)
     p_out = torch.empty_like(b)
     v_out = torch.empty_like(x)
+    o = opts.c()
     default = geom.launch
     p_ms, b_ms = {}, {}
     for u in bands:
@@ -91,7 +104,7 @@ def autotune(geom: Geometry, opts: Options, bands=DEFAULT_BANDS, stacks=DEFAULT_
                         geom.set_launch(default[0], gw, kp, wpc, shw)
                     except _lib.CVPError:
                         continue
-                    b_ms[(gw, kp, wpc, shw)] = _time(lambda: backproject(b, geom, opts, out=v_out), reps)
+                    b_ms[(gw, kp, wpc, shw)] = _time(lambda: _backproject(b, geom, o, v_out), reps)
                     if log:
                         log("backprojection stack %d, %d passes, %d per CU%s: %.2f ms"
                             % (gw, kp, wpc, ", one window" if shw else "", b_ms[(gw, kp, wpc, shw)]))
