@@ -275,17 +275,20 @@ cvp_status cvp_backproject_views_ws(const cvp_geometry *g, const cvp_options *op
  * backprojection).  The per-call pointer setup and the counter reset are one
  * tiny kernel on the same stream, so a batched call can be graph-captured.
  * n: 1..32 geometries on the same device; the batch keeps pointers to them
- * (they must outlive it) and owns its device tables: room for transposed
- * copies of every volume and every projection array, and the members'
- * cut-piece records, each up to 32 GiB in all (above that, or when the memory
- * is not there, the launches do without).
- * When every member has cached records (cvp_geometry_cache_records) at
- * cvp_batch_create, the batched kernels read those instead of tables of the
- * batch; a call after a member's table was freed or rebuilt then returns
+ * (they must outlive it) and owns small device tables and scratch: room for
+ * the members' cut-piece records, where not every member has cached ones
+ * (cvp_geometry_cache_records) at cvp_batch_create, and for the transposed
+ * copies of the volumes or of the projections, whichever is larger.  Every
+ * call fills it anew (and runs on one stream at a time).  scratch_bytes bounds
+ * it (0: none; cvp_batch_create: 32 GiB); what the bound or the free memory
+ * does not hold, the launches do without, with bitwise the same results.
+ * When every member has cached records at creation, the batched kernels read
+ * those; a call after a member's table was freed or rebuilt then returns
  * CVP_E_INVALID.
  */
 typedef struct cvp_batch cvp_batch;   /* opaque */
 cvp_status cvp_batch_create(const cvp_geometry *const *geoms, int32_t n, cvp_batch **out);
+cvp_status cvp_batch_create_limited(const cvp_geometry *const *geoms, int32_t n, int64_t scratch_bytes, cvp_batch **out);
 void cvp_batch_destroy(cvp_batch *b);
 /* d_vols / d_projs: host arrays of n device pointers (layouts as above).
  * Calls that overlap in time must not share a batch object (it holds the

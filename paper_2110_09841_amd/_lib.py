@@ -93,6 +93,7 @@ def _register_extra(L):
     st = ctypes.c_int
     specs = {
         "cvp_batch_create": ([ctypes.POINTER(vp), ctypes.c_int32, ctypes.POINTER(vp)], st),
+        "cvp_batch_create_limited": ([ctypes.POINTER(vp), ctypes.c_int32, ctypes.c_int64, ctypes.POINTER(vp)], st),
         "cvp_batch_destroy": ([vp], None),
         "cvp_project_batched": ([vp, ctypes.POINTER(OptionsC), ctypes.POINTER(vp), ctypes.POINTER(vp), vp], st),
         "cvp_backproject_batched": ([vp, ctypes.POINTER(OptionsC), ctypes.POINTER(vp), ctypes.POINTER(vp), vp], st),

@@ -860,7 +860,7 @@ static int64_t gmax_bytes(const cvp_geometry *g) { return cvp::group_max_cells(g
 // launched in several pieces, each still thousands of workgroups (12.7 GB of
 // records at 512^3 x 248 views: two pieces).
 constexpr int64_t kTableBytes = int64_t(8) << 30;
-// A batch holds tables and copies for its members up to this many bytes each.
+// Most bytes of scratch that a batch holds by default.
 constexpr int64_t kBatchBytes = int64_t(32) << 30;
 
 // Records of one view: rows padded to 256 bytes (records, counts).
@@ -1254,21 +1254,23 @@ struct cvp_batch {
     int device = 0;
     std::vector<const cvp_geometry *> geoms;
     cvp::BatchProblem *d_probs = nullptr;
-    cvp::BatchTable *d_ptab = nullptr;
-    // backprojection groups g = 4 p + w: piece stride 4 (p = 0) or 8 (p = 1),
-    // stack width 16, 8, 4 (w = 0, 1, 2) or from transposed copies (w = 3)
-    cvp::BatchTable *d_btab[8] = {};
-    int *d_counter = nullptr;         // [0] projection, [1 + g] backprojection group g
+    // work tables: [0] projection, [1 + g] backprojection group g = 4 p + w:
+    // piece stride 4 (p = 0) or 8 (p = 1), stack width 16, 8, 4 (w = 0, 1, 2)
+    // or from transposed copies (w = 3)
+    cvp::BatchTable *d_tabs = nullptr;
+    int *d_counter = nullptr;         // per work table
     std::vector<unsigned *> d_gmax;   // per problem: per-group maxima of the volume
-    std::vector<float *> vts;         // per problem: its transposed volume (nullptr: none)
-    size_t plds = 0, blds[8] = {};
+    size_t plds = 0, blds[8] = {};    // blds 0: no member in the group
     int pgrid = 0, bgrid[8] = {};
-    bool cached = false;                  // every member reads a table of records
-    std::vector<const float *> rtabs;     // the geometries' tables captured at creation (empty: the batch's own)
-    std::vector<void *> d_own;            // the batch's own tables and transposed volumes
-    bool vt = false;                      // the projection reads transposed volumes
-    bool direct = false;                  // the backprojection reads transposed copies
-    std::vector<cvp::BackCopy> copies;    // per problem
+    std::vector<const float *> rtabs; // the geometries' tables captured at creation (empty: not read)
+    char *d_pool = nullptr;           // scratch of the calls; the pointers below are nullptr without it
+    std::vector<float *> recs;        // per problem: its records, made in every call
+    std::vector<int *> cnts;
+    std::vector<float *> vts;         // per problem: its transposed volume
+    std::vector<cvp::BackCopy> copies;   // per problem: its transposed projections
+    bool tables = false;              // the kernels read records from tables (the geometries' or recs)
+    bool vt = false;                  // the projection reads transposed volumes
+    bool direct = false;              // the backprojection reads transposed copies
 };
 
 extern "C" {
@@ -1277,22 +1279,72 @@ void cvp_batch_destroy(cvp_batch *b)
 {
     if (!b) return;
     if (b->d_probs) (void)hipFree(b->d_probs);
-    if (b->d_ptab) (void)hipFree(b->d_ptab);
-    for (cvp::BatchTable *t : b->d_btab)
-        if (t) (void)hipFree(t);
+    if (b->d_tabs) (void)hipFree(b->d_tabs);
     if (b->d_counter) (void)hipFree(b->d_counter);
     for (unsigned *t : b->d_gmax)
         if (t) (void)hipFree(t);
-    for (void *t : b->d_own) (void)hipFree(t);
+    if (b->d_pool) (void)hipFree(b->d_pool);
     delete b;
 }
 
-cvp_status cvp_batch_create(const cvp_geometry *const *geoms, int32_t n, cvp_batch **out)
+// The batch's scratch, of at most `most` bytes: records of every member where
+// the geometries keep none, and room for the transposed volumes (projection)
+// and the transposed projections (backprojection) at the same place, both
+// read beside tables of records only.  What does not fit or cannot be
+// allocated is left out.
+static void batch_pool(cvp_batch *b, int64_t most)
+{
+    bool kept = true;
+    int64_t records = 0, volumes = 0, copies = 0;
+    for (const cvp_geometry *g : b->geoms) {
+        kept = kept && g->d_rtab;
+        records += align256(table_bytes(g, g->base.nviews));
+        volumes += align256(g->nvox * (int64_t)sizeof(float));
+        copies += copy_bytes(g, g->base.nviews);
+    }
+    if (kept) records = 0;
+    b->recs.assign(b->n, nullptr);
+    b->cnts.assign(b->n, nullptr);
+    b->vts.assign(b->n, nullptr);
+    b->copies.assign(b->n, cvp::BackCopy());
+    b->vt = records + volumes <= most;
+    b->direct = records + copies <= most;
+    int64_t bytes = 0;
+    for (;;) {
+        bytes = records + std::max(b->vt ? volumes : 0, b->direct ? copies : 0);
+        if (bytes == 0 || (bytes <= most && hipMalloc((void **)&b->d_pool, bytes) == hipSuccess)) break;
+        (void)hipGetLastError();
+        b->d_pool = nullptr;
+        if (b->vt || b->direct) b->vt = b->direct = false;
+        else records = 0;
+    }
+    b->tables = kept || records > 0;
+    if (kept)
+        for (const cvp_geometry *g : b->geoms) b->rtabs.push_back(g->d_rtab);
+    Scratch w(b->d_pool, bytes);
+    for (int q = 0; q < b->n && records > 0; ++q) {
+        const cvp_geometry *g = b->geoms[q];
+        const TableSize t = table_size(g, g->base.nviews);
+        b->recs[q] = static_cast<float *>(w.take(t.rec));
+        b->cnts[q] = static_cast<int *>(w.take(t.cnt));
+    }
+    Scratch v = w;
+    for (int q = 0; q < b->n && b->vt; ++q) b->vts[q] = static_cast<float *>(v.take(b->geoms[q]->nvox * (int64_t)sizeof(float)));
+    for (int q = 0; q < b->n && b->direct; ++q) {
+        const cvp::DevGeom &G = b->geoms[q]->base;
+        b->copies[q].pad = G.rpad;
+        b->copies[q].pt = static_cast<float *>(w.take(cvp::copy_floats(G, G.nviews) * (int64_t)sizeof(float)));
+        b->copies[q].bad = static_cast<int *>(w.take(cvp::copy_flags(G, G.nviews) * (int64_t)sizeof(int)));
+    }
+}
+
+cvp_status cvp_batch_create_limited(const cvp_geometry *const *geoms, int32_t n, int64_t scratch_bytes, cvp_batch **out)
 {
     if (!out) return fail(CVP_E_INVALID, "out is NULL");
     *out = nullptr;
     if (!geoms) return fail(CVP_E_INVALID, "geoms is NULL");
     if (n < 1 || n > cvp::kMaxBatch) return fail(CVP_E_INVALID, "n = %d (must be 1..%d)", n, cvp::kMaxBatch);
+    if (scratch_bytes < 0) return fail(CVP_E_INVALID, "scratch_bytes = %lld", (long long)scratch_bytes);
     for (int q = 0; q < n; ++q) {
         if (!geoms[q]) return fail(CVP_E_INVALID, "geoms[%d] is NULL", q);
         if (geoms[q]->device != geoms[0]->device)
@@ -1306,36 +1358,17 @@ cvp_status cvp_batch_create(const cvp_geometry *const *geoms, int32_t n, cvp_bat
     b->n = n;
     b->device = geoms[0]->device;
     b->geoms.assign(geoms, geoms + n);
-    // With every member's records cached the batched kernels read those; else
-    // the batch makes tables of its own for all of them, up to kBatchBytes
-    // (launches on a larger batch make their records in the kernels).
-    bool own = false;
-    b->cached = true;
-    for (int q = 0; q < n; ++q) b->cached = b->cached && geoms[q]->d_rtab != nullptr;
-    std::vector<float *> recs(n, nullptr);
-    std::vector<int *> cnts(n, nullptr);
-    if (!b->cached) {
-        int64_t total = 0;
-        for (int q = 0; q < n; ++q) total += table_bytes(geoms[q], geoms[q]->base.nviews);
-        own = total <= kBatchBytes;
-        for (int q = 0; q < n && own; ++q) {
-            const cvp_geometry *g = geoms[q];
-            void *t = nullptr;
-            own = hipMalloc(&t, table_bytes(g, g->base.nviews)) == hipSuccess;
-            if (!own) break;
-            b->d_own.push_back(t);
-            recs[q] = static_cast<float *>(t);
-            cnts[q] = reinterpret_cast<int *>(static_cast<char *>(t) + table_size(g, g->base.nviews).rec);
-            own = cvp::launch_record_table(g->base, g->pmax, false, recs[q], cnts[q], nullptr) == hipSuccess;
-        }
-        if (own) own = hipStreamSynchronize(nullptr) == hipSuccess;   // calls may come on any stream
-        if (!own) {
-            (void)hipGetLastError();
-            for (void *t : b->d_own) (void)hipFree(t);
-            b->d_own.clear();
-        }
-        b->cached = own;
-    }
+    // what every launch needs comes before the optional scratch
+    int cus = 0;
+    hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, b->device);
+    if (e == hipSuccess) e = hipMalloc((void **)&b->d_probs, n * sizeof(cvp::BatchProblem));
+    if (e == hipSuccess) e = hipMalloc((void **)&b->d_tabs, 9 * sizeof(cvp::BatchTable));
+    if (e == hipSuccess) e = hipMalloc((void **)&b->d_counter, 9 * sizeof(int));
+    b->d_gmax.assign(n, nullptr);
+    for (int q = 0; q < n && e == hipSuccess; ++q)
+        e = hipMalloc((void **)&b->d_gmax[q], cvp::group_max_cells(geoms[q]->base) * sizeof(unsigned));
+    if (e != hipSuccess) { cvp_batch_destroy(b); return device_fail(e, "batch tables"); }
+    batch_pool(b, scratch_bytes);
     // Projection: every problem keeps its own plan (the batched kernel
     // dispatches on the piece stride per item), so its results are those of
     // its own launches.  Backprojection: every problem keeps its own piece
@@ -1346,33 +1379,15 @@ cvp_status cvp_batch_create(const cvp_geometry *const *geoms, int32_t n, cvp_bat
     static const int kGw[3] = {16, 8, 4};
     std::vector<cvp::BackLaunch> bls(n);
     std::vector<int> grp(n);
-    // transposed copies of the projections for the members' backprojections
-    // from their tables (the copies are filled per call)
-    b->copies.assign(n, cvp::BackCopy());
-    int64_t copies = 0;
-    for (int q = 0; q < n; ++q) copies += copy_bytes(geoms[q], geoms[q]->base.nviews);
-    b->direct = b->cached && copies <= kBatchBytes;
-    for (int q = 0; q < n && b->direct; ++q) {
-        const cvp_geometry *g = geoms[q];
-        void *t = nullptr;
-        b->direct = hipMalloc(&t, copy_bytes(g, g->base.nviews)) == hipSuccess;
-        if (!b->direct) break;
-        b->d_own.push_back(t);
-        b->copies[q].pt = static_cast<float *>(t);
-        b->copies[q].bad = reinterpret_cast<int *>(
-            static_cast<char *>(t) + align256(cvp::copy_floats(g->base, g->base.nviews) * (int64_t)sizeof(float)));
-        b->copies[q].pad = g->base.rpad;
-    }
-    if (!b->direct) (void)hipGetLastError();
     for (int q = 0; q < n; ++q) {
         // the member's own stack width, else the next narrower one whose
         // 8-piece records fit
-        bool planned = false;
         const int pm = geoms[q]->pmax <= 4 ? 4 : 8;
+        bool planned = false;
         for (int gi = 0; gi < 3 && !planned; ++gi) {
             if (kGw[gi] > geoms[q]->bl.gw) continue;
             planned = cvp::plan_backprojection(geoms[q]->base, pm, geoms[q]->zabs, geoms[q]->Dmin, kGw[gi], 0, bls[q],
-                                               false, cvp::kBatchStaticLds);
+                                               b->tables, cvp::kBatchStaticLds, geoms[q]->bp_wpc);
             grp[q] = (pm == 4 ? 0 : 4) + (b->direct ? 3 : gi);
         }
         if (!planned) {
@@ -1402,18 +1417,17 @@ cvp_status cvp_batch_create(const cvp_geometry *const *geoms, int32_t n, cvp_bat
         P.copy = b->copies[q];
         P.in = nullptr;
         P.out = nullptr;
-        P.gmax = nullptr;   // set below
-        P.vt = nullptr;
+        P.gmax = b->d_gmax[q];
+        P.vt = b->vts[q];
         P.stop = nullptr;   // set per call
-        if (b->cached) {
-            P.G.rtab = own ? recs[q] : g->d_rtab;
-            P.G.rtab_n = own ? cnts[q] : g->d_rtab_n;
+        if (b->tables) {
+            P.G.rtab = b->rtabs.empty() ? b->recs[q] : g->d_rtab;
+            P.G.rtab_n = b->rtabs.empty() ? b->cnts[q] : g->d_rtab_n;
             P.G.rtab_pmax = g->pmax;
             P.G.rtab_vs = 1;
-            if (!own) b->rtabs.push_back(g->d_rtab);
         }
         b->plds = std::max(b->plds, pl.lds);
-        b->blds[grp[q]] = std::max(b->blds[grp[q]], b->direct ? cvp::back_direct_lds(bl.pmax) : bl.lds);
+        b->blds[grp[q]] = std::max(b->blds[grp[q]], b->direct ? cvp::back_direct_lds(g->pmax) : bl.lds);
         pcost[q] = (double)g->nvox / pl.nbands;           // voxels per band (all k)
         bcost[q] = (double)g->base.nviews;                // views per voxel stack
     }
@@ -1433,42 +1447,24 @@ cvp_status cvp_batch_create(const cvp_geometry *const *geoms, int32_t n, cvp_bat
         return T;
     };
     const cvp::BatchTable pt = table(pcost, false, -1);
-    int cus = 0;
-    hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, b->device);
-    if (e == hipSuccess) e = hipMalloc((void **)&b->d_probs, n * sizeof(cvp::BatchProblem));
-    if (e == hipSuccess) e = hipMalloc((void **)&b->d_ptab, sizeof(cvp::BatchTable));
-    if (e == hipSuccess) e = hipMalloc((void **)&b->d_counter, 9 * sizeof(int));
+    e = hipMemcpy(b->d_tabs, &pt, sizeof(pt), hipMemcpyHostToDevice);
+    b->pgrid = cus * cvp::batched_blocks_per_cu(false, b->plds, 16, 8, b->tables, b->vt);
     for (int gi = 0; gi < 8 && e == hipSuccess; ++gi) {
         if (b->blds[gi] == 0) continue;   // no member with this stride and width
         const cvp::BatchTable bt = table(bcost, true, gi);
-        e = hipMalloc((void **)&b->d_btab[gi], sizeof(cvp::BatchTable));
-        if (e == hipSuccess) e = hipMemcpy(b->d_btab[gi], &bt, sizeof(bt), hipMemcpyHostToDevice);
+        e = hipMemcpy(b->d_tabs + 1 + gi, &bt, sizeof(bt), hipMemcpyHostToDevice);
         b->bgrid[gi] = cus * cvp::batched_blocks_per_cu(true, b->blds[gi], gi % 4 < 3 ? kGw[gi % 4] : 0, gi < 4 ? 4 : 8,
-                                                        b->cached, b->vt);
+                                                        b->tables, b->vt);
     }
-    b->d_gmax.assign(n, nullptr);
-    for (int q = 0; q < n && e == hipSuccess; ++q) {
-        e = hipMalloc((void **)&b->d_gmax[q], cvp::group_max_cells(probs[q].G) * sizeof(unsigned));
-        probs[q].gmax = b->d_gmax[q];
-    }
-    // room for the members' transposed volumes (read beside tables of records)
-    int64_t volumes = 0;
-    for (int q = 0; q < n; ++q) volumes += geoms[q]->nvox * (int64_t)sizeof(float);
-    b->vt = e == hipSuccess && b->cached && volumes <= kBatchBytes;
-    for (int q = 0; q < n && b->vt; ++q) {
-        void *t = nullptr;
-        b->vt = hipMalloc(&t, geoms[q]->nvox * sizeof(float)) == hipSuccess;
-        if (b->vt) b->d_own.push_back(t);
-        probs[q].vt = static_cast<float *>(t);
-    }
-    if (!b->vt) (void)hipGetLastError();
-    for (int q = 0; q < n; ++q) b->vts.push_back(b->vt ? probs[q].vt : nullptr);
     if (e == hipSuccess) e = hipMemcpy(b->d_probs, probs.data(), n * sizeof(cvp::BatchProblem), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(b->d_ptab, &pt, sizeof(pt), hipMemcpyHostToDevice);
     if (e != hipSuccess) { cvp_batch_destroy(b); return device_fail(e, "batch tables"); }
-    b->pgrid = cus * cvp::batched_blocks_per_cu(false, b->plds, 16, 8, b->cached, b->vt);
     *out = b;
     return ok();
+}
+
+cvp_status cvp_batch_create(const cvp_geometry *const *geoms, int32_t n, cvp_batch **out)
+{
+    return cvp_batch_create_limited(geoms, n, kBatchBytes, out);
 }
 
 static cvp_status batched(const cvp_batch *b, const cvp_options *o, const float *const *ins,
@@ -1495,34 +1491,31 @@ static cvp_status batched(const cvp_batch *b, const cvp_options *o, const float 
         io.sigma[q] = G.sigma;
         io.stop[q] = stops ? stops[q] : nullptr;
     }
-    if (!backward) {
-        // per-group maxima of every volume, for the projection items' scales
-        for (int q = 0; q < b->n; ++q) {
-            hipError_t e = b->vt ? cvp::launch_transpose_max(b->geoms[q]->base, ins[q], b->vts[q], b->d_gmax[q],
-                                                             (hipStream_t)stream, io.stop[q])
-                                 : cvp::launch_group_max(b->geoms[q]->base, ins[q], b->d_gmax[q], (hipStream_t)stream,
-                                                         io.stop[q]);
-            if (e != hipSuccess) return device_fail(e, "batched group maxima");
-        }
-    }
     const bool ex = o->variant == CVP_EXACT, ec = o->elevation_correction != 0;
+    hipStream_t sm = (hipStream_t)stream;
     hipError_t e = hipSuccess;
-    if (!backward) {
-        e = cvp::launch_batched(false, b->d_probs, b->d_ptab, b->d_counter, io, ex, ec, b->pgrid, b->plds, 16, 8,
-                                b->cached, b->vt, (hipStream_t)stream);
-    } else {
-        static const int kGw[3] = {16, 8, 4};
-        for (int q = 0; q < b->n && b->direct && e == hipSuccess; ++q) {
-            cvp::DevGeom G = b->geoms[q]->base;
+    for (int q = 0; q < b->n && e == hipSuccess; ++q) {
+        cvp::DevGeom G = b->geoms[q]->base;
+        if (b->recs[q]) e = cvp::launch_record_table(G, b->geoms[q]->pmax, false, b->recs[q], b->cnts[q], sm, io.stop[q]);
+        if (e != hipSuccess) break;
+        if (backward) {
             G.sigma = io.sigma[q];
-            e = cvp::launch_transpose_projections(G, ins[q], b->copies[q], (hipStream_t)stream, io.stop[q]);
+            if (b->direct) e = cvp::launch_transpose_projections(G, ins[q], b->copies[q], sm, io.stop[q]);
+        } else {
+            // per-group maxima of every volume, for the projection items' scales
+            e = b->vt ? cvp::launch_transpose_max(G, ins[q], b->vts[q], b->d_gmax[q], sm, io.stop[q])
+                      : cvp::launch_group_max(G, ins[q], b->d_gmax[q], sm, io.stop[q]);
         }
-        for (int gi = 0; gi < 8 && e == hipSuccess; ++gi)
-            if (b->d_btab[gi])
-                e = cvp::launch_batched(true, b->d_probs, b->d_btab[gi], b->d_counter + 1 + gi, io, ex, ec,
-                                        b->bgrid[gi], b->blds[gi], gi % 4 < 3 ? kGw[gi % 4] : 0, gi < 4 ? 4 : 8,
-                                        b->cached, b->vt, (hipStream_t)stream);
     }
+    if (e == hipSuccess && !backward)
+        e = cvp::launch_batched(false, b->d_probs, b->d_tabs, b->d_counter, io, ex, ec, b->pgrid, b->plds, 16, 8,
+                                b->tables, b->vt, sm);
+    static const int kGw[3] = {16, 8, 4};
+    for (int gi = 0; gi < 8 && backward && e == hipSuccess; ++gi)
+        if (b->blds[gi])
+            e = cvp::launch_batched(true, b->d_probs, b->d_tabs + 1 + gi, b->d_counter + 1 + gi, io, ex, ec,
+                                    b->bgrid[gi], b->blds[gi], gi % 4 < 3 ? kGw[gi % 4] : 0, gi < 4 ? 4 : 8,
+                                    b->tables, b->vt, sm);
     if (e != hipSuccess) return device_fail(e, "batched launch");
     return ok();
 }

@@ -168,10 +168,10 @@ struct BatchIO {             // per call, by value
     const double *stop[kMaxBatch];   // per problem, or nullptr
 };
 
-// gw, pmax: the backprojection launch's stack width (16, 8 or 4, records made
-// in the kernel; 0: from the transposed copies and tables) and piece stride
-// (4 or 8); cached: the projection reads tables of records; vt: the
-// projection reads the members' transposed volumes
+// gw, pmax: the backprojection launch's stack width (16, 8 or 4; 0: from the
+// transposed copies, with cached only) and piece stride (4 or 8); cached: the
+// kernels read tables of records; vt: the projection reads the members'
+// transposed volumes
 hipError_t launch_batched(bool backward, BatchProblem *probs, const BatchTable *tab, int *counter,
                           const BatchIO &io, bool exact, bool ec, int grid, size_t lds, int gw, int pmax, bool cached,
                           bool vt, hipStream_t s);

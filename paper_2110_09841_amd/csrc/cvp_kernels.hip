@@ -2218,8 +2218,11 @@ __device__ __forceinline__ bool next_item(const BatchTable &T, int *counter, int
     return true;
 }
 
+// (The caller's layout beside a table takes 4 waves per SIMD as in
+// project_kernel: eight of the 16 uneven problems with cached records and no
+// scratch 59.0 -> 37.7 ms; without a table 64.3 -> 62.6.)
 template <bool EXACT, bool EC, bool TAB, bool VT>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5)))
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(VT ? 5 : 4)))
 project_batched_kernel(const BatchProblem *__restrict__ probs, const BatchTable *__restrict__ T,
                        int *counter)
 {
@@ -2242,8 +2245,8 @@ project_batched_kernel(const BatchProblem *__restrict__ probs, const BatchTable 
 // equals its own single-problem launch bitwise, and each kernel holds a
 // single variant of the gather (its registers fit like the single-problem
 // kernel's; one kernel inlining every variant spilled).
-template <bool EXACT, bool EC, int PMAX, int GW>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3)))
+template <bool EXACT, bool EC, int PMAX, int GW, bool TAB>
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(TAB ? 4 : 3)))
 backproject_batched_kernel(const BatchProblem *__restrict__ probs, const BatchTable *__restrict__ T,
                            int *counter)
 {
@@ -2252,8 +2255,8 @@ backproject_batched_kernel(const BatchProblem *__restrict__ probs, const BatchTa
     while (next_item(*T, counter, p, local)) {
         const BatchProblem &P = probs[p];
         if (P.stop && *P.stop != 0.0) continue;
-        backproject_item<EXACT, EC, PMAX, GW, false, false>(P.G, P.ngroups, P.nkchunks, P.kp, P.win_cap, local, smem,
-                                                         P.in, P.out);
+        backproject_item<EXACT, EC, PMAX, GW, false, TAB>(P.G, P.ngroups, P.nkchunks, P.kp, P.win_cap, local, smem,
+                                                          P.in, P.out);
     }
 }
 
@@ -2428,14 +2431,21 @@ hipError_t launch_pb(BatchProblem *probs, const BatchTable *tab, int *counter, i
     return hipGetLastError();
 }
 
+// The batched backprojection of a stack width (0: from transposed copies).
+template <bool EXACT, bool EC, int PMAX, bool TAB>
+auto back_batched_fn(int gw)
+{
+    return gw == 16 ? backproject_batched_kernel<EXACT, EC, PMAX, 16, TAB>
+           : gw == 8 ? backproject_batched_kernel<EXACT, EC, PMAX, 8, TAB>
+           : gw == 4 || !TAB ? backproject_batched_kernel<EXACT, EC, PMAX, 4, TAB>
+                             : backproject_direct_batched_kernel<EXACT, EC, PMAX>;
+}
+
 template <bool EXACT, bool EC, int PMAX>
-hipError_t launch_bb(BatchProblem *probs, const BatchTable *tab, int *counter, int grid, size_t lds, int gw,
+hipError_t launch_bb(BatchProblem *probs, const BatchTable *tab, int *counter, int grid, size_t lds, int gw, bool cached,
                      hipStream_t s)
 {
-    const auto fn = gw == 0 ? backproject_direct_batched_kernel<EXACT, EC, PMAX>
-                    : gw == 16 ? backproject_batched_kernel<EXACT, EC, PMAX, 16>
-                    : gw == 8 ? backproject_batched_kernel<EXACT, EC, PMAX, 8>
-                              : backproject_batched_kernel<EXACT, EC, PMAX, 4>;
+    const auto fn = cached ? back_batched_fn<EXACT, EC, PMAX, true>(gw) : back_batched_fn<EXACT, EC, PMAX, false>(gw);
     hipLaunchKernelGGL(fn, dim3(grid), dim3(kBlock), lds, s, probs, tab, counter);
     return hipGetLastError();
 }
@@ -2447,17 +2457,8 @@ hipError_t launch_batched_form(bool backward, BatchProblem *probs, const BatchTa
     if (!backward)
         return cached ? launch_pb<EXACT, EC, true>(probs, tab, counter, grid, lds, vt, s)
                       : launch_pb<EXACT, EC, false>(probs, tab, counter, grid, lds, vt, s);
-    return pmax <= 4 ? launch_bb<EXACT, EC, 4>(probs, tab, counter, grid, lds, gw, s)
-                     : launch_bb<EXACT, EC, 8>(probs, tab, counter, grid, lds, gw, s);
-}
-
-template <int PMAX>
-const void *back_batched_fn(int gw)
-{
-    if (gw == 0) return (const void *)backproject_direct_batched_kernel<false, true, PMAX>;
-    if (gw == 16) return (const void *)backproject_batched_kernel<false, true, PMAX, 16>;
-    if (gw == 8) return (const void *)backproject_batched_kernel<false, true, PMAX, 8>;
-    return (const void *)backproject_batched_kernel<false, true, PMAX, 4>;
+    return pmax <= 4 ? launch_bb<EXACT, EC, 4>(probs, tab, counter, grid, lds, gw, cached, s)
+                     : launch_bb<EXACT, EC, 8>(probs, tab, counter, grid, lds, gw, cached, s);
 }
 
 const void *project_batched_fn(bool cached, bool vt)
@@ -2485,20 +2486,21 @@ hipError_t launch_batched(bool backward, BatchProblem *probs, const BatchTable *
 int batched_blocks_per_cu(bool backward, size_t lds, int gw, int pmax, bool cached, bool vt)
 {
     int nb = 0;
-    const void *fn = !backward ? project_batched_fn(cached, vt) : pmax <= 4 ? back_batched_fn<4>(gw) : back_batched_fn<8>(gw);
+    const void *fn = !backward ? project_batched_fn(cached, vt)
+                     : pmax <= 4 ? (const void *)(cached ? back_batched_fn<false, true, 4, true>(gw) : back_batched_fn<false, true, 4, false>(gw))
+                                 : (const void *)(cached ? back_batched_fn<false, true, 8, true>(gw) : back_batched_fn<false, true, 8, false>(gw));
     hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, kBlock, lds);
     if (e != hipSuccess || nb < 1) nb = 1;
     return nb;
 }
 
-template <int PMAX>
+template <int PMAX, bool TAB>
 static hipError_t allow_batched_back(size_t n)
 {
     return each_form([&](auto x, auto c) {
         constexpr bool X = decltype(x)::value, C = decltype(c)::value;
-        hipError_t r = allow_lds((const void *)backproject_batched_kernel<X, C, PMAX, 16>, n);
-        if (r == hipSuccess) r = allow_lds((const void *)backproject_batched_kernel<X, C, PMAX, 8>, n);
-        if (r == hipSuccess) r = allow_lds((const void *)backproject_batched_kernel<X, C, PMAX, 4>, n);
+        hipError_t r = hipSuccess;
+        for (int gw = 4; gw <= 16 && r == hipSuccess; gw *= 2) r = allow_lds((const void *)back_batched_fn<X, C, PMAX, TAB>(gw), n);
         return r;
     });
 }
@@ -2512,8 +2514,10 @@ hipError_t configure_batched_lds(size_t n)
         if (r == hipSuccess) r = allow_lds((const void *)project_batched_kernel<X, C, true, true>, n);
         return r;
     });
-    if (e == hipSuccess) e = allow_batched_back<4>(n);
-    if (e == hipSuccess) e = allow_batched_back<8>(n);
+    if (e == hipSuccess) e = allow_batched_back<4, true>(n);
+    if (e == hipSuccess) e = allow_batched_back<8, true>(n);
+    if (e == hipSuccess) e = allow_batched_back<4, false>(n);
+    if (e == hipSuccess) e = allow_batched_back<8, false>(n);
     return e;
 }
 #endif

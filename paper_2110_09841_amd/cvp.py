@@ -204,13 +204,18 @@ def backproject(b, geom: Geometry, opts: Options = Options(), out=None):
 
 
 class Batch:
-    """Several geometries served by one persistent launch per direction."""
+    """Several geometries served by one persistent launch per direction.
+    scratch_bytes bounds the device memory the batch keeps for its calls
+    (cvp_batch_create); the results do not depend on it."""
 
-    def __init__(self, geoms):
+    def __init__(self, geoms, scratch_bytes=None):
         self.geoms = list(geoms)
         arr = (ctypes.c_void_p * len(self.geoms))(*[g.handle.value for g in self.geoms])
         h = ctypes.c_void_p()
-        _lib.check(_lib.lib().cvp_batch_create(arr, len(self.geoms), ctypes.byref(h)))
+        if scratch_bytes is None:
+            _lib.check(_lib.lib().cvp_batch_create(arr, len(self.geoms), ctypes.byref(h)))
+        else:
+            _lib.check(_lib.lib().cvp_batch_create_limited(arr, len(self.geoms), int(scratch_bytes), ctypes.byref(h)))
         self.handle = h
 
     def __del__(self):
