@@ -84,6 +84,7 @@ cvp_status ok()
 
 cvp_status device_fail(hipError_t e, const char *what)
 {
+    (void)hipGetLastError();   // reported here, not by the next launch
     if (e == hipErrorOutOfMemory) return fail(CVP_E_NOMEM, "%s: %s", what, hipGetErrorString(e));
     return fail(CVP_E_DEVICE, "%s: %s", what, hipGetErrorString(e));
 }

@@ -45,7 +45,13 @@ class Geometry:
     vol_dims, voxel_mm, vol_offset_mm, det_cols, det_rows, pitch_mm,
     principal_px, sid_mm, sdd_mm, angles_rad), or a general trajectory with
     ``matrices`` ([views][3][4] camera matrices, see
-    ``synth.matrix_geometry``) in place of the orbit keys."""
+    ``synth.matrix_geometry``) in place of the orbit keys.
+
+    ``scratch_bytes`` (None: all that pays, about 8 GiB and the copies of the
+    volume or the projections at most) bounds the scratch of the operators and
+    solvers on this geometry; their results do not depend on it."""
+
+    scratch_bytes = None
 
     def __init__(self, params):
         self.params = dict(params)
@@ -123,9 +129,21 @@ class Geometry:
         in every launch, with bitwise the same results.  enable=False frees
         them.  Returns the table's size in bytes (0 when freed)."""
         nb = ctypes.c_int64()
-        _lib.check(_lib.lib().cvp_geometry_cache_records(self.handle, int(bool(enable)), ctypes.byref(nb), _stream()))
+        _with_freed_cache(lambda: _lib.lib().cvp_geometry_cache_records(self.handle, int(bool(enable)),
+                                                                        ctypes.byref(nb), _stream()))
         self.records_cached = nb.value > 0
         return int(nb.value)
+
+
+def _with_freed_cache(call):
+    """Runs a call that allocates device memory outside torch; where that is
+    short, once more without the memory torch's allocator keeps unused (the
+    scratch of earlier operator calls, above all)."""
+    status = call()
+    if status == _lib.CVP_E_NOMEM:
+        torch.cuda.empty_cache()
+        status = call()
+    _lib.check(status)
 
 
 def _check_tensor(t, shape, name):
@@ -143,15 +161,18 @@ def _stream():
 
 def operator_scratch(geom, o, device, project=True, backproject=True):
     """Scratch for the operators of ``geom`` with the options ``o`` (an
-    _lib.OptionsC) from torch's caching allocator, on
-    the current stream (cvp_operator_workspace_size): the whole of it, or as
-    much as the free memory holds (down to nothing for a backprojection, the
-    per-group maxima for a projection); the results do not depend on it."""
+    _lib.OptionsC) from torch's caching allocator, on the current stream
+    (cvp_operator_workspace_size): the whole of it, or as much as
+    ``geom.scratch_bytes`` allows and the free memory holds (down to nothing
+    for a backprojection, the per-group maxima for a projection); the results
+    do not depend on it."""
     p, b = ctypes.c_int64(), ctypes.c_int64()
     _lib.check(_lib.lib().cvp_operator_workspace_size(geom.handle, ctypes.byref(o), ctypes.byref(p),
                                                       ctypes.byref(b)))
     want = max(p.value if project else 0, b.value if backproject else 0)
     least = 4 * geom.project_work_words if project else 0
+    if geom.scratch_bytes is not None:
+        want = min(want, int(geom.scratch_bytes))
     while want > least:
         try:
             return torch.empty(want, dtype=torch.uint8, device=device)
