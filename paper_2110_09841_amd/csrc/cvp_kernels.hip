@@ -1320,10 +1320,15 @@ __device__ __forceinline__ void window_rows(const float *r, int k0, int kmax, fl
 // the pixel factor, to win[column][row - wv0] (row pitch Hp) with NT threads;
 // rows off the detector become zeros.  Threads cover 8, 16, 32 or 64 columns
 // (the power of two that holds Wd) of NT / that rows at a time and step down
-// the rows by constant offsets, four loads in flight; an element then costs
-// about 6 instructions at 60 to 70 % of the lanes (34 with a division per
-// element).  Returns whether this thread's values are all finite.
-template <int NT>
+// the rows by constant offsets, so an element costs about 6 instructions at 60
+// to 70 % of the lanes (34 with a division per element).  DEEP: eight rows in
+// flight to the last; else four, and the remainder one by one, for the kernels
+// with a table, whose registers and four waves per SIMD leave less to hide
+// (2 % slower with eight).  Without a table the waits of the remainder were
+// the larger part: 128^3, 120 views, without scratch 3.86 -> 3.06 ms, 256^3,
+// 60 views 7.65 -> 7.03 (before the fixed row counts 3.95 and 7.25).
+// Returns whether this thread's values are all finite.
+template <int NT, bool DEEP>
 __device__ __forceinline__ bool stage_window(float *win, const float *pv, const float *sgv, int wu0, int wv0, int wv1,
                                              int Wd, int Hp, int N, int M, int t)
 {
@@ -1337,7 +1342,25 @@ __device__ __forceinline__ bool stage_window(float *win, const float *pv, const 
         float *dst = win + uu * Hp + (va + r - wv0);
         const unsigned dm = (unsigned)(step * M);
         int v = va + r;
-        if (sgv) {
+        if constexpr (DEEP) {
+            // eight rows at a time, those past the window masked: one wait for them all
+            for (; v <= vb; v += 8 * step) {
+                float x[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) x[e] = v + e * step <= vb ? pv[off + e * dm] : 0.0f;
+                if (sgv) {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) x[e] *= v + e * step <= vb ? sgv[off + e * dm] : 0.0f;
+                }
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    if (v + e * step <= vb) dst[e * step] = x[e];
+                    chk = fmaf(x[e], 0.0f, chk);          // NaN once any value is not finite
+                }
+                off += 8 * dm;
+                dst += 8 * step;
+            }
+        } else if (sgv) {
             for (; v + 3 * step <= vb; v += 4 * step) {
                 float x[4];
 #pragma unroll
@@ -1563,6 +1586,12 @@ __device__ __forceinline__ void gather_column(const BackView &B, const float *rc
                     const float zt = EXACT ? fmaf(k, B.a3f, B.zt0) : 0.0f;
                     float w[R];
                     fixed_rows<R, EC, EXACT>(P, v0, k, B.raw, zt, r2.w, r2.y, w);
+                    // (the caller's array: the rows of the row loop, which a non-finite value
+                    // must reach, and any other with weight -- a lane's row is a cache line of
+                    // its own; at 128^3 voxels of 3.3 rows, 60 views 23.1 -> 20.2 ms)
+                    int lo0 = 0, hi0 = 0;
+                    if constexpr (SRC == kFromCaller)
+                        row_range_unclipped<EC>(fmaf(-k, r1.x, r0.z) + fmaf(-k, r1.y, r0.w), r1.z, r2.z, B.c2f, lo0, hi0);
                     float val[R];
                     if constexpr (SRC == kFromCopy) {
                         load_rows<R>(wcol + B.wv0, (unsigned)(vi - B.wv0) * 4u, val);
@@ -1572,11 +1601,11 @@ __device__ __forceinline__ void gather_column(const BackView &B, const float *rc
                             if (SRC == kFromWindow) {
                                 val[e] = wl[vi + e];
                             } else {
-                                const bool on = kv[ps] && (unsigned)(vi + e) < (unsigned)B.N;
-                                const size_t off = (size_t)(on ? vi + e : 0) * B.M + u;
-                                val[e] = B.pv[off];
-                                if (B.sgv) val[e] *= B.sgv[off];
-                                if (!on) val[e] = 0.0f;
+                                const int v = vi + e;
+                                const bool on = kv[ps] && (unsigned)v < (unsigned)B.N && ((v >= lo0 && v <= hi0) || w[e] != 0.0f);
+                                const unsigned off = (unsigned)v * (unsigned)B.M + (unsigned)u;
+                                val[e] = 0.0f;
+                                if (on) val[e] = B.sgv ? B.pv[off] * B.sgv[off] : B.pv[off];
                             }
                         }
                     }
@@ -1636,7 +1665,7 @@ __device__ __forceinline__ void backproject_item(const DevGeom &G, const int ngr
     const int i0 = q * GW;
     const int k0 = kch * kWave * kp;
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
-    const int wave = TAB ? __builtin_amdgcn_readfirstlane(tid / kWave) : tid / kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int kmax = min(k0 + kWave * kp, G.n3) - 1;
 
     // One record pass covers RV of the wave's views (w, w + 4, ...): LPV
@@ -1758,7 +1787,7 @@ __device__ __forceinline__ void backproject_item(const DevGeom &G, const int ngr
         const bool useWin = Wd * Hp <= winCap;
         B.fixed = true;
         if (useWin)
-            B.fixed = __ballot(!stage_window<kWave>(win, B.pv, sgv, wu0, wv0, wv1, Wd, Hp, G.N, G.M, lane)) == 0;
+            B.fixed = __ballot(!stage_window<kWave, !TAB>(win, B.pv, sgv, wu0, wv0, wv1, Wd, Hp, G.N, G.M, lane)) == 0;
         wave_sync();
 
         // the gather, with the window read from LDS (WIN) or global memory;
@@ -1818,7 +1847,7 @@ __device__ __forceinline__ void backproject_item(const DevGeom &G, const int ngr
 }
 
 template <bool EXACT, bool EC, int PMAX, int GW, bool TT = false, bool TAB = false>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(TAB ? 4 : 3)))
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(TAB ? 4 : PMAX > 8 ? 2 : 3)))
 backproject_kernel(const DevGeom G, const int ngroups, const int nkchunks, const int kp, const int items,
                    const int chunk, const int winCap, const float *__restrict__ proj,
                    float *__restrict__ vol, const double *__restrict__ stop)
@@ -2130,7 +2159,7 @@ __device__ __forceinline__ void backproject_shared_item(const DevGeom &G, const 
         const bool useWin = Wd * Hp <= winCap;
         B.fixed = true;
         if (useWin)
-            B.fixed = __syncthreads_and(stage_window<kBlock>(win, B.pv, B.sgv, wu0, wv0, wv1, Wd, Hp, G.N, G.M, tid));
+            B.fixed = __syncthreads_and(stage_window<kBlock, false>(win, B.pv, B.sgv, wu0, wv0, wv1, Wd, Hp, G.N, G.M, tid));
         else
             __syncthreads();
 
