@@ -129,9 +129,13 @@ size_t backproject_lds_bytes(int gw, int pmax, int winCap)
 constexpr int kBandMost = 8;
 constexpr int64_t kItemsLeast = 3 * 1280;
 // Volumes up to 64 MiB take their work items in plain order (views of a band
-// next to each other, round robin over the XCDs): 3 to 14 % faster than bands
-// by XCD on those workloads, which leaves XCDs idle when bands are few; at
-// 512^3, where the wedges of a band share an XCD's L2, 1 % slower.
+// next to each other, round robin over the XCDs) instead of bands by XCD,
+// which leaves XCDs idle when bands are few; of larger ones the wedges of a
+// band share an XCD's L2.  Plain / by XCD, ms, relaxed, records kept: 200^3 x
+// 48 views 2.61 / 2.70, 256^3 x 48 3.97 / 4.05, 256^3 x 248 13.3 / 13.4, 288^3
+// x 248 19.9 / 19.3, 320^3 x 248 23.4 / 23.4, 384^3 x 96 18.2 / 17.5, 384^3 x
+// 248 38.6 / 36.8, 512^3 x 96 37.1 / 36.7, 512^3 x 248 85.2 / 84.1 (above 64 MiB
+// with 48 views only plain is the faster, by 1 to 3 %).
 constexpr int64_t kLinearVolume = int64_t(64) << 20;
 
 // Projection: bands of U detector columns (a 64-bit band image of U x N and
@@ -956,13 +960,25 @@ static hipError_t run_project(const cvp_geometry *g, const cvp::DevGeom &G, cons
         if (most < std::min(G.nviews, 8)) most = 0;
         if (v && (G.rtab || most > 0)) {
             w = t;
-            // For two slices per lane (and TT's one) the kernel on the caller's
-            // layout, which loads a group's 16 columns at once, is the faster:
-            // relaxed at 128^3, 120 views 2.19 against 2.29 ms, 512 x 512 x
-            // 128, 180 views 31.1 against 34.3, TT there 37 against 47; but
-            // exact at 64^3, 64 views 0.48 against 0.42, relaxed at 256^3,
-            // 120 views 8.7 against 8.1.
-            if (G.n3 > 128 || (G.n3 <= 64 && model != cvp::kModelTT)) vt = v;
+            // From 129 slices on, where a lane of the other kernel takes more
+            // than its two.  Below, the caller's layout, which loads a group's
+            // 16 columns at once, is the faster, except up to 64 slices for
+            // bands of one column, which need few of the 16, and for the exact
+            // form.  Records kept, caller's layout / transposed, ms, relaxed;
+            // exact; relaxed without the elevation correction:
+            //   64^3, 32 views, bands of 1    0.180 / 0.156; 0.184 / 0.150; 0.152 / 0.141
+            //   64^3, 200 views, bands of 6   0.77 / 0.84; 0.93 / 0.89; 0.56 / 0.61
+            //   128 x 128 x 64, 120 views     1.40 / 1.48; 1.63 / 1.64; 1.12 / 1.28
+            //   128 x 128 x 128, 120 views    1.83 / 2.07; 2.36 / 2.52; 1.34 / 1.67
+            //   128 x 128 x 136, 120 views    3.11 / 2.76; 3.90 / 3.42; 2.28 / 2.18
+            //   512 x 512 x 128, 60 views     9.0 / 10.7; 10.7 / 11.7; 7.3 / 9.5
+            //   512 x 512 x 160, 60 views     15.2 / 13.5; 18.1 / 15.5; 12.3 / 12.0
+            // Not for TT, whose longer row loops hide the loads (128 x 128 at
+            // 64, 128, 192, 256 slices 1.55 / 1.94, 2.42 / 2.83, 3.85 / 3.80,
+            // 4.61 / 4.89).
+            if (model != cvp::kModelTT &&
+                (G.n3 > 128 || (G.n3 <= 64 && (pl.U == 1 || model == cvp::kModelExact))))
+                vt = v;
         }
     }
     hipError_t e = hipSuccess;

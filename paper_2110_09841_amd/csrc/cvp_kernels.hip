@@ -224,7 +224,10 @@ __device__ __forceinline__ void piece_record(const DevGeom &G, const ViewGeom &V
     const double md = fmax(fmax(V.c2 + 0.5, G.N - 0.5 - V.c2), 0.0);
     const double need0 = ceil(beta + 1.006), need1 = ceil(beta + 2.004 * rho32 * md + 1.006);
     const int r0 = need0 <= G.rpad ? (int)need0 : 0;
-    const int r1 = need1 <= G.rpad && rho32 < 0.9 ? (int)need1 : 0;
+    // (a kernel without the elevation correction, EC false, makes no use of the
+    // second moments: with the count they cost it 60 registers, all spilled;
+    // a table is made with EC for either)
+    const int r1 = EC && need1 <= G.rpad && rho32 < 0.9 ? (int)need1 : 0;
     rec[0] = __int_as_float(u | (r1 << 16) | (r0 << 20));
 }
 
@@ -804,7 +807,8 @@ __device__ __forceinline__ void project_item(const DevGeom &G, const int U, cons
     const int view = item % G.nviews;
     const int u0 = (item / G.nviews) * U;
     const int ub = min(u0 + U, G.M) - 1;
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = TAB ? tid / kWave : __builtin_amdgcn_readfirstlane(tid / kWave);
     const int Npad = (G.N + 2 * pad) | 1;
     const int ngroups = (G.n1 + GW - 1) / GW;
 
@@ -1029,14 +1033,29 @@ __device__ __forceinline__ void project_item(const DevGeom &G, const int U, cons
         // piece record serves 64 KH voxels.  From the transposed volume a
         // column is one contiguous row of n3 values, loaded when its turn
         // comes; from the caller's layout, where the 16 columns of a group
-        // share each 64-byte line, all of them are loaded at once (and fewer
-        // slices fit the registers: two, or one beside the FP64 stage).  The loops over columns, pieces and
-        // slices are not unrolled (the row-count variants would be repeated
-        // for each): their values are taken by uniform register indices.
-        constexpr int KH = VT ? 8 : TAB ? 2 : 1, CW = VT ? 1 : GW;
+        // share each 64-byte line, all of them are loaded at once, and only
+        // two slices fit the registers (TT without a table, with its FP64
+        // stage at five waves per SIMD: one).  The loops over columns and
+        // pieces, and over eight slices, are not unrolled (the row-count
+        // variants would be repeated for each): their values are taken by
+        // uniform register indices.  Two slices are written out, which frees
+        // the 16 registers of an indexed vector: 512 x 512 x 128, 180 views,
+        // cached records 27.0 -> 26.0 ms (25.5 with the row loop at five
+        // waves), 256 x 256 x 128, 90 views 6.2 -> 5.9.
+        constexpr int KH = VT ? 8 : TAB || !TT ? 2 : 1, CW = VT ? 1 : GW;
         for (int kc = 0; kc < G.n3; kc += kWave * KH) {
-            const int nh = min(KH, (G.n3 - kc + kWave - 1) / kWave);
+            const int nh = KH == 1 ? 1 : min(KH, (G.n3 - kc + kWave - 1) / kWave);
             const float kf0 = (float)(kc + lane);
+            auto each_slice = [&](auto &&f) {
+                if constexpr (KH <= 2) {
+                    f(0, kf0);
+                    if (KH == 2 && nh == 2) f(KH - 1, kf0 + (float)kWave);
+                } else {
+                    float kf = kf0;
+#pragma unroll 1
+                    for (int h = 0; h < nh; ++h, kf += (float)kWave) f(h, kf);
+                }
+            };
 #pragma unroll 1
             for (int cq = 0; cq < GW; cq += CW) {
                 if (VT && ((cols >> cq) & 1u) == 0) continue;
@@ -1059,7 +1078,7 @@ __device__ __forceinline__ void project_item(const DevGeom &G, const int U, cons
                     const int np = __builtin_amdgcn_readlane(ncol, c);
                     if (np == 0) continue;
                     // (16 wide: a uniform index into 8 or fewer is compiled to a chain of selects)
-                    typename FloatVec<16>::type base;
+                    typename FloatVec<KH <= 2 ? KH : 16>::type base;
                     unsigned any = 0u;
 #pragma unroll
                     for (int h = 0; h < KH; ++h) {
@@ -1111,14 +1130,12 @@ __device__ __forceinline__ void project_item(const DevGeom &G, const int U, cons
                             with_rows(rows, [&](auto tag) {
                                 constexpr int R = decltype(tag)::value;
                                 auto slices = [&](auto insideTag) {
-                                    float kf = kf0;
-#pragma unroll 1
-                                    for (int h = 0; h < nh; ++h, kf += (float)kWave) {
+                                    auto slice = [&](int h, float kf) {
                                         const float v0 = floorf(fmaf(-kf, beta, P.ys));
                                         const int vi = (int)v0;
                                         if (!decltype(insideTag)::value &&
                                             (unsigned)(vi + (R - 1)) >= (unsigned)(G.N + (R - 1)))
-                                            continue;
+                                            return;
                                         const float zt = EXACT ? fmaf(kf, a3f, zt0) : 0.0f;
                                         const double coef = (double)base[h] * W;
                                         float w[R];
@@ -1126,16 +1143,15 @@ __device__ __forceinline__ void project_item(const DevGeom &G, const int U, cons
                                         unsigned long long *const q = bcol + vi;
 #pragma unroll
                                         for (int e = 0; e < R; ++e) lds_add_fixed(q + e, w[e], coef);
-                                    }
+                                    };
+                                    each_slice(slice);
                                 };
                                 if (inside) slices(std::true_type{});
                                 else slices(std::false_type{});
                             });
                             continue;
                         }
-#pragma unroll 1
-                        for (int h = 0; h < nh; ++h) {
-                            const float kf = kf0 + (float)(h * kWave);
+                        each_slice([&](int h, float kf) {
                             const float zt = fmaf(kf, a3f, zt0);        // top of voxel k, relative to s3
                             const float coef = ldexpf(base[h] * r[1], sc);
                             const float Yh = fmaf(-kf, r[4], r[2]);
@@ -1152,7 +1168,7 @@ __device__ __forceinline__ void project_item(const DevGeom &G, const int U, cons
                                 sweep_rows<EC, EXACT>(vlo0, vhi0, max(vlo0, 0), min(vhi0, G.N - 1), Yh, Yl, r[4],
                                                       Yl + r[5], beta, rho, c2f, coef, raw, zt, r[11], r[9], bcol);
                             }
-                        }
+                        });
                     }
                 }
             }
@@ -1172,14 +1188,19 @@ __device__ __forceinline__ void project_item(const DevGeom &G, const int U, cons
     }
 }
 
-// Register budgets: the projection is held to 96 VGPRs (5 waves per SIMD; the
-// kernels that make their records spill in the FP64 stage) and the window
-// backprojection without a table to 168 (3 waves per SIMD); both ran about 20%
-// faster at 512^3 x 248 views than at their natural 190-220 VGPRs with 2 waves
-// per SIMD.  With a table but the caller's layout, two slices of 16 columns
-// take 4 waves per SIMD (at 5 they spill inside the voxel loop).
+// Register budgets.  The projection from the transposed volume is held to 96
+// VGPRs (5 waves per SIMD) and the window backprojection without a table to
+// 168 (3 waves per SIMD, 2 for footprints of more than 8 columns, whose LDS
+// admits no more); both ran about 20% faster at 512^3 x 248 views than at
+// their natural 190-220 VGPRs with 2 waves per SIMD.  On the caller's layout
+// two slices of 16 columns take 4 waves per SIMD with the elevation correction
+// (at 5 they spill inside the voxel loop: 256 x 256 x 128, 90 views, cached
+// records 5.9 against 7.6 ms) and 5 without (4.5 at 4 waves, 4.1 at 5).
+// Without a table two slices at 4 waves beat one at 5, which spilled as much
+// in the FP64 stage and served half the voxels per record: 128^3, 120 views,
+// no scratch 3.75 -> 3.32 ms, 256^3, 60 views 9.5 -> 8.4.
 template <bool EXACT, bool EC, int PMAX, bool TT, bool TAB, bool VT>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(TAB && !VT ? 4 : 5)))
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(VT || (TAB ? !EC : TT) ? 5 : 4)))
 project_kernel(const DevGeom G, const int U, const int pad, const int nbands, const int linear,
                const float *__restrict__ vol,
                float *__restrict__ proj, const unsigned *__restrict__ gmax, const double *__restrict__ stop)
