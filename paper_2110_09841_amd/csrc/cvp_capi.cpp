@@ -868,6 +868,11 @@ constexpr int64_t kTableBytes = int64_t(8) << 30;
 // Most bytes of scratch that a batch holds by default.
 constexpr int64_t kBatchBytes = int64_t(32) << 30;
 
+// A launch holds fewer than 2^32 threads: at most this many workgroups, in
+// eights.  The narrow stacks of the launches from transposed projections come to
+// more from 8192 x 8192 columns on; wider ones without a copy take those.
+constexpr int kMostItems = (1 << 24) - 8;
+
 // Records of one view: rows padded to 256 bytes (records, counts).
 struct TableSize { int64_t rec, cnt; };
 static TableSize table_size(const cvp_geometry *g, int64_t views)
@@ -1035,7 +1040,7 @@ static hipError_t run_backproject(const cvp_geometry *g, const cvp::DevGeom &G, 
                                   const double *stop = nullptr)
 {
     const bool records = makes_records(g, G);
-    if (g->pmax <= 8) {
+    if (g->pmax <= 8 && g->bld.items <= kMostItems) {
         Scratch w(work, work_bytes);
         int step = back_views(g, records, w.n, G.nviews);
         cvp::BackPart part;
@@ -1072,7 +1077,7 @@ static hipError_t run_backproject(const cvp_geometry *g, const cvp::DevGeom &G, 
 
 static int64_t backproject_full_bytes(const cvp_geometry *g, bool records)
 {
-    if (g->pmax > 8) return 0;
+    if (g->pmax > 8 || g->bld.items > kMostItems) return 0;
     const int64_t all = back_bytes(g, records, g->base.nviews), most = std::max(kTableBytes, back_bytes(g, records, 8));
     if (all <= most) return all + 256;
     return most + align256(cvp::back_part_floats(g->bld) * (int64_t)sizeof(float)) + 256;
