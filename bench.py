@@ -22,11 +22,12 @@ sample of the same workload (A x and A^T b over three views, extrapolated),
 plus a one-thread run of the 64^3 workload; --cpu-baseline-full runs the
 whole CPU-baseline plan instead (minutes, no GPU) and prints its record.
 
-The roofline counts FP32 VALU lane-operations of the method per voxel-view
-(costmodel.py, fixed constants per step); the instruction overhead beside it
-is the kernel's measured VALU lane-instructions per voxel-view (rocprofv3
-SQ_INSTS_VALU of the committed counter summary, while the kernel source
-matches it) over that count.
+The roofline is the executed FP32 VALU lane-operations (rocprofv3
+SQ_INSTS_VALU of the committed counter summary x 64, while the kernel source
+matches it; else null) against the VALU's peak at its nominal clock.  Beside
+it stand the operations that the method's row-by-row formulation counts per
+voxel-view (costmodel.py, fixed constants per step); the kernels evaluate most
+pieces with fewer.
 """
 import argparse
 import json
@@ -527,7 +528,7 @@ def main():
         rec = autotune(G, opts, reps=2)
         plan.update(tuned=list(G.launch) + [G.bp_workgroups_per_cu, int(G.bp_shared_window)],
                     project_ms=rec["project_ms"],
-                    backproject_ms=rec["backproject_ms"])
+                    backproject_without_scratch_ms=rec["backproject_ms"])
     x = torch.from_numpy(x_h).cuda()
     b = torch.from_numpy(b_h).cuda()
     p_out = torch.empty(G.proj_shape, dtype=torch.float32, device="cuda")
@@ -572,14 +573,19 @@ def main():
     counts = costmodel.estimate_counts(g)
     rA = costmodel.roofline(g, exact, ec, tA.mean(), counts)
     rB = costmodel.roofline(g, exact, ec, tB.mean(), counts)
-    dom, rdom, name = (tA, rA, "cvp_project") if tA.mean() >= tB.mean() else (tB, rB, "cvp_backproject")
-    traffic = measured_counters(name)
+    dom, rdom, name, other = ((tA, rA, "cvp_project", "cvp_backproject") if tA.mean() >= tB.mean() else
+                              (tB, rB, "cvp_backproject", "cvp_project"))
+    profiled = not exact and ec and record_cache is not None       # the form the counters were taken of
+    traffic = measured_counters(name) if profiled else None
 
-    def overhead(kernel, r):
-        c = measured_counters(kernel)
+    def issue(kernel, seconds):
+        """Executed FP32 VALU lane-operations (SQ_INSTS_VALU x 64) of one
+        launch: per voxel-view, per second, and as a share of the peak."""
+        c = measured_counters(kernel) if profiled else None
         if not c or not c.get("sq_insts_valu"):
-            return None
-        return c["sq_insts_valu"] * 64 / vv / r["ops_per_vv"]
+            return {"instructions_per_voxel_view": None, "achieved": None, "frac": None}
+        n = 64.0 * c["sq_insts_valu"]
+        return {"instructions_per_voxel_view": n / vv, "achieved": n / seconds / 1e12, "frac": n / seconds / rdom["peak"]}
     out = {
         "metric": "voxel-view updates/s (CVP Ax+A^T b, 512^3, 248 views); CGLS time to 1e-3 residual",
         "value": float(value),
@@ -604,17 +610,12 @@ def main():
         "record_cache": record_cache,
         "project": {"ms": 1e3 * tA.mean(), "voxel_views_per_s": vv / tA.mean()},
         "backproject": {"ms": 1e3 * tB.mean(), "voxel_views_per_s": vv / tB.mean()},
-        "roofline": {"bound": "alu", "kernel": name, "achieved": rdom["achieved"] / 1e12,
-                     "peak": rdom["peak"] / 1e12, "unit": "TOP/s (FP32 VALU lane-ops)",
-                     "frac": rdom["frac"], "ops_per_voxel_view": rdom["ops_per_vv"],
+        "roofline": {"bound": "alu", "kernel": name, "peak": rdom["peak"] / 1e12,
+                     "unit": "TOP/s (executed FP32 VALU lane-ops)", **issue(name, dom.mean()),
+                     "method_ops_per_voxel_view": rdom["ops_per_vv"],
                      "counts_per_voxel_view": {"column_pieces": rdom["n_c"], "pixels": rdom["n_p"],
                                                "ec_edge_pixels": rdom["n_e"]},
-                     "instruction_overhead": overhead(name, rdom),
-                     "other_kernel": {"kernel": "cvp_project" if name == "cvp_backproject" else "cvp_backproject",
-                                      "frac": (rA if name == "cvp_backproject" else rB)["frac"],
-                                      "instruction_overhead": overhead(
-                                          "cvp_project" if name == "cvp_backproject" else "cvp_backproject",
-                                          rA if name == "cvp_backproject" else rB)},
+                     "other_kernel": {"kernel": other, **issue(other, (tB if name == "cvp_project" else tA).mean())},
                      "traffic": traffic["bytes"] if traffic else None, "traffic_unit": "bytes per launch",
                      "traffic_detail": traffic},
     }

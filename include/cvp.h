@@ -181,19 +181,25 @@ cvp_status cvp_project_ws(const cvp_geometry *g, const cvp_options *opts,
                           void *hip_stream);
 
 /*
- * Scratch with which the operators run fastest: with project_bytes of it
+ * Scratch with which the operators run fastest.  With project_bytes of it
  * cvp_project_ws and cvp_project_views also copy the volume to [n2][n1][n3]
- * order and read the copy column by column, the backprojection copies the
- * scaled projections to [views][cols][rows] order (the backprojection fields
- * of the launch plan do not apply then), and both directions make the cut-piece records of their views in one pass before the operator kernel
- * instead of in every workgroup (unless the geometry caches them for opts, see
- * cvp_geometry_cache_records; at most 8 GiB of records at a time, views
- * beyond that in further launches).  Every work size an entry point accepts
- * gives bitwise the same results; a call uses what fits.  The functions named
- * ..._ws take optional scratch of any size, any alignment (NULL, 0: none) that
- * overlaps no vector of the call, from a caller that keeps calls overlapping
- * in time on distinct scratch; project_bytes also covers the view subsets,
- * and a solver uses the larger of the two.
+ * order and, from 129 slices on, read the copy column by column (up to 64
+ * slices for the exact form and for bands of one column; never for TT); with
+ * backproject_bytes the backprojection copies the scaled projections to
+ * [views][cols][rows] order (the backprojection fields of the launch plan do
+ * not apply then).  Both directions make the cut-piece records of their views
+ * in one pass before the operator kernel instead of in every workgroup, unless
+ * the geometry caches them for opts (cvp_geometry_cache_records): 8 GiB of
+ * records at a time at most, or those of 8 views where that is more, views
+ * beyond that in further launches.  Footprints of more than 8 columns, and
+ * backprojections of 2^24 stacks of 4 columns and more, use no copy and no
+ * records.  Every work size an entry point accepts gives bitwise the same
+ * results (next to a projection value that is not finite: the same to
+ * rounding); a call uses what fits.  The functions named ..._ws take optional
+ * scratch of any size, any alignment (NULL, 0: none) that overlaps no vector
+ * of the call, from a caller that keeps calls overlapping in time on distinct
+ * scratch; project_bytes also covers the view subsets, and a solver uses the
+ * larger of the two.
  */
 cvp_status cvp_operator_workspace_size(const cvp_geometry *g, const cvp_options *opts, int64_t *project_bytes,
                                        int64_t *backproject_bytes);
@@ -537,6 +543,9 @@ cvp_status cvp_synth_add_gaussian(float *d_out, int64_t n, float sigma, uint64_t
  *                   work item's fixed-point band image takes 8 bytes per
  *                   detector row and column of LDS (at most 156 KB in all), so
  *                   small values let more workgroups share a compute unit.
+ * The backprojection's fields describe the launches that stage detector
+ * windows: those without scratch (or with less than 8 views' worth of it, see
+ * cvp_operator_workspace_size).
  *   bp_stack_cols   voxel columns per backprojection workgroup (16, 8 or 4).
  *   bp_passes       64-voxel passes per backprojection stack (1 or 2): two
  *                   passes share each view's piece records and detector
@@ -562,9 +571,11 @@ cvp_status cvp_synth_add_gaussian(float *d_out, int64_t n, float sigma, uint64_t
  * uses the geometry; launches already enqueued keep the plan they were
  * given, and batches keep the plans of their members at cvp_batch_create.
  * Results of a given plan are bitwise reproducible; backprojections do not
- * depend on the plan at all, while two plans may differ in the last bit of a
- * few projection values (the fixed-point scale of a work item depends on the
- * part of the volume it reads). */
+ * depend on the plan at all, while projections under two plans may differ in
+ * the last bits: the fixed-point scale of a work item depends on the part of
+ * the volume it reads, and a band so wide that the spare rows at its ends no
+ * longer fit the LDS evaluates every piece by the general row loop, whose
+ * weights round differently. */
 typedef struct {
     int32_t proj_band_cols;
     int32_t bp_stack_cols;
@@ -589,9 +600,9 @@ cvp_status cvp_geometry_sizes(const cvp_geometry *g, int64_t *n_voxels,
  * voxels and 248 views).  From then on cvp_project, cvp_backproject, their
  * _ws / _views / _noalloc variants and the solvers of the cutting voxel
  * projector (both forms, EC on or off) read the records instead of computing
- * them in each launch; results are bitwise the same.  The TT projector and
- * the batched launches keep computing their own.  Without its FP64 stage the
- * backprojection needs less LDS per workgroup, so its plan is re-derived for a
+ * them in each launch; results are bitwise the same.  The TT projector keeps
+ * computing its own; a batch reads them where every member has them at its
+ * creation.  Without its FP64 stage the window backprojection needs less LDS per workgroup, so its plan is re-derived for a
  * smaller LDS budget (the same stack shape when it fits; likewise back when
  * the table is freed).  enable = 0 frees the table.
  * *bytes (may be NULL) receives the table's size.  The fill is enqueued on

@@ -2268,9 +2268,10 @@ __device__ __forceinline__ bool next_item(const BatchTable &T, int *counter, int
     return true;
 }
 
-// (The caller's layout beside a table takes 4 waves per SIMD as in
-// project_kernel: eight of the 16 uneven problems with cached records and no
-// scratch 59.0 -> 37.7 ms; without a table 64.3 -> 62.6.)
+// (The caller's layout takes 4 waves per SIMD as in project_kernel: eight of the
+// 16 uneven problems without scratch, with cached records 59.0 ms at 5 waves,
+// 35.5 at 4; without a table, whose two piece strides spill in the FP64 stage
+// at any of them, 80.1, 61.2 and, at 3, 61.8.)
 template <bool EXACT, bool EC, bool TAB, bool VT>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(VT ? 5 : 4)))
 project_batched_kernel(const BatchProblem *__restrict__ probs, const BatchTable *__restrict__ T,
